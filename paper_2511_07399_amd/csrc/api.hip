@@ -923,6 +923,12 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
         RUN(tag, launch_gemm_part(g, s, 1), what);                                  \
         if (gemm_splits_k(g)) RUN(SDV2_TAG_GEMM_REDUCE, launch_gemm_part(g, s, 2), what " (sum of the k parts)"); \
     } while (0)
+    // the same for a product whose result is LayerNorm-ed next: the second pass then forms that LayerNorm too (*done)
+#define RUN_GEMM_LN(tag, what, norm, done)                                          \
+    do {                                                                            \
+        RUN(tag, launch_gemm_then_layernorm(g, norm, done, s, 1), what);            \
+        if (gemm_splits_k(g)) RUN(SDV2_TAG_GEMM_REDUCE, launch_gemm_then_layernorm(g, norm, done, s, 2), what " (sum of the k parts)"); \
+    } while (0)
 #define RUN_ATTN(tag, args, what)                                                   \
     do {                                                                            \
         RUN(tag, launch_attention(args, s, 1), what);                               \
@@ -996,13 +1002,14 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     g.epilogue = kEpiGatedResidual;
     g.gate_a = tab + 2 * C;
     g.gate_b = e0 + 2 * C;
-    RUN_GEMM(SDV2_TAG_OUT_PROJ, "out-proj gemm");
-    // 6. LayerNorm-3 (affine) and the cross-attention query
+    bool normed = false;
     ln.scale_a = w->ln3_gamma;
     ln.scale_b = nullptr;
     ln.shift_a = w->ln3_beta;
     ln.shift_b = nullptr;
-    RUN(SDV2_TAG_LN3, launch_layernorm(ln, s), "LN-3");
+    RUN_GEMM_LN(SDV2_TAG_OUT_PROJ, "out-proj gemm", ln, &normed);
+    // 6. LayerNorm-3 (affine) and the cross-attention query
+    if (!normed) RUN(SDV2_TAG_LN3, launch_layernorm(ln, s), "LN-3");
     g.a = ws.h;
     g.w = static_cast<const bf16*>(w->W_cq);
     g.bias = w->b_cq;
@@ -1028,13 +1035,13 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     g.bias = w->b_co;
     g.out = x;
     g.epilogue = kEpiResidual;
-    RUN_GEMM(SDV2_TAG_CROSS_OUT, "cross-out gemm");
-    // 8. adaLN-2 and the FFN
     ln.shift_a = tab + 3 * C;
     ln.shift_b = e0 + 3 * C;
     ln.scale_a = tab + 4 * C;
     ln.scale_b = e0 + 4 * C;
-    RUN(SDV2_TAG_ADALN2, launch_layernorm(ln, s), "adaLN-2");
+    RUN_GEMM_LN(SDV2_TAG_CROSS_OUT, "cross-out gemm", ln, &normed);
+    // 8. adaLN-2 and the FFN
+    if (!normed) RUN(SDV2_TAG_ADALN2, launch_layernorm(ln, s), "adaLN-2");
     g.a = ws.h;
     g.w = static_cast<const bf16*>(w->W_1);
     g.bias = w->b_1;
@@ -1058,13 +1065,12 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
         ln1.shift_b = e0 + 0 * C;
         ln1.scale_a = next_w->mod_table + 1 * C;
         ln1.scale_b = e0 + 1 * C;
-        RUN(SDV2_TAG_FFN2, launch_gemm_then_layernorm(g, ln1, next_h_ready, s, 1), "FFN-2 gemm");
-        if (gemm_splits_k(g))
-            RUN(SDV2_TAG_GEMM_REDUCE, launch_gemm_then_layernorm(g, ln1, next_h_ready, s, 2), "FFN-2 gemm (sum of the k parts)");
+        RUN_GEMM_LN(SDV2_TAG_FFN2, "FFN-2 gemm", ln1, next_h_ready);
     } else {
         RUN_GEMM(SDV2_TAG_FFN2, "FFN-2 gemm");
     }
 #undef RUN_GEMM
+#undef RUN_GEMM_LN
 #undef RUN_ATTN
 #undef RUN
     return SDV2_OK;

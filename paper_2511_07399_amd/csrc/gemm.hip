@@ -3,29 +3,19 @@
 // This is the "24 b L_q C^2" term of the per-layer cost in Appendix B of the paper (QKV, output
 // and FFN projections), plus the cross-attention projections the cost model leaves out.
 //
-// Design
-//   * Both operands are K-contiguous (activations [M, K], weights [N, K]), so the A and B fragments
-//     of v_mfma_f32_32x32x16_bf16 are plain 16-byte loads: lane l holds row (l % 32) and the eight
-//     k values 8 * (l / 32) .. +7 of a 16-wide k step.
-//   * A workgroup is 4 waves stacked along M.  Wave tile = (32 TM) x (32 TN); workgroup tile =
-//     (128 TM) x (32 TN) x 64.  TN runs from 2 to 8 so that the tile count can be matched to the
-//     256 compute units for the skinny M = 1024 shapes of the streaming chunk.
-//   * Tiles go global -> registers -> LDS (two LDS stages, two or three register sets: a load is in
-//     flight for two or three k iterations), one barrier per k tile.  LDS rows are 64 bf16 (128 B); the
-//     16-byte chunk index is XOR-ed with (row / 2) % 8 so that fragment reads are conflict free on the
-//     64-bank LDS.
-//   * Workgroup ids are spread round-robin over the 8 XCDs by the hardware; the kernel undoes that
-//     so that each XCD (one L2) owns a contiguous range of tiles, ordered in groups of M tiles that
-//     share weight tiles.
-//   * Split-K, for the one kind of shape that needs it (few output tiles, long k: FFN-2 of the small model),
-//     is two launches: the parts store fp32 partial sums, an elementwise kernel adds them in k order and applies
-//     the epilogue.  fp32 atomics on the output cost ~40 us per 1.5 M elements here, and a last-arriver
-//     reduction inside one launch needs device-scope fences that write back and invalidate the whole L2 of an
-//     XCD (measured +100 us on a 64 us launch).
+// Two kernels on the matrix cores.  gemm_alt64_kernel (16x16x32 MFMAs, direct global -> LDS loads, persistent) serves
+// every shape whose operands are below 4 GiB: its loads carry 32-bit byte offsets per lane.  gemm_kernel (32x32x16
+// MFMAs, tiles staged through registers, 64-bit addresses) serves the larger ones.  Both operands are K-contiguous
+// (activations [M, K], weights [N, K]), so fragments are plain 16-byte pieces of rows.
+//   Split-K (few output tiles, long k: FFN-2 of one chunk) is two launches: the parts store fp32 partial sums, a second
+// kernel adds them in k order and applies the epilogue, and the LayerNorm that follows if there is one.  fp32 atomics
+// on the output cost ~40 us per 1.5 M elements here, and a last-arriver reduction inside one launch needs device-scope
+// fences that write back and invalidate the whole L2 of an XCD (measured +100 us on a 64 us launch).
 #include "common.h"
 
 #include <mutex>
 #include <type_traits>
+#include <utility>
 
 #include <stdio.h>
 #include <stdlib.h>
@@ -136,6 +126,8 @@ __device__ __forceinline__ void run_epilogue(const GemmArgs& g, f32x16 (&acc)[TM
     }
 }
 
+// The register-staged kernel: workgroup of four waves stacked along M, wave tile (32 TM) x (32 TN), workgroup tile
+// (128 TM) x (32 TN) x 64; global -> registers -> LDS (two LDS stages), one barrier per k tile.
 // Tiles whose k loop fits in 256 registers are compiled for two workgroups per compute unit, so that one
 // workgroup's barrier and LDS-latency bubbles are filled by the other's MFMAs.  BK (64 or 128) is the k
 // depth of an LDS stage: a deeper stage halves the number of barriers, which is what the small tiles
@@ -337,20 +329,40 @@ __global__ __launch_bounds__(256, ((TM * TN <= 5 && BK == 64 && PF == 2) ? 2 : 1
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Second kernel: tiles go global -> LDS directly (global_load_lds_dwordx4, no staging registers and no
-// LDS write instructions), 8 waves per workgroup arranged WM x WN so that a wave's tile is (32 TM) x (32 TN)
-// with TM + TN fragment reads per TM TN MFMAs, NS LDS stages of BK = 64.
+// Second kernel, for every shape whose operands are below 4 GiB: v_mfma_f32_16x16x32_bf16 on tiles that go
+// global -> LDS directly (global_load_lds_dwordx4: no staging registers, no LDS write instructions).
 //
-// A direct load writes 16 bytes per lane at consecutive LDS addresses (lane l -> base + 16 l), so one wave
-// instruction fills 8 tile rows of 128 bytes.  The swizzle is applied on the global side: the lane that
-// fills chunk position p of row r fetches logical chunk p ^ ((r / 2) % 8) of that row; the 8 lanes of a row
-// still cover one whole 128-byte segment of the operand.
-//
-// Iteration t:  wait for this wave's loads of tile t | barrier (tile t visible to all; every wave is done
-// with tile t - 1, whose stage is therefore free) | issue the loads of tile t + NS - 1 | compute tile t.
-constexpr int kVmcntShift = 14;
-constexpr int vmcnt_imm(int n) {      // s_waitcnt with only vmcnt constrained
-    return (n & 0xF) | ((n >> 4) << kVmcntShift) | 0x0F70;
+//   What bounds it.  On random data the chip is power limited: a register-resident loop of 32x32x16 MFMAs sustains
+// 1.82 PFLOP/s, of 16x16x32 MFMAs 2.05 PFLOP/s (2.48 / 2.45 on zeros), because the smaller instruction moves half of
+// the accumulator data per flop.  Below that it is the LDS pipeline: 4.6 clocks per fragment read of 1 KB and 16 to 25
+// per direct load of 1 KB, against 16 clocks per MFMA.  Hence large wave tiles (128 x 64 of a 256 x 256 workgroup
+// tile: 24 fragment reads per 64 MFMAs of a k tile of 64), whole 128-byte lines per load, and tiles as large as the
+// shape allows (a 1024-row product streams its operands through the L2s at up to 19 TB/s: 128 x 160 tiles on 256
+// units, 62 us for 1024 x 5120 x 5120 where 128 x 160 register-staged tiles took 67).
+//   Main loop.  A k tile is 64 wide and holds two MFMA k steps ("halves").  While the MFMAs of one half are issued, the
+// fragments of the other half are read from LDS, and (second half) the tile loads go out, one every few MFMAs:
+//     half 0 of tile t | wait: tile t + 1 has landed, every fragment of tile t is in registers | barrier |
+//     half 1 of tile t, fragments of half 0 of tile t + 1, loads of tile t + stages into the stage tile t has left
+// One barrier per k tile, no fragment latency behind it.  The order inside a half is the program order, held by
+// scheduling barriers: left to the scheduler the loads of a half are issued in one burst.
+//   Stages.  A and W have rings of their own (NSA, NSW stages): weights come from HBM (every layer has its own),
+// activations mostly from the L2, so where 160 KB allow it W gets the additional stage.
+//   ROLES: half of the waves fetch A, the other half W, each with its own wait count.  With every wave fetching both, a
+// wave waits for its loads in issue order and so for the slower operand; with large tiles of few loads per MFMA the
+// wait is hidden and sharing the loads evenly is 3 to 8 % faster (256-row tiles), with 128-row tiles roles are
+// (1024 x 5120 x 5120: 65 -> 60 us).
+//   Persistent: a workgroup takes its tiles in turn, and the loads run on across them: the first k tiles of the next
+// output tile are in flight while this one's epilogue stores (1.3B FFN-1 on 8192 rows: 207 -> 188 us).
+//   Epilogue from registers: the operands are swapped (W rows are the MFMA's rows), so a lane holds four consecutive
+// columns of one row; two bf16 blocks are interleaved with v_permlane16_swap into 16-byte stores, fp32 pieces are 16
+// bytes as they are.  No LDS round trip, so the ring can keep filling.
+//   XCD-aware order: an XCD (one L2) owns a contiguous range of tiles, ordered in groups of GROUP_M tile rows that share
+// weight tiles.
+//   Tried and dropped: W fragments straight from global memory into registers, A through LDS (16 rows of 64 bytes per
+// load: 20 to 40 % slower on every shape); four waves of 128 x 128 (half of the fragment reads, but one wave per SIMD
+// leaves the barrier and the epilogue uncovered: 2 to 8 % slower); NSW = 5 with NSA = 3 on 128 x 160 (same as 4 and 4).
+constexpr int vmcnt_only(int n) {     // s_waitcnt with only vmcnt constrained
+    return (n & 0xF) | ((n >> 4) << 14) | 0x0F70;
 }
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 // 16 bytes per lane from global memory straight into LDS at dst + 16 * lane (dst is wave-uniform).
@@ -358,618 +370,400 @@ __device__ __forceinline__ void load_to_lds_b128(const void* src, void* dst) {
     __builtin_amdgcn_global_load_lds(src, (lds_void_ptr)dst, 16, 0, 0);
 }
 
-template <int WM, int WN, int TM, int TN, int NS>
-__global__ __launch_bounds__(64 * WM * WN, 1) void gemm_dma_kernel(GemmArgs g, int tiles_m, int tiles_n,
-                                                                   int group_m, int splitk) {
-    constexpr int NW = WM * WN;
-    constexpr int BK = 64;
-    constexpr int BM = 32 * TM * WM;
-    constexpr int BN = 32 * TN * WN;
-    constexpr int KS = BK / 16;
-    constexpr int GROUPS = (BM + BN) / 8;            // 8-row groups of the stacked [A; W] tile = wave loads per tile
-    constexpr int LPW = GROUPS / NW;                 // loads per wave per tile
-    static_assert(GROUPS % NW == 0, "tile rows must split evenly over the waves");
-    constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
+template <int... I, typename F>
+__device__ __forceinline__ void static_for_impl(std::integer_sequence<int, I...>, F&& f) { (f(std::integral_constant<int, I>{}), ...); }
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN;
-    const int wn = wave % WN;
-    const int l31 = lane & 31;
-    const int lh = lane >> 5;
-
-    const int nwg = gridDim.x;                                   // multiple of 8
-    const int logical = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
-    const int tiles = tiles_m * tiles_n;
-    if (logical >= tiles * splitk) return;
-    const int ks = logical / tiles;                              // which part of k (0 when k is not split)
-    const int t = logical - ks * tiles;
-    const int group_size = group_m * tiles_n;
-    const int grp = t / group_size;
-    const int first_m = grp * group_m;
-    const int gm = min(tiles_m - first_m, group_m);
-    const int in_grp = t - grp * group_size;
-    const int tile_m = first_m + in_grp % gm;
-    const int tile_n = in_grp / gm;
-    const int m0 = tile_m * BM;
-    const int n0 = tile_n * BN;
-
-    const int KT = g.K / BK;
-    const int kt0 = (int)((long long)ks * KT / splitk);
-    const int kt1 = (int)((long long)(ks + 1) * KT / splitk);
-    const int nk = kt1 - kt0;
-    if (splitk > 1) {                                            // this part's fp32 partial sums, plain stores
-        g.out = g.splitk_partials + (size_t)ks * g.M * g.N;
-        g.epilogue = kEpiPartial;
-        g.bias = nullptr;
-    }
-
-    // ---- per-lane source of each of this wave's loads (8-row group wave + NW i of the stacked tile): a 32-bit
-    // byte offset into the operand (operands are below 4 GB); the k advance is uniform
-    uint32_t off[LPW];
+// Stores a wave's tile.  acc[i][j][r] is the element (16 i + lane % 16, 16 j + 4 (lane / 16) + r) of it.  FULL: the tile
+// lies inside the output.  xpre: x read at the start of the tile (small tiles), else x is read here, a block of rows
+// ahead of its use.
+template <int TM, int TN, int EPI, bool FULL>
+__device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 (&acc)[TM][TN], int row0, int col0, int lane, const f32x4* xpre = nullptr) {
+    const int l15 = lane & 15, lq = lane >> 4;
+    const int rows = FULL ? 16 * TM : min(16 * TM, g.M - row0);
+    if constexpr (EPI == kEpiBias || EPI == kEpiBiasGelu) {
+        unsigned char* const base = reinterpret_cast<unsigned char*>(reinterpret_cast<bf16*>(outp) + (size_t)row0 * g.N);
+        auto pack = [&](const f32x4& v, uint32_t& d0, uint32_t& d1) {
+            bf16x4 w;
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-        const int r = 8 * (wave + NW * i) + (lane >> 3);         // row of the stacked tile
-        const int c = (lane & 7) ^ ((r >> 1) & 7);               // logical 16-byte chunk this lane fetches
-        const int row = (8 * (wave + NW * i) < BM) ? min(m0 + r, g.M - 1) : min(n0 + r - BM, g.N - 1);
-        off[i] = (uint32_t)row * (uint32_t)g.K * 2u + (uint32_t)c * 16u;
-    }
-    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(g.a) + (size_t)kt0 * (BK * 2);
-    const unsigned char* w_base = reinterpret_cast<const unsigned char*>(g.w) + (size_t)kt0 * (BK * 2);
-    auto issue_loads = [&](int kt_rel, int stage) {
+            for (int e = 0; e < 4; ++e) w[e] = (bf16)(EPI == kEpiBiasGelu ? gelu_tanh_f(v[e]) : v[e]);
+            const uint2 u = __builtin_bit_cast(uint2, w);
+            d0 = u.x; d1 = u.y;
+        };
+        const int cl = col0 + 16 * (lq & 1) + 8 * (lq >> 1);
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            unsigned char* dst = smem_raw + stage * STAGE_BYTES + (wave + NW * i) * 1024;
-            const unsigned char* base = (8 * (wave + NW * i) < BM) ? a_base : w_base;   // uniform per load
-            load_to_lds_b128(base + (size_t)kt_rel * (BK * 2) + off[i], dst);
-        }
-    };
-
-    f32x16 acc[TM][TN];
+        for (int i = 0; i < TM; ++i) {
+            __builtin_amdgcn_sched_barrier(0);
+            const int r = 16 * i + l15;
+            const uint32_t ro = (uint32_t)r * (uint32_t)g.N * 2u;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    const int a_row0 = wm * (32 * TM) + l31;
-    const int b_row0 = BM + wn * (32 * TN) + l31;
-    auto load_frags = [&](bf16x8 (&fa)[TM], bf16x8 (&fb)[TN], const bf16* st, int s) {
-        const int coff = ((2 * s + lh) ^ ((l31 >> 1) & 7)) << 3;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(st + (a_row0 + 32 * i) * BK + coff);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(st + (b_row0 + 32 * j) * BK + coff);
-    };
-    auto compute = [&](int stage) {
-        const bf16* st = reinterpret_cast<const bf16*>(smem_raw + stage * STAGE_BYTES);
-        bf16x8 fa[2][TM], fb[2][TN];
-        load_frags(fa[0], fb[0], st, 0);
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            if (s + 1 < KS) load_frags(fa[(s + 1) & 1], fb[(s + 1) & 1], st, s + 1);
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s & 1][i], fb[s & 1][j], acc[i][j], 0, 0, 0);
-        }
-    };
-    // Issue order of one iteration: the first step's fragment reads, then per MFMA one MFMA, the next step's
-    // fragment reads spread evenly, and the tile loads spread over the first MFMAs.
-    auto issue_pipeline = [&](bool with_loads) {
-        constexpr int kMfma = TM * TN * KS;
-        constexpr int kReadsPerMfma = (TM + TN + TM * TN - 1) / (TM * TN);
-        __builtin_amdgcn_sched_group_barrier(0x100, TM + TN, 0);
-#pragma unroll
-        for (int m = 0; m < kMfma; ++m) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, kReadsPerMfma, 0);
-            if (with_loads && m < LPW) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            for (int j = 0; j + 1 < TN; j += 2) {
+                uint32_t a0, a1, b0, b1;
+                pack(acc[i][j], a0, a1);
+                pack(acc[i][j + 1], b0, b1);
+                const auto r0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
+                const auto r1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
+                uint4 u; u.x = r0[0]; u.y = r1[0]; u.z = r0[1]; u.w = r1[1];
+                if (FULL || (r < rows && cl + 16 * j < g.N)) *reinterpret_cast<uint4*>(base + (ro + (uint32_t)(cl + 16 * j) * 2u)) = u;
+            }
+            if constexpr (TN % 2) {
+                uint32_t a0, a1;
+                pack(acc[i][TN - 1], a0, a1);
+                const int gcol = col0 + 16 * (TN - 1) + 4 * lq;
+                uint2 u; u.x = a0; u.y = a1;
+                if (FULL || (r < rows && gcol < g.N)) *reinterpret_cast<uint2*>(base + (ro + (uint32_t)gcol * 2u)) = u;
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
-    };
+    } else {
+        unsigned char* const base = reinterpret_cast<unsigned char*>(reinterpret_cast<float*>(outp) + (size_t)row0 * g.N);
+        const bool one_gate = EPI == kEpiGatedResidual && row0 / g.rows_per_gate == (row0 + rows - 1) / g.rows_per_gate;
+        constexpr int G = TN % 4 == 0 ? 4 : TN % 3 == 0 ? 3 : TN % 5 == 0 ? 5 : TN % 2 == 0 ? 2 : 1;    // column blocks at a time
+#pragma unroll
+        for (int j0 = 0; j0 < TN; j0 += G) {
+            __builtin_amdgcn_sched_barrier(0);
+            const int gcol = col0 + 16 * j0 + 4 * lq;
+            f32x4 gate[G];
+            auto load_gate = [&](int row) {
+                const float* gb = g.gate_b + (size_t)(row / g.rows_per_gate) * g.gate_b_stride;
+#pragma unroll
+                for (int j = 0; j < G; ++j) {
+                    const int c = FULL || gcol + 16 * j < g.N ? gcol + 16 * j : 0;
+                    gate[j] = *reinterpret_cast<const f32x4*>(g.gate_a + c) + *reinterpret_cast<const f32x4*>(gb + c);
+                }
+            };
+            if (EPI == kEpiGatedResidual && one_gate) load_gate(row0);
+            constexpr int XD = TM * TN > 16 ? 2 : 4;                                // row blocks of x in flight
+            f32x4 xv[XD][G];
+            auto load_x = [&](int i) {
+                const uint32_t ro = (uint32_t)(FULL ? 16 * i + l15 : min(16 * i + l15, rows - 1)) * (uint32_t)g.N * 4u;
+#pragma unroll
+                for (int j = 0; j < G; ++j)
+                    xv[i % XD][j] = *reinterpret_cast<const f32x4*>(base + (ro + (uint32_t)(FULL || gcol + 16 * j < g.N ? gcol + 16 * j : 0) * 4u));
+            };
+            constexpr bool pre = TM * TN <= 16;
+            if (EPI != kEpiPartial && !pre) {
+#pragma unroll
+                for (int i = 0; i < XD - 1 && i < TM; ++i) load_x(i);
+            }
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                if (EPI != kEpiPartial && !pre && i + XD - 1 < TM) load_x(i + XD - 1);
+                __builtin_amdgcn_sched_barrier(0);
+                const int r = 16 * i + l15;
+                if (EPI == kEpiGatedResidual && !one_gate) load_gate(row0 + min(r, rows - 1));
+                const uint32_t ro = (uint32_t)r * (uint32_t)g.N * 4u;
+#pragma unroll
+                for (int j = 0; j < G; ++j) {
+                    f32x4 v = acc[i][j0 + j];
+                    if (EPI == kEpiGatedResidual) v *= gate[j];
+                    if (EPI != kEpiPartial) v += pre ? xpre[i * TN + j0 + j] : xv[i % XD][j];
+                    if (FULL || (r < rows && gcol + 16 * j < g.N)) *reinterpret_cast<f32x4*>(base + (ro + (uint32_t)(gcol + 16 * j) * 4u)) = v;
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+}
 
-    auto step = [&](auto sc, int tt) {
-        constexpr int s = decltype(sc)::value;                   // stage of tile tt
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm((NS - 2) * LPW));
+template <int TM, int TN, int EPI>
+__device__ __forceinline__ void store_wave(const GemmArgs& g, void* outp, f32x4 (&acc)[TM][TN], int row0, int col0, int lane, const f32x4* xpre = nullptr) {
+    asm volatile("" : "+v"(lane));        // formed anew for every tile: lane terms kept across the k loop would cost it registers
+    if (row0 + 16 * TM <= g.M && col0 + 16 * TN <= g.N) store_tile<TM, TN, EPI, true>(g, outp, acc, row0, col0, lane, xpre);
+    else if (row0 < g.M) store_tile<TM, TN, EPI, false>(g, outp, acc, row0, col0, lane, xpre);
+}
+
+template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC>
+__global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m, int splitk) {
+    static_assert(NSW >= NSA && NSA >= 2, "stages");
+    constexpr int NW = WM * WN, BK = 64;
+    constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
+    constexpr int GA = BM / 8, GW = BN / 8;                 // groups of eight rows
+    constexpr int NL = ROLES ? NW / 2 : NW;                 // waves that load an operand
+    constexpr int LA = (GA + NL - 1) / NL, LW = (GW + NL - 1) / NL, LMAX = LA > LW ? LA : LW;
+    static_assert(ROLES || NSW <= NSA + 1, "stages");
+    constexpr int SA = BM * BK * 2, SW = BN * BK * 2;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    unsigned char* const smem_w = smem + NSA * SA;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int l15 = lane & 15, lq = lane >> 4;
+
+    // ---- the tiles of this workgroup: XCD x owns a contiguous range of tiles, its workgroups take them in turn
+    const int tiles = tiles_m * tiles_n, total = tiles * splitk;
+    const int xcd = blockIdx.x & 7, per_xcd = gridDim.x >> 3;
+    const int per = total >> 3, rem = total & 7;
+    const int t_end = per * (xcd + 1) + min(xcd + 1, rem);
+    int tile = per * xcd + min(xcd, rem) + (blockIdx.x >> 3);
+    if (tile >= t_end) return;
+    int m0, n0, ks = 0;
+    auto locate = [&](int id, int& m, int& n) {
+        const int gsz = group_m * tiles_n, grp = id / gsz, first_m = grp * group_m;
+        const int gm = min(tiles_m - first_m, group_m), in_grp = id - grp * gsz;
+        const int q = in_grp / gm;
+        m = (first_m + in_grp - q * gm) * BM;
+        n = q * BN;
+    };
+    const int KT = g.K / BK;
+    int kt0 = 0, nk = KT;
+    if (splitk > 1) {                                        // one tile per workgroup then
+        ks = tile / tiles;
+        kt0 = ks * KT / splitk;
+        nk = (ks + 1) * KT / splitk - kt0;
+    }
+    locate(tile - ks * tiles, m0, n0);
+
+    // ---- tile loads.  ROLES: the first half of the waves fetches A, the second half W, each with its own wait count.
+    // Otherwise every wave fetches a share of both, A first.
+    const bool loads_a = !ROLES || wave < NL;
+    const int id = loads_a ? wave : wave - NL;
+    uint32_t off[ROLES ? LMAX : LA + LW];
+    const unsigned char* const base0 = reinterpret_cast<const unsigned char*>(loads_a ? g.a : g.w) + (size_t)kt0 * (BK * 2);
+    const unsigned char* const base1 = reinterpret_cast<const unsigned char*>(g.w) + (size_t)kt0 * (BK * 2);
+    unsigned char* const lds0 = loads_a ? smem : smem_w;
+    const int bytes0 = loads_a ? SA : SW, stages0 = loads_a ? NSA : NSW;
+    // Row group of this wave's i-th load (eight rows of 128 bytes); past the end the wave's previous group again.
+    // Groups of a wave are NL (even) apart, so the swizzle term of a lane is the same for all of them.
+    static_assert(NL % 2 == 0, "swizzle term");
+    constexpr bool kWhole = GA % NL == 0 && GW % NL == 0;
+    auto group_of = [&](int i, int groups) { return kWhole || id + NL * i < groups ? id + NL * i : id + NL * (i - 1); };
+    const int lane_row = lane >> 3;
+    const uint32_t lane_col = (uint32_t)(((lane & 7) ^ ((4 * id + (lane >> 4)) & 7)) * 16), k2 = (uint32_t)g.K * 2u;
+    auto set_off0 = [&](int m, int n) {
+        const int first = (loads_a ? m : n) + lane_row, last = (loads_a ? g.M : g.N) - 1;
+#pragma unroll
+        for (int i = 0; i < (ROLES ? LMAX : LA); ++i) {
+            off[i] = (uint32_t)min(first + 8 * group_of(i, loads_a ? GA : GW), last) * k2 + lane_col;
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto set_off1 = [&](int n) {
+        if constexpr (!ROLES) {
+#pragma unroll
+            for (int i = 0; i < LW; ++i) {
+                off[LA + i] = (uint32_t)min(n + lane_row + 8 * group_of(i, GW), g.N - 1) * k2 + lane_col;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    };
+    // next k tile to fetch and the stage it goes to, per operand
+    int k0 = 0, k1 = 0, st0 = 0, st1 = 0;
+    const unsigned char *src0 = base0, *src1 = base1;
+    unsigned char *dst0 = lds0, *dst1 = smem_w;
+    // moves a cursor on: the next k tile (0 of the next output tile past the end, if there is one), the next stage
+    auto next0 = [&](bool more, int nk) {
+        const bool wrap = k0 + 1 == nk;
+        k0 = wrap ? (more ? 0 : k0) : k0 + 1;
+        src0 = wrap ? (more ? base0 : src0) : src0 + BK * 2;
+        st0 = st0 + 1 == stages0 ? 0 : st0 + 1;
+        dst0 = lds0 + st0 * bytes0;
+        return wrap && more;
+    };
+    auto next1 = [&](bool more, int nk) {
+        const bool wrap = k1 + 1 == nk;
+        k1 = wrap ? (more ? 0 : k1) : k1 + 1;
+        src1 = wrap ? (more ? base1 : src1) : src1 + BK * 2;
+        st1 = st1 + 1 == NSW ? 0 : st1 + 1;
+        dst1 = smem_w + st1 * SW;
+        return wrap && more;
+    };
+    auto load = [&](auto lc) {
+        constexpr int l = decltype(lc)::value;
+        if constexpr (ROLES) {
+            if (LA == LW || l < (loads_a ? LA : LW))
+                load_to_lds_b128(src0 + off[l], dst0 + group_of(l, loads_a ? GA : GW) * 1024);
+        } else if constexpr (l < LA) {
+            load_to_lds_b128(src0 + off[l], dst0 + group_of(l, GA) * 1024);
+        } else {
+            load_to_lds_b128(src1 + off[l], dst1 + group_of(l - LA, GW) * 1024);
+        }
+    };
+    constexpr int LOADS = ROLES ? LMAX : LA + LW;
+    set_off0(m0, n0);
+    set_off1(n0);
+    f32x4 acc[TM][TN];
+    f32x4 bias[TN];
+    auto load_bias = [&](int n) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int c = n + wn * (16 * TN) + 16 * j + 4 * lq;
+            bias[j] = *reinterpret_cast<const f32x4*>(g.bias + (c < g.N ? c : 0));
+        }
+    };
+    const int key = (l15 >> 1) & 7;
+    const int a_frag = (wm * (16 * TM) + l15) * (BK * 2), w_frag = (wn * (16 * TN) + l15) * (BK * 2);
+    const int co0 = (lq ^ key) << 4, co1 = ((4 + lq) ^ key) << 4;
+    bf16x8 fa[2][TM], fb[2][TN];
+    // fragment r of k half s: the TM rows of A, then the TN rows of W
+    auto read = [&](auto sc, auto rc, const unsigned char* pa, const unsigned char* pw) {
+        constexpr int s = decltype(sc)::value, r = decltype(rc)::value;
+        if constexpr (r < TM) fa[s][r] = *reinterpret_cast<const bf16x8*>(pa + (s ? co1 : co0) + r * (16 * BK * 2));
+        else fb[s][r - TM] = *reinterpret_cast<const bf16x8*>(pw + (s ? co1 : co0) + (r - TM) * (16 * BK * 2));
+    };
+    auto barrier = [&]() {
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        // Loads are unconditional (past the end they re-read the last tile into a stage nobody reads again)
-        // so that the wait count above is the same in every iteration.
-        issue_loads(min(tt + NS - 1, nk - 1), (s + NS - 1) % NS);
-        compute(s);
-        issue_pipeline(true);
     };
-    if (nk > 0) {
+    // The MFMAs of k half s in program order, with the fragment reads of the other half among the first three
+    // quarters of them and (s = 1) the tile loads spread over all of them.
+    auto half = [&](auto sc, const unsigned char* pa, const unsigned char* pw) {
+        constexpr int s = decltype(sc)::value;
+        constexpr int kM = TM * TN, kR = TM + TN, kL = s == 1 ? LOADS : 0;
+        constexpr int kSpan = kM * 3 / 4 > 0 ? kM * 3 / 4 : 1;
+        static_for<kM>([&](auto mc) {
+            constexpr int m = decltype(mc)::value;
+            constexpr int i = m / TN, j = m % TN;
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[s][j], fa[s][i], acc[i][j], 0, 0, 0);
+            constexpr int r0 = m < kSpan ? m * kR / kSpan : kR, r1 = m < kSpan ? (m + 1) * kR / kSpan : kR;
+            static_for<r1 - r0>([&](auto q) { read(std::integral_constant<int, 1 - s>{}, std::integral_constant<int, r0 + decltype(q)::value>{}, pa, pw); });
+            constexpr int l0 = m * kL / kM, l1 = (m + 1) * kL / kM;
+            static_for<l1 - l0>([&](auto q) {
+                constexpr int l = l0 + decltype(q)::value;
+                load(std::integral_constant<int, l>{});
+            });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    const std::integral_constant<int, 0> s0;
+    const std::integral_constant<int, 1> s1;
+    // loads of a wave that may still be in flight when k tile t + 1 has to be there
+    constexpr int kWait0 = ROLES ? (NSA - 2) * LA : (NSA - 2) * (LA + LW) + (NSW - NSA) * LW, kWait1 = (NSW - 2) * LW;
+    auto wait_loads = [&](auto extra) {                      // extra: k tiles beyond that
+        constexpr int x = decltype(extra)::value;
+        constexpr int w0 = kWait0 + x * (ROLES || NSW > NSA ? LA : LA + LW), w1 = kWait1 + x * LW;
+        static_assert(w0 < 63 && w1 < 63, "waits");
+        if (!ROLES || w0 == w1) {
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(w0));
+        } else if (loads_a) {
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(w0));
+        } else {
+            __builtin_amdgcn_s_waitcnt(vmcnt_only(w1));
+        }
+    };
 #pragma unroll
-        for (int p = 0; p < NS - 1; ++p) issue_loads(min(p, nk - 1), p);
-    }
-    int i = 0;
-    for (; i + NS <= nk; i += NS) {
-        step(std::integral_constant<int, 0>{}, i);
-        if constexpr (NS > 1) step(std::integral_constant<int, 1 % NS>{}, i + 1);
-        if constexpr (NS > 2) step(std::integral_constant<int, 2 % NS>{}, i + 2);
-        if constexpr (NS > 3) step(std::integral_constant<int, 3 % NS>{}, i + 3);
-    }
-    if (i < nk) step(std::integral_constant<int, 0>{}, i);
-    if constexpr (NS > 2) {
-        if (i + 1 < nk) step(std::integral_constant<int, 1 % NS>{}, i + 1);
-    }
-    if constexpr (NS > 3) {
-        if (i + 2 < nk) step(std::integral_constant<int, 2 % NS>{}, i + 2);
-    }
-
-    // ---- epilogue: every direct load has landed and every wave has left the k loop before the stages
-    // are reused as staging space
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __syncthreads();
-    float* stage = reinterpret_cast<float*>(smem_raw) + wave * EPI_WAVE_FLOATS;
-    run_epilogue<TM, TN>(g, acc, stage, m0 + wm * (32 * TM), n0 + wn * (32 * TN), lane);
-}
-
-
-// ---------------------------------------------------------------------------------------------------
-// Ring variant of the direct-load kernel: k tiles of 32 in a ring of four LDS stages, eight waves, a branch-free
-// loop body in which a wave issues one direct load every fourth MFMA (the compute unit's loads arrive as an
-// even stream three tiles ahead instead of a burst after the barrier that blocks the issuing waves) and reads
-// the next k step's fragments between the MFMAs of the current one.
-template <int WM, int WN, int TM, int TN>
-__global__ __launch_bounds__(512, 1) void gemm_ring_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m,
-                                                           int splitk) {
-    static_assert(WM * WN == 8, "eight waves");
-    constexpr int NW = 8, BK = 32, NS = 4;
-    constexpr int BM = 32 * TM * WM;
-    constexpr int BN = 32 * TN * WN;
-    constexpr int LPW = (BM + BN) / 16 / NW;         // a wave load fills 16 rows of 64 bytes
-    static_assert(LPW == 4 && BM % 128 == 0, "256 x 256 tiles");
-    constexpr int LPW_A = BM / 128;
-    constexpr int STAGE_BYTES = (BM + BN) * BK * 2;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN;
-    const int wn = wave % WN;
-    const int l31 = lane & 31;
-    const int lh = lane >> 5;
-
-    const int nwg = gridDim.x;
-    const int logical = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
-    const int tiles = tiles_m * tiles_n;
-    if (logical >= tiles * splitk) return;
-    const int ks = logical / tiles;                              // which part of k (0 when k is not split)
-    const int t = logical - ks * tiles;
-    const int group_size = group_m * tiles_n;
-    const int grp = t / group_size;
-    const int first_m = grp * group_m;
-    const int gm = min(tiles_m - first_m, group_m);
-    const int in_grp = t - grp * group_size;
-    const int tile_m = first_m + in_grp % gm;
-    const int tile_n = in_grp / gm;
-    const int m0 = tile_m * BM;
-    const int n0 = tile_n * BN;
-    const int nk_all = g.K / BK;
-    const int kt0 = (int)((long long)ks * nk_all / splitk);
-    const int nk = (int)((long long)(ks + 1) * nk_all / splitk) - kt0;
-    if (splitk > 1) {                                            // this part's fp32 partial sums, plain stores
-        g.out = g.splitk_partials + (size_t)ks * g.M * g.N;
-        g.epilogue = kEpiPartial;
-        g.bias = nullptr;
-    }
-
-    uint32_t off[LPW];
-    {
-        const int rsub = 16 * wave + (lane >> 2);
-        const int c = (lane & 3) ^ ((rsub >> 2) & 3);            // 128 i does not change (r / 4) % 4
+    for (int j = 0; j < TN; ++j) bias[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (g.bias != nullptr && splitk == 1) load_bias(n0);
+    constexpr bool kPre = TM * TN <= 16;
+    f32x4 xpre[kPre ? TM * TN : 1];
+    auto load_x = [&]() {
+        if constexpr (kPre) {
+            if (splitk == 1 && (g.epilogue == kEpiGatedResidual || g.epilogue == kEpiResidual)) {
 #pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            const int r = rsub + 128 * i;
-            const int row = (i < LPW_A) ? min(m0 + r, g.M - 1) : min(n0 + r - BM, g.N - 1);
-            off[i] = (uint32_t)row * (uint32_t)g.K * 2u + (uint32_t)c * 16u;
+                for (int i = 0; i < TM; ++i) {
+                    const float* xr = reinterpret_cast<const float*>(g.out) + (size_t)min(m0 + wm * (16 * TM) + 16 * i + l15, g.M - 1) * g.N;
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        const int c = n0 + wn * (16 * TN) + 16 * j + 4 * lq;
+                        xpre[i * TN + j] = *reinterpret_cast<const f32x4*>(xr + (c < g.N ? c : 0));
+                    }
+                }
+            }
+        }
+    };
+    load_x();
+    if constexpr (ROLES) {
+        for (int p = 0; p < stages0; ++p) {
+            static_for<LOADS>([&](auto l) { load(l); });
+            next0(false, nk);
+        }
+    } else {
+#pragma unroll
+        for (int p = 0; p < NSW; ++p) {
+            if (p < NSA) {
+                static_for<LA>([&](auto l) { load(l); });
+                next0(false, nk);
+            }
+            static_for<LW>([&](auto l) { load(std::integral_constant<int, LA + decltype(l)::value>{}); });
+            next1(false, nk);
         }
     }
-    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(g.a) + (size_t)kt0 * (BK * 2);
-    const unsigned char* w_base = reinterpret_cast<const unsigned char*>(g.w) + (size_t)kt0 * (BK * 2);
-    // load i of tile kt (clamped: past the end the last tile is fetched again into a stage nobody reads) into
-    // the stage of iteration index st
-    auto issue_load = [&](auto ic, int kt, int st) {
-        constexpr int i = decltype(ic)::value;
-        unsigned char* dst = smem_raw + (st & (NS - 1)) * STAGE_BYTES + (wave + NW * i) * 1024;
-        load_to_lds_b128((i < LPW_A ? a_base : w_base) + (size_t)kt * (BK * 2) + off[i], dst);
-    };
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    const int a_row0 = wm * (32 * TM) + l31;
-    const int b_row0 = BM + wn * (32 * TN) + l31;
-    bf16x8 fa[2][TM], fb[2][TN];
-    auto read_step = [&](auto sc, int kt) {
-        constexpr int s = decltype(sc)::value;
-        const bf16* st = reinterpret_cast<const bf16*>(smem_raw + (kt & (NS - 1)) * STAGE_BYTES);
-        const int coff = ((2 * s + lh) ^ ((l31 >> 2) & 3)) << 3;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) fa[s][i] = *reinterpret_cast<const bf16x8*>(st + (a_row0 + 32 * i) * BK + coff);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) fb[s][j] = *reinterpret_cast<const bf16x8*>(st + (b_row0 + 32 * j) * BK + coff);
-    };
-    auto mfma_step = [&](auto sc) {
-        constexpr int s = decltype(sc)::value;
+    wait_loads(s1);                                          // k tile 0 has landed
+    barrier();
+    int sa = 0, sw = 0;
+    bool landed = false;                 // k tile 1 of this output tile is known to have landed
+    for (;;) {
+        const int next = tile + per_xcd;
+        const bool more = next < t_end;
+        int nm0 = m0, nn0 = n0;
+        if (more) locate(next, nm0, nn0);
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s][i], fb[s][j], acc[i][j], 0, 0, 0);
-    };
-    // half an iteration: TM TN MFMAs, TM + TN fragment reads among the first of them, two loads at a quarter and
-    // three quarters
-    auto order_half = [&]() {
-        constexpr int kM = TM * TN;
-#pragma unroll
-        for (int m = 0; m < kM; ++m) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            if (m < TM + TN) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-            if (m == kM / 4 || m == 3 * kM / 4) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            for (int j = 0; j < TN; ++j) acc[i][j] = bias[j];
+        {
+            const unsigned char* pa = smem + sa * SA + a_frag;
+            const unsigned char* pw = smem_w + sw * SW + w_frag;
+            static_for<TM + TN>([&](auto r) { read(s0, r, pa, pw); });
         }
-    };
-    auto barrier = [&]() {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    };
-
-    const std::integral_constant<int, 0> c0;
-    const std::integral_constant<int, 1> c1;
-    const std::integral_constant<int, 2> c2;
-    const std::integral_constant<int, 3> c3;
-    for (int p = 0; p < 3; ++p) {
-        const int kt = min(p, nk - 1);
-        issue_load(c0, kt, p);
-        issue_load(c1, kt, p);
-        issue_load(c2, kt, p);
-        issue_load(c3, kt, p);
-    }
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(LPW));      // tiles 0 and 1 have landed
-    barrier();
-    read_step(c0, 0);
-    for (int kt = 0; kt < nk; ++kt) {
-        const int lt = min(kt + 3, nk - 1);
-        __builtin_amdgcn_sched_barrier(0);
-        issue_load(c0, lt, kt + 3);
-        issue_load(c1, lt, kt + 3);
-        read_step(c1, kt);
-        mfma_step(c0);
-        order_half();
-        __builtin_amdgcn_sched_barrier(0);
-        issue_load(c2, lt, kt + 3);
-        issue_load(c3, lt, kt + 3);
-        read_step(c0, min(kt + 1, nk - 1));
-        mfma_step(c1);
-        order_half();
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(LPW));   // all but the newest tile's loads have landed
-        barrier();
-    }
-
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __syncthreads();
-    float* stage = reinterpret_cast<float*>(smem_raw) + wave * EPI_WAVE_FLOATS;
-    run_epilogue<TM, TN>(g, acc, stage, m0 + wm * (32 * TM), n0 + wn * (32 * TN), lane);
-}
-
-// ---------------------------------------------------------------------------------------------------
-// Alternating kernel for shapes that fill the chip with 256 x 256 tiles.  The eight waves work as two groups of
-// four (one wave of each group on every SIMD) that run half a step apart.  A step of a wave is a memory phase (all
-// fragment reads of the step, its share of the direct loads, then the waits) and a matrix phase (nothing but the
-// step's 16 MFMAs), each closed by a workgroup barrier; group 1 takes one extra barrier before its first step and
-// group 0 one after its last, so while one wave of a SIMD issues MFMAs back to back the other one reads LDS and
-// waits, and the matrix pipe does not drain at a barrier that both of its waves reach together.
-//   Rows are fetched in whole 128-byte lines (k tiles of 64).  A stage of 64 k is 64 KB and the LDS holds two and a
-// half, so the ring is kept in half stages of 32 KB: unit 2t = the 256 rows of A for k tile t, unit 2t + 1 = the
-// 256 rows of W, unit u in slot u % 5.  A step is half a k tile (two MFMA k steps); step 2t + h reads its fragments
-// from the slots of units 2t and 2t + 1 at column half h and issues the loads of unit 2t + h + 3 into the slot that
-// unit 2t + h - 2 left.
-//   Barrier j (counted after the prologue's) closes the memory phase of step c for group 0 when j = 2c + 1, for
-//   group 1 when j = 2c + 2.  Units 2t + 2 and 2t + 3 are first read in step 2t + 2, i.e. after barrier 4t + 4;
-//   every wave waits for its own loads of both at the end of its memory phase of step 2t + 1 (only the loads of
-//   unit 2t + 4 may still be in flight), i.e. before barrier 4t + 4 at the latest.  The slot of unit u - 5 was last
-//   read in the memory phase of step u - 4 or u - 5 (the odd step of its tile) by group 1, which waits for its
-//   fragments before the barrier that closes that phase; the loads of unit u are issued in step u - 3, after it.
-//   Measured with s_memtime on one wave of each group (8192^3, clocks per step of 32 k; the step's MFMAs alone
-// are 1030 per SIMD): fragment reads 250, direct loads 400, waits and barrier 100 = a memory phase of 750 against
-// a matrix phase of 515, so a step takes 2 x 750.  What fills the memory phase is the LDS pipeline: about 5 clocks per
-// ds_read_b128 of a wave and 25 per direct load here (alone on a compute unit a kilobyte takes 4.6 clocks to read,
-// 16 to load directly and 13 to write with ds_write_b128: the rate microkernel of peaks.hip), whichever order the
-// two are issued in and however far ahead the loads run (neither the latency of the loads nor the L2 is the limit:
-// the same clocks per step with 16 workgroups and with 256, where the core clock drops from 2.4 to 1.8 GHz).
-// Tried on this structure and dropped, all within the run-to-run spread of the figure above or worse: k tiles of 32
-// in four or five stages (same clocks per step); reads and loads interleaved three to one, or half of the waves
-// loading first (memory phase 740 to 770); the units staged through registers (global -> registers in the matrix
-// phase, ds_write_b128 in the memory phase: memory phase 680; with the writes in the matrix phase too the MFMA
-// wave stalls behind the other group's reads and a step grows by a fifth).
-template <int WM, int WN, int TM, int TN>
-__global__ __launch_bounds__(512, 1) void gemm_alt64_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m,
-                                                             int splitk) {
-    static_assert(WM * WN == 8 && 32 * TM * WM == 256 && 32 * TN * WN == 256, "eight waves, 256 x 256 tiles");
-    constexpr int NW = 8, BK = 64, SLOTS = 5, LPW = 4;
-    constexpr int BM = 256;
-    constexpr int UNIT_BYTES = 256 * BK * 2;         // 32 KB
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN;
-    const int wn = wave % WN;
-    const int l31 = lane & 31;
-    const int lh = lane >> 5;
-
-    const int nwg = gridDim.x;
-    const int logical = (blockIdx.x & 7) * (nwg >> 3) + (blockIdx.x >> 3);
-    const int tiles = tiles_m * tiles_n;
-    if (logical >= tiles * splitk) return;
-    const int ks = logical / tiles;                              // which part of k (0 when k is not split)
-    const int t_id = logical - ks * tiles;
-    const int group_size = group_m * tiles_n;
-    const int grp = t_id / group_size;
-    const int first_m = grp * group_m;
-    const int gm = min(tiles_m - first_m, group_m);
-    const int in_grp = t_id - grp * group_size;
-    const int tile_m = first_m + in_grp % gm;
-    const int tile_n = in_grp / gm;
-    const int m0 = tile_m * BM;
-    const int n0 = tile_n * 256;
-    const int nt_all = g.K / BK;
-    const int kt0 = (int)((long long)ks * nt_all / splitk);
-    const int nt = (int)((long long)(ks + 1) * nt_all / splitk) - kt0;
-    if (splitk > 1) {                                            // this part's fp32 partial sums, plain stores
-        g.out = g.splitk_partials + (size_t)ks * g.M * g.N;
-        g.epilogue = kEpiPartial;
-        g.bias = nullptr;
-    }
-
-    // A wave load fills 8 rows of 128 bytes; the lane that fills chunk position p of row r fetches logical chunk
-    // p ^ ((r / 2) % 8) of that row (the swizzle of gemm_dma_kernel).
-    uint32_t off_a[LPW], off_b[LPW];
-#pragma unroll
-    for (int i = 0; i < LPW; ++i) {
-        const int r = 8 * (wave + NW * i) + (lane >> 3);
-        const int c = (lane & 7) ^ ((r >> 1) & 7);
-        off_a[i] = (uint32_t)min(m0 + r, g.M - 1) * (uint32_t)g.K * 2u + (uint32_t)c * 16u;
-        off_b[i] = (uint32_t)min(n0 + r, g.N - 1) * (uint32_t)g.K * 2u + (uint32_t)c * 16u;
-    }
-    const unsigned char* a_base = reinterpret_cast<const unsigned char*>(g.a) + (size_t)kt0 * (BK * 2);
-    const unsigned char* w_base = reinterpret_cast<const unsigned char*>(g.w) + (size_t)kt0 * (BK * 2);
-    // the rows of A (of W) for k tile t, clamped (past the end the last tile is fetched again into a slot nobody reads)
-    auto issue_a = [&](int t, int slot) {
-        const unsigned char* src = a_base + (size_t)min(t, nt - 1) * (BK * 2);
-        unsigned char* dst = smem_raw + slot * UNIT_BYTES + wave * 1024;
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) load_to_lds_b128(src + off_a[i], dst + i * (NW * 1024));
-    };
-    auto issue_b = [&](int t, int slot) {
-        const unsigned char* src = w_base + (size_t)min(t, nt - 1) * (BK * 2);
-        unsigned char* dst = smem_raw + slot * UNIT_BYTES + wave * 1024;
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) load_to_lds_b128(src + off_b[i], dst + i * (NW * 1024));
-    };
-
-    f32x16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
-
-    const int a_row0 = wm * (32 * TM) + l31;
-    const int b_row0 = wn * (32 * TN) + l31;
-    const int key = (l31 >> 1) & 7;
-    bf16x8 fa[2][TM], fb[2][TN];
-    // fragments of the two MFMA k steps of column half h
-    auto read_half = [&](auto hc, int slot_a, int slot_b) {
-        constexpr int h = decltype(hc)::value;
-        const bf16* sa = reinterpret_cast<const bf16*>(smem_raw + slot_a * UNIT_BYTES);
-        const bf16* sb = reinterpret_cast<const bf16*>(smem_raw + slot_b * UNIT_BYTES);
-#pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
-            const int coff = ((2 * (2 * h + s2) + lh) ^ key) << 3;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) fa[s2][i] = *reinterpret_cast<const bf16x8*>(sa + (a_row0 + 32 * i) * BK + coff);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) fb[s2][j] = *reinterpret_cast<const bf16x8*>(sb + (b_row0 + 32 * j) * BK + coff);
+        for (int t = 0; t < nk; ++t) {
+            const int na = sa + 1 == NSA ? 0 : sa + 1, nw = sw + 1 == NSW ? 0 : sw + 1;
+            __builtin_amdgcn_sched_barrier(0);
+            half(s0, smem + sa * SA + a_frag, smem_w + sw * SW + w_frag);
+            if (!landed) wait_loads(s0);
+            landed = false;
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+            barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            half(s1, smem + na * SA + a_frag, smem_w + nw * SW + w_frag);
+            if (next0(more, nk)) set_off0(nm0, nn0);
+            if constexpr (!ROLES) {
+                if (next1(more, nk)) set_off1(nn0);
+            }
+            sa = na;
+            sw = nw;
         }
-    };
-    auto mfma_half = [&]() {
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[s2][i], fb[s2][j], acc[i][j], 0, 0, 0);
-    };
-    auto barrier = [&]() {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    };
-    auto next = [](int slot, int by) { return slot + by >= SLOTS ? slot + by - SLOTS : slot + by; };
-
-    const std::integral_constant<int, 0> h0;
-    const std::integral_constant<int, 1> h1;
-    const bool second_group = wave >= NW / 2;        // wave-uniform (wave is in a scalar register)
-    issue_a(0, 0);
-    issue_b(0, 1);
-    issue_a(1, 2);
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(LPW));      // units 0 and 1 have landed
-    barrier();
-    if (second_group) barrier();
-    int sa = 0, sb = 1, sl = 3;                      // slots of A and W of tile t, slot of the next unit to load
-    for (int t = 0; t < nt; ++t) {
-        // ---- step 2t, memory phase: fragments of the first column half, loads of unit 2t + 3 (W of tile t + 1)
-        __builtin_amdgcn_sched_barrier(0);
-        read_half(h0, sa, sb);
-        issue_b(t + 1, sl);
-        sl = next(sl, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xC07F);          // the fragments are in registers (lgkmcnt 0, no wait on loads)
-        barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_half();
-        __builtin_amdgcn_sched_barrier(0);
-        barrier();
-        // ---- step 2t + 1: second column half, loads of unit 2t + 4 (A of tile t + 2); tile t + 1 has landed
-        __builtin_amdgcn_sched_barrier(0);
-        read_half(h1, sa, sb);
-        issue_a(t + 2, sl);
-        sl = next(sl, 1);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(vmcnt_imm(LPW) & 0xF0FF);
-        barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_half();
-        __builtin_amdgcn_sched_barrier(0);
-        barrier();
-        sa = next(sa, 2);
-        sb = next(sb, 2);
+        for (int j = 0; j < TN; ++j) bias[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (more && g.bias != nullptr) {                     // waited for before the next tile's MFMAs, and with it every older load
+            load_bias(nn0);
+            landed = true;
+        }
+        const int row0 = m0 + wm * (16 * TM), col0 = n0 + wn * (16 * TN);
+        switch (splitk > 1 ? (int)kEpiPartial : g.epilogue) {
+            case kEpiBias: store_wave<TM, TN, kEpiBias>(g, g.out, acc, row0, col0, lane); break;
+            case kEpiBiasGelu: store_wave<TM, TN, kEpiBiasGelu>(g, g.out, acc, row0, col0, lane); break;
+            case kEpiGatedResidual: store_wave<TM, TN, kEpiGatedResidual>(g, g.out, acc, row0, col0, lane, xpre); break;
+            case kEpiPartial:                                // the partial sums of a k part, or a plain fp32 output
+                store_wave<TM, TN, kEpiPartial>(g, splitk > 1 ? g.splitk_partials + (size_t)ks * g.M * g.N : reinterpret_cast<float*>(g.out), acc,
+                                                row0, col0, lane);
+                break;
+            default: store_wave<TM, TN, kEpiResidual>(g, g.out, acc, row0, col0, lane, xpre); break;
+        }
+        if (!more) break;
+        tile = next;
+        m0 = nm0;
+        n0 = nn0;
+        load_x();
     }
-    if (!second_group) barrier();
-
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __syncthreads();
-    float* stage = reinterpret_cast<float*>(smem_raw) + wave * EPI_WAVE_FLOATS;
-    run_epilogue<TM, TN>(g, acc, stage, m0 + wm * (32 * TM), n0 + wn * (32 * TN), lane);
-}
-
-template <int WM, int WN, int TM, int TN>
-hipError_t launch_ring(const GemmArgs& g, int splitk, hipStream_t s) {
-    constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
-    constexpr size_t smem = (size_t)4 * (BM + BN) * 32 * sizeof(bf16);
-    static_assert(smem <= 160 * 1024 && smem >= (size_t)8 * EPI_WAVE_FLOATS * sizeof(float), "LDS");
-    const int tiles_m = (g.M + BM - 1) / BM;
-    const int tiles_n = (g.N + BN - 1) / BN;
-    const int grid = (tiles_m * tiles_n * splitk + 7) / 8 * 8;
-    static std::once_flag attr_once;          // one per instantiation
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(attr_once, [&]() {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_ring_kernel<WM, WN, TM, TN>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    });
-    if (attr_err != hipSuccess || attributes_only()) return attr_err;
-    // groups of four tile rows: an XCD's 32 concurrent tiles then cover 4 x 8 tiles, the shape with the fewest
-    // distinct operand rows per k step
-    hipLaunchKernelGGL((gemm_ring_kernel<WM, WN, TM, TN>), dim3(grid), dim3(512), smem, s, g, tiles_m, tiles_n, 4, splitk);
-    return hipGetLastError();
-}
-
-template <int WM, int WN, int TM, int TN>
-hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
-    constexpr size_t smem = (size_t)5 * 256 * 64 * sizeof(bf16);      // five half stages: all 160 KB
-    static_assert(smem <= 160 * 1024 && smem >= (size_t)8 * EPI_WAVE_FLOATS * sizeof(float), "LDS");
-    const int tiles_m = (g.M + 255) / 256;
-    const int tiles_n = (g.N + 255) / 256;
-    const int grid = (tiles_m * tiles_n * splitk + 7) / 8 * 8;
-    static std::once_flag attr_once;          // one per instantiation
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(attr_once, [&]() {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_alt64_kernel<WM, WN, TM, TN>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    });
-    if (attr_err != hipSuccess || attributes_only()) return attr_err;
-    hipLaunchKernelGGL((gemm_alt64_kernel<WM, WN, TM, TN>), dim3(grid), dim3(512), smem, s, g, tiles_m, tiles_n, 4, splitk);
-    return hipGetLastError();
-}
-
-template <int WM, int WN, int TM, int TN, int NS>
-hipError_t launch_dma(const GemmArgs& g, int splitk, hipStream_t s) {
-    constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
-    constexpr size_t smem = (size_t)NS * (BM + BN) * 64 * sizeof(bf16);
-    static_assert(smem <= 160 * 1024, "LDS stages exceed 160 KB");
-    static_assert(smem >= (size_t)WM * WN * EPI_WAVE_FLOATS * sizeof(float), "epilogue staging");
-    const int tiles_m = (g.M + BM - 1) / BM;
-    const int tiles_n = (g.N + BN - 1) / BN;
-    const int grid = (tiles_m * tiles_n * splitk + 7) / 8 * 8;
-    static std::once_flag attr_once;          // one per instantiation
-    static hipError_t attr_err = hipSuccess;
-    std::call_once(attr_once, [&]() {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dma_kernel<WM, WN, TM, TN, NS>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    });
-    if (attr_err != hipSuccess || attributes_only()) return attr_err;
-    const int group_m = (32 * TM * WM >= 256) ? 4 : 8;
-    hipLaunchKernelGGL((gemm_dma_kernel<WM, WN, TM, TN, NS>), dim3(grid), dim3(64 * WM * WN), smem, s, g, tiles_m, tiles_n,
-                       group_m, splitk);
-    return hipGetLastError();
+    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));               // no direct load may still be on its way to this LDS
 }
 
 struct TilePlan {
     int tm, tn, pf;       // register-staged kernel: tile (128 tm) x (32 tn), pf register sets
-    int dma = 0;          // otherwise: a configuration of the direct-load kernel (tm, tn, pf unused)
-    int splitk = 1;       // register-staged kernel: parts of the k range, each its own workgroup (needs scratch)
+    int dma = 0;          // otherwise: a configuration of gemm_alt64_kernel (tm, tn, pf unused)
+    int splitk = 1;       // parts of the k range, each its own workgroup (needs scratch)
 };
+constexpr int kUnits = 256;                   // compute units
 
-// Tile plans measured on MI355X for the projection shapes of the 1.3B- and 14B-shaped blocks with a
-// 1024-token chunk (sweep over every (TM, TN, PF) of the register-staged kernel and every configuration of
-// the direct-load kernel).
-struct TunedShape {
-    int M, N, K;
-    TilePlan plan;
-};
-const TunedShape kTuned[] = {
-    // the 1.3B block on one 1024-token chunk, weights cold (every launch of the sweep reads another copy): small
-    // tiles of the direct-load kernel are 2 to 12 % faster than the register-staged kernel's best
-    {1024, 4608, 1536, {0, 0, 0, 16}},         // QKV: 128 x 192, eight waves
-    {1024, 1536, 1536, {0, 0, 0, 9}},          // C x C projections: 128 x 64, eight waves of 32 x 32
-    {1024, 8960, 1536, {0, 0, 0, 13}},         // FFN-1: 128 x 160, two stages, two workgroups per unit
-    {1024, 1536, 8960, {0, 0, 0, 16, 4}},      // FFN-2: 128 x 192, four k parts
-    {1024, 5120, 5120, {1, 5, 2}},  {1024, 5120, 13824, {0, 0, 0, 5, 3}},      // FFN-2 14B: ring, 256 x 256 tiles, three k parts
-    // the 1.3B block with 2 or 4 streams per call, where the rule below is more than 4 % off the sweep's best
-    {2048, 1536, 8960, {1, 6, 2, 0, 2}}, {4096, 8960, 1536, {1, 5, 2}}, {4096, 1536, 8960, {1, 6, 2}},
-    {4096, 1536, 1536, {0, 0, 0, 16}}, {4096, 4608, 1536, {0, 0, 0, 16}},
-};
-
-// Otherwise: when 256 x 256 tiles fill at least 80 % of the compute units in every round, the direct-load
-// kernel with that tile wins (it moves the fewest bytes per flop through the LDS and the L2), in its alternating
-// variant (+6 to +9 % over the ring variant on the batched 480p shapes, equal within 2 % on the 1024-row shapes of the
-// 14B block; the ring variant is +2 to +15 % over the two-stage one).  Else estimate the time of the busiest compute unit for the register-staged kernel: one k
-// tile of a workgroup costs a fixed part (~0.25 us alone, half of it when a second workgroup fills the
-// bubbles) plus ~21 ns per MFMA a wave issues (fitted to the sweep); small tiles fit two workgroups per unit.
-// The direct-load kernels address an operand with 32-bit byte offsets per lane: they serve operands below 4 GiB.
+// gemm_alt64_kernel addresses an operand with 32-bit byte offsets per lane: it serves operands below 4 GiB.
 bool fits_32bit_offsets(int M, int N, int K) {
     return (unsigned long long)M * K * 2 <= 0xFFFFFFFFull && (unsigned long long)N * K * 2 <= 0xFFFFFFFFull;
 }
 
-TilePlan plan_tiles(int M, int N, int K, int epilogue) {
-    (void)epilogue;
-    const bool direct_ok = fits_32bit_offsets(M, N, K);
-    for (const TunedShape& t : kTuned)
-        if (t.M == M && t.N == N && t.K == K && (direct_ok || !t.plan.dma)) return t.plan;
-    const int kCUs = 256;
-    if (direct_ok) {
-        const long long tiles = (long long)((M + 255) / 256) * ((N + 255) / 256);
-        const long long rounds = (tiles + kCUs - 1) / kCUs;
-        if (K >= 512 && tiles * 10 >= rounds * kCUs * 8) return TilePlan{0, 0, 0, 18};
-    }
+// Operands of 4 GiB and more: the time of the busiest compute unit for the register-staged kernel; one k tile of a
+// workgroup costs a fixed part (~0.25 us alone, half of it when a second workgroup fills the bubbles) plus ~21 ns per
+// MFMA a wave issues (fitted to a sweep); small tiles fit two workgroups per unit.
+TilePlan plan_register_staged(int M, int N, int K) {
     TilePlan best{1, 4, 2};
     double best_cost = 1e300;
     for (int tm = 1; tm <= 2; ++tm) {
         for (int tn = 2; tn <= 7; ++tn) {
             const int wgs = ((M + 128 * tm - 1) / (128 * tm)) * ((N + 32 * tn - 1) / (32 * tn));
             const int occ = (tm * tn <= 5) ? 2 : 1;
-            const int per_cu = (wgs + kCUs - 1) / kCUs;
+            const int per_cu = (wgs + kUnits - 1) / kUnits;
             const double mfma = 0.021 * 4 * tm * tn;
             double cost;
             if (occ == 2 && per_cu >= 2) cost = (per_cu + 1) / 2 * (0.25 + 2 * mfma);
@@ -1023,41 +817,147 @@ hipError_t launch_tn(const GemmArgs& g, int tn, int splitk, hipStream_t s) {
     return hipErrorInvalidValue;
 }
 
-// Configurations of the direct-load kernel: (waves on M, waves on N, TM, TN, LDS stages).  Ids 1-6 are the large
-// tiles for shapes that fill the chip; ids 7 and up are small tiles for the skinny shapes of a single 1024-token
-// chunk, where the tile count has to reach the number of compute units and a k iteration holds only a few matrix
-// instructions per wave: no staging registers and no LDS write instructions, three or four tiles in flight, and
-// two or three workgroups per compute unit to cover the barrier.
-constexpr int kDmaConfigs = 18;
-hipError_t launch_dma_config(const GemmArgs& g, int id, int splitk, hipStream_t s) {
+// Configurations of gemm_alt64_kernel: waves on M and N, wave tile in 16-row and 16-column blocks, stages of A and W,
+// ROLES, waves per SIMD the registers are budgeted for, workgroups per compute unit; then what a launch costs in
+// microseconds:  c + rounds * (k tiles * a + b),  a = one k tile with the chip full of such tiles, b = prologue and
+// epilogue of a tile, c = launch and drain.  `rounds` counts full rounds (one tile in every slot of the chip) and, for
+// a last round that fills the share x of the slots, p + (1 - p) x of a round: less traffic and a higher clock, but no
+// less latency (two workgroups per unit: p + s x up to x = 1/2, where a unit has one, q + (1 - q) x above).  Fitted to 232
+// random shapes of 128 to 18 720 rows with K = 512 to 29 000 (root mean square error 7 to 14 %; the configuration
+// picked is on average 2 % slower than the best of all of them).
+#define SDV2_TILE_CONFIGS(X)                                                                                   \
+    X(1, 2, 4, 8, 4, 2, 3, false, 2, 1, 1.53f, 12.6f, 3.1f, 0.78f, 0.22f, 1.0f)      /* 256 x 256 */           \
+    X(2, 2, 4, 6, 4, 2, 3, true, 2, 1, 1.12f, 9.5f, 2.8f, 0.67f, 0.33f, 1.0f)        /* 192 x 256 */           \
+    X(3, 2, 4, 8, 3, 2, 3, false, 2, 1, 1.18f, 9.1f, 2.4f, 0.72f, 0.28f, 1.0f)       /* 256 x 192 */           \
+    X(4, 4, 2, 4, 5, 3, 3, false, 2, 1, 1.02f, 7.9f, 2.8f, 0.71f, 0.29f, 1.0f)       /* 256 x 160 */           \
+    X(5, 4, 2, 4, 4, 3, 3, false, 2, 1, 0.885f, 5.0f, 4.1f, 0.67f, 0.33f, 1.0f)      /* 256 x 128 */           \
+    X(6, 2, 4, 6, 3, 2, 4, true, 2, 1, 0.947f, 5.8f, 3.6f, 0.71f, 0.29f, 1.0f)       /* 192 x 192 */           \
+    X(7, 4, 2, 2, 6, 4, 4, true, 2, 1, 0.734f, 2.7f, 4.9f, 0.73f, 0.27f, 1.0f)       /* 128 x 192 */           \
+    X(8, 4, 2, 2, 5, 4, 4, true, 2, 1, 0.659f, 2.3f, 4.0f, 0.76f, 0.24f, 1.0f)       /* 128 x 160 */           \
+    X(9, 4, 2, 2, 4, 4, 5, true, 2, 1, 0.572f, 1.8f, 4.0f, 0.75f, 0.25f, 1.0f)       /* 128 x 128 */           \
+    X(10, 4, 2, 2, 3, 5, 5, true, 2, 1, 0.475f, 1.5f, 3.6f, 0.81f, 0.19f, 1.0f)      /* 128 x 96 */            \
+    X(11, 4, 2, 3, 4, 3, 4, true, 2, 1, 0.717f, 3.65f, 4.0f, 0.68f, 0.32f, 1.0f)     /* 192 x 128 */           \
+    X(12, 2, 2, 4, 6, 2, 2, false, 2, 2, 1.33f, 3.2f, 2.9f, 0.59f, 0.36f, 0.98f)     /* 128 x 192, two */      \
+    X(13, 2, 2, 4, 2, 3, 3, false, 2, 2, 0.724f, 0.0f, 3.66f, 0.44f, 0.32f, 0.89f)   /* 128 x 64, two */       \
+    X(14, 2, 2, 2, 4, 3, 3, false, 2, 2, 0.731f, 0.0f, 3.73f, 0.45f, 0.36f, 1.0f)    /* 64 x 128, two */       \
+    X(15, 2, 2, 2, 3, 4, 4, false, 2, 2, 0.600f, 0.31f, 3.81f, 0.45f, 0.26f, 0.97f)  /* 64 x 96, two */        \
+    X(16, 2, 2, 2, 2, 5, 5, false, 2, 2, 0.482f, 0.0f, 3.82f, 0.47f, 0.22f, 1.0f)    /* 64 x 64, two */        \
+    X(17, 2, 2, 2, 1, 6, 6, false, 2, 2, 0.346f, 0.35f, 3.52f, 0.53f, 0.10f, 1.0f)   /* 64 x 32, two */        \
+    X(18, 2, 2, 1, 1, 8, 8, false, 2, 2, 0.245f, 1.09f, 3.14f, 0.53f, 0.19f, 1.0f)   /* 32 x 32, two */
+constexpr int kTileConfigs = 18;
+
+template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC, int PER_UNIT>
+hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
+    constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
+    constexpr size_t smem = (size_t)(NSA * BM + NSW * BN) * 64 * sizeof(bf16);
+    static_assert(smem * PER_UNIT <= 160 * 1024, "LDS stages exceed 160 KB");
+    const int tiles_m = (g.M + BM - 1) / BM;
+    const int tiles_n = (g.N + BN - 1) / BN;
+    int grid = (tiles_m * tiles_n * splitk + 7) / 8 * 8;
+    // one workgroup per slot of the chip, which then takes its tiles in turn.  A k part is a tile range of its own, and
+    // the loads may not run past the next tile (k shorter than the ring): one tile per workgroup then.
+    if (splitk == 1 && g.K / 64 > NSW && grid > kUnits * PER_UNIT) grid = kUnits * PER_UNIT;
+    static std::once_flag attr_once;          // one per instantiation
+    static hipError_t attr_err = hipSuccess;
+    std::call_once(attr_once, [&]() {
+        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_alt64_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    });
+    if (attr_err != hipSuccess || attributes_only()) return attr_err;
+    // tile rows that share weight tiles: an XCD's 32 concurrent large tiles then cover 4 x 8 tiles, the shape with the
+    // fewest distinct operand rows per k step
+    const int group_m = BM >= 192 ? 4 : 8;
+    hipLaunchKernelGGL((gemm_alt64_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>), dim3(grid), dim3(64 * WM * WN), smem, s, g,
+                       tiles_m, tiles_n, group_m, splitk);
+    return hipGetLastError();
+}
+
+struct TileCost {
+    int bm, bn, per_unit;
+    float a, b, c, p, s, q;
+};
+const TileCost kCost[kTileConfigs + 1] = {
+    {0, 0, 0, 0, 0, 0, 0, 0, 0},
+#define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit, a, b, c, p, s, q) {16 * tm * wm, 16 * tn * wn, per_unit, a, b, c, p, s, q},
+    SDV2_TILE_CONFIGS(X)
+#undef X
+};
+
+hipError_t launch_tile_config(const GemmArgs& g, int id, int splitk, hipStream_t s) {
     if (!fits_32bit_offsets(g.M, g.N, g.K)) return hipErrorInvalidValue;     // only reachable through the tuning override
     switch (id) {
-        case 1: return launch_dma<4, 2, 2, 4, 2>(g, splitk, s);      // 256 x 256, wave tile 64 x 128
-        case 2: return launch_dma<2, 4, 4, 2, 2>(g, splitk, s);      // 256 x 256, wave tile 128 x 64
-        case 3: return launch_dma<2, 4, 2, 2, 3>(g, splitk, s);      // 128 x 256
-        case 4: return launch_dma<4, 2, 2, 2, 3>(g, splitk, s);      // 256 x 128
-        case 5: return launch_ring<4, 2, 2, 4>(g, splitk, s);        // 256 x 256, ring of four k32 stages
-        case 6: return launch_ring<2, 4, 4, 2>(g, splitk, s);
-        case 7: return launch_dma<4, 1, 1, 2, 3>(g, splitk, s);      // 128 x 64, four waves, 72 KB: two workgroups per unit
-        case 8: return launch_dma<4, 1, 1, 2, 4>(g, splitk, s);      // 128 x 64, four stages
-        case 9: return launch_dma<4, 2, 1, 1, 4>(g, splitk, s);      // 128 x 64, eight waves of 32 x 32
-        case 10: return launch_dma<2, 2, 1, 2, 4>(g, splitk, s);     // 64 x 128, four waves
-        case 11: return launch_dma<2, 2, 2, 2, 3>(g, splitk, s);     // 128 x 128, four waves of 64 x 64
-        case 12: return launch_dma<2, 4, 2, 1, 3>(g, splitk, s);     // 128 x 128, eight waves of 64 x 32
-        case 13: return launch_dma<4, 1, 1, 5, 2>(g, splitk, s);     // 128 x 160, four waves, two stages (72 KB)
-        case 14: return launch_dma<4, 1, 1, 5, 3>(g, splitk, s);     // 128 x 160, three stages
-        case 15: return launch_dma<4, 1, 1, 6, 3>(g, splitk, s);     // 128 x 192
-        case 16: return launch_dma<4, 2, 1, 3, 3>(g, splitk, s);     // 128 x 192, eight waves of 32 x 96
-        case 17: return launch_alt64<4, 2, 2, 4>(g, splitk, s);      // 256 x 256, two wave groups half a step apart, ring of five half stages
-        case 18: return launch_alt64<2, 4, 4, 2>(g, splitk, s);
+#define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit, ...) \
+    case id: return launch_alt64<wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit>(g, splitk, s);
+        SDV2_TILE_CONFIGS(X)
+#undef X
     }
     return hipErrorInvalidValue;
+}
+
+// Estimated microseconds of configuration `id` on an M x N output with `k_tiles` k tiles of 64 in each of `parts` parts.
+float tile_cost(int id, int M, int N, float k_tiles, int parts) {
+    const TileCost& t = kCost[id];
+    const long long tiles = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * parts;
+    const int slots = kUnits * t.per_unit;
+    const float full = (float)(tiles / slots), x = (float)(tiles % slots) / (float)slots;
+    float last = 0.0f;
+    if (x > 0.0f) last = (t.per_unit == 1 || x <= 0.5f) ? t.p + t.s * x : t.q + (1.0f - t.q) * x;
+    return t.c + (full + last) * (k_tiles * t.a + t.b);
+}
+
+// The planner: the configuration and number of k parts with the smallest estimate.  A k split pays for a second pass
+// over parts + 1 or 2 fp32 planes at about 5.5 TB/s; a residual epilogue gets back the LayerNorm that this pass forms
+// (4 us).  Parts of at least 512 and at most 32 MiB of partial sums (what the entry point without a workspace has).
+// One shape is planned by hand, FFN-2 of the 14B block on one chunk, where two parts of 42 MB are 5 % faster than the
+// best plan within 32 MiB.
+struct TunedShape {
+    int M, N, K, dma, splitk;
+};
+const TunedShape kTuned[] = {{1024, 5120, 13824, 4, 2}};
+
+TilePlan search_plan(int M, int N, int K, int epilogue) {
+    for (const TunedShape& t : kTuned)
+        if (t.M == M && t.N == N && t.K == K) return TilePlan{0, 0, 0, t.dma, t.splitk};
+    TilePlan best{0, 0, 0, 1, 1};
+    float best_cost = 1e30f;
+    const int kParts[] = {1, 2, 3, 4, 6};
+    for (const int parts : kParts) {
+        if (parts > 1 && (K < 512 * parts || (size_t)parts * M * N * sizeof(float) > ((size_t)32 << 20))) break;
+        float second = 0.0f;
+        if (parts > 1) second = 2.5f + (float)M * N * (4.0f * parts + (epilogue >= kEpiGatedResidual ? 8.0f : 2.0f)) / 5.5e6f -
+                                (epilogue >= kEpiGatedResidual ? 4.0f : 0.0f);
+        for (int id = 1; id <= kTileConfigs; ++id) {
+            const float cost = tile_cost(id, M, N, (float)K / (64 * parts), parts) + second;
+            if (cost < best_cost) {
+                best_cost = cost;
+                best = TilePlan{0, 0, 0, id, parts};
+            }
+        }
+    }
+    return best;
+}
+
+// Plans of the shapes a thread has used last (a step asks for the same half dozen over and over; a search is 18 x 5
+// estimates, about 2 us).
+TilePlan plan_tiles(int M, int N, int K, int epilogue) {
+    if (!fits_32bit_offsets(M, N, K)) return plan_register_staged(M, N, K);
+    struct Entry {
+        int M, N, K, residual;
+        TilePlan plan;
+    };
+    constexpr int kEntries = 64;
+    static thread_local Entry cache[kEntries] = {};
+    const int residual = epilogue >= kEpiGatedResidual ? 1 : 0;
+    const uint32_t h = (uint32_t)M * 2654435761u ^ (uint32_t)N * 2246822519u ^ (uint32_t)K * 3266489917u ^ (uint32_t)residual;
+    Entry& e = cache[(h ^ (h >> 16)) % kEntries];
+    if (e.M != M || e.N != N || e.K != K || e.residual != residual) e = Entry{M, N, K, residual, search_plan(M, N, K, epilogue)};
+    return e.plan;
 }
 
 }  // namespace
 
 // Plan override for tuning runs and tests, set through sdv2_tuning_set("gemm_tile", ...): "tm,tn[,pf[,splitk]]"
-// picks a tile of the register-staged kernel, "d<id>[,splitk]" a configuration of the direct-load kernel; an empty
+// picks a tile of the register-staged kernel, "d<id>[,splitk]" a configuration of gemm_alt64_kernel; an empty
 // string or null clears it.  Not read from the environment: a production
 // process cannot change a kernel plan by accident, and a launch costs no getenv.
 static bool g_have_tile_override = false;
@@ -1070,7 +970,7 @@ bool set_gemm_tile_override(const char* e) {
     }
     int a, b, d = 2;
     int dk = 1;
-    if (sscanf(e, "d%d,%d", &a, &dk) >= 1 && a >= 1 && a <= kDmaConfigs && dk >= 1 && dk <= 16) {
+    if (sscanf(e, "d%d,%d", &a, &dk) >= 1 && a >= 1 && a <= kTileConfigs && dk >= 1 && dk <= 16) {
         g_tile_override = TilePlan{0, 0, 0, a, dk};
         g_have_tile_override = true;
         return true;
@@ -1226,7 +1126,7 @@ static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln
     const int splitk = usable_splitk(g, p);
     hipError_t e = hipSuccess;
     if (part != 2) {
-        if (p.dma) e = launch_dma_config(g, p.dma, splitk, s);
+        if (p.dma) e = launch_tile_config(g, p.dma, splitk, s);
         else if (p.pf == 3) e = p.tm == 1 ? launch_tn<1, 3>(g, p.tn, splitk, s) : launch_tn<2, 3>(g, p.tn, splitk, s);
         else e = p.tm == 1 ? launch_tn<1, 2>(g, p.tn, splitk, s) : launch_tn<2, 2>(g, p.tn, splitk, s);
     }
@@ -1253,19 +1153,15 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) { return launch_gemm_im
 void gemm_plan_name(int M, int N, int K, int epilogue, char* out, size_t cap) {
     TilePlan p = plan_tiles(M, N, K, epilogue);
     tile_override(&p);
-    static const int kDma[kDmaConfigs + 1][5] = {{0, 0, 0, 0, 0}, {4, 2, 2, 4, 2}, {2, 4, 4, 2, 2}, {2, 4, 2, 2, 3}, {4, 2, 2, 2, 3},
-                                                 {4, 2, 2, 4, 0}, {2, 4, 4, 2, 0}, {4, 1, 1, 2, 3}, {4, 1, 1, 2, 4}, {4, 2, 1, 1, 4},
-                                                 {2, 2, 1, 2, 4}, {2, 2, 2, 2, 3}, {2, 4, 2, 1, 3}, {4, 1, 1, 5, 2}, {4, 1, 1, 5, 3},
-                                                 {4, 1, 1, 6, 3}, {4, 2, 1, 3, 3}, {4, 2, 2, 4, 0}, {2, 4, 4, 2, 0}};
-    if (p.dma >= 17)
-        snprintf(out, cap, "gemm_alt64_kernel<%d, %d, %d, %d>", kDma[p.dma][0], kDma[p.dma][1], kDma[p.dma][2], kDma[p.dma][3]);
-    else if (p.dma == 5 || p.dma == 6)
-        snprintf(out, cap, "gemm_ring_kernel<%d, %d, %d, %d>", kDma[p.dma][0], kDma[p.dma][1], kDma[p.dma][2], kDma[p.dma][3]);
-    else if (p.dma)
-        snprintf(out, cap, "gemm_dma_kernel<%d, %d, %d, %d, %d>", kDma[p.dma][0], kDma[p.dma][1], kDma[p.dma][2], kDma[p.dma][3],
-                 kDma[p.dma][4]);
-    else
-        snprintf(out, cap, "gemm_kernel<%d, %d, 64, %d>", p.tm, p.tn, p.pf);
+    switch (p.dma) {
+#define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, ...)                                                                 \
+    case id:                                                                                                             \
+        snprintf(out, cap, "gemm_alt64_kernel<%d, %d, %d, %d, %d, %d, %s, %d>", wm, wn, tm, tn, nsa, nsw, roles ? "true" : "false", occ); \
+        return;
+        SDV2_TILE_CONFIGS(X)
+#undef X
+    }
+    snprintf(out, cap, "gemm_kernel<%d, %d, 64, %d>", p.tm, p.tn, p.pf);
 }
 
 hipError_t launch_gemm_then_layernorm(const GemmArgs& g, const LnArgs& ln, bool* ln_done, hipStream_t s, int part) {
