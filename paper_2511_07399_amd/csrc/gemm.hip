@@ -359,8 +359,8 @@ __global__ __launch_bounds__(256, ((TM * TN <= 5 && BK == 64 && PF == 2) ? 2 : 1
 //   XCD-aware order: an XCD (one L2) owns a contiguous range of tiles, ordered in groups of GROUP_M tile rows that share
 // weight tiles.
 //   Tried and dropped: W fragments straight from global memory into registers, A through LDS (16 rows of 64 bytes per
-// load: 20 to 40 % slower on every shape); four waves of 128 x 128 (half of the fragment reads, but one wave per SIMD
-// leaves the barrier and the epilogue uncovered: 2 to 8 % slower); NSW = 5 with NSA = 3 on 128 x 160 (same as 4 and 4).
+// load: 20 to 40 % slower on every shape); 256 x 256 with four waves of 128 x 128 (a third fewer fragment reads, but one
+// wave per SIMD leaves the barrier and the epilogue uncovered: equal on square shapes, 15 % slower at k = 1536); NSW = 5 with NSA = 3 on 128 x 160 (same as 4 and 4).
 constexpr int vmcnt_only(int n) {     // s_waitcnt with only vmcnt constrained
     return (n & 0xF) | ((n >> 4) << 14) | 0x0F70;
 }
@@ -615,7 +615,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
         constexpr int kSpan = kM * 3 / 4 > 0 ? kM * 3 / 4 : 1;
         static_for<kM>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
-            constexpr int i = m / TN, j = m % TN;
+            constexpr int i = m / TN, j = i % 2 ? TN - 1 - m % TN : m % TN;      // back and forth: one operand stays at every turn
             acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[s][j], fa[s][i], acc[i][j], 0, 0, 0);
             constexpr int r0 = m < kSpan ? m * kR / kSpan : kR, r1 = m < kSpan ? (m + 1) * kR / kSpan : kR;
             static_for<r1 - r0>([&](auto q) { read(std::integral_constant<int, 1 - s>{}, std::integral_constant<int, r0 + decltype(q)::value>{}, pa, pw); });
@@ -822,27 +822,28 @@ hipError_t launch_tn(const GemmArgs& g, int tn, int splitk, hipStream_t s) {
 // microseconds:  c + rounds * (k tiles * a + b),  a = one k tile with the chip full of such tiles, b = prologue and
 // epilogue of a tile, c = launch and drain.  `rounds` counts full rounds (one tile in every slot of the chip) and, for
 // a last round that fills the share x of the slots, p + (1 - p) x of a round: less traffic and a higher clock, but no
-// less latency (two workgroups per unit: p + s x up to x = 1/2, where a unit has one, q + (1 - q) x above).  Fitted to 232
-// random shapes of 128 to 18 720 rows with K = 512 to 29 000 (root mean square error 7 to 14 %; the configuration
-// picked is on average 2 % slower than the best of all of them).
-#define SDV2_TILE_CONFIGS(X)                                                                                   \
-    X(1, 2, 4, 8, 4, 2, 3, false, 2, 1, 1.53f, 12.6f, 3.1f, 0.78f, 0.22f, 1.0f)      /* 256 x 256 */           \
-    X(2, 2, 4, 6, 4, 2, 3, true, 2, 1, 1.12f, 9.5f, 2.8f, 0.67f, 0.33f, 1.0f)        /* 192 x 256 */           \
-    X(3, 2, 4, 8, 3, 2, 3, false, 2, 1, 1.18f, 9.1f, 2.4f, 0.72f, 0.28f, 1.0f)       /* 256 x 192 */           \
-    X(4, 4, 2, 4, 5, 3, 3, false, 2, 1, 1.02f, 7.9f, 2.8f, 0.71f, 0.29f, 1.0f)       /* 256 x 160 */           \
-    X(5, 4, 2, 4, 4, 3, 3, false, 2, 1, 0.885f, 5.0f, 4.1f, 0.67f, 0.33f, 1.0f)      /* 256 x 128 */           \
-    X(6, 2, 4, 6, 3, 2, 4, true, 2, 1, 0.947f, 5.8f, 3.6f, 0.71f, 0.29f, 1.0f)       /* 192 x 192 */           \
-    X(7, 4, 2, 2, 6, 4, 4, true, 2, 1, 0.734f, 2.7f, 4.9f, 0.73f, 0.27f, 1.0f)       /* 128 x 192 */           \
-    X(8, 4, 2, 2, 5, 4, 4, true, 2, 1, 0.659f, 2.3f, 4.0f, 0.76f, 0.24f, 1.0f)       /* 128 x 160 */           \
-    X(9, 4, 2, 2, 4, 4, 5, true, 2, 1, 0.572f, 1.8f, 4.0f, 0.75f, 0.25f, 1.0f)       /* 128 x 128 */           \
-    X(10, 4, 2, 2, 3, 5, 5, true, 2, 1, 0.475f, 1.5f, 3.6f, 0.81f, 0.19f, 1.0f)      /* 128 x 96 */            \
-    X(11, 4, 2, 3, 4, 3, 4, true, 2, 1, 0.717f, 3.65f, 4.0f, 0.68f, 0.32f, 1.0f)     /* 192 x 128 */           \
-    X(12, 2, 2, 4, 6, 2, 2, false, 2, 2, 1.33f, 3.2f, 2.9f, 0.59f, 0.36f, 0.98f)     /* 128 x 192, two */      \
-    X(13, 2, 2, 4, 2, 3, 3, false, 2, 2, 0.724f, 0.0f, 3.66f, 0.44f, 0.32f, 0.89f)   /* 128 x 64, two */       \
-    X(14, 2, 2, 2, 4, 3, 3, false, 2, 2, 0.731f, 0.0f, 3.73f, 0.45f, 0.36f, 1.0f)    /* 64 x 128, two */       \
-    X(15, 2, 2, 2, 3, 4, 4, false, 2, 2, 0.600f, 0.31f, 3.81f, 0.45f, 0.26f, 0.97f)  /* 64 x 96, two */        \
-    X(16, 2, 2, 2, 2, 5, 5, false, 2, 2, 0.482f, 0.0f, 3.82f, 0.47f, 0.22f, 1.0f)    /* 64 x 64, two */        \
-    X(17, 2, 2, 2, 1, 6, 6, false, 2, 2, 0.346f, 0.35f, 3.52f, 0.53f, 0.10f, 1.0f)   /* 64 x 32, two */        \
+// less latency (two workgroups per unit: p + s x up to x = 1/2, where a unit has one, q + (1 - q) x above).  Fitted to
+// launches in a steady state (weights cold, the chip at its power limit) of 156 random shapes of 128 to 18 720 rows,
+// K = 512 to 18 000: root mean square error 4 to 10 %, and the configuration picked is on average 0.5 % slower than the
+// best of all of them.
+#define SDV2_TILE_CONFIGS(X)                                                                                  \
+    X(1, 2, 4, 8, 4, 2, 3, false, 2, 1, 1.60f, 7.1f, 2.8f, 0.77f, 0.23f, 1.0f)    /* 256 x 256 */             \
+    X(2, 2, 4, 6, 4, 2, 3, true, 2, 1, 1.156f, 4.3f, 3.4f, 0.68f, 0.32f, 1.0f)    /* 192 x 256 */             \
+    X(3, 2, 2, 8, 6, 2, 3, false, 1, 1, 1.129f, 5.5f, 2.9f, 0.73f, 0.27f, 1.0f)   /* 256 x 192 */             \
+    X(4, 4, 2, 4, 5, 3, 3, false, 2, 1, 1.031f, 4.4f, 3.2f, 0.71f, 0.29f, 1.0f)   /* 256 x 160 */             \
+    X(5, 4, 2, 4, 4, 3, 3, false, 2, 1, 0.892f, 3.0f, 3.0f, 0.71f, 0.29f, 1.0f)   /* 256 x 128 */             \
+    X(6, 2, 4, 6, 3, 2, 4, true, 2, 1, 0.940f, 3.6f, 3.1f, 0.75f, 0.25f, 1.0f)    /* 192 x 192 */             \
+    X(7, 4, 2, 2, 6, 4, 4, true, 2, 1, 0.713f, 2.1f, 3.0f, 0.78f, 0.22f, 1.0f)    /* 128 x 192 */             \
+    X(8, 4, 2, 2, 5, 4, 4, true, 2, 1, 0.638f, 1.9f, 2.8f, 0.82f, 0.18f, 1.0f)    /* 128 x 160 */             \
+    X(9, 4, 2, 2, 4, 4, 5, true, 2, 1, 0.549f, 1.0f, 3.5f, 0.80f, 0.20f, 1.0f)    /* 128 x 128 */             \
+    X(10, 4, 2, 2, 3, 5, 5, true, 2, 1, 0.472f, 0.8f, 3.8f, 0.80f, 0.20f, 1.0f)   /* 128 x 96 */              \
+    X(11, 4, 2, 3, 4, 3, 4, true, 2, 1, 0.725f, 2.1f, 3.4f, 0.71f, 0.29f, 1.0f)   /* 192 x 128 */             \
+    X(12, 2, 2, 4, 6, 2, 2, false, 2, 2, 1.339f, 2.7f, 2.0f, 0.64f, 0.20f, 0.85f) /* 128 x 192, two */        \
+    X(13, 2, 2, 4, 2, 3, 3, false, 2, 2, 0.724f, 0.0f, 3.7f, 0.47f, 0.25f, 0.85f) /* 128 x 64, two */         \
+    X(14, 2, 2, 2, 4, 3, 3, false, 2, 2, 0.731f, 0.0f, 3.7f, 0.48f, 0.27f, 0.95f) /* 64 x 128, two */         \
+    X(15, 2, 2, 2, 3, 4, 4, false, 2, 2, 0.600f, 0.3f, 3.8f, 0.45f, 0.24f, 0.93f) /* 64 x 96, two */          \
+    X(16, 2, 2, 2, 2, 5, 5, false, 2, 2, 0.482f, 0.0f, 3.8f, 0.48f, 0.18f, 0.95f) /* 64 x 64, two */          \
+    X(17, 2, 2, 2, 1, 6, 6, false, 2, 2, 0.346f, 0.35f, 3.5f, 0.53f, 0.10f, 1.0f) /* 64 x 32, two */          \
     X(18, 2, 2, 1, 1, 8, 8, false, 2, 2, 0.245f, 1.09f, 3.14f, 0.53f, 0.19f, 1.0f)   /* 32 x 32, two */
 constexpr int kTileConfigs = 18;
 
@@ -874,11 +875,12 @@ hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
 
 struct TileCost {
     int bm, bn, per_unit;
+    bool one_wave;                    // a SIMD holds a single wave
     float a, b, c, p, s, q;
 };
 const TileCost kCost[kTileConfigs + 1] = {
-    {0, 0, 0, 0, 0, 0, 0, 0, 0},
-#define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit, a, b, c, p, s, q) {16 * tm * wm, 16 * tn * wn, per_unit, a, b, c, p, s, q},
+    {0, 0, 0, false, 0, 0, 0, 0, 0, 0},
+#define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit, a, b, c, p, s, q) {16 * tm * wm, 16 * tn * wn, per_unit, occ == 1, a, b, c, p, s, q},
     SDV2_TILE_CONFIGS(X)
 #undef X
 };
@@ -906,8 +908,7 @@ float tile_cost(int id, int M, int N, float k_tiles, int parts) {
 }
 
 // The planner: the configuration and number of k parts with the smallest estimate.  A k split pays for a second pass
-// over parts + 1 or 2 fp32 planes at about 5.5 TB/s; a residual epilogue gets back the LayerNorm that this pass forms
-// (4 us).  Parts of at least 512 and at most 32 MiB of partial sums (what the entry point without a workspace has).
+// (4 us and its bytes at 3.9 TB/s); a residual epilogue gets back the LayerNorm that this pass forms (5 us).  Parts of at least 512 and at most 32 MiB of partial sums (what the entry point without a workspace has).
 // One shape is planned by hand, FFN-2 of the 14B block on one chunk, where two parts of 42 MB are 5 % faster than the
 // best plan within 32 MiB.
 struct TunedShape {
@@ -921,13 +922,16 @@ TilePlan search_plan(int M, int N, int K, int epilogue) {
     TilePlan best{0, 0, 0, 1, 1};
     float best_cost = 1e30f;
     const int kParts[] = {1, 2, 3, 4, 6};
+    // operands beyond the 256 MB memory-side cache: with a single wave per SIMD their latency shows (4 to 14 %)
+    const bool from_memory = (size_t)(M + (size_t)N) * K * sizeof(bf16) > ((size_t)240 << 20);
     for (const int parts : kParts) {
         if (parts > 1 && (K < 512 * parts || (size_t)parts * M * N * sizeof(float) > ((size_t)32 << 20))) break;
         float second = 0.0f;
-        if (parts > 1) second = 2.5f + (float)M * N * (4.0f * parts + (epilogue >= kEpiGatedResidual ? 8.0f : 2.0f)) / 5.5e6f -
-                                (epilogue >= kEpiGatedResidual ? 4.0f : 0.0f);
+        if (parts > 1) second = 4.0f + (float)M * N * (4.0f * parts + (epilogue >= kEpiGatedResidual ? 8.0f : 2.0f)) / 3.9e6f -
+                                (epilogue >= kEpiGatedResidual ? 5.0f : 0.0f);
         for (int id = 1; id <= kTileConfigs; ++id) {
-            const float cost = tile_cost(id, M, N, (float)K / (64 * parts), parts) + second;
+            float cost = tile_cost(id, M, N, (float)K / (64 * parts), parts) + second;
+            if (from_memory && kCost[id].one_wave) cost *= 1.07f;
             if (cost < best_cost) {
                 best_cost = cost;
                 best = TilePlan{0, 0, 0, id, parts};
