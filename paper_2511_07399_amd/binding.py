@@ -11,6 +11,9 @@ import os
 
 import torch
 
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch.cuda.current_device
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libsdv2.so")
 MAX_BATCH = 8
@@ -202,12 +205,15 @@ def _check(rc):
         raise Sdv2Error(rc, _lib.sdv2_last_error().decode())
 
 
+# Pointers and the stream go through as plain integers (the argument types turn them into void pointers), and the stream
+# comes from torch's raw getter: the small calls of a chunk (motion, noise rate, refresh) cost the host as much here as
+# in their launches when every call built wrapper objects.
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return _raw_stream(_current_device())
 
 
 def _dev(t, dtype):
@@ -278,7 +284,7 @@ def kv_cache_init(cfg, storage):
     """storage: a uint8 device tensor of at least kv_cache_bytes(cfg) bytes.  Returns the opaque handle."""
     load_library()
     h = C.c_void_p()
-    _check(_lib.sdv2_kv_cache_init(C.byref(cfg), _ptr(storage), storage.numel() * storage.element_size(),
+    _check(_lib.sdv2_kv_cache_init(C.byref(cfg), _ptr(storage), storage.nbytes,
                                    C.byref(h)))
     return h
 
@@ -306,7 +312,7 @@ def sink_similarity(handle, layer, stream_id, alpha, workspace, frame_back=0):
     """alpha (device fp32 [sink frames]) <- cos(frame `frame_back` of the latest append, sink frame i)."""
     _dev(alpha, torch.float32)
     _check(_lib.sdv2_sink_similarity(handle, layer, stream_id, frame_back, _ptr(alpha), _ptr(workspace),
-                                     workspace.numel() * workspace.element_size(), _stream()))
+                                     workspace.nbytes, _stream()))
 
 
 def kv_cache_refresh_sink(handle, layer, stream_id, sink_frame, frame_back=0):
@@ -329,13 +335,13 @@ def motion_state_bytes(cfg):
 
 
 def motion_init(cfg, state):
-    _check(_lib.sdv2_motion_init(C.byref(cfg), _ptr(state), state.numel() * state.element_size(), _stream()))
+    _check(_lib.sdv2_motion_init(C.byref(cfg), _ptr(state), state.nbytes, _stream()))
 
 
 def motion_update(cfg, state, frames, prev_frame, d_out, dhat_out, s_out):
     """frames: device fp32 [T, n]; prev_frame: device fp32 [n] or None; outputs device fp32 [T]."""
     _dev(frames, torch.float32)
-    _check(_lib.sdv2_motion_update(C.byref(cfg), _ptr(state), state.numel() * state.element_size(), _ptr(frames),
+    _check(_lib.sdv2_motion_update(C.byref(cfg), _ptr(state), state.nbytes, _ptr(frames),
                                    None if prev_frame is None else _ptr(prev_frame), frames.shape[0],
                                    frames.shape[1], _ptr(d_out), _ptr(dhat_out), _ptr(s_out), _stream()))
 
@@ -392,7 +398,7 @@ def text_kv_workspace_bytes(cfg):
 def text_kv_prepare(cfg, bw, ctx, kt, vtt, workspace):
     _dev(ctx, torch.bfloat16)
     _check(_lib.sdv2_text_kv_prepare(C.byref(cfg), C.byref(bw), _ptr(ctx), _ptr(kt), _ptr(vtt), _ptr(workspace),
-                                     workspace.numel() * workspace.element_size(), _stream()))
+                                     workspace.nbytes, _stream()))
 
 
 def conditioning_workspace_bytes(cfg, B):
@@ -411,7 +417,7 @@ def conditioning(cfg, mw, B, e0, workspace, timesteps=None, tvec=None):
     if tvec is not None:
         _dev(tvec, torch.float32)
     _check(_lib.sdv2_conditioning(C.byref(cfg), C.byref(mw), B, _timesteps(timesteps), _ptr(tvec), _ptr(e0),
-                                  _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()))
+                                  _ptr(workspace), workspace.nbytes, _stream()))
 
 
 # ------------------------------------------------------------------------------------------ block and step
@@ -430,7 +436,7 @@ def dit_block_forward(cfg, bw, cache, layer, x, e0, kt_list, vtt_list, chunks, w
     _dev(e0, torch.float32)
     _check(_lib.sdv2_dit_block_forward(C.byref(cfg), C.byref(bw), cache, layer, _ptr(x), _ptr(e0),
                                        _ptr_array(kt_list), _ptr_array(vtt_list), chunks, len(chunks),
-                                       _ptr(workspace), workspace.numel() * workspace.element_size(), _stream()))
+                                       _ptr(workspace), workspace.nbytes, _stream()))
 
 
 def denoise_step(cfg, mw, cache, x, kt_array, vtt_array, chunks, workspace, timesteps=None, tvec=None):
@@ -440,7 +446,7 @@ def denoise_step(cfg, mw, cache, x, kt_array, vtt_array, chunks, workspace, time
         _dev(tvec, torch.float32)
     _check(_lib.sdv2_denoise_step(C.byref(cfg), C.byref(mw), cache, _ptr(x), _timesteps(timesteps), _ptr(tvec),
                                   kt_array, vtt_array, chunks, len(chunks), _ptr(workspace),
-                                  workspace.numel() * workspace.element_size(), _stream()))
+                                  workspace.nbytes, _stream()))
 
 
 ptr_array = _ptr_array
@@ -462,7 +468,7 @@ def gemm_bf16(a, w, bias, out, epilogue=0, gate_a=None, gate_b=None, gate_b_stri
     _dev(out, torch.bfloat16 if epilogue in (0, 1) else torch.float32)
     _check(_lib.sdv2_gemm_bf16(_ptr(a), _ptr(w), _ptr(bias), _ptr(out), M, N, K, epilogue, _ptr(gate_a), _ptr(gate_b),
                                gate_b_stride, rows_per_gate, _ptr(workspace),
-                               0 if workspace is None else workspace.numel() * workspace.element_size(), _stream()))
+                               0 if workspace is None else workspace.nbytes, _stream()))
 
 
 def gemm_noalloc_max_scratch_bytes():
@@ -494,7 +500,7 @@ def attention_bf16(q, k_list, vt_list, kv_lens, caps, o, n_heads, workspace):
     B, L, _ = q.shape
     kl = (C.c_int32 * B)(*kv_lens)
     cp = (C.c_int32 * B)(*caps)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = 0 if workspace is None else workspace.nbytes
     _check(_lib.sdv2_attention_bf16(_ptr(q), _ptr_array(k_list), _ptr_array(vt_list), kl, cp, _ptr(o), B, L, n_heads,
                                     _ptr(workspace), ws_bytes, _stream()))
 
@@ -525,8 +531,8 @@ def prof_peak_mfma(iters, workgroups, sink):
 
 def prof_peak_copy(src, dst):
     load_library()
-    n = src.numel() * src.element_size()
-    assert dst.numel() * dst.element_size() == n
+    n = src.nbytes
+    assert dst.nbytes == n
     _check(_lib.sdv2_prof_peak_copy(_ptr(src), _ptr(dst), n, _stream()))
     return n
 
@@ -534,7 +540,7 @@ def prof_peak_copy(src, dst):
 def prof_lds_rates(iters, scratch):
     """Enqueues the three LDS-rate launches; the three tick counts are the first three int64 of ``scratch``."""
     load_library()
-    _check(_lib.sdv2_prof_lds_rates(iters, _ptr(scratch), scratch.numel() * scratch.element_size(), _stream()))
+    _check(_lib.sdv2_prof_lds_rates(iters, _ptr(scratch), scratch.nbytes, _stream()))
 
 
 def prof_kernel_name(kind, B, L, a0, a1, a2):
@@ -563,7 +569,7 @@ def stream_batch_create(cfg, n_steps, cache_stream_ids, n_frames, rows):
     ids = (C.c_int32 * n_steps)(*cache_stream_ids)
     h = C.c_void_p()
     _check(_lib.sdv2_stream_batch_create(C.byref(cfg), n_steps, ids, n_frames, _ptr(rows),
-                                         rows.numel() * rows.element_size(), C.byref(h)))
+                                         rows.nbytes, C.byref(h)))
     return h
 
 
@@ -584,7 +590,7 @@ def stream_batch_step(h, cfg, mw, cache, x_in, frame_pos0, timesteps, kt, vtt, x
     emitted, rows = C.c_int32(), C.c_int32()
     _check(_lib.sdv2_stream_batch_step(h, C.byref(cfg), C.byref(mw), cache, _ptr(x_in), frame_pos0, ts, kt, vtt,
                                        _ptr(x_out), C.byref(emitted), C.byref(rows), _ptr(workspace),
-                                       workspace.numel() * workspace.element_size(), _stream()))
+                                       workspace.nbytes, _stream()))
     return bool(emitted.value), rows.value
 
 
@@ -602,8 +608,8 @@ def denoise_graph_create(cfg, mw, cache, x, kt_array, vtt_array, stream_ids, n_f
     h = C.c_void_p()
     _check(_lib.sdv2_denoise_graph_create(C.byref(cfg), C.byref(mw), cache, _ptr(x), kt_array, vtt_array, ids,
                                           len(stream_ids), n_frames, _ptr(workspace),
-                                          workspace.numel() * workspace.element_size(), _ptr(state),
-                                          state.numel() * state.element_size(), C.byref(h)))
+                                          workspace.nbytes, _ptr(state),
+                                          state.nbytes, C.byref(h)))
     return h
 
 
@@ -629,7 +635,7 @@ def io_weights(tensors):
 
 
 def _nbytes(t):
-    return t.numel() * t.element_size()
+    return t.nbytes
 
 
 def timestep_vector(cfg, mw, timesteps, tvec, workspace):

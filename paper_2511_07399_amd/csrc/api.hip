@@ -134,6 +134,7 @@ AppendStream append_stream(const sdv2_kv_cache* c, int layer, int stream, int64_
     s.vt_cache = reinterpret_cast<bf16*>(u + c->k_bytes);
     s.ids = reinterpret_cast<long long*>(u + 2 * c->k_bytes);
     s.g0 = g0;
+    s.ring0 = ring_position(g0, c->cfg.sink_tokens, c->cfg.window_tokens);
     s.frame_pos0 = frame_pos0;
     s.cap = c->cap;
     return s;
@@ -284,6 +285,9 @@ int32_t sdv2_kv_cache_append_evict(sdv2_kv_cache* cache, int32_t layer, int32_t 
     a.H = cf.n_heads;
     a.S = cf.sink_tokens;
     a.W = cf.window_tokens;
+    a.quads = cf.tokens_per_frame % 4 == 0;          // sink, window and every append are whole frames
+    a.g_k = nullptr;
+    a.eps = 0.0f;
     a.st = append_stream(cache, layer, stream_id, cache->total[idx] - n_tokens, 0);
     hipError_t e = launch_plain_append(a, static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) {
@@ -540,6 +544,7 @@ int32_t sdv2_gemm_bf16(const void* a_dev, const void* w_dev, const float* bias_d
     if (epilogue == kEpiGatedResidual && (!gate_a_dev || !gate_b_dev || rows_per_gate <= 0))
         return fail(SDV2_INVALID_ARG, "gated epilogue needs gate_a, gate_b and rows_per_gate > 0");
     GemmArgs g;
+    memset(&g, 0, sizeof(g));
     g.a = static_cast<const bf16*>(a_dev);
     g.w = static_cast<const bf16*>(w_dev);
     g.bias = bias_dev;
@@ -696,13 +701,11 @@ int32_t sdv2_text_kv_prepare(const sdv2_model_cfg* cfg, const sdv2_block_weights
     g.w = static_cast<const bf16*>(w->W_ck);
     g.bias = w->b_ck;
     g.out = krows;
-    HIP_TRY(launch_gemm(g, s), "text K gemm");
-    HIP_TRY(launch_rmsnorm_inplace(krows, w->g_ck, Lt, C, C, cfg->eps, s), "text K norm");
-    g.w = static_cast<const bf16*>(w->W_cv);
-    g.bias = w->b_cv;
-    g.out = vrows;
-    HIP_TRY(launch_gemm(g, s), "text V gemm");
-    HIP_TRY(launch_text_relayout(krows, vrows, static_cast<bf16*>(kt_dev), static_cast<bf16*>(vtt_dev), Lt, C,
+    g.w2 = static_cast<const bf16*>(w->W_cv);
+    g.bias2 = w->b_cv;
+    g.out2 = vrows;
+    HIP_TRY(launch_gemm(g, s), "text K and V gemm");
+    HIP_TRY(launch_text_relayout(krows, vrows, w->g_ck, cfg->eps, static_cast<bf16*>(kt_dev), static_cast<bf16*>(vtt_dev), Lt, C,
                                  cfg->n_heads, (int)align_up((size_t)Lt, 64), s),
             "text relayout");
     return SDV2_OK;
@@ -857,7 +860,7 @@ void fill_rope_table(const sdv2_model_cfg* cfg, RopeAppendArgs* a) {
     for (int axis = 0; axis < 3; ++axis)
         for (int j = 0; j < counts[axis]; ++j, ++p) {
             a->pair_axis[p] = axis;
-            a->inv_freq[p] = pow((double)cfg->rope_base, -(double)j / counts[axis]);
+            a->inv_turn[p] = pow((double)cfg->rope_base, -(double)j / counts[axis]) / (2.0 * M_PI);
         }
 }
 
@@ -1334,6 +1337,7 @@ int32_t sdv2_denoise_graph_launch(sdv2_denoise_graph* g, const float* timesteps_
             return fail(SDV2_BAD_STATE, "stream %d: advance = 0 without a matching append", c.stream_id);
         const int64_t total_new = cache->total[idx0] + (c.advance ? L : 0);
         d.g0[b] = total_new - L;
+        d.ring0[b] = ring_position(d.g0[b], cf.sink_tokens, cf.window_tokens);
         d.frame_pos0[b] = c.frame_pos0;
         d.kv_len[b] = (int)(total_new < capacity ? total_new : capacity);
         d.timestep[b] = timesteps_host[b];

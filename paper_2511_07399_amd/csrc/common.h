@@ -23,10 +23,22 @@ constexpr int kLatentChannels = 16;      // VAE latent channels; a token covers 
 // its keys.  The map is its own inverse.
 __host__ __device__ __forceinline__ int vt_column(int s) { return (s & ~12) | ((s & 4) << 1) | ((s & 8) >> 1); }
 
+// Sum over the wavefront, in every lane: two quad permutations and two mirrors inside a row of 16 lanes, then the row and
+// half swaps.  All on the vector unit: a shuffle through the LDS crossbar costs about ten times the latency, and the
+// row kernels of a single chunk are chains of these.
+template <int CTRL>
+__device__ __forceinline__ float dpp_f(float v) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-    return v;
+    v += dpp_f<0xB1>(v);         // quad_perm [1, 0, 3, 2]
+    v += dpp_f<0x4E>(v);         // quad_perm [2, 3, 0, 1]
+    v += dpp_f<0x141>(v);        // row_half_mirror
+    v += dpp_f<0x140>(v);        // row_mirror
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
 __device__ __forceinline__ float gelu_tanh_f(float x) {
@@ -61,6 +73,11 @@ struct GemmArgs {
     // and applies the epilogue, so the result does not depend on scheduling.
     float* splitk_partials;
     size_t splitk_floats;
+    // Optional second product of the same A, shape and epilogue (0 or 1), computed in the same launch: half the tiles are
+    // too few for the chip where one is.  Null: none.
+    const bf16* w2;
+    const float* bias2;
+    void* out2;
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // fp32 partial sums the planned launch of an [M, K] x [N, K] product needs (0: its plan does not split k)
@@ -74,6 +91,7 @@ bool set_gemm_tile_override(const char* spec);
 // graph (the kernels then read it from there instead of from their by-value arguments).
 struct StepDesc {
     long long g0[kMaxBatch];          // token id of the chunk's first token, per stream of the call
+    int ring0[kMaxBatch];             // its ring position (ring_position)
     int frame_pos0[kMaxBatch];        // RoPE frame index of the chunk's first frame
     int kv_len[kMaxBatch];            // resident slots after the append
     float timestep[kMaxBatch];
@@ -134,9 +152,19 @@ struct AppendStream {
     bf16* vt_cache;       // [H][128][cap]
     long long* ids;       // [cap]
     long long g0;         // token id of the chunk's first token
+    int ring0;            // its ring position (ring_position)
     int frame_pos0;
     int cap;
 };
+// Position in the ring of W slots behind a sink of S slots of the token with id g0; negative while it still belongs to
+// the sink.  Formed once per append (a 64-bit remainder), so that a kernel finds token g0 + i (i < W) by slot_of.
+__host__ __device__ __forceinline__ int ring_position(long long g0, int S, int W) {
+    return g0 < S ? (int)(g0 - S) : (int)((g0 - S) % W);
+}
+__device__ __forceinline__ int slot_of(int i, int ring0, int S, int W) {
+    const int r = ring0 + i;
+    return S + (r >= W ? r - W : r);
+}
 struct RopeAppendArgs {
     const bf16* qkv;      // [B*L, 3C]   (or separate k, v when q_out == null)
     bf16* q_out;          // [B*L, C]
@@ -146,18 +174,21 @@ struct RopeAppendArgs {
     int tokens_per_frame, grid_w;
     int S, W;
     float eps;
-    double inv_freq[kHeadDim / 2];    // rotation frequency of each pair of a head
+    double inv_turn[kHeadDim / 2];    // rotation frequency of each pair of a head, in turns per position
     int pair_axis[kHeadDim / 2];      // 0 frame, 1 row, 2 col
     AppendStream st[kMaxBatch];
     const StepDesc* desc;             // null: g0 and frame_pos0 of st[]; else they are read from the device descriptor
 };
 hipError_t launch_rope_append(const RopeAppendArgs& a, hipStream_t s);
 
-// Plain append of final k, v rows [n, C] (standalone cache call).
+// Append of k, v rows [n, C]: final rows (standalone cache call), or keys that still need their RMSNorm (text keys).
 struct PlainAppendArgs {
     const bf16* k;        // [n, C]
     const bf16* v;        // [n, C]
     int n, C, H, S, W;
+    int quads;            // every fourth token starts at a slot that is a multiple of four
+    const float* g_k;     // null: keys are final; else gain of the RMSNorm over C
+    float eps;
     AppendStream st;
 };
 hipError_t launch_plain_append(const PlainAppendArgs& a, hipStream_t s);
@@ -193,7 +224,7 @@ struct RotateKeysArgs {
 hipError_t launch_rotate_keys(const RotateKeysArgs& a, hipStream_t s);
 
 // Motion-aware noise scheduler (Section 4.1).  Device state: kMotionHeaderFloats header floats (s, frame count as
-// int bits), then the ring of the last k + 1 intensities, then kMotionMaxFrames * kMotionBlocks partial sums.
+// int bits, the ticket of the running launch), then the ring of the last k + 1 intensities, then kMotionMaxFrames * kMotionBlocks partial sums.
 constexpr int kMotionHeaderFloats = 16;
 constexpr int kMotionBlocks = 64;
 constexpr int kMotionMaxFrames = 16;
@@ -213,8 +244,8 @@ struct MotionArgs {
 hipError_t launch_motion_init(float* state, int n_floats, float s_init, hipStream_t s);
 hipError_t launch_motion_update(const MotionArgs& a, hipStream_t s);
 
-// Re-layout of text K/V rows [L_t, C] into the cache layouts.
-hipError_t launch_text_relayout(const bf16* k_rows, const bf16* v_rows, bf16* kt, bf16* vtt,
+// RMSNorm of the text key rows [L_t, C] and re-layout of both into the cache layouts.
+hipError_t launch_text_relayout(const bf16* k_rows, const bf16* v_rows, const float* g_k, float eps, bf16* kt, bf16* vtt,
                                 int L_t, int C, int H, int cap, hipStream_t s);
 
 // y[b][n] = act_out(sum_k act_in(x[b][k]) W[n][k] + bias[n]); x, y fp32; W bf16 [N, K]; B <= kMaxBatch.

@@ -14,11 +14,6 @@ namespace sdv2 {
 
 namespace {
 
-// physical slot of token id g:  g in the sink, else ring position
-__device__ __forceinline__ int slot_of(long long g, int S, int W) {
-    return g < S ? (int)g : S + (int)((g - S) % W);
-}
-
 // ------------------------------------------------------------------ LayerNorm (+ modulation or affine)
 // Two wavefronts per row, two rows per workgroup: a row of the small model is only 6 KB, and with one
 // wavefront per row the kernel is a chain of latencies (load, two shuffle reductions, store) on a quarter of
@@ -153,16 +148,58 @@ __global__ __launch_bounds__(256) void rmsnorm_inplace_kernel(bf16* x, const flo
 
 // ------------------------------------------------------------------ q/k RMSNorm + RoPE + append, and V^T append
 // Blocks [0, norm_blocks): one wave per token.  A lane reads 16 bytes (four rotation pairs) of q and of k per
-// step, four heads per wave load, keeps the row in registers, reduces the sums of squares over the whole row,
-// then normalises, rotates and writes q to its buffer and k to the token's ring slot.  Lane j forms the
-// rotation of pair j, in double so that the angle stays exact for any stream length, and the lanes pick
-// up their four by shuffle.
+// step, four heads per wave load, keeps the row in registers (IT steps: C <= 512 IT), reduces the sums of squares over
+// the whole row, then normalises, rotates and writes q to its buffer and k to the token's ring slot.  Lane j forms the
+// rotation of pair j: the angle in turns, in double, so that it stays exact for any stream length, its fraction then in
+// single precision; the lanes pick up their four by shuffle.  Few tokens: a chain of latencies (load, sum, rotate,
+// store), so only what the row needs is compiled in.
 // Blocks [norm_blocks, ...): one (64-token tile, head) each: v goes through LDS and is written
 // transposed into the V^T cache, a slot's column given by vt_column.
-constexpr int SDV2_MAX_HEADS_ROPE = 64;   // C <= 8192 and 128 channels per head
 constexpr int VT_TOK = 64;
 constexpr int VT_LD = kHeadDim + 2;     // LDS row stride in elements: odd number of words, no bank conflicts
 
+// Tile of up to 64 tokens (n of them, rows of ld elements at src) of one head into the V^T cache of st; tok0 = index of
+// the first token in the append that starts at ring position ring0.  quads: tokens 4 q .. 4 q + 3 sit in four consecutive columns (their slots start at a multiple of four),
+// so a lane stores four of them at once, sixteen lanes a row of 128 bytes; else token by token.
+__device__ __forceinline__ void append_vt_tile(const bf16* src, size_t ld, int n, const AppendStream& st, int h, int tok0,
+                                               int ring0, int S, int W, bool quads, bf16* tile) {
+    for (int idx = threadIdx.x; idx < VT_TOK * 16; idx += 256) {
+        const int tok = idx >> 4, c = idx & 15;
+        if (tok < n) {
+            const bf16x8 v = *reinterpret_cast<const bf16x8*>(src + tok * ld + c * 8);
+            bf16x2* dst = reinterpret_cast<bf16x2*>(tile + tok * VT_LD + c * 8);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dst[e] = bf16x2{v[2 * e], v[2 * e + 1]};
+        }
+    }
+    __syncthreads();
+    bf16* const vo = st.vt_cache + (size_t)h * kHeadDim * st.cap;
+    if (quads) {
+        const int q = threadIdx.x & 15, first = threadIdx.x >> 4;
+        if (4 * q >= n) return;
+        bf16* const col = vo + vt_column(slot_of(tok0 + 4 * q, ring0, S, W));
+        const bool whole = 4 * q + 4 <= n;
+#pragma unroll
+        for (int i = 0; i < kHeadDim / 16; ++i) {
+            const int d = first + 16 * i;
+            bf16x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = tile[(4 * q + e) * VT_LD + d];
+            if (whole) *reinterpret_cast<bf16x4*>(col + (size_t)d * st.cap) = v;
+            else
+                for (int e = 0; 4 * q + e < n; ++e) col[(size_t)d * st.cap + e] = v[e];
+        }
+        return;
+    }
+    // lane = token, each wave takes 32 of the 128 channels
+    const int tok = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (tok < n) {
+        bf16* const col = vo + vt_column(slot_of(tok0 + tok, ring0, S, W));
+        for (int d = wave * 32; d < wave * 32 + 32; ++d) col[(size_t)d * st.cap] = tile[tok * VT_LD + d];
+    }
+}
+
+template <int IT>
 __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a, int norm_blocks, int tiles_per_stream) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -176,17 +213,37 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a, int 
         const bf16* qp = a.qkv + (size_t)row * 3 * C;
         const bf16* kp = qp + C;
         // a wave load covers four heads: lane l holds pairs 4 (l % 16) .. + 3 of head l / 16 + 4 it
-        constexpr int kMaxIt = (SDV2_MAX_HEADS_ROPE + 3) / 4;
         const int hl = lane >> 4;
         const int p0 = 4 * (lane & 15);                      // first of this lane's four rotation pairs
-        bf16x8 qv[kMaxIt], kv[kMaxIt];
-        float sq = 0.0f, sk = 0.0f;
+        bf16x8 qv[IT], kv[IT];
 #pragma unroll
-        for (int it = 0; it < kMaxIt; ++it) {
+        for (int it = 0; it < IT; ++it) {
             const int h = hl + 4 * it;
             if (h < a.H) {
                 qv[it] = *reinterpret_cast<const bf16x8*>(qp + h * kHeadDim + 2 * p0);
                 kv[it] = *reinterpret_cast<const bf16x8*>(kp + h * kHeadDim + 2 * p0);
+            }
+        }
+        // position of the token; lane j forms the rotation of pair j, then every lane fetches its four
+        const int frame = (a.desc ? a.desc->frame_pos0[b] : st.frame_pos0) + i / a.tokens_per_frame;
+        const int inside = i % a.tokens_per_frame;
+        const int axis = a.pair_axis[lane];
+        const int pos = axis == 0 ? frame : (axis == 1 ? inside / a.grid_w : inside % a.grid_w);
+        const double turns = (double)pos * a.inv_turn[lane];
+        float sf_own, cf_own;
+        sincosf((float)((turns - rint(turns)) * 6.283185307179586477), &sf_own, &cf_own);
+        float cf[4], sf[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            cf[e] = __shfl(cf_own, p0 + e, kWave);
+            sf[e] = __shfl(sf_own, p0 + e, kWave);
+        }
+        const long long g = (a.desc ? a.desc->g0[b] : st.g0) + i;
+        const int slot = slot_of(i, a.desc ? a.desc->ring0[b] : st.ring0, a.S, a.W);
+        float sq = 0.0f, sk = 0.0f;
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            if (hl + 4 * it < a.H) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     sq += (float)qv[it][e] * (float)qv[it][e];
@@ -196,26 +253,10 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a, int 
         }
         const float rq = rsqrtf(wave_sum(sq) / (float)C + a.eps);
         const float rk = rsqrtf(wave_sum(sk) / (float)C + a.eps);
-        // position of the token; lane j forms the rotation of pair j, then every lane fetches its four
-        const int frame = (a.desc ? a.desc->frame_pos0[b] : st.frame_pos0) + i / a.tokens_per_frame;
-        const int inside = i % a.tokens_per_frame;
-        const int axis = a.pair_axis[lane];
-        const int pos = axis == 0 ? frame : (axis == 1 ? inside / a.grid_w : inside % a.grid_w);
-        double sn, cs;
-        sincos((double)pos * a.inv_freq[lane], &sn, &cs);
-        const float cf_own = (float)cs, sf_own = (float)sn;
-        float cf[4], sf[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            cf[e] = __shfl(cf_own, p0 + e, kWave);
-            sf[e] = __shfl(sf_own, p0 + e, kWave);
-        }
-        const long long g = (a.desc ? a.desc->g0[b] : st.g0) + i;
-        const int slot = slot_of(g, a.S, a.W);
         if (lane == 0) st.ids[slot] = g;
         bf16* qo = a.q_out + (size_t)row * C;
 #pragma unroll
-        for (int it = 0; it < kMaxIt; ++it) {
+        for (int it = 0; it < IT; ++it) {
             const int h = hl + 4 * it;
             if (h < a.H) {
                 const int c = h * kHeadDim + 2 * p0;
@@ -246,29 +287,12 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a, int 
     const int tile_id = vb / a.H;
     const int b = tile_id / tiles_per_stream;
     const int tok0 = (tile_id - b * tiles_per_stream) * VT_TOK;
-    const AppendStream& st = a.st[b];
-    // read: 64 tokens x 128 channels, 16-byte chunks, stored to LDS as 4-byte words
-    for (int idx = threadIdx.x; idx < VT_TOK * 16; idx += 256) {
-        const int tok = idx >> 4, c = idx & 15;
-        if (tok0 + tok < a.L) {
-            const bf16* vp = a.qkv + ((size_t)b * a.L + tok0 + tok) * 3 * C + 2 * C + h * kHeadDim + c * 8;
-            const bf16x8 v = *reinterpret_cast<const bf16x8*>(vp);
-            bf16x2* dst = reinterpret_cast<bf16x2*>(tile + tok * VT_LD + c * 8);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dst[e] = bf16x2{v[2 * e], v[2 * e + 1]};
-        }
-    }
-    __syncthreads();
-    // write: lane = token, each wave takes 32 of the 128 channels
-    const int tok = lane;
-    if (tok0 + tok < a.L) {
-        const int slot = slot_of((a.desc ? a.desc->g0[b] : st.g0) + tok0 + tok, a.S, a.W);
-        bf16* vo = st.vt_cache + (size_t)h * kHeadDim * st.cap + vt_column(slot);
-        for (int d = wave * 32; d < wave * 32 + 32; ++d) vo[(size_t)d * st.cap] = tile[tok * VT_LD + d];
-    }
+    append_vt_tile(a.qkv + ((size_t)b * a.L + tok0) * 3 * C + 2 * C + h * kHeadDim, (size_t)3 * C, min(VT_TOK, a.L - tok0), a.st[b], h,
+                   tok0, a.desc ? a.desc->ring0[b] : a.st[b].ring0, a.S, a.W, a.tokens_per_frame % 4 == 0, tile);
 }
 
-// ------------------------------------------------------------------ plain append of final rows
+// ------------------------------------------------------------------ append of rows without rotation
+template <int IT>
 __global__ __launch_bounds__(256) void plain_append_kernel(PlainAppendArgs a, int k_blocks) {
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
@@ -277,11 +301,38 @@ __global__ __launch_bounds__(256) void plain_append_kernel(PlainAppendArgs a, in
         const int row = blockIdx.x * 4 + wave;
         if (row >= a.n) return;
         const long long g = a.st.g0 + row;
-        const int slot = slot_of(g, a.S, a.W);
+        const int slot = slot_of(row, a.st.ring0, a.S, a.W);
         if (lane == 0 && a.st.ids != nullptr) a.st.ids[slot] = g;
-        for (int h = 0; h < a.H; ++h) {
-            const bf16x2 kv = *reinterpret_cast<const bf16x2*>(a.k + (size_t)row * C + h * kHeadDim + 2 * lane);
-            *reinterpret_cast<bf16x2*>(a.st.k_cache + ((size_t)h * a.st.cap + slot) * kHeadDim + 2 * lane) = kv;
+        const int hl = lane >> 4, c0 = 8 * (lane & 15);      // a wave load covers four heads
+        bf16x8 kv[IT];
+        float sq = 0.0f;
+#pragma unroll
+        for (int it = 0; it < IT; ++it)
+            if (hl + 4 * it < a.H) kv[it] = *reinterpret_cast<const bf16x8*>(a.k + (size_t)row * C + (hl + 4 * it) * kHeadDim + c0);
+        float r = 1.0f;
+        if (a.g_k != nullptr) {
+#pragma unroll
+            for (int it = 0; it < IT; ++it)
+                if (hl + 4 * it < a.H)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) sq += (float)kv[it][e] * (float)kv[it][e];
+            r = rsqrtf(wave_sum(sq) / (float)C + a.eps);
+        }
+#pragma unroll
+        for (int it = 0; it < IT; ++it) {
+            const int h = hl + 4 * it;
+            if (h < a.H) {
+                if (a.g_k != nullptr) {
+                    const f32x4 g0 = *reinterpret_cast<const f32x4*>(a.g_k + h * kHeadDim + c0);
+                    const f32x4 g1 = *reinterpret_cast<const f32x4*>(a.g_k + h * kHeadDim + c0 + 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        kv[it][e] = (bf16)((float)kv[it][e] * r * g0[e]);
+                        kv[it][e + 4] = (bf16)((float)kv[it][e + 4] * r * g1[e]);
+                    }
+                }
+                *reinterpret_cast<bf16x8*>(a.st.k_cache + ((size_t)h * a.st.cap + slot) * kHeadDim + c0) = kv[it];
+            }
         }
         return;
     }
@@ -289,22 +340,8 @@ __global__ __launch_bounds__(256) void plain_append_kernel(PlainAppendArgs a, in
     const int vb = blockIdx.x - k_blocks;
     const int h = vb % a.H;
     const int tok0 = (vb / a.H) * VT_TOK;
-    for (int idx = threadIdx.x; idx < VT_TOK * 16; idx += 256) {
-        const int tok = idx >> 4, c = idx & 15;
-        if (tok0 + tok < a.n) {
-            const bf16x8 v = *reinterpret_cast<const bf16x8*>(a.v + (size_t)(tok0 + tok) * C + h * kHeadDim + c * 8);
-            bf16x2* dst = reinterpret_cast<bf16x2*>(tile + tok * VT_LD + c * 8);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dst[e] = bf16x2{v[2 * e], v[2 * e + 1]};
-        }
-    }
-    __syncthreads();
-    const int tok = lane;
-    if (tok0 + tok < a.n) {
-        const int slot = slot_of(a.st.g0 + tok0 + tok, a.S, a.W);
-        bf16* vo = a.st.vt_cache + (size_t)h * kHeadDim * a.st.cap + vt_column(slot);
-        for (int d = wave * 32; d < wave * 32 + 32; ++d) vo[(size_t)d * a.st.cap] = tile[tok * VT_LD + d];
-    }
+    append_vt_tile(a.v + (size_t)tok0 * C + h * kHeadDim, (size_t)C, min(VT_TOK, a.n - tok0), a.st, h, tok0, a.st.ring0, a.S, a.W,
+                   a.quads != 0, tile);
 }
 
 // ------------------------------------------------------------------ conditioning
@@ -325,38 +362,74 @@ __global__ void timestep_embedding_kernel(TimestepArgs ts, const StepDesc* desc,
     emb[idx] = (float)(j < half ? cos(arg) : sin(arg));
 }
 
-// one wave per output n; the B input rows reuse each weight row
-__global__ __launch_bounds__(256) void gemv_kernel(const float* x, const bf16* w, const float* bias, float* y, int B,
-                                                   int N, int K, int silu_in) {
+// y[b][n] = sum_k act(x[b][k]) W[n][k] + bias[n] for up to NB rows x.  Bound by the weight stream (the modulation
+// projection of the 14B model is 315 MB).  The activated inputs go through LDS, GEMV_K of them at a time, formed once per
+// workgroup; a wave owns R weight rows at a time, so that an input read from LDS serves R of them.  (One wave per row that
+// formed the activation itself, eight exponentials per eight weights, ran at 1.07 TB/s: 293 us.)  The R NB sums are
+// reduced by halving: at every step a lane keeps half of the values and sends the other half.
+constexpr int GEMV_K = 1024;
+template <int NB, int R>
+__global__ __launch_bounds__(256) void gemv_kernel(const float* x, const bf16* w, const float* bias, float* y, int B, int N,
+                                                   int K, int silu_in) {
+    __shared__ __attribute__((aligned(16))) float xs[NB][GEMV_K];
     const int lane = threadIdx.x & 63;
-    const int n = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (n >= N) return;
-    float acc[kMaxBatch];
+    const int n0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * R;
+    float acc[R * NB];
 #pragma unroll
-    for (int b = 0; b < kMaxBatch; ++b) acc[b] = 0.0f;
-    const bf16* wp = w + (size_t)n * K;
-    for (int k = lane * 8; k < K; k += 64 * 8) {
-        const bf16x8 wv = *reinterpret_cast<const bf16x8*>(wp + k);
+    for (int i = 0; i < R * NB; ++i) acc[i] = 0.0f;
+    for (int k0 = 0; k0 < K; k0 += GEMV_K) {
+        const int kn = min(GEMV_K, K - k0);                   // a multiple of 8
+        bf16x8 wv[GEMV_K / 512][R];
 #pragma unroll
-        for (int b = 0; b < kMaxBatch; ++b) {
-            if (b < B) {
-                const float* xp = x + (size_t)b * K + k;
+        for (int c = 0; c < GEMV_K / 512; ++c) {
+            const int k = min(512 * c + lane * 8, kn - 8);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    float xv = xp[e];
-                    if (silu_in) xv = silu_f(xv);
-                    acc[b] += xv * (float)wv[e];
+            for (int r = 0; r < R; ++r) wv[c][r] = *reinterpret_cast<const bf16x8*>(w + (size_t)min(n0 + r, N - 1) * K + k0 + k);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            for (int k = threadIdx.x; k < kn; k += 256) {
+                float v = b < B ? x[(size_t)b * K + k0 + k] : 0.0f;
+                if (silu_in) v = silu_f(v);
+                xs[b][k] = v;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < GEMV_K / 512; ++c) {
+            const int k = 512 * c + lane * 8;
+            if (k < kn) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b) {
+                    const f32x4 x0 = *reinterpret_cast<const f32x4*>(&xs[b][k]), x1 = *reinterpret_cast<const f32x4*>(&xs[b][k + 4]);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            acc[r * NB + b] += x0[e] * (float)wv[c][r][e];
+                            acc[r * NB + b] += x1[e] * (float)wv[c][r][e + 4];
+                        }
+                    }
                 }
             }
         }
     }
+    int index = 0, off = 32;
 #pragma unroll
-    for (int b = 0; b < kMaxBatch; ++b) {
-        if (b < B) {
-            const float s = wave_sum(acc[b]);
-            if (lane == 0) y[(size_t)b * N + n] = s + bias[n];
+    for (int s = R * NB / 2; s >= 1; s /= 2, off /= 2) {
+        const bool upper = (lane & off) != 0;
+#pragma unroll
+        for (int i = 0; i < s; ++i) {
+            const float keep = upper ? acc[i + s] : acc[i], send = upper ? acc[i] : acc[i + s];
+            acc[i] = keep + __shfl_xor(send, off, kWave);
         }
+        index += upper ? s : 0;
     }
+    const int tail = off;                                     // lanes that differ below bit `off` hold parts of one sum
+    for (; off >= 1; off /= 2) acc[0] += __shfl_xor(acc[0], off, kWave);
+    const int n = n0 + index / NB, b = index % NB;
+    if ((tail == 0 || (lane & (2 * tail - 1)) == 0) && n < N && b < B) y[(size_t)b * N + n] = acc[0] + bias[n];
 }
 
 }  // namespace
@@ -391,24 +464,41 @@ hipError_t launch_rmsnorm_inplace(bf16* x, const float* gain, int rows, int C, i
     return hipGetLastError();
 }
 
+// F(IT) with the smallest compiled number of 512-channel steps that covers H heads (at most 64)
+#define SDV2_BY_STEPS(H, F)                         \
+    do {                                            \
+        const int steps__ = ((H) + 3) / 4;          \
+        if (steps__ <= 1) F(1);                     \
+        else if (steps__ <= 2) F(2);                \
+        else if (steps__ <= 3) F(3);                \
+        else if (steps__ <= 4) F(4);                \
+        else if (steps__ <= 6) F(6);                \
+        else if (steps__ <= 8) F(8);                \
+        else if (steps__ <= 10) F(10);              \
+        else F(16);                                 \
+    } while (0)
+
 hipError_t launch_rope_append(const RopeAppendArgs& a, hipStream_t s) {
     const int norm_blocks = (a.B * a.L + 3) / 4;
     const int tiles_per_stream = (a.L + VT_TOK - 1) / VT_TOK;
     const int v_blocks = a.B * tiles_per_stream * a.H;
-    hipLaunchKernelGGL(rope_append_kernel, dim3(norm_blocks + v_blocks), dim3(256), 0, s, a, norm_blocks,
-                       tiles_per_stream);
+#define F(IT) hipLaunchKernelGGL(rope_append_kernel<IT>, dim3(norm_blocks + v_blocks), dim3(256), 0, s, a, norm_blocks, tiles_per_stream)
+    SDV2_BY_STEPS(a.H, F);
+#undef F
     return hipGetLastError();
 }
 
 hipError_t launch_plain_append(const PlainAppendArgs& a, hipStream_t s) {
     const int k_blocks = (a.n + 3) / 4;
     const int v_blocks = ((a.n + VT_TOK - 1) / VT_TOK) * a.H;
-    hipLaunchKernelGGL(plain_append_kernel, dim3(k_blocks + v_blocks), dim3(256), 0, s, a, k_blocks);
+#define F(IT) hipLaunchKernelGGL(plain_append_kernel<IT>, dim3(k_blocks + v_blocks), dim3(256), 0, s, a, k_blocks)
+    SDV2_BY_STEPS(a.H, F);
+#undef F
     return hipGetLastError();
 }
 
-hipError_t launch_text_relayout(const bf16* k_rows, const bf16* v_rows, bf16* kt, bf16* vtt, int L_t, int C, int H,
-                                int cap, hipStream_t s) {
+hipError_t launch_text_relayout(const bf16* k_rows, const bf16* v_rows, const float* g_k, float eps, bf16* kt, bf16* vtt, int L_t,
+                                int C, int H, int cap, hipStream_t s) {
     // the text K/V buffers are a cache with no ring: slot = token index
     PlainAppendArgs a;
     a.k = k_rows;
@@ -418,19 +508,34 @@ hipError_t launch_text_relayout(const bf16* k_rows, const bf16* v_rows, bf16* kt
     a.H = H;
     a.S = cap;          // every token is "sink": slot(g) = g
     a.W = 1;
+    a.quads = 1;
+    a.g_k = g_k;
+    a.eps = eps;
     a.st.k_cache = kt;
     a.st.vt_cache = vtt;
     a.st.ids = nullptr;
     a.st.g0 = 0;
+    a.st.ring0 = ring_position(0, cap, 1);
     a.st.frame_pos0 = 0;
     a.st.cap = cap;
     return launch_plain_append(a, s);
 }
 
+template <int NB>
+static hipError_t launch_gemv_t(const float* x, const bf16* w, const float* bias, float* y, int B, int N, int K, int silu_in,
+                                hipStream_t s) {
+    // eight rows per wave where that still gives every compute unit a workgroup; else one (timestep MLP: latency)
+    if (N >= 8192) hipLaunchKernelGGL((gemv_kernel<NB, 8>), dim3((N + 31) / 32), dim3(256), 0, s, x, w, bias, y, B, N, K, silu_in);
+    else hipLaunchKernelGGL((gemv_kernel<NB, 1>), dim3((N + 3) / 4), dim3(256), 0, s, x, w, bias, y, B, N, K, silu_in);
+    return hipGetLastError();
+}
+
 hipError_t launch_gemv(const float* x, const bf16* w, const float* bias, float* y, int B, int N, int K, int silu_in,
                        hipStream_t s) {
-    hipLaunchKernelGGL(gemv_kernel, dim3((N + 3) / 4), dim3(256), 0, s, x, w, bias, y, B, N, K, silu_in);
-    return hipGetLastError();
+    if (B == 1) return launch_gemv_t<1>(x, w, bias, y, B, N, K, silu_in, s);
+    if (B == 2) return launch_gemv_t<2>(x, w, bias, y, B, N, K, silu_in, s);
+    if (B <= 4) return launch_gemv_t<4>(x, w, bias, y, B, N, K, silu_in, s);
+    return launch_gemv_t<8>(x, w, bias, y, B, N, K, silu_in, s);
 }
 
 hipError_t launch_timestep_embedding(const float* t_host, const StepDesc* desc, float* emb, int B, int t_dim, double base,

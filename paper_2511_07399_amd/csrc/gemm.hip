@@ -508,10 +508,18 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     };
     const int KT = g.K / BK;
     int kt0 = 0, nk = KT;
+    const bool pair = g.w2 != nullptr;                       // two products with A in common: tile range ks is product ks
+    const bool split = splitk > 1 && !pair;
     if (splitk > 1) {                                        // one tile per workgroup then
         ks = tile / tiles;
-        kt0 = ks * KT / splitk;
-        nk = (ks + 1) * KT / splitk - kt0;
+        if (split) {
+            kt0 = ks * KT / splitk;
+            nk = (ks + 1) * KT / splitk - kt0;
+        } else if (ks == 1) {
+            g.w = g.w2;
+            g.bias = g.bias2;
+            g.out = g.out2;
+        }
     }
     locate(tile - ks * tiles, m0, n0);
 
@@ -645,7 +653,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     };
 #pragma unroll
     for (int j = 0; j < TN; ++j) bias[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (g.bias != nullptr && splitk == 1) load_bias(n0);
+    if (g.bias != nullptr && !split) load_bias(n0);
     constexpr bool kPre = TM * TN <= 16;
     f32x4 xpre[kPre ? TM * TN : 1];
     auto load_x = [&]() {
@@ -722,12 +730,12 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
             landed = true;
         }
         const int row0 = m0 + wm * (16 * TM), col0 = n0 + wn * (16 * TN);
-        switch (splitk > 1 ? (int)kEpiPartial : g.epilogue) {
+        switch (split ? (int)kEpiPartial : g.epilogue) {
             case kEpiBias: store_wave<TM, TN, kEpiBias>(g, g.out, acc, row0, col0, lane); break;
             case kEpiBiasGelu: store_wave<TM, TN, kEpiBiasGelu>(g, g.out, acc, row0, col0, lane); break;
             case kEpiGatedResidual: store_wave<TM, TN, kEpiGatedResidual>(g, g.out, acc, row0, col0, lane, xpre); break;
             case kEpiPartial:                                // the partial sums of a k part, or a plain fp32 output
-                store_wave<TM, TN, kEpiPartial>(g, splitk > 1 ? g.splitk_partials + (size_t)ks * g.M * g.N : reinterpret_cast<float*>(g.out), acc,
+                store_wave<TM, TN, kEpiPartial>(g, split ? g.splitk_partials + (size_t)ks * g.M * g.N : reinterpret_cast<float*>(g.out), acc,
                                                 row0, col0, lane);
                 break;
             default: store_wave<TM, TN, kEpiResidual>(g, g.out, acc, row0, col0, lane, xpre); break;
@@ -1125,6 +1133,20 @@ static int usable_splitk(const GemmArgs& g, const TilePlan& p) {
 // part 0: the whole product; 1: only the kernel on the matrix cores; 2: only the pass that adds the k parts (nothing
 // when the plan does not split).  The benchmark times the two parts separately.
 static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln_done, hipStream_t s, int part = 0) {
+    if (g.w2 != nullptr) {
+        // both products in one launch, planned as one of twice the width, without a k split
+        TilePlan p2 = plan_tiles(g.M, 2 * g.N, g.K, kEpiBias);
+        tile_override(&p2);
+        if (p2.dma && fits_32bit_offsets(g.M, g.N, g.K)) return launch_tile_config(g, p2.dma, 2, s);
+        GemmArgs one = g;
+        one.w2 = nullptr;
+        const hipError_t e1 = launch_gemm_impl(one, nullptr, nullptr, s);
+        if (e1 != hipSuccess) return e1;
+        one.w = g.w2;
+        one.bias = g.bias2;
+        one.out = g.out2;
+        return launch_gemm_impl(one, nullptr, nullptr, s);
+    }
     TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue);
     tile_override(&p);
     const int splitk = usable_splitk(g, p);

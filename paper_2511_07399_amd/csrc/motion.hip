@@ -3,14 +3,55 @@
 //   dhat_t = clip(max_{i in {t-k..t}} d_i / sigma, 0, 1),
 //   s_t    = lambda [s_max - (s_max - s_min) dhat_t] + (1 - lambda) s_{t-1}.
 // The frame differences are one pass over the latents (HBM-bound, a few hundred KB per frame); the recurrence is a
-// handful of scalar operations per frame, done on the device by one wave so that s_t is there without a round trip.
+// handful of scalar operations per frame, done in the same launch by one wave so that s_t is there without a round trip.
 #include "common.h"
 
 namespace sdv2 {
 namespace {
 
-// grid = (kMotionBlocks, T): partial sums of (v_t - v_{t-1})^2 in fp32, one float per workgroup.
-__global__ __launch_bounds__(256) void motion_diff_kernel(MotionArgs a) {
+// d_t from the partial sums (added in double, fixed butterfly), then the ring of the last k + 1 values, the window
+// maximum, the clip and the moving average, for t = 0 .. T-1 in order; one wave.
+__device__ __forceinline__ void motion_recurrence(const MotionArgs& a, int n_blocks, int lane) {
+    float s = a.state[0];
+    int count = __float_as_int(a.state[1]);
+    float* ring = a.state + kMotionHeaderFloats;
+    const int ring_len = a.k + 1;
+    for (int t = 0; t < a.T; ++t) {
+        double sum = 0.0;
+        for (int b = lane; b < n_blocks; b += kWave)
+            sum += (double)__hip_atomic_load(a.partial + (size_t)t * n_blocks + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+        const float d = (float)sqrt(sum / (double)a.n);
+        // the window: what the ring holds besides the entry that d replaces, and d
+        const int have = count < ring_len ? count : ring_len, pos = count % ring_len;
+        float mx = d;
+        for (int i = lane; i < have; i += kWave)
+            if (i != pos) mx = fmaxf(mx, ring[i]);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+        ++count;
+        const float dhat = fminf(fmaxf(mx / a.sigma, 0.0f), 1.0f);
+        s = a.lambda * (a.s_max - (a.s_max - a.s_min) * dhat) + (1.0f - a.lambda) * s;
+        if (lane == 0) {
+            ring[pos] = d;
+            a.d_out[t] = d;
+            a.dhat_out[t] = dhat;
+            a.s_out[t] = s;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");       // ring[pos] before the next frame's reads
+    }
+    if (lane == 0) {
+        a.state[0] = s;
+        a.state[1] = __int_as_float(count);
+    }
+}
+
+// grid = (kMotionBlocks, T): partial sums of (v_t - v_{t-1})^2 in fp32, one float per workgroup; the workgroup that is
+// the last to hand in its sum runs the recurrence.  A second launch for it cost as much as the pass itself.  The sums and
+// the ticket (state[2], 0 between calls) are device-scope atomics, which go through to memory: a sum has arrived there
+// before its workgroup takes a ticket (the wait on its store), so whoever holds the last ticket reads all of them.
+__global__ __launch_bounds__(256) void motion_update_kernel(MotionArgs a) {
     const int t = blockIdx.y;
     const float* cur = a.frames + (size_t)t * a.n;
     const float* prev = t == 0 ? a.prev : a.frames + (size_t)(t - 1) * a.n;
@@ -33,43 +74,22 @@ __global__ __launch_bounds__(256) void motion_diff_kernel(MotionArgs a) {
         }
     }
     __shared__ float red[4];
+    __shared__ int last;
     acc = wave_sum(acc);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) a.partial[(size_t)t * gridDim.x + blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-// One wave.  For t = 0 .. T-1 in order: d_t from the partial sums (added in double, fixed butterfly), then on lane 0
-// the ring of the last k + 1 values, the window maximum, the clip and the moving average.
-__global__ __launch_bounds__(kWave) void motion_controller_kernel(MotionArgs a, int n_blocks) {
-    const int lane = threadIdx.x;
-    float s = a.state[0];
-    int count = __float_as_int(a.state[1]);
-    float* ring = a.state + kMotionHeaderFloats;
-    const int ring_len = a.k + 1;
-    for (int t = 0; t < a.T; ++t) {
-        double sum = 0.0;
-        for (int b = lane; b < n_blocks; b += kWave) sum += (double)a.partial[(size_t)t * n_blocks + b];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
-        if (lane == 0) {
-            const float d = (float)sqrt(sum / (double)a.n);
-            ring[count % ring_len] = d;
-            ++count;
-            const int have = count < ring_len ? count : ring_len;
-            float mx = 0.0f;
-            for (int i = 0; i < have; ++i) mx = fmaxf(mx, ring[i]);
-            const float dhat = fminf(fmaxf(mx / a.sigma, 0.0f), 1.0f);
-            s = a.lambda * (a.s_max - (a.s_max - a.s_min) * dhat) + (1.0f - a.lambda) * s;
-            a.d_out[t] = d;
-            a.dhat_out[t] = dhat;
-            a.s_out[t] = s;
-        }
+    unsigned* const ticket = reinterpret_cast<unsigned*>(a.state + 2);
+    if (threadIdx.x == 0) {
+        __hip_atomic_store(a.partial + (size_t)t * gridDim.x + blockIdx.x, (red[0] + red[1]) + (red[2] + red[3]), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0x0F70);                            // vmcnt 0: the sum is in memory
+        asm volatile("" ::: "memory");
+        const unsigned n = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        last = n == gridDim.x * gridDim.y - 1;
+        if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (lane == 0) {
-        a.state[0] = s;
-        a.state[1] = __int_as_float(count);
-    }
+    __syncthreads();
+    if (last && threadIdx.x < kWave) motion_recurrence(a, gridDim.x, threadIdx.x);
 }
 
 __global__ void motion_init_kernel(float* state, int n_floats, float s_init) {
@@ -85,10 +105,7 @@ hipError_t launch_motion_init(float* state, int n_floats, float s_init, hipStrea
 }
 
 hipError_t launch_motion_update(const MotionArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(motion_diff_kernel, dim3(kMotionBlocks, a.T), dim3(256), 0, s, a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(motion_controller_kernel, dim3(1), dim3(kWave), 0, s, a, kMotionBlocks);
+    hipLaunchKernelGGL(motion_update_kernel, dim3(kMotionBlocks, a.T), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

@@ -11,32 +11,45 @@ constexpr int kSimBlock = 256;
 
 // Partial sums of <h, s_i>, |h|^2, |s_i|^2 over the value rows.  V^T is [H][128][cap] with a column permutation inside
 // every 16 slots, so element (head, d, token j) of a frame that starts at slot s0 sits in column vt_column(s0 + j).
-// grid = (blocks over the H * 128 rows, sink frames); each block writes three floats, summed in a fixed order by the
-// second kernel: the result does not depend on scheduling.
+// grid = (blocks over the H * 128 rows, sink frames), a wave per row; each block writes three floats, summed in a fixed
+// order by the second kernel: the result does not depend on scheduling.
 __global__ __launch_bounds__(kSimBlock) void sink_similarity_partial_kernel(SinkSimArgs a) {
     const int sink = blockIdx.y;
     const int sink0 = sink * a.P;
     const int rows = a.H * kHeadDim;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float dot = 0.0f, hh = 0.0f, ss = 0.0f;
     // Four consecutive slots that start at a multiple of four sit in four consecutive columns (the permutation
-    // moves whole groups of four), so frames that start at multiples of four are read 8 bytes at a time.
+    // moves whole groups of four), so frames that start at multiples of four are read 8 bytes at a time, and four
+    // pieces of both frames per lane are in flight.
     const bool quads = (a.P % 4 == 0) && (a.src0 % 4 == 0);
-    for (int row = blockIdx.x; row < rows; row += gridDim.x) {
+    for (int row = blockIdx.x * (kSimBlock / kWave) + wave; row < rows; row += gridDim.x * (kSimBlock / kWave)) {
         const bf16* v = a.vt + (size_t)row * a.cap;
         if (quads) {
-            for (int q = threadIdx.x; q < a.P / 4; q += kSimBlock) {
-                const bf16x4 x = *reinterpret_cast<const bf16x4*>(v + vt_column(a.src0 + 4 * q));
-                const bf16x4 y = *reinterpret_cast<const bf16x4*>(v + vt_column(sink0 + 4 * q));
+            const int n = a.P / 4;
+            for (int q0 = lane; q0 < n; q0 += 4 * kWave) {
+                bf16x4 x[4], y[4];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float xf = (float)x[e], yf = (float)y[e];
-                    dot += xf * yf;
-                    hh += xf * xf;
-                    ss += yf * yf;
+                for (int u = 0; u < 4; ++u) {
+                    const int q = min(q0 + kWave * u, n - 1);
+                    x[u] = *reinterpret_cast<const bf16x4*>(v + vt_column(a.src0 + 4 * q));
+                    y[u] = *reinterpret_cast<const bf16x4*>(v + vt_column(sink0 + 4 * q));
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    if (q0 + kWave * u < n) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float xf = (float)x[u][e], yf = (float)y[u][e];
+                            dot += xf * yf;
+                            hh += xf * xf;
+                            ss += yf * yf;
+                        }
+                    }
                 }
             }
         } else {
-            for (int j = threadIdx.x; j < a.P; j += kSimBlock) {
+            for (int j = lane; j < a.P; j += kWave) {
                 const float x = (float)v[vt_column(a.src0 + j)];
                 const float y = (float)v[vt_column(sink0 + j)];
                 dot += x * y;
@@ -49,7 +62,6 @@ __global__ __launch_bounds__(kSimBlock) void sink_similarity_partial_kernel(Sink
     dot = wave_sum(dot);
     hh = wave_sum(hh);
     ss = wave_sum(ss);
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) {
         red[0][wave] = dot;
         red[1][wave] = hh;
@@ -83,8 +95,9 @@ __global__ __launch_bounds__(kWave) void sink_similarity_final_kernel(SinkSimArg
 }
 
 // s_i <- h_t: the P key rows, value columns and token ids of the frame at slot src0 are copied to the sink frame at
-// slot dst0.  Blocks [0, k_blocks) copy key rows (256 bytes per head and token, 16 bytes per lane), the rest value
-// rows of V^T (P columns each) and, in the first of them, the ids.
+// slot dst0.  Blocks [0, k_blocks) copy key rows (256 bytes per head and token, 16 bytes per lane), the rest four value
+// rows of V^T each (P columns, a wave per row, 8 bytes per lane where the frames start at multiples of four slots: 2 bytes
+// at a time the copy ran at 1.8 TB/s) and, in the first of them, the ids.
 __global__ __launch_bounds__(256) void refresh_sink_kernel(SinkCopyArgs a, int k_blocks) {
     if ((int)blockIdx.x < k_blocks) {
         // sixteen lanes per (head, token): 16 bytes each
@@ -97,46 +110,65 @@ __global__ __launch_bounds__(256) void refresh_sink_kernel(SinkCopyArgs a, int k
         dst[c] = src[c];
         return;
     }
-    const int row = blockIdx.x - k_blocks;                       // (head, d) row of V^T
+    const int row = (blockIdx.x - k_blocks) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;      // (head, d) row of V^T
     bf16* v = a.vt + (size_t)row * a.cap;
-    for (int j = threadIdx.x; j < a.P; j += 256) v[vt_column(a.dst0 + j)] = v[vt_column(a.src0 + j)];
-    if (row == 0)
+    if (a.P % 4 == 0 && a.src0 % 4 == 0 && a.dst0 % 4 == 0) {
+        const int n = a.P / 4;
+        for (int q0 = lane; q0 < n; q0 += 4 * kWave) {
+            bf16x4 x[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const bf16x4*>(v + vt_column(a.src0 + 4 * min(q0 + kWave * u, n - 1)));
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                if (q0 + kWave * u < n) *reinterpret_cast<bf16x4*>(v + vt_column(a.dst0 + 4 * (q0 + kWave * u))) = x[u];
+        }
+    } else {
+        for (int j = lane; j < a.P; j += kWave) v[vt_column(a.dst0 + j)] = v[vt_column(a.src0 + j)];
+    }
+    if ((int)blockIdx.x == k_blocks)
         for (int j = threadIdx.x; j < a.P; j += 256) a.ids[a.dst0 + j] = a.ids[a.src0 + j];
 }
 
 // Every filled slot's key, heads x frame pairs: (x0, x1) <- (x0 c - x1 s, x0 s + x1 c) with (c, s) the cosine and
 // sine of -delta * omega_j, formed in double on the host (there are only kMaxFramePairs of them).
+// grid = (filled slots x groups of 4 pairs = 16 bytes, heads), two pieces per thread.
 __global__ __launch_bounds__(256) void rotate_keys_kernel(RotateKeysArgs a) {
-    // one thread per (head, filled slot, group of 4 pairs = 16 bytes)
-    const int groups = (a.n_pairs + 3) / 4;
-    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
-    const long long total = (long long)a.H * a.n_slots * groups;
-    if (idx >= total) return;
-    const int gq = (int)(idx % groups);
-    const long long t = idx / groups;
-    const int si = (int)(t % a.n_slots);
-    const int h = (int)(t / a.n_slots);
-    const int slot = si < a.sink_fill ? si : a.S + (si - a.sink_fill);
-    bf16x8* p = reinterpret_cast<bf16x8*>(a.k + ((size_t)h * a.cap + slot) * kHeadDim) + gq;
-    bf16x8 x = *p;
+    const unsigned groups = (unsigned)(a.n_pairs + 3) / 4, total = (unsigned)a.n_slots * groups;
+    bf16* const head = a.k + (size_t)blockIdx.y * a.cap * kHeadDim;
+    bf16x8* p[2];
+    bf16x8 x[2];
+    unsigned gq[2];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int j = 4 * gq + e;
-        if (j < a.n_pairs) {
-            const float c = a.cs[j], s = a.sn[j];
-            const float x0 = (float)x[2 * e], x1 = (float)x[2 * e + 1];
-            x[2 * e] = (bf16)(x0 * c - x1 * s);
-            x[2 * e + 1] = (bf16)(x0 * s + x1 * c);
-        }
+    for (int u = 0; u < 2; ++u) {
+        const unsigned idx = blockIdx.x * 512u + 256u * u + threadIdx.x;
+        const unsigned i = min(idx, total - 1), si = i / groups;
+        gq[u] = i - si * groups;
+        const int slot = (int)si < a.sink_fill ? (int)si : a.S + ((int)si - a.sink_fill);
+        p[u] = reinterpret_cast<bf16x8*>(head + (size_t)slot * kHeadDim) + gq[u];
+        x[u] = *p[u];
     }
-    *p = x;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        if (blockIdx.x * 512u + 256u * u + threadIdx.x >= total) break;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int j = 4 * gq[u] + e;
+            if (j < a.n_pairs) {
+                const float c = a.cs[j], s = a.sn[j];
+                const float x0 = (float)x[u][2 * e], x1 = (float)x[u][2 * e + 1];
+                x[u][2 * e] = (bf16)(x0 * c - x1 * s);
+                x[u][2 * e + 1] = (bf16)(x0 * s + x1 * c);
+            }
+        }
+        *p[u] = x[u];
+    }
 }
 
 }  // namespace
 
 int sink_similarity_blocks(int H) {
-    const int rows = H * kHeadDim;
-    return rows < 1024 ? rows : 1024;
+    const int blocks = H * kHeadDim / (kSimBlock / kWave);
+    return blocks < 512 ? blocks : 512;
 }
 
 hipError_t launch_sink_similarity(const SinkSimArgs& a, hipStream_t s) {
@@ -150,15 +182,15 @@ hipError_t launch_sink_similarity(const SinkSimArgs& a, hipStream_t s) {
 
 hipError_t launch_refresh_sink(const SinkCopyArgs& a, hipStream_t s) {
     const int k_blocks = (a.H * a.P + 15) / 16;
-    const int v_blocks = a.H * kHeadDim;
+    const int v_blocks = a.H * kHeadDim / 4;
     hipLaunchKernelGGL(refresh_sink_kernel, dim3(k_blocks + v_blocks), dim3(256), 0, s, a, k_blocks);
     return hipGetLastError();
 }
 
 hipError_t launch_rotate_keys(const RotateKeysArgs& a, hipStream_t s) {
     if (a.n_slots == 0) return hipSuccess;
-    const long long total = (long long)a.H * a.n_slots * ((a.n_pairs + 3) / 4);
-    hipLaunchKernelGGL(rotate_keys_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a);
+    const unsigned total = (unsigned)a.n_slots * (unsigned)((a.n_pairs + 3) / 4);          // at most 2^30 slots x 6
+    hipLaunchKernelGGL(rotate_keys_kernel, dim3((total + 511) / 512, a.H), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 
