@@ -20,23 +20,23 @@ __global__ __launch_bounds__(kSimBlock) void sink_similarity_partial_kernel(Sink
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     float dot = 0.0f, hh = 0.0f, ss = 0.0f;
     // Four consecutive slots that start at a multiple of four sit in four consecutive columns (the permutation
-    // moves whole groups of four), so frames that start at multiples of four are read 8 bytes at a time, and four
-    // pieces of both frames per lane are in flight.
+    // moves whole groups of four), so frames that start at multiples of four are read 8 bytes at a time, and eight
+    // pieces of both frames per lane are in flight (one round of loads for 2048 tokens).
     const bool quads = (a.P % 4 == 0) && (a.src0 % 4 == 0);
     for (int row = blockIdx.x * (kSimBlock / kWave) + wave; row < rows; row += gridDim.x * (kSimBlock / kWave)) {
         const bf16* v = a.vt + (size_t)row * a.cap;
         if (quads) {
             const int n = a.P / 4;
-            for (int q0 = lane; q0 < n; q0 += 4 * kWave) {
-                bf16x4 x[4], y[4];
+            for (int q0 = lane; q0 < n; q0 += 8 * kWave) {
+                bf16x4 x[8], y[8];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < 8; ++u) {
                     const int q = min(q0 + kWave * u, n - 1);
                     x[u] = *reinterpret_cast<const bf16x4*>(v + vt_column(a.src0 + 4 * q));
                     y[u] = *reinterpret_cast<const bf16x4*>(v + vt_column(sink0 + 4 * q));
                 }
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
+                for (int u = 0; u < 8; ++u) {
                     if (q0 + kWave * u < n) {
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
@@ -95,37 +95,48 @@ __global__ __launch_bounds__(kWave) void sink_similarity_final_kernel(SinkSimArg
 }
 
 // s_i <- h_t: the P key rows, value columns and token ids of the frame at slot src0 are copied to the sink frame at
-// slot dst0.  Blocks [0, k_blocks) copy key rows (256 bytes per head and token, 16 bytes per lane), the rest four value
-// rows of V^T each (P columns, a wave per row, 8 bytes per lane where the frames start at multiples of four slots: 2 bytes
-// at a time the copy ran at 1.8 TB/s) and, in the first of them, the ids.
-__global__ __launch_bounds__(256) void refresh_sink_kernel(SinkCopyArgs a, int k_blocks) {
-    if ((int)blockIdx.x < k_blocks) {
-        // sixteen lanes per (head, token): 16 bytes each
-        const int item = blockIdx.x * 16 + (threadIdx.x >> 4);
-        if (item >= a.H * a.P) return;
-        const int h = item / a.P, j = item - h * a.P;
-        const int c = threadIdx.x & 15;
-        const bf16x8* src = reinterpret_cast<const bf16x8*>(a.k + ((size_t)h * a.cap + a.src0 + j) * kHeadDim);
-        bf16x8* dst = reinterpret_cast<bf16x8*>(a.k + ((size_t)h * a.cap + a.dst0 + j) * kHeadDim);
-        dst[c] = src[c];
+// slot dst0.  Blocks [0, v_blocks) copy four value rows of V^T each (P columns, a wave per row, 8 bytes per lane where the
+// frames start at multiples of four slots: 2 bytes at a time the copy ran at 1.8 TB/s) and, in the first of them, the
+// ids; the rest copy key rows, 16 bytes per lane and four pieces in flight.  The value rows come first: their few long
+// blocks would otherwise be the tail.
+constexpr int kCopyPieces = 4;
+
+__global__ __launch_bounds__(256) void refresh_sink_kernel(SinkCopyArgs a, int v_blocks) {
+    if ((int)blockIdx.x >= v_blocks) {
+        // a head's frame is P contiguous rows of sixteen 16-byte pieces
+        const unsigned per_head = (unsigned)a.P * 16u, total = (unsigned)a.H * per_head;
+        const unsigned i0 = (blockIdx.x - v_blocks) * (256u * kCopyPieces) + threadIdx.x;
+        bf16x8 x[kCopyPieces];
+        bf16x8* dst[kCopyPieces];
+#pragma unroll
+        for (int u = 0; u < kCopyPieces; ++u) {
+            const unsigned i = min(i0 + 256u * u, total - 1);
+            const unsigned h = i / per_head, c = i - h * per_head;
+            bf16* const head = a.k + (size_t)h * a.cap * kHeadDim;
+            x[u] = reinterpret_cast<const bf16x8*>(head + (size_t)a.src0 * kHeadDim)[c];
+            dst[u] = reinterpret_cast<bf16x8*>(head + (size_t)a.dst0 * kHeadDim) + c;
+        }
+#pragma unroll
+        for (int u = 0; u < kCopyPieces; ++u)
+            if (i0 + 256u * u < total) *dst[u] = x[u];
         return;
     }
-    const int row = (blockIdx.x - k_blocks) * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;      // (head, d) row of V^T
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;      // (head, d) row of V^T
     bf16* v = a.vt + (size_t)row * a.cap;
     if (a.P % 4 == 0 && a.src0 % 4 == 0 && a.dst0 % 4 == 0) {
         const int n = a.P / 4;
-        for (int q0 = lane; q0 < n; q0 += 4 * kWave) {
-            bf16x4 x[4];
+        for (int q0 = lane; q0 < n; q0 += 8 * kWave) {
+            bf16x4 x[8];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = *reinterpret_cast<const bf16x4*>(v + vt_column(a.src0 + 4 * min(q0 + kWave * u, n - 1)));
+            for (int u = 0; u < 8; ++u) x[u] = *reinterpret_cast<const bf16x4*>(v + vt_column(a.src0 + 4 * min(q0 + kWave * u, n - 1)));
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < 8; ++u)
                 if (q0 + kWave * u < n) *reinterpret_cast<bf16x4*>(v + vt_column(a.dst0 + 4 * (q0 + kWave * u))) = x[u];
         }
     } else {
         for (int j = lane; j < a.P; j += kWave) v[vt_column(a.dst0 + j)] = v[vt_column(a.src0 + j)];
     }
-    if ((int)blockIdx.x == k_blocks)
+    if (blockIdx.x == 0)
         for (int j = threadIdx.x; j < a.P; j += 256) a.ids[a.dst0 + j] = a.ids[a.src0 + j];
 }
 
@@ -181,9 +192,9 @@ hipError_t launch_sink_similarity(const SinkSimArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_refresh_sink(const SinkCopyArgs& a, hipStream_t s) {
-    const int k_blocks = (a.H * a.P + 15) / 16;
-    const int v_blocks = a.H * kHeadDim / 4;
-    hipLaunchKernelGGL(refresh_sink_kernel, dim3(k_blocks + v_blocks), dim3(256), 0, s, a, k_blocks);
+    const unsigned v_blocks = (unsigned)a.H * kHeadDim / 4;
+    const unsigned k_blocks = ((unsigned)a.H * (unsigned)a.P * 16u + 256u * kCopyPieces - 1) / (256u * kCopyPieces);
+    hipLaunchKernelGGL(refresh_sink_kernel, dim3(k_blocks + v_blocks), dim3(256), 0, s, a, (int)v_blocks);
     return hipGetLastError();
 }
 
