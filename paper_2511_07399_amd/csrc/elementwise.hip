@@ -334,6 +334,10 @@ __global__ __launch_bounds__(256) void plain_append_kernel(PlainAppendArgs a, in
                 *reinterpret_cast<bf16x8*>(a.st.k_cache + ((size_t)h * a.st.cap + slot) * kHeadDim + c0) = kv[it];
             }
         }
+        // a cache may have more heads than a model's 64 (final keys only: text keys belong to a model)
+        for (int h = hl + 4 * IT; h < a.H; h += 4)
+            *reinterpret_cast<bf16x8*>(a.st.k_cache + ((size_t)h * a.st.cap + slot) * kHeadDim + c0) =
+                *reinterpret_cast<const bf16x8*>(a.k + (size_t)row * C + h * kHeadDim + c0);
         return;
     }
     __shared__ bf16 tile[VT_TOK * VT_LD];
@@ -464,7 +468,7 @@ hipError_t launch_rmsnorm_inplace(bf16* x, const float* gain, int rows, int C, i
     return hipGetLastError();
 }
 
-// F(IT) with the smallest compiled number of 512-channel steps that covers H heads (at most 64)
+// F(IT) with the smallest compiled number of 512-channel steps that covers H heads (the largest, 64 heads, beyond)
 #define SDV2_BY_STEPS(H, F)                         \
     do {                                            \
         const int steps__ = ((H) + 3) / 4;          \

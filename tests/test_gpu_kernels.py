@@ -343,6 +343,25 @@ def test_append_evict_is_bit_exact(P, Sf, Wf, H, sizes):
     binding.kv_cache_destroy(h)
 
 
+@pytest.mark.parametrize("H", [4, 5, 12, 40, 63, 64, 65, 70])
+def test_append_of_every_head_count(H):
+    """Keys of all heads arrive (a row is copied in steps of four heads, compiled for up to 64): copies, so exact."""
+    P, D = 6, 128
+    ccfg = binding.cache_cfg(1, 1, H, P, P, 2 * P)
+    storage = torch.full((binding.kv_cache_bytes(ccfg),), 0xFF, dtype=torch.uint8, device=DEV)
+    h = binding.kv_cache_init(ccfg, storage)
+    k, v = bf16_randn((P, H * D), H), bf16_randn((P, H * D), H + 1)
+    binding.kv_cache_append_evict(h, 0, 0, k.to(DEV), v.to(DEV))
+    torch.cuda.synchronize()
+    kp, vp, _, cap = binding.kv_cache_device_ptrs(h, 0, 0)
+    base, nb = storage.data_ptr(), H * cap * D * 2
+    K = storage[kp - base:kp - base + nb].view(torch.bfloat16).view(H, cap, D)[:, :P].permute(1, 0, 2).reshape(P, H * D)
+    V = storage[vp - base:vp - base + nb].view(torch.bfloat16).view(H, D, cap)
+    V = V[:, :, binding.vt_columns(cap).to(DEV)][:, :, :P].permute(2, 0, 1).reshape(P, H * D)
+    assert torch.equal(K.cpu(), k) and torch.equal(V.cpu(), v)
+    binding.kv_cache_destroy(h)
+
+
 def test_append_evict_errors_leave_state_untouched():
     P, H = 4, 1
     ccfg = binding.cache_cfg(1, 1, H, P, 4, 8)
