@@ -124,6 +124,17 @@ def test_gemm_matches_oracle(M, N, K, epi, tile):
         binding.tuning_set("gemm_tile", None)
 
 
+@pytest.mark.parametrize("tile", range(1, 19))
+@pytest.mark.parametrize("M,N,K,epi", [
+    (1, 128, 64, 0),            # one row, one k tile: fewer than any ring of stages holds
+    (257, 384, 128, 1),         # one row past the largest tile
+    (515, 640, 704, 2),         # ragged in both directions, eleven k tiles
+    (5200, 3328, 640, 3),       # more tiles than workgroups for the small tiles: the next tile's loads under the epilogue
+])
+def test_gemm_every_tile_at_its_edges(M, N, K, epi, tile):
+    test_gemm_matches_oracle(M, N, K, epi, "d%d" % tile)
+
+
 def test_gemm_full_size_batched_480p_shape_sampled_rows():
     """FFN-1 of the 14B-shaped block on 4 streams x 4680 tokens (M 18720, N 13824, K 5120: the direct-load kernel,
     74 x 54 tiles, ragged last M tile): whole output finite, 48 sampled rows against the oracle."""
