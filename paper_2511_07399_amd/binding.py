@@ -11,7 +11,6 @@ import os
 
 import torch
 
-_raw_stream = torch._C._cuda_getCurrentRawStream
 _current_device = torch.cuda.current_device
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -213,7 +212,7 @@ def _ptr(t):
 
 
 def _stream():
-    return _raw_stream(_current_device())
+    return torch._C._cuda_getCurrentRawStream(_current_device())
 
 
 def _dev(t, dtype):
