@@ -606,7 +606,8 @@ int32_t sdv2_gemm_bf16_noalloc(const void* a_dev, const void* w_dev, const float
                                int32_t gate_b_stride, int32_t rows_per_gate, void* hip_stream) {
     if (M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > 3) return fail(SDV2_INVALID_ARG, "bad M, N, K or epilogue");
     const size_t need = gemm_splitk_floats(M, N, K, epilogue) * sizeof(float);
-    if (need > kNoAllocScratchBytes)
+    // a split of more parts than the scratch holds takes as many as it does; less than two parts are no split
+    if (need > kNoAllocScratchBytes && (size_t)M * N * 2 * sizeof(float) > kNoAllocScratchBytes)
         return fail(SDV2_INVALID_ARG, "this shape's k-split needs %zu bytes of scratch, more than the built-in %zu: use "
                     "sdv2_gemm_bf16 with a workspace", need, (size_t)kNoAllocScratchBytes);
     void* ptr = nullptr;
@@ -806,10 +807,12 @@ BlockWorkspace carve_block(const sdv2_model_cfg* cfg, int B, int L, int max_kv, 
     const size_t a2 = attention_workspace_bytes(B, L, (int)C, cfg->text_len);
     w.attn_bytes = a1 > a2 ? a1 : a2;
     w.attn = reinterpret_cast<float*>(take(w.attn_bytes));
-    // split-K room for the largest need among the block's six projections
+    // split-K room for the largest need among the block's six projections, with as many rows or fewer: fewer rows can
+    // split where more do not, and a workspace for a batch serves the smaller batches too (the stream batch's first and
+    // last micro-steps are such)
     const int shapes[6][3] = {{(int)(3 * C), (int)C, kEpiBias}, {(int)C, (int)C, kEpiGatedResidual}, {(int)C, (int)C, kEpiBias},
                               {(int)C, (int)C, kEpiResidual},   {(int)F, (int)C, kEpiBiasGelu},      {(int)C, (int)F, kEpiGatedResidual}};
-    w.gemm_floats = 0;
+    w.gemm_floats = gemm_splitk_floats_bound((int)rows, (int)(F > 3 * C ? F : 3 * C));
     for (const auto& sh : shapes) {
         const size_t f = gemm_splitk_floats((int)rows, sh[0], sh[1], sh[2]);
         if (f > w.gemm_floats) w.gemm_floats = f;

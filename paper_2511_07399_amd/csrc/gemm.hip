@@ -916,30 +916,28 @@ float tile_cost(int id, int M, int N, float k_tiles, int parts) {
 }
 
 // The planner: the configuration and number of k parts with the smallest estimate.  A k split pays for a second pass
-// (4 us and its bytes at 3.9 TB/s); a residual epilogue gets back the LayerNorm that this pass forms (5 us).  Parts of at least 512 and at most 32 MiB of partial sums (what the entry point without a workspace has).
-// One shape is planned by hand, FFN-2 of the 14B block on one chunk, where two parts of 42 MB are 5 % faster than the
-// best plan within 32 MiB.
-struct TunedShape {
-    int M, N, K, dma, splitk;
-};
-const TunedShape kTuned[] = {{1024, 5120, 13824, 4, 2}};
+// (4 us and its bytes at 3.9 TB/s); a residual epilogue gets back the LayerNorm that this pass forms (5 us).  Parts of
+// at least 512, and at most 48 MiB of partial sums.  Up to 32 MiB they fit the entry point without a workspace; more than
+// that has to be 1.5 % better by the estimate, which is careful: measured with cold weights, best within 32 MiB against
+// the plan with 32 to 48 MiB: 1024 x 5120 x 13824 146 -> 131 us, 1024 x 5120 x 20480 213 -> 188, 1024 x 3072 x 12288
+// 87 -> 77, 1560 x 3072 x 12288 124 -> 120, 512 x 5120 x 13824 81 -> 78.
+constexpr size_t kMaxPartialBytes = (size_t)48 << 20, kSmallPartialBytes = (size_t)32 << 20;
 
 TilePlan search_plan(int M, int N, int K, int epilogue) {
-    for (const TunedShape& t : kTuned)
-        if (t.M == M && t.N == N && t.K == K) return TilePlan{0, 0, 0, t.dma, t.splitk};
     TilePlan best{0, 0, 0, 1, 1};
     float best_cost = 1e30f;
     const int kParts[] = {1, 2, 3, 4, 6};
     // operands beyond the 256 MB memory-side cache: with a single wave per SIMD their latency shows (4 to 14 %)
     const bool from_memory = (size_t)(M + (size_t)N) * K * sizeof(bf16) > ((size_t)240 << 20);
     for (const int parts : kParts) {
-        if (parts > 1 && (K < 512 * parts || (size_t)parts * M * N * sizeof(float) > ((size_t)32 << 20))) break;
+        if (parts > 1 && (K < 512 * parts || (size_t)parts * M * N * sizeof(float) > kMaxPartialBytes)) break;
         float second = 0.0f;
         if (parts > 1) second = 4.0f + (float)M * N * (4.0f * parts + (epilogue >= kEpiGatedResidual ? 8.0f : 2.0f)) / 3.9e6f -
                                 (epilogue >= kEpiGatedResidual ? 5.0f : 0.0f);
         for (int id = 1; id <= kTileConfigs; ++id) {
             float cost = tile_cost(id, M, N, (float)K / (64 * parts), parts) + second;
             if (from_memory && kCost[id].one_wave) cost *= 1.07f;
+            if (parts > 1 && (size_t)parts * M * N * sizeof(float) > kSmallPartialBytes) cost *= 1.015f;
             if (cost < best_cost) {
                 best_cost = cost;
                 best = TilePlan{0, 0, 0, id, parts};
@@ -1126,8 +1124,9 @@ static int usable_splitk(const GemmArgs& g, const TilePlan& p) {
     if (p.splitk <= 1 || g.splitk_partials == nullptr) return 1;
     int splitk = p.splitk;
     if (splitk > g.K / 128) splitk = g.K / 128;                 // at least two k tiles per part
-    if (splitk < 2 || (size_t)splitk * g.M * g.N > g.splitk_floats) return 1;
-    return splitk;
+    const size_t fit = g.splitk_floats / ((size_t)g.M * g.N);   // parts that the scratch holds
+    if ((size_t)splitk > fit) splitk = (int)fit;
+    return splitk < 2 ? 1 : splitk;
 }
 
 // part 0: the whole product; 1: only the kernel on the matrix cores; 2: only the pass that adds the k parts (nothing
@@ -1201,6 +1200,11 @@ bool gemm_splits_k(const GemmArgs& g) {
     TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue);
     tile_override(&p);
     return usable_splitk(g, p) > 1;
+}
+
+size_t gemm_splitk_floats_bound(int M, int N) {
+    const size_t most = (size_t)6 * M * N, cap = kMaxPartialBytes / sizeof(float);
+    return most < cap ? most : cap;
 }
 
 size_t gemm_splitk_floats(int M, int N, int K, int epilogue) {

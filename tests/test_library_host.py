@@ -211,3 +211,13 @@ def test_stream_batch_of_latents_sizes_on_the_host(lib):
         # the rows buffer of the handle (hidden states) also holds the latent rows
         assert binding.stream_batch_rows_bytes(cfg, n, 1) >= n * 64 * L * 4
     assert binding.stream_batch_latents_workspace_bytes(cfg, 9, 1) == 0
+
+
+@pytest.mark.parametrize("C_,heads,F", [(1536, 12, 8960), (3072, 24, 12288), (5120, 40, 13824)])
+def test_a_workspace_for_a_batch_serves_smaller_ones(lib, C_, heads, F):
+    """Fewer rows can split k where more rows do not: the size must grow with the rows all the same, because a workspace
+    is made for the largest call (the stream batch fills up over calls of 1, 2, ... rows)."""
+    for P in (32, 32), (30, 52):             # (smaller frames have split-KV room that does not grow with the rows)
+        cfg = binding.model_cfg(C_, heads, F, P[0], P[1], 512, 30)
+        sizes = [binding.block_workspace_bytes(cfg, B, P[0] * P[1]) for B in range(1, 9)]
+        assert sizes[0] > 0 and sizes == sorted(sizes)

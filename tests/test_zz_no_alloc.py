@@ -70,3 +70,15 @@ def test_noalloc_gemm_rejects_what_does_not_fit():
     assert e.value.code == binding.INVALID_ARG
     torch.cuda.synchronize()
     assert float(out.abs().max()) == 0.0
+
+
+def test_noalloc_gemm_takes_as_many_parts_as_the_scratch_holds():
+    # the plan is four k parts of 512 x 5120 floats (40 MiB), of which the scratch holds three
+    M, N, K = 512, 5120, 13824
+    assert binding.gemm_workspace_bytes(M, N, K, 3) > binding.gemm_noalloc_max_scratch_bytes() > 2 * 4 * M * N
+    a, w = draw((M, K), 400), draw((N, K), 401, 0.05)
+    x0 = draw((M, N), 402).float()
+    out = x0.to(DEV)
+    binding.gemm_bf16_noalloc(a.to(DEV), w.to(DEV), None, out, 3)
+    ref = x0.double() + (a.float() @ w.float().t()).double()
+    assert max_rel_err(out.cpu().double().numpy(), ref.numpy()) < 1e-4
