@@ -135,6 +135,28 @@ def test_gemm_every_tile_at_its_edges(M, N, K, epi, tile):
     test_gemm_matches_oracle(M, N, K, epi, "d%d" % tile)
 
 
+@pytest.mark.parametrize("tile", [None, "1,4"] + ["d%d" % i for i in range(1, 19)])
+def test_gemm_adds_the_bias_to_the_finished_sum(tile):
+    """A bias 25 times the product's size must not coarsen the sum of the products: fp32 output against 64 bits.  One
+    rounding of the result (2^-24 relative, at most) and the sum's own error (1e-6 of the product, above the 6e-7 that a
+    chain of 4096 terms shows): 1.0e-7 of the result.  Accumulators that start from the bias show 5e-7."""
+    M, N, K = 300, 640, 4096
+    a, w = bf16_randn((M, K), 21).to(DEV), bf16_randn((N, K), 22, 0.02).to(DEV)
+    g = torch.Generator().manual_seed(23)
+    bias = (torch.randn(N, generator=g) * 32.0).to(DEV)
+    acc = a.double() @ w.double().t()
+    want = acc + bias.double()
+    out = torch.zeros(M, N, device=DEV)
+    binding.tuning_set("gemm_tile", tile)
+    try:
+        binding.gemm_bf16(a, w, bias, out, 3)
+        torch.cuda.synchronize()
+    finally:
+        binding.tuning_set("gemm_tile", None)
+    err = (out.double() - want).norm().item()
+    assert err <= 2.0 ** -24 * want.norm().item() + 1e-6 * acc.norm().item(), err / want.norm().item()
+
+
 def test_gemm_full_size_batched_480p_shape_sampled_rows():
     """FFN-1 of the 14B-shaped block on 4 streams x 4680 tokens (M 18720, N 13824, K 5120: the direct-load kernel,
     74 x 54 tiles, ragged last M tile): whole output finite, 48 sampled rows against the oracle."""
