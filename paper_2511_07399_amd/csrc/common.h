@@ -23,22 +23,23 @@ constexpr int kLatentChannels = 16;      // VAE latent channels; a token covers 
 // its keys.  The map is its own inverse.
 __host__ __device__ __forceinline__ int vt_column(int s) { return (s & ~12) | ((s & 4) << 1) | ((s & 8) >> 1); }
 
-// Sum over the wavefront, in every lane: two quad permutations and two mirrors inside a row of 16 lanes, then the row and
-// half swaps.  All on the vector unit: a shuffle through the LDS crossbar costs about ten times the latency, and the
-// row kernels of a single chunk are chains of these.
+// Sum over the wavefront, in every lane, the lanes 32, 16, 8, 4, 2 and 1 apart added in this order: the half and row swaps,
+// then two rotations of a row of 16 lanes (by then its halves, then its quarters, are equal, so a rotation is the exchange)
+// and two quad permutations.  All on the vector unit: a shuffle through the LDS crossbar costs about ten times the latency,
+// and the row kernels of a single chunk are chains of these.  A sum of shuffles in the same order has the same bits.
 template <int CTRL>
 __device__ __forceinline__ float dpp_f(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
 }
 __device__ __forceinline__ float wave_sum(float v) {
-    v += dpp_f<0xB1>(v);         // quad_perm [1, 0, 3, 2]
-    v += dpp_f<0x4E>(v);         // quad_perm [2, 3, 0, 1]
-    v += dpp_f<0x141>(v);        // row_half_mirror
-    v += dpp_f<0x140>(v);        // row_mirror
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(h[0]) + __uint_as_float(h[1]);
     const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
     v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+    v += dpp_f<0x128>(v);        // row_ror:8
+    v += dpp_f<0x124>(v);        // row_ror:4
+    v += dpp_f<0x4E>(v);         // quad_perm [2, 3, 0, 1]
+    return v + dpp_f<0xB1>(v);   // quad_perm [1, 0, 3, 2]
 }
 
 __device__ __forceinline__ float gelu_tanh_f(float x) {

@@ -111,3 +111,25 @@ def test_motion_call_validation():
     with pytest.raises(binding.Sdv2Error) as e:
         binding.motion_init(binding.motion_cfg(3, -1.0, 0.5, 0.1, 0.9, 0.5), state)
     assert e.value.code == binding.INVALID_ARG
+
+
+def test_wave_sums_add_the_halves_first():
+    """The order of a sum over a wavefront: lanes 32 apart, then 16, 8, 4, 2, 1.  Seen in the partial sums that the state
+    keeps behind its header (16 floats) and ring (k + 1 floats, rounded up to 16): 64 per frame, one per workgroup.  Every
+    lane holds one squared difference that is exact in single precision."""
+    binding.load_library()
+    k, n = 3, 64 * 256 * 4
+    cfg = binding.motion_cfg(k, 1.0, 0.5, 0.1, 0.9, 0.5)
+    state = torch.empty(binding.motion_state_bytes(cfg), dtype=torch.uint8, device=DEV)
+    binding.motion_init(cfg, state)
+    d = torch.zeros(n // 4, 4)
+    d[:, 0] = torch.randint(1, 4096, (n // 4,), generator=torch.Generator().manual_seed(9)).float() / 64.0
+    outs = [torch.empty(1, dtype=torch.float32, device=DEV) for _ in range(3)]
+    binding.motion_update(cfg, state, d.reshape(1, n).to(DEV), torch.zeros(n, device=DEV), *outs)
+    torch.cuda.synchronize()
+    got = state.view(torch.float32)[32:32 + 64].cpu().numpy()
+    v = (d[:, 0].numpy() ** 2).reshape(64, 4, 64)
+    for off in (32, 16, 8, 4, 2, 1):
+        v = v + v[:, :, np.arange(64) ^ off]
+    want = (v[:, 0, 0] + v[:, 1, 0]) + (v[:, 2, 0] + v[:, 3, 0])
+    assert v.dtype == np.float32 and np.array_equal(got, want)
