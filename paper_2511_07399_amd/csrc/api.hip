@@ -863,7 +863,7 @@ void fill_rope_table(const sdv2_model_cfg* cfg, RopeAppendArgs* a) {
     for (int axis = 0; axis < 3; ++axis)
         for (int j = 0; j < counts[axis]; ++j, ++p) {
             a->pair_axis[p] = axis;
-            a->inv_turn[p] = pow((double)cfg->rope_base, -(double)j / counts[axis]) / (2.0 * M_PI);
+            a->inv_freq[p] = pow((double)cfg->rope_base, -(double)j / counts[axis]);
         }
 }
 

@@ -177,7 +177,7 @@ struct RopeAppendArgs {
     int tokens_per_frame, grid_w;
     int S, W;
     float eps;
-    double inv_turn[kHeadDim / 2];    // rotation frequency of each pair of a head, in turns per position
+    double inv_freq[kHeadDim / 2];    // rotation frequency of each pair of a head
     int pair_axis[kHeadDim / 2];      // 0 frame, 1 row, 2 col
     AppendStream st[kMaxBatch];
     const StepDesc* desc;             // null: g0 and frame_pos0 of st[]; else they are read from the device descriptor

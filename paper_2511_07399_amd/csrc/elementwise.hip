@@ -150,10 +150,10 @@ __global__ __launch_bounds__(256) void rmsnorm_inplace_kernel(bf16* x, const flo
 // Blocks [0, norm_blocks): one wave per token.  A lane reads 16 bytes (four rotation pairs) of q and of k per
 // step, four heads per wave load, keeps the row in registers (IT steps: C <= 512 IT), reduces the sums of squares over
 // the whole row, then normalises, rotates and writes q to its buffer and k to the token's ring slot.  Lane j forms the
-// rotation of pair j: the angle in turns, in double, so that it stays exact for any stream length; sine and cosine of its
-// fraction rounded to single precision, plus what the rounding left out times the derivative, so that only the last bit
-// differs from a sincos in double (half the kernel's instructions); the lanes pick up their four by shuffle.  Few tokens:
-// a chain of latencies (load, sum, rotate, store), so only what the row needs is compiled in.
+// rotation of pair j, angle, sine and cosine in double, so that what is rounded to single precision is exact for any stream
+// length (a single-precision sincos, even of the exactly reduced angle, is off by its own last bit); the lanes pick up
+// their four by shuffle.  Few tokens: a chain of latencies (load, sum, rotate, store), so only what the row needs is
+// compiled in, and the rotation is formed while the row is on its way.
 // Blocks [norm_blocks, ...): one (64-token tile, head) each: v goes through LDS and is written
 // transposed into the V^T cache, a slot's column given by vt_column.
 constexpr int VT_TOK = 64;
@@ -230,12 +230,9 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a, int 
         const int inside = i % a.tokens_per_frame;
         const int axis = a.pair_axis[lane];
         const int pos = axis == 0 ? frame : (axis == 1 ? inside / a.grid_w : inside % a.grid_w);
-        const double turns = (double)pos * a.inv_turn[lane];
-        const double angle = (turns - rint(turns)) * 6.283185307179586477;
-        const float angle_hi = (float)angle, angle_lo = (float)(angle - (double)angle_hi);
-        float sf_hi, cf_hi;
-        sincosf(angle_hi, &sf_hi, &cf_hi);
-        const float sf_own = fmaf(angle_lo, cf_hi, sf_hi), cf_own = fmaf(-angle_lo, sf_hi, cf_hi);
+        double sn, cs;
+        sincos((double)pos * a.inv_freq[lane], &sn, &cs);
+        const float cf_own = (float)cs, sf_own = (float)sn;
         float cf[4], sf[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

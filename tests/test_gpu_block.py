@@ -17,6 +17,7 @@ from parity_util import (GpuRunner, OracleRunner, branch_floor, max_rel_err, run
                          visible_branches)
 
 pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
 TOL_X = 2e-2
 TOL_KV = 1e-2
 
@@ -423,3 +424,39 @@ def test_wan14b_480p_block_staggered_streams():
             assert np.array_equal(gpu.slot_map(0, s), want.slot_map()), (rnd, s)
     assert ora.caches[0][0].state()["evicted"] > 0
     gpu.close()
+
+
+def test_rotation_of_the_keys_is_correctly_rounded():
+    """Cosine and sine of the rotary angle are those of 64 bits rounded once to single precision.  Keys (a, 0) with a in
+    {1, 2} and a mean square of one come out of the norm as a times the gain, exactly, so a cached pair is the bf16
+    rounding of (a g cos, a g sin) and can be told bit for bit: 16384 columns x 21 pairs x 12 heads, of which about one in
+    65536 lies so close to a rounding point of bf16 that the last bit of the cosine decides."""
+    wl = wk.Workload("rotation", C=1536, H=12, F=128, grid_h=1, grid_w=16384, frames_per_chunk=1, sink_frames=0,
+                     window_frames=1, L_t=16, B=1, N=1, steps=(1,), chunks=1)
+    pairs = wl.C // 2
+    amp = torch.ones(pairs)
+    amp[::3] = 2.0                                            # (2/3) 1 + (1/3) 4 = 2 per pair, 1 per channel
+    keys = torch.stack([amp, torch.zeros(pairs)], 1).reshape(wl.C)
+
+    def edit(w, layer=0):
+        for n in ("q", "k", "v"):
+            w["W_" + n] *= 0.0
+            w["b_" + n].copy_(keys.to(w["b_" + n].dtype))
+        w["g_k"].copy_((0.5 + 1.5 * torch.rand(wl.C, generator=torch.Generator().manual_seed(5))).to(w["g_k"].dtype))
+
+    gpu = GpuRunner(wl, edit=edit)
+    gpu.cfg.eps = 1e-30                                       # 1 + eps is 1
+    x = wk.chunk_input(wl, 0).to(DEV).reshape(1, wl.L, wl.C).contiguous()
+    gpu.block(0, x, torch.zeros(1, 6, wl.C, device=DEV), [(0, 3, 1, 1)])
+    torch.cuda.synchronize()
+    K = torch.from_numpy(gpu.cache_logical(0, 0)[0]).to(torch.bfloat16)
+    gain = gpu.layers[0]["g_k"].cpu().float()
+    gpu.close()
+    pos = oracle.dit_block.token_positions(wl.L, wl.P, wl.grid_w, 3).astype(np.float64)
+    angles = np.concatenate([pos[:, a:a + 1] * oracle.dit_block.ROPE_BASE ** (-np.arange(d) / d)
+                             for a, d in enumerate(oracle.dit_block.rope_pair_split(128))], 1)
+    cos, sin = (torch.from_numpy(f(angles).astype(np.float32)) for f in (np.cos, np.sin))
+    m = (keys * gain).reshape(wl.H, 64, 2)[:, :, 0]           # exact: a power of two times the gain
+    want = torch.stack([(m * cos[:, None]).to(torch.bfloat16), (m * sin[:, None]).to(torch.bfloat16)], 3)
+    differ = (K.reshape(wl.L, wl.H, 64, 2) != want).sum().item()
+    assert differ == 0, differ
