@@ -411,10 +411,9 @@ __global__ __launch_bounds__(256) void gemv_kernel(const float* x, const bf16* w
 #pragma unroll
                     for (int r = 0; r < R; ++r) {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            acc[r * NB + b] += x0[e] * (float)wv[c][r][e];
-                            acc[r * NB + b] += x1[e] * (float)wv[c][r][e + 4];
-                        }
+                        for (int e = 0; e < 4; ++e) acc[r * NB + b] += x0[e] * (float)wv[c][r][e];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[r * NB + b] += x1[e] * (float)wv[c][r][e + 4];
                     }
                 }
             }

@@ -460,3 +460,30 @@ def test_rotation_of_the_keys_is_correctly_rounded():
     want = torch.stack([(m * cos[:, None]).to(torch.bfloat16), (m * sin[:, None]).to(torch.bfloat16)], 3)
     differ = (K.reshape(wl.L, wl.H, 64, 2) != want).sum().item()
     assert differ == 0, differ
+
+
+@pytest.mark.parametrize("C,B", [(512, 1), (1536, 3)])
+def test_modulation_is_summed_in_channel_order(C, B):
+    """e0 = W_mod silu(t) + b: a lane adds its eight channels of every 512 in order, then the lanes 32, 16, .. 1 apart are
+    added, whatever the number of rows a wave works on.  With t >= 128, silu(t) is t, so the sum can be followed in
+    float32, bit for bit."""
+    wl = wk.Workload("modulation", C, C // 128, 128, 2, 2, 1, 1, 1, 16, 1, 1, (1,), 1)
+    t = {k: v.to(DEV) for k, v in wk.model_weights(wl, 0).items()}
+    mw = binding.model_weights(t, (binding.BlockWeights * 1)())
+    cfg = binding.model_cfg(C, C // 128, 128, 2, 2, 16, 1, wl.t_dim)
+    tvec = 128.0 + 128.0 * torch.rand(B, C, generator=torch.Generator().manual_seed(31))
+    e0 = torch.empty(B, 6, C, device=DEV)
+    ws = torch.empty(max(binding.conditioning_workspace_bytes(cfg, B), 256), dtype=torch.uint8, device=DEV)
+    binding.conditioning(cfg, mw, B, e0, ws, tvec=tvec.to(DEV))
+    torch.cuda.synchronize()
+    w = t["W_mod"].cpu().float().numpy().astype(np.float64).reshape(-1, C // 512, 64, 8)
+    x = tvec.numpy().astype(np.float64).reshape(B, C // 512, 64, 8)
+    for b in range(B):
+        acc = np.zeros((w.shape[0], 64), dtype=np.float32)
+        for c in range(C // 512):
+            for e in range(8):                                # a fused multiply-add: the product is exact in 64 bits
+                acc = (w[:, c, :, e] * x[b, c, :, e] + acc).astype(np.float32)
+        for off in (32, 16, 8, 4, 2, 1):
+            acc = acc + acc[:, np.arange(64) ^ off]
+        want = acc[:, 0] + t["b_mod"].cpu().numpy()
+        assert np.array_equal(e0[b].reshape(-1).cpu().numpy(), want)
