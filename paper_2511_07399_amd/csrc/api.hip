@@ -318,7 +318,7 @@ int32_t latest_frame_slot(const sdv2_kv_cache* cache, size_t idx, int32_t frame_
 size_t sdv2_sink_similarity_workspace_bytes(const sdv2_kv_cache* cache) {
     if (!cache) return 0;
     const int m = cache->cfg.sink_tokens / cache->cfg.tokens_per_frame;
-    return align_up((size_t)(m > 0 ? m : 1) * sink_similarity_blocks(cache->cfg.n_heads) * 3 * sizeof(float), 256);
+    return align_up((size_t)(m > 0 ? m : 1) * sink_similarity_blocks(cache->cfg.n_heads) * 3 * sizeof(double), 256);
 }
 
 int32_t sdv2_sink_similarity(sdv2_kv_cache* cache, int32_t layer, int32_t stream_id, int32_t frame_back,
@@ -345,7 +345,7 @@ int32_t sdv2_sink_similarity(sdv2_kv_cache* cache, int32_t layer, int32_t stream
     a.P = cf.tokens_per_frame;
     a.src0 = src0;
     a.m = m;
-    a.partial = static_cast<float*>(workspace_dev);
+    a.partial = static_cast<double*>(workspace_dev);
     a.alpha = alpha_dev;
     hipError_t e = launch_sink_similarity(a, static_cast<hipStream_t>(hip_stream));
     if (e != hipSuccess) return hip_fail(e, "sink similarity kernel");

@@ -202,7 +202,7 @@ struct SinkSimArgs {
     int H, cap, P;        // P = tokens per frame
     int src0;             // first slot of the frame h_t
     int m;                // sink frames; sink frame i starts at slot i * P
-    float* partial;       // [m][blocks][3] fp32
+    double* partial;      // [m][blocks][3]
     float* alpha;         // [m]
 };
 int sink_similarity_blocks(int H);

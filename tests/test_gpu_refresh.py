@@ -275,3 +275,28 @@ def test_refresh_kernels_at_full_cache_sizes(name):
         assert np.abs(K[slot] - want).max() <= 1e-2 * np.abs(want).max(), slot
     assert np.array_equal(V, vo0)
     pair.close()
+
+
+@pytest.mark.parametrize("H,P", [(40, 2048), (40, 777), (12, 1560)])
+def test_similarity_of_many_heads_is_a_single_precision_number(H, P):
+    """alpha against 64 bits on the same bf16 rows: its own rounding to single precision (2^-25 for values in [1/2, 1)) and
+    2e-8 for the partial sums.  Sums of a whole row per lane are 6e-8 off at 40 heads of 2048 tokens."""
+    binding.load_library()
+    cf = binding.cache_cfg(1, 1, H, P, P, 2 * P)
+    storage = torch.zeros(binding.kv_cache_bytes(cf), dtype=torch.uint8, device=DEV)
+    g = torch.Generator(device=DEV)
+    for seed in range(8):
+        g.manual_seed(seed)
+        h = binding.kv_cache_init(cf, storage)
+        sink = torch.randn((P, 128 * H), generator=g, device=DEV).to(torch.bfloat16)
+        new = (0.6 * sink.float() + 0.4 * torch.randn((P, 128 * H), generator=g, device=DEV)).to(torch.bfloat16)
+        for rows in (sink, new):
+            binding.kv_cache_append_evict(h, 0, 0, rows, rows)
+        alpha = torch.empty(1, device=DEV)
+        ws = torch.empty(binding.sink_similarity_workspace_bytes(h), dtype=torch.uint8, device=DEV)
+        binding.sink_similarity(h, 0, 0, alpha, ws)
+        x, y = new.double().flatten(), sink.double().flatten()
+        want = ((x @ y) / (x.norm() * y.norm())).item()
+        assert 0.5 < want < 1.0
+        assert abs(alpha.item() - want) <= 2.0 ** -25 + 2e-8, (seed, alpha.item() - want)
+        binding.kv_cache_destroy(h)
