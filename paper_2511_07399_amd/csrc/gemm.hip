@@ -1062,7 +1062,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(GemmArgs g, int s
     const float* prow = g.splitk_partials + (size_t)row * g.N;
     const int stream = row / g.rows_per_gate;
     const int ln_stream = row / ln.rows_per_stream;
-    const float pivot = xrow[0];                          // any value near the row's mean: read before the row is rewritten
+    const float pivot = xrow[0];                          // a value near the row's mean: read before the row is rewritten
     f32x4 v[NV], sc[NV], sh[NV];
     // everything the row needs is requested at once: the parts, x, bias and gate, and the LayerNorm's scale and shift
 #pragma unroll
@@ -1111,10 +1111,38 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(GemmArgs g, int s
     sum = (part[0][0] + part[1][0]) + (part[2][0] + part[3][0]);
     sq = (part[0][1] + part[1][1]) + (part[2][1] + part[3][1]);
     const float inv_c = 1.0f / (float)g.N;
-    const float dmean = sum * inv_c;
-    const float var = fmaxf(sq * inv_c - dmean * dmean, 0.0f);
+    float dmean = sum * inv_c;
+    float var = fmaxf(sq * inv_c - dmean * dmean, 0.0f);
+    float mean = pivot + dmean;
+    // The pivot is of the row before the update.  Where the update has moved the mean far from it, the variance is the small
+    // difference of two large numbers: form it again around the mean.  The same decision in every thread of the row.
+    if (dmean * dmean > 256.0f * var) {
+        __syncthreads();                                  // part[] has been read
+        sum = 0.0f;
+        sq = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (t + 256 * i < nvec) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float d = v[i][e] - mean;
+                    sum += d;
+                    sq += d * d;
+                }
+            }
+        }
+        sum = wave_sum(sum);
+        sq = wave_sum(sq);
+        if (lane == 0) {
+            part[wave][0] = sum;
+            part[wave][1] = sq;
+        }
+        __syncthreads();
+        dmean = ((part[0][0] + part[1][0]) + (part[2][0] + part[3][0])) * inv_c;
+        var = fmaxf(((part[0][1] + part[1][1]) + (part[2][1] + part[3][1])) * inv_c - dmean * dmean, 0.0f);
+        mean += dmean;
+    }
     const float rstd = rsqrtf(var + ln.eps);
-    const float mean = pivot + dmean;
     bf16* op = ln.out + (size_t)row * g.N;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {

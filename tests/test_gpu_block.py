@@ -6,6 +6,8 @@ accumulation against the float64 oracle on the same bf16-rounded inputs.  Cached
 roundings of the oracle's values: bar 1e-2.
 """
 
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -487,3 +489,33 @@ def test_modulation_is_summed_in_channel_order(C, B):
             acc = acc + acc[:, np.arange(64) ^ off]
         want = acc[:, 0] + t["b_mod"].cpu().numpy()
         assert np.array_equal(e0[b].reshape(-1).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("bias", ["b_o", "b_co"])
+def test_layernorm_after_a_split_product_that_moves_the_row(bias):
+    """LN-3 and adaLN-2 may be formed in the pass that adds the k parts of the product before them.  Here that product
+    moves every row by 10^4 (its bias) while the row's spread stays about one.  x is fp32, so at 10^4 each of its three
+    updates rounds by 2.8e-4 rms; on top comes what the bf16 tensors cost (5e-3 of the updates, as without the move).
+    Twice that is the bar; a variance taken around the row before the update is 5 times past it."""
+    wl = wk.Workload("moved", C=1024, H=8, F=4096, grid_h=8, grid_w=16, frames_per_chunk=1, sink_frames=1,
+                     window_frames=2, L_t=64, B=1, N=1, steps=(1,), chunks=1)
+    assert binding.gemm_workspace_bytes(wl.L, wl.C, wl.C, 2) > 0 and binding.gemm_workspace_bytes(wl.L, wl.C, wl.C, 3) > 0
+
+    def edit(w, layer=0):
+        w["mod_table"][2] = 1.0
+        w["mod_table"][5] = 1.0
+        w[bias] += 10000.0
+
+    gpu, ora = GpuRunner(wl, edit=edit), OracleRunner(wl, edit=edit)
+    x = wk.chunk_input(wl, 0)
+    e0 = torch.zeros(6, wl.C)
+    xg = x.to(DEV).reshape(1, wl.L, wl.C).contiguous()
+    gpu.block(0, xg, e0.to(DEV).reshape(1, 6, wl.C).contiguous(), [(0, 0, 1, 1)])
+    torch.cuda.synchronize()
+    gpu.close()
+    dbg = {}
+    xo = ora.block(0, x.double().numpy(), e0.double().numpy(), (0, 0, 1, 1), debug=dbg)
+    upd = dbg["upd_ffn"] if bias == "b_co" else dbg["upd_cross"] + dbg["upd_ffn"]
+    size = math.sqrt((upd ** 2).mean())
+    err = math.sqrt(((xg[0].cpu().double().numpy() - xo) ** 2).mean())
+    assert err <= 2.0 * (5e-3 * size + math.sqrt(3.0) * 2.8e-4), (err, size)
