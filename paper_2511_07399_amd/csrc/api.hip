@@ -803,13 +803,13 @@ BlockWorkspace carve_block(const sdv2_model_cfg* cfg, int B, int L, int max_kv, 
     w.q = reinterpret_cast<bf16*>(take(rows * C * 2));
     w.o = reinterpret_cast<bf16*>(take(rows * C * 2));
     w.u = reinterpret_cast<bf16*>(take(rows * F * 2));
-    const size_t a1 = attention_workspace_bytes(B, L, (int)C, max_kv);
-    const size_t a2 = attention_workspace_bytes(B, L, (int)C, cfg->text_len);
+    // Room for the parts of a split key range and of a split k range: the largest need of a call with as many rows or fewer.
+    // Fewer rows can split where more do not, and a workspace made for a batch serves the smaller batches and shorter chunks
+    // too (the stream batch's first and last micro-steps are such).
+    const size_t a1 = attention_workspace_bytes_bound(B, L, (int)C, max_kv);
+    const size_t a2 = attention_workspace_bytes_bound(B, L, (int)C, cfg->text_len);
     w.attn_bytes = a1 > a2 ? a1 : a2;
     w.attn = reinterpret_cast<float*>(take(w.attn_bytes));
-    // split-K room for the largest need among the block's six projections, with as many rows or fewer: fewer rows can
-    // split where more do not, and a workspace for a batch serves the smaller batches too (the stream batch's first and
-    // last micro-steps are such)
     const int shapes[6][3] = {{(int)(3 * C), (int)C, kEpiBias}, {(int)C, (int)C, kEpiGatedResidual}, {(int)C, (int)C, kEpiBias},
                               {(int)C, (int)C, kEpiResidual},   {(int)F, (int)C, kEpiBiasGelu},      {(int)C, (int)F, kEpiGatedResidual}};
     w.gemm_floats = gemm_splitk_floats_bound((int)rows, (int)(F > 3 * C ? F : 3 * C));

@@ -781,6 +781,18 @@ size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len) {
     return (size_t)splits * rows * C * sizeof(float) + (size_t)splits * rows * H * 2 * sizeof(float);
 }
 
+// The plan splits only while workgroups of QT queries of a head are few: into at most slots / workgroups parts of at least
+// six key tiles.  So parts * B * L <= slots * QT / H, which is 65536 / H for both workgroup sizes.
+size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len) {
+    const size_t H = C / D, most_rows = 512 * 128 / H;
+    const int by_tiles = (max_kv_len + KT - 1) / KT / 6;
+    const size_t parts = by_tiles < 16 ? by_tiles : 16;
+    const size_t rows = parts * B * L < most_rows ? parts * B * L : most_rows;
+    const size_t bound = parts <= 1 ? 0 : rows * (C * sizeof(float) + H * 2 * sizeof(float));
+    const size_t planned = attention_workspace_bytes(B, L, C, max_kv_len);      // above the bound only for a forced number of parts
+    return planned > bound ? planned : bound;
+}
+
 void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
     int max_kv = 0;
     for (int b = 0; b < a.B; ++b) max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;

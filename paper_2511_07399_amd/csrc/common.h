@@ -117,6 +117,8 @@ int attention_plan_splits(int B, int L, int H, int max_kv_len);
 // Tuning hooks: waves per workgroup (4, 8; 0 = planner) and key-range splits (0 = planner); -1 leaves a value as is.
 void set_attention_overrides(int waves, int splits);
 size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len);
+// the most that a call of at most B streams of at most L queries needs; grows with B, L and max_kv_len
+size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len);
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part = 0);   // part 1: the kernel; 2: the merge pass only
 bool attention_has_merge_pass(const AttnArgs& a);
 void attention_plan_name(const AttnArgs& a, char* out, size_t cap);      // only B, L, H, kv_len and cap are read

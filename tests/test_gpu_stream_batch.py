@@ -81,6 +81,15 @@ def test_ragged_three_frame_chunks_three_steps():
     assert max(errs) <= TOL_X, errs
 
 
+def test_fill_and_drain_where_fewer_rows_split_more_keys():
+    """22 x 39 tokens and eight heads: a call of three rows splits its keys in more parts than one of four, so the third
+    micro-step needs more room for them than the steady state."""
+    wl = wk.Workload("split keys", C=1024, H=8, F=4096, grid_h=22, grid_w=39, frames_per_chunk=1, sink_frames=1,
+                     window_frames=2, L_t=64, B=1, N=1, steps=(4,), chunks=5)
+    errs = run_both(wl, 4, 5, 1)
+    assert max(errs) <= TOL_X, errs
+
+
 @pytest.mark.timeout(600)
 def test_wan13b_block_four_steps():
     """One 1.3B-shaped block, four depths (4096 rows in the steady-state call), six chunks, gates of order one."""

@@ -217,7 +217,23 @@ def test_stream_batch_of_latents_sizes_on_the_host(lib):
 def test_a_workspace_for_a_batch_serves_smaller_ones(lib, C_, heads, F):
     """Fewer rows can split k where more rows do not: the size must grow with the rows all the same, because a workspace
     is made for the largest call (the stream batch fills up over calls of 1, 2, ... rows)."""
-    for P in (32, 32), (30, 52):             # (smaller frames have split-KV room that does not grow with the rows)
+    for P in (32, 32), (30, 52):
         cfg = binding.model_cfg(C_, heads, F, P[0], P[1], 512, 30)
         sizes = [binding.block_workspace_bytes(cfg, B, P[0] * P[1]) for B in range(1, 9)]
         assert sizes[0] > 0 and sizes == sorted(sizes)
+
+
+@pytest.mark.parametrize("C_,heads,F", [(512, 4, 2048), (1024, 8, 4096), (1536, 12, 8960), (5120, 40, 13824), (8192, 64, 24576)])
+@pytest.mark.parametrize("grid", [(1, 4), (8, 16), (16, 16), (22, 39), (30, 52)])
+def test_every_workspace_serves_fewer_streams_and_shorter_chunks(lib, C_, heads, F, grid):
+    """The parts of a split key range take room too, and small frames split it in many parts: every size function grows with
+    the streams and with the frames of a chunk, so that the call's own check never refuses a part of what was planned for."""
+    cfg = binding.model_cfg(C_, heads, F, grid[0], grid[1], 512, 30)
+    P = grid[0] * grid[1]
+    for size in (lambda B, f: binding.block_workspace_bytes(cfg, B, f * P), lambda B, f: binding.denoise_workspace_bytes(cfg, B, f * P),
+                 lambda B, f: binding.denoise_latents_workspace_bytes(cfg, B, f * P),
+                 lambda B, f: binding.stream_batch_latents_workspace_bytes(cfg, B, f)):
+        table = [[size(B, f) for f in range(1, 5)] for B in range(1, 9)]
+        assert table[0][0] > 0
+        assert all(row == sorted(row) for row in table), table
+        assert all(list(col) == sorted(col) for col in zip(*table)), table
