@@ -587,6 +587,12 @@ int32_t sdv2_prof_end(int32_t* tags_out, float* ms_out, int32_t capacity, int32_
  *   a0 heads, a1 keys, cache capacity a2 slots.  Host only; `out` receives a NUL-terminated string. */
 int32_t sdv2_prof_kernel_name(int32_t kind, int32_t B, int32_t L, int32_t a0, int32_t a1, int32_t a2, char* out,
                               size_t capacity);
+/* sdv2_prof_gemm_plan: what the planner picks for a product of M rows, N columns and K (epilogue 0 .. 3, or 4 for a plain
+ * fp32 store) in a call with workspace_bytes of scratch; products = 2: two products of the same A in one launch.
+ *   *tile_out: tile configuration ("gemm_tile" = "d<id>" forces it; 0: the register-staged kernel);  *parts_out: parts of
+ *   k;  *us_out: the planner's estimate in microseconds (0 for the register-staged kernel).  Host only. */
+int32_t sdv2_prof_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t products, size_t workspace_bytes,
+                            int32_t* tile_out, int32_t* parts_out, float* us_out);
 int32_t sdv2_prof_peak_mfma(int32_t iters, int32_t workgroups, float* sink_dev, size_t sink_floats, double* flops_out,
                             void* hip_stream);
 int32_t sdv2_prof_peak_copy(const void* src_dev, void* dst_dev, size_t bytes, void* hip_stream);

@@ -81,7 +81,7 @@ EXPORTS = (
     "sdv2_conditioning_workspace_bytes", "sdv2_conditioning", "sdv2_block_workspace_bytes",
     "sdv2_dit_block_forward", "sdv2_denoise_workspace_bytes", "sdv2_denoise_step", "sdv2_gemm_workspace_bytes", "sdv2_gemm_bf16",
     "sdv2_attention_workspace_bytes", "sdv2_attention_bf16", "sdv2_prof_begin", "sdv2_prof_end",
-    "sdv2_prof_peak_mfma", "sdv2_prof_peak_copy", "sdv2_prof_lds_rates", "sdv2_prof_kernel_name", "sdv2_tuning_set", "sdv2_gemm_noalloc_max_scratch_bytes",
+    "sdv2_prof_peak_mfma", "sdv2_prof_peak_copy", "sdv2_prof_lds_rates", "sdv2_prof_kernel_name", "sdv2_prof_gemm_plan", "sdv2_tuning_set", "sdv2_gemm_noalloc_max_scratch_bytes",
     "sdv2_gemm_bf16_noalloc", "sdv2_stream_batch_rows_bytes", "sdv2_stream_batch_create", "sdv2_stream_batch_destroy",
     "sdv2_stream_batch_reset", "sdv2_stream_batch_step", "sdv2_denoise_graph_state_bytes", "sdv2_denoise_graph_create",
     "sdv2_denoise_graph_launch", "sdv2_denoise_graph_destroy", "sdv2_timestep_vector", "sdv2_latent_io_workspace_bytes",
@@ -162,6 +162,7 @@ def load_library():
     lib.sdv2_prof_lds_rates.argtypes = [i32, vp, sz, vp]
     lib.sdv2_tuning_set.argtypes = [C.c_char_p, C.c_char_p]
     lib.sdv2_prof_kernel_name.argtypes = [i32, i32, i32, i32, i32, i32, C.c_char_p, sz]
+    lib.sdv2_prof_gemm_plan.argtypes = [i32, i32, i32, i32, i32, sz, C.POINTER(i32), C.POINTER(i32), C.POINTER(C.c_float)]
     lib.sdv2_gemm_noalloc_max_scratch_bytes.restype = sz
     lib.sdv2_denoise_graph_state_bytes.restype = sz
     lib.sdv2_denoise_graph_create.argtypes = [C.POINTER(ModelCfg), C.POINTER(ModelWeights), vp, f32p, C.POINTER(vp),
@@ -548,6 +549,14 @@ def prof_kernel_name(kind, B, L, a0, a1, a2):
     buf = C.create_string_buffer(128)
     _check(_lib.sdv2_prof_kernel_name(0 if kind == "gemm" else 1, B, L, a0, a1, a2, buf, 128))
     return buf.value.decode()
+
+
+def prof_gemm_plan(M, N, K, epilogue=0, products=1, workspace_bytes=0):
+    """(tile configuration, k parts, estimated microseconds) of a product in a call with that much scratch."""
+    load_library()
+    tile, parts, us = C.c_int32(), C.c_int32(), C.c_float()
+    _check(_lib.sdv2_prof_gemm_plan(M, N, K, epilogue, products, workspace_bytes, C.byref(tile), C.byref(parts), C.byref(us)))
+    return tile.value, parts.value, us.value
 
 
 def tuning_set(name, value=None):

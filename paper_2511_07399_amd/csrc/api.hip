@@ -1875,6 +1875,15 @@ int32_t sdv2_prof_kernel_name(int32_t kind, int32_t B, int32_t L, int32_t a0, in
     return fail(SDV2_INVALID_ARG, "kind must be 0 (GEMM) or 1 (attention)");
 }
 
+int32_t sdv2_prof_gemm_plan(int32_t M, int32_t N, int32_t K, int32_t epilogue, int32_t products, size_t workspace_bytes,
+                            int32_t* tile_out, int32_t* parts_out, float* us_out) {
+    if (!tile_out || !parts_out || !us_out) return fail(SDV2_INVALID_ARG, "null pointer");
+    if (M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > 4 || products < 1 || products > 2)
+        return fail(SDV2_INVALID_ARG, "bad M, N, K, epilogue or products");
+    gemm_plan(M, N, K, epilogue, products, workspace_bytes, tile_out, parts_out, us_out);
+    return SDV2_OK;
+}
+
 int32_t sdv2_prof_begin(int32_t max_samples) {
     if (max_samples <= 0 || max_samples > (1 << 20)) return fail(SDV2_INVALID_ARG, "max_samples out of range");
     if (g_prof.on) return fail(SDV2_BAD_STATE, "profiling already on");

@@ -87,6 +87,8 @@ size_t gemm_splitk_floats(int M, int N, int K, int epilogue);
 size_t gemm_splitk_floats_bound(int M, int N);
 // Name of the kernel instantiation the plan picks for a shape, spelled as a profiler prints it (benchmark only).
 void gemm_plan_name(int M, int N, int K, int epilogue, char* out, size_t cap);
+// The plan of a call with `bytes` of scratch: configuration (0: register-staged kernel), k parts, estimated microseconds.
+void gemm_plan(int M, int N, int K, int epilogue, int products, size_t bytes, int* tile, int* parts, float* us);
 // Tuning hooks (tests and sweeps): a tile plan that replaces the planner's for every shape; false if not understood.
 bool set_gemm_tile_override(const char* spec);
 

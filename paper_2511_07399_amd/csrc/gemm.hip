@@ -925,29 +925,44 @@ float tile_cost(int id, int M, int N, float k_tiles, int parts) {
     return t.c + (full + last) * (k_tiles * t.a + t.b);
 }
 
-// The planner: the configuration and number of k parts with the smallest estimate.  A k split pays for a second pass
-// (4 us and its bytes at 3.9 TB/s); a residual epilogue gets back the LayerNorm that this pass forms (5 us).  Parts of
-// at least 512, and at most 48 MiB of partial sums.  Up to 32 MiB they fit the entry point without a workspace; more than
+// The planner: the configuration and number of k parts with the smallest estimate among those that the call can run.  A k
+// split pays for a second pass (4 us and its bytes at 3.9 TB/s); a residual epilogue gets back the LayerNorm that this pass
+// forms (5 us).  Parts of at least 512, as many as the call's scratch holds (a tile picked for a split that is then not made
+// is up to 1.8 times slower than the best whole one: 77 text tokens of 40 heads), and at most 48 MiB of partial sums.  Up to 32 MiB they fit the entry point without a workspace; more than
 // that has to be 1.5 % better by the estimate, which is careful: measured with cold weights, best within 32 MiB against
 // the plan with 32 to 48 MiB: 1024 x 5120 x 13824 146 -> 131 us, 1024 x 5120 x 20480 213 -> 188, 1024 x 3072 x 12288
 // 87 -> 77, 1560 x 3072 x 12288 124 -> 120, 512 x 5120 x 13824 81 -> 78.
 constexpr size_t kMaxPartialBytes = (size_t)48 << 20, kSmallPartialBytes = (size_t)32 << 20;
+constexpr int kMaxParts = 6;
 
-TilePlan search_plan(int M, int N, int K, int epilogue) {
+// Parts of k (1: no split) that leave 512 of k to each and whose partial sums fit in `bytes` of scratch.
+int most_parts(int M, int N, int K, size_t bytes) {
+    const size_t fit = (bytes < kMaxPartialBytes ? bytes : kMaxPartialBytes) / ((size_t)M * N * sizeof(float));
+    const int by_k = K / 512;
+    int parts = fit < (size_t)kMaxParts ? (int)fit : kMaxParts;
+    if (parts > by_k) parts = by_k;
+    return parts < 1 ? 1 : parts;
+}
+
+// Estimated microseconds of configuration `id` for one or two products of a shape, split in `parts` parts of k.
+float plan_cost(int id, int M, int N, int K, int epilogue, int parts, int products) {
+    const bool residual = epilogue == kEpiGatedResidual || epilogue == kEpiResidual;
+    float cost = tile_cost(id, M, N, (float)K / (64 * parts), parts * products);
+    if (parts > 1) cost += 4.0f + (float)M * N * (4.0f * parts + (residual ? 8.0f : 2.0f)) / 3.9e6f - (residual ? 5.0f : 0.0f);
+    // operands beyond the 256 MB memory-side cache: with a single wave per SIMD their latency shows (4 to 14 %)
+    if (kCost[id].one_wave && ((size_t)M + (size_t)products * N) * K * sizeof(bf16) > ((size_t)240 << 20)) cost *= 1.07f;
+    if (parts > 1 && (size_t)parts * M * N * sizeof(float) > kSmallPartialBytes) cost *= 1.015f;
+    return cost;
+}
+
+TilePlan search_plan(int M, int N, int K, int epilogue, int max_parts, int products) {
     TilePlan best{0, 0, 0, 1, 1};
     float best_cost = 1e30f;
-    const int kParts[] = {1, 2, 3, 4, 6};
-    // operands beyond the 256 MB memory-side cache: with a single wave per SIMD their latency shows (4 to 14 %)
-    const bool from_memory = (size_t)(M + (size_t)N) * K * sizeof(bf16) > ((size_t)240 << 20);
+    const int kParts[] = {1, 2, 3, 4, kMaxParts};
     for (const int parts : kParts) {
-        if (parts > 1 && (K < 512 * parts || (size_t)parts * M * N * sizeof(float) > kMaxPartialBytes)) break;
-        float second = 0.0f;
-        if (parts > 1) second = 4.0f + (float)M * N * (4.0f * parts + (epilogue >= kEpiGatedResidual ? 8.0f : 2.0f)) / 3.9e6f -
-                                (epilogue >= kEpiGatedResidual ? 5.0f : 0.0f);
+        if (parts > max_parts) break;
         for (int id = 1; id <= kTileConfigs; ++id) {
-            float cost = tile_cost(id, M, N, (float)K / (64 * parts), parts) + second;
-            if (from_memory && kCost[id].one_wave) cost *= 1.07f;
-            if (parts > 1 && (size_t)parts * M * N * sizeof(float) > kSmallPartialBytes) cost *= 1.015f;
+            const float cost = plan_cost(id, M, N, K, epilogue, parts, products);
             if (cost < best_cost) {
                 best_cost = cost;
                 best = TilePlan{0, 0, 0, id, parts};
@@ -957,22 +972,27 @@ TilePlan search_plan(int M, int N, int K, int epilogue) {
     return best;
 }
 
-// Plans of the shapes a thread has used last (a step asks for the same half dozen over and over; a search is 18 x 5
+// The plan of a call with `bytes` of scratch for partial sums; products = 2: two of the same A in one launch, which makes no
+// split.  Kept for the shapes a thread has used last (a step asks for the same half dozen over and over; a search is 18 x 5
 // estimates, about 2 us).
-TilePlan plan_tiles(int M, int N, int K, int epilogue) {
+TilePlan plan_tiles(int M, int N, int K, int epilogue, size_t bytes, int products = 1) {
     if (!fits_32bit_offsets(M, N, K)) return plan_register_staged(M, N, K);
     struct Entry {
-        int M, N, K, residual;
+        int M, N, K, kind;
         TilePlan plan;
     };
     constexpr int kEntries = 64;
     static thread_local Entry cache[kEntries] = {};
-    const int residual = epilogue >= kEpiGatedResidual ? 1 : 0;
-    const uint32_t h = (uint32_t)M * 2654435761u ^ (uint32_t)N * 2246822519u ^ (uint32_t)K * 3266489917u ^ (uint32_t)residual;
+    const int residual = epilogue == kEpiGatedResidual || epilogue == kEpiResidual ? 1 : 0;
+    const int max_parts = products > 1 ? 1 : most_parts(M, N, K, bytes);
+    const int kind = residual + 2 * products + 8 * max_parts;
+    const uint32_t h = (uint32_t)M * 2654435761u ^ (uint32_t)N * 2246822519u ^ (uint32_t)K * 3266489917u ^ (uint32_t)kind;
     Entry& e = cache[(h ^ (h >> 16)) % kEntries];
-    if (e.M != M || e.N != N || e.K != K || e.residual != residual) e = Entry{M, N, K, residual, search_plan(M, N, K, epilogue)};
+    if (e.M != M || e.N != N || e.K != K || e.kind != kind) e = Entry{M, N, K, kind, search_plan(M, N, K, epilogue, max_parts, products)};
     return e.plan;
 }
+
+size_t scratch_bytes(const GemmArgs& g) { return g.splitk_partials == nullptr ? 0 : g.splitk_floats * sizeof(float); }
 
 }  // namespace
 
@@ -1171,8 +1191,8 @@ static int usable_splitk(const GemmArgs& g, const TilePlan& p) {
 // when the plan does not split).  The benchmark times the two parts separately.
 static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln_done, hipStream_t s, int part = 0) {
     if (g.w2 != nullptr) {
-        // both products in one launch, planned as one of twice the width, without a k split
-        TilePlan p2 = plan_tiles(g.M, 2 * g.N, g.K, kEpiBias);
+        // both products in one launch, without a k split
+        TilePlan p2 = plan_tiles(g.M, g.N, g.K, g.epilogue, 0, 2);
         tile_override(&p2);
         if (p2.dma && fits_32bit_offsets(g.M, g.N, g.K)) return launch_tile_config(g, p2.dma, 2, s);
         GemmArgs one = g;
@@ -1184,7 +1204,7 @@ static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln
         one.out = g.out2;
         return launch_gemm_impl(one, nullptr, nullptr, s);
     }
-    TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue);
+    TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue, scratch_bytes(g));
     tile_override(&p);
     const int splitk = usable_splitk(g, p);
     hipError_t e = hipSuccess;
@@ -1214,7 +1234,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) { return launch_gemm_im
 
 // Name of the kernel instantiation the plan picks for a shape, spelled as a profiler prints it.
 void gemm_plan_name(int M, int N, int K, int epilogue, char* out, size_t cap) {
-    TilePlan p = plan_tiles(M, N, K, epilogue);
+    TilePlan p = plan_tiles(M, N, K, epilogue, kMaxPartialBytes);
     tile_override(&p);
     switch (p.dma) {
 #define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, ...)                                                                 \
@@ -1227,6 +1247,14 @@ void gemm_plan_name(int M, int N, int K, int epilogue, char* out, size_t cap) {
     snprintf(out, cap, "gemm_kernel<%d, %d, 64, %d>", p.tm, p.tn, p.pf);
 }
 
+void gemm_plan(int M, int N, int K, int epilogue, int products, size_t bytes, int* tile, int* parts, float* us) {
+    TilePlan p = plan_tiles(M, N, K, epilogue, bytes, products);
+    tile_override(&p);
+    *tile = p.dma;
+    *parts = p.splitk;
+    *us = p.dma ? plan_cost(p.dma, M, N, K, epilogue, p.splitk, products) : 0.0f;
+}
+
 hipError_t launch_gemm_then_layernorm(const GemmArgs& g, const LnArgs& ln, bool* ln_done, hipStream_t s, int part) {
     *ln_done = false;
     return launch_gemm_impl(g, &ln, ln_done, s, part);
@@ -1235,18 +1263,18 @@ hipError_t launch_gemm_then_layernorm(const GemmArgs& g, const LnArgs& ln, bool*
 hipError_t launch_gemm_part(const GemmArgs& g, hipStream_t s, int part) { return launch_gemm_impl(g, nullptr, nullptr, s, part); }
 
 bool gemm_splits_k(const GemmArgs& g) {
-    TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue);
+    TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue, scratch_bytes(g));
     tile_override(&p);
     return usable_splitk(g, p) > 1;
 }
 
 size_t gemm_splitk_floats_bound(int M, int N) {
-    const size_t most = (size_t)6 * M * N, cap = kMaxPartialBytes / sizeof(float);
+    const size_t most = (size_t)kMaxParts * M * N, cap = kMaxPartialBytes / sizeof(float);
     return most < cap ? most : cap;
 }
 
 size_t gemm_splitk_floats(int M, int N, int K, int epilogue) {
-    TilePlan p = plan_tiles(M, N, K, epilogue);
+    TilePlan p = plan_tiles(M, N, K, epilogue, kMaxPartialBytes);
     tile_override(&p);
     if (p.splitk <= 1) return 0;
     return (size_t)p.splitk * M * N;

@@ -237,3 +237,29 @@ def test_every_workspace_serves_fewer_streams_and_shorter_chunks(lib, C_, heads,
         assert table[0][0] > 0
         assert all(row == sorted(row) for row in table), table
         assert all(list(col) == sorted(col) for col in zip(*table)), table
+
+
+@pytest.mark.parametrize("M,N,K,epilogue,products", [
+    (77, 3328, 3328, 0, 2), (128, 5120, 5120, 0, 2), (77, 5120, 5120, 0, 2), (512, 1536, 1536, 0, 2),      # text keys and values
+    (1024, 64, 5120, 4, 1), (4680, 64, 5120, 4, 1),                                                        # output head
+    (1024, 5120, 13824, 2, 1), (1560, 3072, 12288, 3, 1), (128, 5120, 5120, 2, 1), (300, 2560, 7680, 1, 1),
+])
+def test_a_plan_is_the_best_that_the_call_can_run(lib, M, N, K, epilogue, products):
+    """Without scratch: no k split and, by the planner's own estimate, no better tile.  With scratch: as many parts as it
+    holds, and never worse than a split in fewer parts or none."""
+    part = 4 * M * N
+    for scratch in (0, part, 2 * part - 1, 2 * part, 3 * part + 5, 48 << 20, 1 << 40):
+        tile, parts, us = binding.prof_gemm_plan(M, N, K, epilogue, products, scratch)
+        assert 1 <= tile <= 18 and (parts == 1 or (products == 1 and parts * part <= scratch))
+        others = []
+        try:
+            for want in (1, 2, 3, 4, 6):
+                if want > 1 and (products > 1 or want * part > min(scratch, 48 << 20) or K < 512 * want):
+                    continue
+                for t in range(1, 19):
+                    binding.tuning_set("gemm_tile", "d%d,%d" % (t, want))
+                    assert binding.prof_gemm_plan(M, N, K, epilogue, products, scratch)[:2] == (t, want)
+                    others.append(binding.prof_gemm_plan(M, N, K, epilogue, products, scratch)[2])
+        finally:
+            binding.tuning_set("gemm_tile", None)
+        assert us == min(others)
