@@ -529,10 +529,9 @@ int32_t sdv2_gemm_bf16(const void* a_dev, const void* w_dev, const float* bias_d
  * to a scratch array built into the library's device image (sdv2_gemm_noalloc_max_scratch_bytes() = 32 MiB per GPU
  * that loads the library, held until the process ends).  The call allocates nothing, frees nothing, and does not
  * synchronise.
- * A planned k-split of more parts than the scratch holds takes the parts that fit (the sum's order then differs from
- * that of a call with the full workspace).
- * Errors: a shape whose planned k-split does not fit with two parts either: SDV2_INVALID_ARG (use sdv2_gemm_bf16 with a
- * workspace); otherwise as sdv2_gemm_bf16.
+ * A shape whose k-split wants more than that scratch is planned within it: with fewer parts, or as a whole (the sum's
+ * order then differs from that of a call with the full workspace).
+ * Errors: as sdv2_gemm_bf16.
  * Every call on one GPU uses that GPU's one scratch array: calls that overlap in time on the same GPU (different
  * streams) race on it; calls ordered on one stream do not.  Nothing in the scratch has to start at zero: every
  * partial sum that the reduce pass reads is stored by the same call first. */

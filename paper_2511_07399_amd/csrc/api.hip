@@ -605,11 +605,8 @@ int32_t sdv2_gemm_bf16_noalloc(const void* a_dev, const void* w_dev, const float
                                int32_t N, int32_t K, int32_t epilogue, const float* gate_a_dev, const float* gate_b_dev,
                                int32_t gate_b_stride, int32_t rows_per_gate, void* hip_stream) {
     if (M <= 0 || N <= 0 || K <= 0 || epilogue < 0 || epilogue > 3) return fail(SDV2_INVALID_ARG, "bad M, N, K or epilogue");
+    // the plan is the best that the scratch holds: fewer parts than with a full workspace, or none
     const size_t need = gemm_splitk_floats(M, N, K, epilogue) * sizeof(float);
-    // a split of more parts than the scratch holds takes as many as it does; less than two parts are no split
-    if (need > kNoAllocScratchBytes && (size_t)M * N * 2 * sizeof(float) > kNoAllocScratchBytes)
-        return fail(SDV2_INVALID_ARG, "this shape's k-split needs %zu bytes of scratch, more than the built-in %zu: use "
-                    "sdv2_gemm_bf16 with a workspace", need, (size_t)kNoAllocScratchBytes);
     void* ptr = nullptr;
     if (need) {
         const int32_t rc = noalloc_scratch(&ptr);

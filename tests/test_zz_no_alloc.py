@@ -58,18 +58,23 @@ def test_noalloc_gemm_two_calls_in_a_row_second_smaller():
         binding.tuning_set("gemm_tile", None)
 
 
-def test_noalloc_gemm_rejects_what_does_not_fit():
-    # FFN-2 of the 14B block splits k in three parts of 1024 x 5120 floats: 63 MB
-    M, N, K = 1024, 5120, 13824
-    assert binding.gemm_workspace_bytes(M, N, K, 2) > binding.gemm_noalloc_max_scratch_bytes()
-    a, w = torch.zeros(M, K, dtype=torch.bfloat16, device=DEV), torch.zeros(N, K, dtype=torch.bfloat16, device=DEV)
-    out = torch.zeros(M, N, dtype=torch.float32, device=DEV)
-    g = torch.zeros(N, dtype=torch.float32, device=DEV)
-    with pytest.raises(binding.Sdv2Error) as e:
-        binding.gemm_bf16_noalloc(a, w, None, out, 2, g, g.reshape(1, N), N, M)
-    assert e.value.code == binding.INVALID_ARG
-    torch.cuda.synchronize()
-    assert float(out.abs().max()) == 0.0
+@pytest.mark.parametrize("M,N,K,epi", [
+    (1024, 5120, 13824, 2),         # FFN-2 of the 14B block
+    (1024, 5120, 20480, 3),
+    (1560, 3072, 12288, 2),         # two parts of 18 MiB
+    (3072, 1536, 8960, 2),          # FFN-2 of the 1.3B block on three streams
+])
+def test_noalloc_gemm_runs_whole_what_its_scratch_does_not_hold(M, N, K, epi):
+    assert 2 * 4 * M * N > binding.gemm_noalloc_max_scratch_bytes()
+    assert binding.gemm_workspace_bytes(M, N, K, epi) > binding.gemm_noalloc_max_scratch_bytes()
+    a, w = draw((M, K), 500).to(DEV), draw((N, K), 501, 0.05).to(DEV)
+    x0 = draw((M, N), 502).float().to(DEV)
+    gate_a, gate_b = draw((N,), 503, 0.3).float().to(DEV), draw((1, N), 504, 0.3).float().to(DEV)
+    out = x0.clone()
+    binding.gemm_bf16_noalloc(a, w, None, out, epi, gate_a, gate_b, N, M)
+    acc = a.double() @ w.double().t()
+    ref = x0.double() + (acc * (gate_a + gate_b[0]).double() if epi == 2 else acc)
+    assert max_rel_err(out.cpu().double().numpy(), ref.cpu().numpy()) < 1e-4
 
 
 def test_noalloc_gemm_takes_as_many_parts_as_the_scratch_holds():
