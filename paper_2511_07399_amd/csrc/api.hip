@@ -809,7 +809,7 @@ BlockWorkspace carve_block(const sdv2_model_cfg* cfg, int B, int L, int max_kv, 
     w.attn = reinterpret_cast<float*>(take(w.attn_bytes));
     const int shapes[6][3] = {{(int)(3 * C), (int)C, kEpiBias}, {(int)C, (int)C, kEpiGatedResidual}, {(int)C, (int)C, kEpiBias},
                               {(int)C, (int)C, kEpiResidual},   {(int)F, (int)C, kEpiBiasGelu},      {(int)C, (int)F, kEpiGatedResidual}};
-    w.gemm_floats = gemm_splitk_floats_bound((int)rows, (int)(F > 3 * C ? F : 3 * C));
+    w.gemm_floats = gemm_splitk_floats_bound((int)rows, (int)(F > 3 * C ? F : 3 * C), (int)(F > C ? F : C));
     for (const auto& sh : shapes) {
         const size_t f = gemm_splitk_floats((int)rows, sh[0], sh[1], sh[2]);
         if (f > w.gemm_floats) w.gemm_floats = f;

@@ -83,8 +83,8 @@ struct GemmArgs {
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // fp32 partial sums the planned launch of an [M, K] x [N, K] product needs (0: its plan does not split k)
 size_t gemm_splitk_floats(int M, int N, int K, int epilogue);
-// the most that the planned launch of any product of at most M rows and N columns needs; grows with both
-size_t gemm_splitk_floats_bound(int M, int N);
+// the most that the planned launch of any product of at most M rows, N columns and K needs; grows with each
+size_t gemm_splitk_floats_bound(int M, int N, int K);
 // Name of the kernel instantiation the plan picks for a shape, spelled as a profiler prints it (benchmark only).
 void gemm_plan_name(int M, int N, int K, int epilogue, char* out, size_t cap);
 // The plan of a call with `bytes` of scratch: configuration (0: register-staged kernel), k parts, estimated microseconds.

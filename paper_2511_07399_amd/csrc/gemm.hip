@@ -928,16 +928,23 @@ float tile_cost(int id, int M, int N, float k_tiles, int parts) {
 // The planner: the configuration and number of k parts with the smallest estimate among those that the call can run.  A k
 // split pays for a second pass (4 us and its bytes at 3.9 TB/s); a residual epilogue gets back the LayerNorm that this pass
 // forms (5 us).  Parts of at least 512, as many as the call's scratch holds (a tile picked for a split that is then not made
-// is up to 1.8 times slower than the best whole one: 77 text tokens of 40 heads), and at most 48 MiB of partial sums.  Up to 32 MiB they fit the entry point without a workspace; more than
+// is up to 1.8 times slower than the best whole one: 77 text tokens of 40 heads), and at most 48 MiB of partial sums (long sums: below).  Up to 32 MiB they fit the entry point without a workspace; more than
 // that has to be 1.5 % better by the estimate, which is careful: measured with cold weights, best within 32 MiB against
 // the plan with 32 to 48 MiB: 1024 x 5120 x 13824 146 -> 131 us, 1024 x 5120 x 20480 213 -> 188, 1024 x 3072 x 12288
 // 87 -> 77, 1560 x 3072 x 12288 124 -> 120, 512 x 5120 x 13824 81 -> 78.
 constexpr size_t kMaxPartialBytes = (size_t)48 << 20, kSmallPartialBytes = (size_t)32 << 20;
 constexpr int kMaxParts = 6;
+// Sums of more than 12 288 products take at least three parts where the scratch and 64 MiB hold them: the error of a sum
+// grows with the root of its longest chain.  1024 x 5120 x 13824 (FFN-2 of the 14B block), relative error against 64 bits:
+// whole 7.5e-7, two parts 5.2e-7, three 4.2e-7; 145, 128 and 139 us.
+constexpr int kLongSum = 12288, kLongSumParts = 3;
+constexpr size_t kMaxLongSumBytes = (size_t)64 << 20;
+
+size_t most_partial_bytes(int K) { return K > kLongSum ? kMaxLongSumBytes : kMaxPartialBytes; }
 
 // Parts of k (1: no split) that leave 512 of k to each and whose partial sums fit in `bytes` of scratch.
 int most_parts(int M, int N, int K, size_t bytes) {
-    const size_t fit = (bytes < kMaxPartialBytes ? bytes : kMaxPartialBytes) / ((size_t)M * N * sizeof(float));
+    const size_t cap = most_partial_bytes(K), fit = (bytes < cap ? bytes : cap) / ((size_t)M * N * sizeof(float));
     const int by_k = K / 512;
     int parts = fit < (size_t)kMaxParts ? (int)fit : kMaxParts;
     if (parts > by_k) parts = by_k;
@@ -959,7 +966,9 @@ TilePlan search_plan(int M, int N, int K, int epilogue, int max_parts, int produ
     TilePlan best{0, 0, 0, 1, 1};
     float best_cost = 1e30f;
     const int kParts[] = {1, 2, 3, 4, kMaxParts};
+    const int min_parts = K > kLongSum && max_parts >= kLongSumParts ? kLongSumParts : 1;
     for (const int parts : kParts) {
+        if (parts < min_parts) continue;
         if (parts > max_parts) break;
         for (int id = 1; id <= kTileConfigs; ++id) {
             const float cost = plan_cost(id, M, N, K, epilogue, parts, products);
@@ -1234,7 +1243,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t s) { return launch_gemm_im
 
 // Name of the kernel instantiation the plan picks for a shape, spelled as a profiler prints it.
 void gemm_plan_name(int M, int N, int K, int epilogue, char* out, size_t cap) {
-    TilePlan p = plan_tiles(M, N, K, epilogue, kMaxPartialBytes);
+    TilePlan p = plan_tiles(M, N, K, epilogue, most_partial_bytes(K));
     tile_override(&p);
     switch (p.dma) {
 #define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, ...)                                                                 \
@@ -1268,13 +1277,13 @@ bool gemm_splits_k(const GemmArgs& g) {
     return usable_splitk(g, p) > 1;
 }
 
-size_t gemm_splitk_floats_bound(int M, int N) {
-    const size_t most = (size_t)kMaxParts * M * N, cap = kMaxPartialBytes / sizeof(float);
+size_t gemm_splitk_floats_bound(int M, int N, int K) {
+    const size_t most = (size_t)kMaxParts * M * N, cap = most_partial_bytes(K) / sizeof(float);
     return most < cap ? most : cap;
 }
 
 size_t gemm_splitk_floats(int M, int N, int K, int epilogue) {
-    TilePlan p = plan_tiles(M, N, K, epilogue, kMaxPartialBytes);
+    TilePlan p = plan_tiles(M, N, K, epilogue, most_partial_bytes(K));
     tile_override(&p);
     if (p.splitk <= 1) return 0;
     return (size_t)p.splitk * M * N;

@@ -157,6 +157,22 @@ def test_gemm_adds_the_bias_to_the_finished_sum(tile):
     assert err <= 2.0 ** -24 * want.norm().item() + 1e-6 * acc.norm().item(), err / want.norm().item()
 
 
+def test_gemm_of_a_long_sum_is_split_in_three():
+    """FFN-2 of the 14B-shaped block (1024 x 5120 x 13824), fp32 output, against 64 bits.  The rounding error of a sum grows
+    with the root of its longest chain: 4.2e-7 relative for chains of 4608 products, 5.2e-7 for 6912, 7.5e-7 for all of
+    them.  The bar lies between the first two."""
+    M, N, K = 1024, 5120, 13824
+    g = torch.Generator(device=DEV).manual_seed(1)
+    a = torch.randn(M, K, generator=g, device=DEV).to(torch.bfloat16)
+    w = (torch.randn(N, K, generator=g, device=DEV) * 0.02).to(torch.bfloat16)
+    ws = torch.empty(binding.gemm_workspace_bytes(M, N, K, 3), dtype=torch.uint8, device=DEV)
+    out = torch.zeros(M, N, device=DEV)
+    binding.gemm_bf16(a, w, None, out, 3, workspace=ws)
+    want = a.double() @ w.double().t()
+    err = ((out.double() - want).norm() / want.norm()).item()
+    assert err <= 4.7e-7, err
+
+
 def test_gemm_full_size_batched_480p_shape_sampled_rows():
     """FFN-1 of the 14B-shaped block on 4 streams x 4680 tokens (M 18720, N 13824, K 5120: the direct-load kernel,
     74 x 54 tiles, ragged last M tile): whole output finite, 48 sampled rows against the oracle."""

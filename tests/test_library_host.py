@@ -246,15 +246,18 @@ def test_every_workspace_serves_fewer_streams_and_shorter_chunks(lib, C_, heads,
 ])
 def test_a_plan_is_the_best_that_the_call_can_run(lib, M, N, K, epilogue, products):
     """Without scratch: no k split and, by the planner's own estimate, no better tile.  With scratch: as many parts as it
-    holds, and never worse than a split in fewer parts or none."""
+    holds, and never worse than a split in fewer parts or none; sums of more than 12 288 in at least three parts where they
+    fit."""
     part = 4 * M * N
+    cap = (64 if K > 12288 else 48) << 20
     for scratch in (0, part, 2 * part - 1, 2 * part, 3 * part + 5, 48 << 20, 1 << 40):
+        least = 3 if K > 12288 and products == 1 and 3 * part <= min(scratch, cap) else 1
         tile, parts, us = binding.prof_gemm_plan(M, N, K, epilogue, products, scratch)
         assert 1 <= tile <= 18 and (parts == 1 or (products == 1 and parts * part <= scratch))
         others = []
         try:
             for want in (1, 2, 3, 4, 6):
-                if want > 1 and (products > 1 or want * part > min(scratch, 48 << 20) or K < 512 * want):
+                if want < least or (want > 1 and (products > 1 or want * part > min(scratch, cap) or K < 512 * want)):
                     continue
                 for t in range(1, 19):
                     binding.tuning_set("gemm_tile", "d%d,%d" % (t, want))
