@@ -4,7 +4,7 @@
 // and FFN projections), plus the cross-attention projections the cost model leaves out.
 //
 // Two kernels on the matrix cores.  gemm_alt64_kernel (16x16x32 MFMAs, direct global -> LDS loads, persistent) serves
-// every shape whose operands are below 4 GiB: its loads carry 32-bit byte offsets per lane.  gemm_kernel (32x32x16
+// every shape whose operands, and 128 rows of the output, are below 4 GiB: it uses 32-bit byte offsets per lane.  gemm_kernel (32x32x16
 // MFMAs, tiles staged through registers, 64-bit addresses) serves the larger ones.  Both operands are K-contiguous
 // (activations [M, K], weights [N, K]), so fragments are plain 16-byte pieces of rows.
 //   Split-K (few output tiles, long k: FFN-2 of one chunk) is two launches: the parts store fp32 partial sums, a second
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(256, ((TM * TN <= 5 && BK == 64 && PF == 2) ? 2 : 1
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Second kernel, for every shape whose operands are below 4 GiB: v_mfma_f32_16x16x32_bf16 on tiles that go
+// Second kernel, for every shape within 32-bit byte offsets (fits_32bit_offsets): v_mfma_f32_16x16x32_bf16 on tiles that go
 // global -> LDS directly (global_load_lds_dwordx4: no staging registers, no LDS write instructions).
 //
 //   What bounds it.  On random data the chip is power limited: a register-resident loop of 32x32x16 MFMAs sustains
@@ -766,12 +766,15 @@ struct TilePlan {
 };
 constexpr int kUnits = 256;                   // compute units
 
-// gemm_alt64_kernel addresses an operand with 32-bit byte offsets per lane: it serves operands below 4 GiB.
+// gemm_alt64_kernel addresses an operand, and the output from the first row of a wave's tile (at most 128 rows of fp32), with
+// 32-bit byte offsets per lane: it serves operands below 4 GiB and rows of which that many are below 4 GiB.
 bool fits_32bit_offsets(int M, int N, int K) {
-    return (unsigned long long)M * K * 2 <= 0xFFFFFFFFull && (unsigned long long)N * K * 2 <= 0xFFFFFFFFull;
+    constexpr unsigned long long kLimit = 0xFFFFFFFFull;
+    return (unsigned long long)M * K * 2 <= kLimit && (unsigned long long)N * K * 2 <= kLimit &&
+           (unsigned long long)(M < 128 ? M : 128) * N * 4 <= kLimit;
 }
 
-// Operands of 4 GiB and more: the time of the busiest compute unit for the register-staged kernel; one k tile of a
+// Shapes beyond that: the time of the busiest compute unit for the register-staged kernel; one k tile of a
 // workgroup costs a fixed part (~0.25 us alone, half of it when a second workgroup fills the bubbles) plus ~21 ns per
 // MFMA a wave issues (fitted to a sweep); small tiles fit two workgroups per unit.
 TilePlan plan_register_staged(int M, int N, int K) {

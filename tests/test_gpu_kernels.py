@@ -173,6 +173,21 @@ def test_gemm_of_a_long_sum_is_split_in_three():
     assert err <= 4.7e-7, err
 
 
+def test_gemm_of_rows_so_wide_that_a_tile_spans_4_gib():
+    """64 rows of 16 908 288 fp32 columns: a row index times the row's bytes exceeds 32 bits in the last rows.  Residual
+    epilogue; every row at columns from both ends and the middle."""
+    M, N, K = 64, 16908288, 64
+    g = torch.Generator(device=DEV).manual_seed(12)
+    a = torch.randn(M, K, generator=g, device=DEV).to(torch.bfloat16)
+    w = torch.randn(N, K, generator=g, device=DEV, dtype=torch.bfloat16)
+    out = torch.empty(M, N, device=DEV)
+    out.copy_(torch.arange(M, device=DEV, dtype=torch.float32)[:, None])
+    binding.gemm_bf16(a, w, None, out, 3)
+    for c0 in (0, N // 2 - 4096, N - 8192):
+        want = torch.arange(M, device=DEV)[:, None] + a.double() @ w[c0:c0 + 8192].double().t()
+        assert max_rel_err(f64(out[:, c0:c0 + 8192]), f64(want)) < 1e-4, c0
+
+
 def test_gemm_full_size_batched_480p_shape_sampled_rows():
     """FFN-1 of the 14B-shaped block on 4 streams x 4680 tokens (M 18720, N 13824, K 5120: the direct-load kernel,
     74 x 54 tiles, ragged last M tile): whole output finite, 48 sampled rows against the oracle."""

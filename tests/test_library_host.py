@@ -159,6 +159,9 @@ def test_stream_batch_handle_and_planner_hooks_on_the_host(lib):
     # an activation matrix of 4 GiB or more is beyond the 32-bit lane offsets of the direct-load kernels
     assert binding.prof_kernel_name("gemm", 8, 40000, 8192, 8192, 0).startswith("gemm_kernel<")
     assert binding.prof_kernel_name("gemm", 8, 30000, 8192, 8192, 0).startswith("gemm_alt64_kernel<")
+    # so are 64 rows of 20 million fp32 columns, which a wave's tile of that kernel could span; 32 rows are not
+    assert binding.prof_kernel_name("gemm", 1, 64, 20971520, 64, 3).startswith("gemm_kernel<")
+    assert binding.prof_kernel_name("gemm", 1, 32, 20971520, 64, 3).startswith("gemm_alt64_kernel<")
     assert binding.prof_kernel_name("attention", 1, 1024, 12, 3072, 3072) == "attention_ks_kernel<2, 4>"
     assert binding.prof_kernel_name("attention", 1, 1024, 12, 3072, 3136).startswith("attention_kernel<")
     assert binding.prof_kernel_name("attention", 4, 4680, 40, 10920, 10944) == "attention_kernel<8>"
