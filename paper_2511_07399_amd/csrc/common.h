@@ -217,6 +217,7 @@ struct SinkCopyArgs {
     long long* ids;       // [cap]
     int H, cap, P;
     int src0, dst0;       // first slots of the source frame and of the sink frame
+    int key_heads, key_tokens;      // set by the launcher: heads and tokens per head of one launch's keys, from k on
 };
 hipError_t launch_refresh_sink(const SinkCopyArgs& a, hipStream_t s);
 constexpr int kMaxFramePairs = kHeadDim / 2;
@@ -225,6 +226,7 @@ struct RotateKeysArgs {
     int H, cap, S;
     int sink_fill;        // filled sink slots [0, sink_fill)
     int n_slots;          // sink_fill + filled window slots [S, S + n_slots - sink_fill)
+    int slot0;            // set by the launcher: how many of them come before this launch's n_slots
     int n_pairs;          // leading pairs of a head that belong to the frame axis
     float cs[kMaxFramePairs], sn[kMaxFramePairs];
 };

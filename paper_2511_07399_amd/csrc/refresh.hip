@@ -3,6 +3,7 @@
 // s_i <- h_t, and the move of all cached keys by a whole number of frames in rotary phase.  All three are single
 // passes over parts of one (layer, stream) cache: bound by HBM / L2 bandwidth.
 #include "common.h"
+#include "refresh_ranges.h"
 
 namespace sdv2 {
 namespace {
@@ -106,8 +107,8 @@ constexpr int kCopyPieces = 4;
 
 __global__ __launch_bounds__(256) void refresh_sink_kernel(SinkCopyArgs a, int v_blocks) {
     if ((int)blockIdx.x >= v_blocks) {
-        // a head's frame is P contiguous rows of sixteen 16-byte pieces
-        const unsigned per_head = (unsigned)a.P * 16u, total = (unsigned)a.H * per_head;
+        // a head's part of the frame is contiguous rows of sixteen 16-byte pieces
+        const unsigned per_head = (unsigned)a.key_tokens * 16u, total = (unsigned)a.key_heads * per_head;
         const unsigned i0 = (blockIdx.x - v_blocks) * (256u * kCopyPieces) + threadIdx.x;
         bf16x8 x[kCopyPieces];
         bf16x8* dst[kCopyPieces];
@@ -155,9 +156,10 @@ __global__ __launch_bounds__(256) void rotate_keys_kernel(RotateKeysArgs a) {
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const unsigned idx = blockIdx.x * 512u + 256u * u + threadIdx.x;
-        const unsigned i = min(idx, total - 1), si = i / groups;
-        gq[u] = i - si * groups;
-        const int slot = (int)si < a.sink_fill ? (int)si : a.S + ((int)si - a.sink_fill);
+        const unsigned i = min(idx, total - 1), s = i / groups;
+        gq[u] = i - s * groups;
+        const int si = a.slot0 + (int)s;
+        const int slot = si < a.sink_fill ? si : a.S + (si - a.sink_fill);
         p[u] = reinterpret_cast<bf16x8*>(head + (size_t)slot * kHeadDim) + gq[u];
         x[u] = *p[u];
     }
@@ -194,18 +196,37 @@ hipError_t launch_sink_similarity(const SinkSimArgs& a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_refresh_sink(const SinkCopyArgs& a, hipStream_t s) {
-    const unsigned v_blocks = (unsigned)a.H * kHeadDim / 4;
-    const unsigned k_blocks = ((unsigned)a.H * (unsigned)a.P * 16u + 256u * kCopyPieces - 1) / (256u * kCopyPieces);
-    hipLaunchKernelGGL(refresh_sink_kernel, dim3(k_blocks + v_blocks), dim3(256), 0, s, a, (int)v_blocks);
-    return hipGetLastError();
+hipError_t launch_refresh_sink(const SinkCopyArgs& all, hipStream_t s) {
+    SinkCopyArgs a = all;
+    unsigned v_blocks = (unsigned)a.H * kHeadDim / 4;                   // all value rows go with the first range of keys
+    hipError_t e = hipSuccess;
+    for_refresh_ranges(a.H, a.P, 16, a.H, [&](int h0, int heads, int t0, int tokens) {
+        if (e != hipSuccess) return;
+        a.k = all.k + ((size_t)h0 * a.cap + t0) * kHeadDim;
+        a.key_heads = heads;
+        a.key_tokens = tokens;
+        const unsigned k_blocks = ((unsigned)heads * (unsigned)tokens * 16u + 256u * kCopyPieces - 1) / (256u * kCopyPieces);
+        hipLaunchKernelGGL(refresh_sink_kernel, dim3(k_blocks + v_blocks), dim3(256), 0, s, a, (int)v_blocks);
+        e = hipGetLastError();
+        v_blocks = 0;
+    });
+    return e;
 }
 
-hipError_t launch_rotate_keys(const RotateKeysArgs& a, hipStream_t s) {
-    if (a.n_slots == 0) return hipSuccess;
-    const unsigned total = (unsigned)a.n_slots * (unsigned)((a.n_pairs + 3) / 4);          // at most 2^30 slots x 6
-    hipLaunchKernelGGL(rotate_keys_kernel, dim3((total + 511) / 512, a.H), dim3(256), 0, s, a);
-    return hipGetLastError();
+hipError_t launch_rotate_keys(const RotateKeysArgs& all, hipStream_t s) {
+    if (all.n_slots == 0) return hipSuccess;
+    RotateKeysArgs a = all;
+    const int groups = (a.n_pairs + 3) / 4;
+    hipError_t e = hipSuccess;
+    for_refresh_ranges(a.H, all.n_slots, groups, kMaxGridRows, [&](int h0, int heads, int slot0, int slots) {
+        if (e != hipSuccess) return;
+        a.k = all.k + (size_t)h0 * a.cap * kHeadDim;
+        a.slot0 = slot0;
+        a.n_slots = slots;
+        hipLaunchKernelGGL(rotate_keys_kernel, dim3(((unsigned)slots * (unsigned)groups + 511) / 512, heads), dim3(256), 0, s, a);
+        e = hipGetLastError();
+    });
+    return e;
 }
 
 }  // namespace sdv2

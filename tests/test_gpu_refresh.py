@@ -300,3 +300,33 @@ def test_similarity_of_many_heads_is_a_single_precision_number(H, P):
         assert 0.5 < want < 1.0
         assert abs(alpha.item() - want) <= 2.0 ** -25 + 2e-8, (seed, alpha.item() - want)
         binding.kv_cache_destroy(h)
+
+
+def test_refresh_of_more_heads_than_a_grid_has_rows():
+    """70 000 heads of two tokens per frame: the rotation is launched in two ranges of heads, the copy in one."""
+    H, P = 70000, 2
+    binding.load_library()
+    cf = binding.cache_cfg(1, 1, H, P, P, 2 * P)
+    storage = torch.zeros(binding.kv_cache_bytes(cf), dtype=torch.uint8, device=DEV)
+    h = binding.kv_cache_init(cf, storage)
+    g = torch.Generator(device=DEV).manual_seed(3)
+    rows = [torch.randn((P, 128 * H), generator=g, device=DEV).to(torch.bfloat16) for _ in range(2)]
+    for r in rows:
+        binding.kv_cache_append_evict(h, 0, 0, r, r)
+    _, _, _, cap = binding.kv_cache_device_ptrs(h, 0, 0)
+    K = storage[:H * cap * 256].view(torch.bfloat16).view(H, cap, 128)
+    new = rows[1].view(P, H, 128).permute(1, 0, 2)
+    binding.kv_cache_refresh_sink(h, 0, 0, 0)
+    assert torch.equal(K[:, :P], new) and torch.equal(K[:, P:2 * P], new)
+    binding.kv_cache_rotate_keys(h, 0, 0, 5)
+    torch.cuda.synchronize()
+    n = oracle.dit_block.rope_pair_split(128)[0]
+    angle = -5.0 * oracle.dit_block.ROPE_BASE ** (-torch.arange(n, device=DEV, dtype=torch.float64) / n)
+    x = new.double().reshape(H, P, 64, 2)
+    want = x.clone()
+    want[:, :, :n, 0] = x[:, :, :n, 0] * angle.cos() - x[:, :, :n, 1] * angle.sin()
+    want[:, :, :n, 1] = x[:, :, :n, 0] * angle.sin() + x[:, :, :n, 1] * angle.cos()
+    for s0 in (0, P):
+        got = K[:, s0:s0 + P].double().reshape(H, P, 64, 2)
+        assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-6).all()       # one rounding to bf16 (the sums' fp32 below it)
+    binding.kv_cache_destroy(h)

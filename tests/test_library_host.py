@@ -4,6 +4,7 @@ declares, sizes its buffers as documented and rejects bad arguments before touch
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -269,3 +270,37 @@ def test_a_plan_is_the_best_that_the_call_can_run(lib, M, N, K, epilogue, produc
         finally:
             binding.tuning_set("gemm_tile", None)
         assert us == min(others)
+
+
+def test_refresh_launches_cover_caches_beyond_32_bits(tmp_path):
+    """The ranges that a sink copy and a key rotation are launched in: they cover every (head, token) once, and none holds
+    more 16-byte pieces or heads than a launch can index.  One range at the sizes of a model."""
+    source = tmp_path / "ranges.cpp"
+    source.write_text('''
+#include "refresh_ranges.h"
+extern "C" int ranges(int H, int T, int pieces, int max_heads, int* out, int capacity) {
+    int n = 0;
+    sdv2::for_refresh_ranges(H, T, pieces, max_heads, [&](int h0, int hn, int t0, int tn) {
+        if (n < capacity) { out[4 * n] = h0; out[4 * n + 1] = hn; out[4 * n + 2] = t0; out[4 * n + 3] = tn; }
+        ++n;
+    });
+    return n;
+}''')
+    so = tmp_path / "ranges.so"
+    csrc = os.path.join(os.path.dirname(binding.LIB_PATH), "csrc")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", csrc, str(source), "-o", str(so)], check=True)
+    f = C.CDLL(str(so)).ranges
+    for H, T, pieces, max_heads in ((12, 1560, 16, 12), (40, 10920, 6, 65535), (64, 1 << 20, 16, 64),      # models
+                                    (1, 1 << 28, 16, 1), (1, 1 << 30, 6, 65535), (4, 1 << 26, 16, 4), (1024, 1 << 18, 16, 1024),
+                                    (3, (1 << 28) + 5, 16, 3), (70000, 64, 6, 65535), (200000, 3, 6, 65535), (65535, 1, 1, 65535)):
+        buf = (C.c_int * 4096)()
+        n = f(H, T, pieces, max_heads, buf, 1024)
+        assert 1 <= n <= 1024
+        got = [tuple(buf[4 * i:4 * i + 4]) for i in range(n)]
+        assert all(0 < hn <= max_heads and 0 < tn and hn * tn * pieces <= 1 << 31 for _, hn, _, tn in got)
+        heads = sorted({(h0, hn) for h0, hn, _, _ in got})
+        assert heads[0][0] == 0 and all(a + b == c for (a, b), (c, _) in zip(heads, heads[1:])) and sum(heads[-1]) == H
+        for h in heads:
+            tokens = [(t0, tn) for h0, hn, t0, tn in got if (h0, hn) == h]
+            assert tokens[0][0] == 0 and all(a + b == c for (a, b), (c, _) in zip(tokens, tokens[1:])) and sum(tokens[-1]) == T
+        assert (n == 1) == (H * T * pieces <= 1 << 31 and H <= max_heads)
