@@ -365,6 +365,7 @@ constexpr int vmcnt_only(int n) {     // s_waitcnt with only vmcnt constrained
     return (n & 0xF) | ((n >> 4) << 14) | 0x0F70;
 }
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
+typedef const __attribute__((address_space(4))) float* scalar_float_ptr;      // read through the scalar cache where uniform
 // 16 bytes per lane from global memory straight into LDS at dst + 16 * lane (dst is wave-uniform).
 __device__ __forceinline__ void load_to_lds_b128(const void* src, void* dst) {
     __builtin_amdgcn_global_load_lds(src, (lds_void_ptr)dst, 16, 0, 0);
@@ -376,22 +377,41 @@ template <int N, typename F>
 __device__ __forceinline__ void static_for(F&& f) { static_for_impl(std::make_integer_sequence<int, N>{}, f); }
 
 // Stores a wave's tile.  acc[i][j][r] is the element (16 i + lane % 16, 16 j + 4 (lane / 16) + r) of it.  FULL: the tile
-// lies inside the output.  bias_own: the bias of column block lane % 16.  The bias joins the finished sum: an accumulator
+// lies inside the output.  bias_own: the bias of column block lane % 16; SCALAR: it is fetched here instead, through the
+// scalar cache (the wave's columns are uniform).  The bias joins the finished sum: an accumulator
 // that starts from it rounds every partial sum at the bias's magnitude (1024 x 1536 x 1536, relative error against 64 bits:
 // 1.4e-7 after, 3.1e-7 from a bias of the result's size, 2.6e-8 and 3.5e-7 from one 40 times as large).  xpre: x read at the
 // start of the tile (small tiles), else x is read here, a block of rows ahead of its use.
-template <int TM, int TN, int EPI, bool FULL>
+template <int TM, int TN, int EPI, bool FULL, bool SCALAR>
 __device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 (&acc)[TM][TN], const f32x4& bias_own, int row0, int col0, int lane,
                                            const f32x4* xpre = nullptr) {
     const int l15 = lane & 15, lq = lane >> 4;
     const int rows = FULL ? 16 * TM : min(16 * TM, g.M - row0);
     static_assert(TN <= 16, "a row of lanes holds the bias of its column blocks");
     f32x4 bias[TN];
-    static_for<TN>([&](auto jc) {
-        constexpr int j = decltype(jc)::value;
+    if constexpr (!SCALAR) {
+        static_for<TN>([&](auto jc) {
+            constexpr int j = decltype(jc)::value;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) bias[j][e] = dpp_f<0x150 + j>(bias_own[e]);      // row_newbcast: lane j of the row of 16
-    });
+            for (int e = 0; e < 4; ++e) bias[j][e] = dpp_f<0x150 + j>(bias_own[e]);      // row_newbcast: lane j of the row of 16
+        });
+    } else {
+        const bool any = g.bias != nullptr;
+        const scalar_float_ptr s = (scalar_float_ptr)reinterpret_cast<uintptr_t>(g.bias);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            bias[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (any) {
+                const int c = col0 + 16 * j < g.N ? col0 + 16 * j : 0;                        // N is a multiple of 16
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float b0 = s[c + e], b1 = s[c + 4 + e], b2 = s[c + 8 + e], b3 = s[c + 12 + e];
+                    asm("" : "+s"(b0), "+s"(b1), "+s"(b2), "+s"(b3));                           // values to choose from, not addresses
+                    bias[j][e] = lq < 2 ? (lq == 0 ? b0 : b1) : (lq == 2 ? b2 : b3);
+                }
+            }
+        }
+    }
     if constexpr (EPI == kEpiBias || EPI == kEpiBiasGelu) {
         unsigned char* const base = reinterpret_cast<unsigned char*>(reinterpret_cast<bf16*>(outp) + (size_t)row0 * g.N);
         auto pack = [&](const f32x4& v, uint32_t& d0, uint32_t& d1) {
@@ -477,12 +497,12 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 
     }
 }
 
-template <int TM, int TN, int EPI>
+template <int TM, int TN, int EPI, bool SCALAR>
 __device__ __forceinline__ void store_wave(const GemmArgs& g, void* outp, f32x4 (&acc)[TM][TN], const f32x4& bias_own, int row0, int col0, int lane,
                                            const f32x4* xpre = nullptr) {
     asm volatile("" : "+v"(lane));        // formed anew for every tile: lane terms kept across the k loop would cost it registers
-    if (row0 + 16 * TM <= g.M && col0 + 16 * TN <= g.N) store_tile<TM, TN, EPI, true>(g, outp, acc, bias_own, row0, col0, lane, xpre);
-    else if (row0 < g.M) store_tile<TM, TN, EPI, false>(g, outp, acc, bias_own, row0, col0, lane, xpre);
+    if (row0 + 16 * TM <= g.M && col0 + 16 * TN <= g.N) store_tile<TM, TN, EPI, true, SCALAR>(g, outp, acc, bias_own, row0, col0, lane, xpre);
+    else if (row0 < g.M) store_tile<TM, TN, EPI, false, SCALAR>(g, outp, acc, bias_own, row0, col0, lane, xpre);
 }
 
 template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC>
@@ -526,6 +546,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
         if (split) {
             kt0 = ks * KT / splitk;
             nk = (ks + 1) * KT / splitk - kt0;
+            g.bias = nullptr;                                // the pass that adds the parts has it
         } else if (ks == 1) {
             g.w = g.w2;
             g.bias = g.bias2;
@@ -604,7 +625,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     set_off1(n0);
     f32x4 acc[TM][TN];
     // The bias is the same for the sixteen lanes of a row: each keeps one column block's (four registers across the k loop
-    // where every lane with all of its blocks would take 4 TN).
+    // where every lane with all of its blocks would take 4 TN).  The 256 x 256 tile has not even those: spilled, they put
+    // waits for scratch among its loads (1024 x 15360 x 5120: 154 us), so it fetches them when it stores (137 us).
+    constexpr bool kScalarBias = TM * TN >= 32 && OCC == 2;
     f32x4 bias = {0.f, 0.f, 0.f, 0.f};
     auto load_bias = [&](int n) {
         const int c = n + wn * (16 * TN) + 16 * min(l15, TN - 1) + 4 * lq;
@@ -661,7 +684,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
             __builtin_amdgcn_s_waitcnt(vmcnt_only(w1));
         }
     };
-    if (g.bias != nullptr && !split) bias = load_bias(n0);
+    if (g.bias != nullptr) bias = load_bias(n0);
     constexpr bool kPre = TM * TN <= 16;
     f32x4 xpre[kPre ? TM * TN : 1];
     auto load_x = [&]() {
@@ -738,14 +761,14 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
         }
         const int row0 = m0 + wm * (16 * TM), col0 = n0 + wn * (16 * TN);
         switch (split ? (int)kEpiPartial : g.epilogue) {
-            case kEpiBias: store_wave<TM, TN, kEpiBias>(g, g.out, acc, bias, row0, col0, lane); break;
-            case kEpiBiasGelu: store_wave<TM, TN, kEpiBiasGelu>(g, g.out, acc, bias, row0, col0, lane); break;
-            case kEpiGatedResidual: store_wave<TM, TN, kEpiGatedResidual>(g, g.out, acc, bias, row0, col0, lane, xpre); break;
+            case kEpiBias: store_wave<TM, TN, kEpiBias, kScalarBias>(g, g.out, acc, bias, row0, col0, lane); break;
+            case kEpiBiasGelu: store_wave<TM, TN, kEpiBiasGelu, kScalarBias>(g, g.out, acc, bias, row0, col0, lane); break;
+            case kEpiGatedResidual: store_wave<TM, TN, kEpiGatedResidual, kScalarBias>(g, g.out, acc, bias, row0, col0, lane, xpre); break;
             case kEpiPartial:                                // the partial sums of a k part, or a plain fp32 output
-                store_wave<TM, TN, kEpiPartial>(g, split ? g.splitk_partials + (size_t)ks * g.M * g.N : reinterpret_cast<float*>(g.out), acc,
+                store_wave<TM, TN, kEpiPartial, kScalarBias>(g, split ? g.splitk_partials + (size_t)ks * g.M * g.N : reinterpret_cast<float*>(g.out), acc,
                                                 bias, row0, col0, lane);
                 break;
-            default: store_wave<TM, TN, kEpiResidual>(g, g.out, acc, bias, row0, col0, lane, xpre); break;
+            default: store_wave<TM, TN, kEpiResidual, kScalarBias>(g, g.out, acc, bias, row0, col0, lane, xpre); break;
         }
         if (!more) break;
 #pragma unroll
