@@ -33,7 +33,8 @@ def f64(t):
 
 # ------------------------------------------------------------------------------------------ GEMM
 GEMM_CASES = [
-    # M, N, K, epilogue, tile override ("tm,tn[,pf[,parts of k]]" register-staged kernel, "d<id>" direct-load kernel) or None
+    # M, N, K, epilogue, tile override ("tm,tn[,pf[,parts of k]]" register-staged kernel, "d<id>[,parts of k]" a tile of the
+    # direct-load kernel) or None
     (128, 128, 64, 0, None),
     (1, 128, 64, 0, None),                 # a single row
     (200, 384, 192, 0, "1,3"),             # ragged M, N tile of 96
@@ -49,41 +50,41 @@ GEMM_CASES = [
     (1024, 2048, 512, 1, None),            # tiny workload FFN-1
     (1024, 4608, 1536, 0, None),           # 1.3B QKV
     (1024, 1536, 8960, 2, None),           # 1.3B FFN-2
-    (1024, 15360, 5120, 0, None),          # 14B QKV: the planner picks the direct-load kernel
-    (1000, 1536, 512, 0, "d1"),            # direct-load kernel, 256 x 256 tiles, ragged M
-    (300, 640, 192, 3, "d2"),              # direct-load kernel, N not a multiple of the tile, 3 k tiles
+    (1024, 15360, 5120, 0, None),          # 14B QKV: 240 tiles of 256 x 256
+    (1000, 1536, 512, 0, "d1"),            # 256 x 256, ragged M
+    (300, 640, 192, 3, "d2"),              # 192 x 256, N not a multiple of the tile, 3 k tiles
     (256, 256, 64, 2, "d2"),               # a single k tile
-    (520, 2048, 1024, 1, "d3"),            # 128 x 256 tiles, three LDS stages, GELU
-    (128, 512, 512, 2, "d4"),              # 256 x 128 tiles, a single ragged M tile
-    (260, 384, 128, 0, "d3"),              # two k tiles in a three-stage ring
-    (1000, 1536, 512, 1, "d5"),            # ring of four k32 stages, GELU, ragged M
-    (300, 640, 192, 2, "d6"),              # ring variant, N not a multiple of the tile, 6 k tiles
-    (256, 256, 64, 3, "d6"),               # two k tiles: fewer than the ring holds
-    (130, 256, 32 * 2, 0, "d5"),           # K = 64
-    (520, 768, 1024, 2, "d6,3"),           # ring with three k parts (fp32 partial sums + reduce), gated residual
-    (1000, 512, 640, 1, "d5,2"),           # ring, two k parts, GELU in the reduce pass, ragged M
-    (1000, 1536, 512, 1, "d17"),           # two wave groups half a step apart, half stages of 64 k; GELU, ragged M
-    (300, 640, 192, 2, "d18"),             # 3 k tiles, N not a multiple of the tile
+    (520, 2048, 1024, 1, "d3"),            # 256 x 192, one wave per SIMD, GELU
+    (128, 512, 512, 2, "d4"),              # 256 x 160, a single ragged M tile
+    (260, 384, 128, 0, "d3"),              # two k tiles in rings of two and three stages
+    (1000, 1536, 512, 1, "d5"),            # 256 x 128, GELU, ragged M
+    (300, 640, 192, 2, "d6"),              # 192 x 192, N not a multiple of the tile, 3 k tiles
+    (256, 256, 64, 3, "d6"),               # one k tile: fewer than the rings hold
+    (130, 256, 32 * 2, 0, "d5"),           # the same, a single ragged M tile
+    (520, 768, 1024, 2, "d6,3"),           # three k parts (fp32 partial sums + reduce), gated residual
+    (1000, 512, 640, 1, "d5,2"),           # two k parts, GELU in the reduce pass, ragged M
+    (1000, 1536, 512, 1, "d17"),           # 64 x 32, rings of six stages; GELU, ragged M
+    (300, 640, 192, 2, "d18"),             # 32 x 32, rings of eight stages, 3 k tiles
     (256, 256, 64, 3, "d18"),              # one k tile
     (130, 256, 128, 0, "d17"),             # two k tiles
     (520, 768, 1024, 2, "d18,3"),          # three k parts
-    (2048, 2048, 2048, 0, "d18"),          # 64 full tiles, 32 k tiles
-    (1024, 1024, 320, 0, "d17"),           # five k tiles: one turn of the slot ring
-    (1024, 1024, 384, 0, "d18"),           # six k tiles
+    (2048, 2048, 2048, 0, "d18"),          # 4096 tiles on 512 workgroups, 32 k tiles
+    (1024, 1024, 320, 0, "d17"),           # five k tiles: one fewer than the rings hold
+    (1024, 1024, 384, 0, "d18"),           # six k tiles of eight stages
     (300, 512, 1024, 2, "1,4,2,2"),        # k split in two parts + reduce kernel, gated residual, ragged M
     (260, 256, 2048, 3, "2,8,2,4"),        # four parts, residual
     (1024, 1536, 1536, 1, "1,5,2,3"),      # three parts, GELU in the reduce kernel, ragged N tile
     (130, 384, 192, 0, "1,3,2,8"),         # more parts asked than k allows: clamped to one part per two k tiles
-    (300, 384, 320, 0, "d7"),              # small tiles of the direct-load kernel: 128 x 64, three stages, 5 k tiles
-    (1024, 1536, 1536, 2, "d8"),           # 128 x 64, four stages: the C x C projections of the 1.3B block
-    (200, 640, 192, 1, "d9"),              # 128 x 64 with eight waves of 32 x 32, 3 k tiles in a four-stage ring
-    (260, 512, 448, 3, "d10"),             # 64 x 128
-    (520, 768, 1024, 2, "d11,2"),          # 128 x 128 four waves, two k parts
-    (333, 640, 512, 1, "d12"),             # 128 x 128 eight waves, ragged M and N
-    (1024, 8960, 1536, 1, "d13"),          # 128 x 160 two stages: FFN-1 of the 1.3B block
-    (300, 1280, 256, 0, "d14"),            # 128 x 160 three stages
-    (130, 768, 640, 2, "d15,3"),           # 128 x 192, three k parts
-    (1000, 1536, 512, 1, "d16"),           # 128 x 192 with eight waves of 32 x 96
+    (300, 384, 320, 0, "d7"),              # 128 x 192, 5 k tiles
+    (1024, 1536, 1536, 2, "d8"),           # 128 x 160: the C x C projections of the 1.3B block
+    (200, 640, 192, 1, "d9"),              # 128 x 128, 3 k tiles in rings of four and five stages
+    (260, 512, 448, 3, "d10"),             # 128 x 96
+    (520, 768, 1024, 2, "d11,2"),          # 192 x 128, two k parts
+    (333, 640, 512, 1, "d12"),             # 128 x 192 on four waves, two workgroups per unit; ragged M and N
+    (1024, 8960, 1536, 1, "d13"),          # 128 x 64: FFN-1 of the 1.3B block, 1120 tiles
+    (300, 1280, 256, 0, "d14"),            # 64 x 128
+    (130, 768, 640, 2, "d15,3"),           # 64 x 96, three k parts
+    (1000, 1536, 512, 1, "d16"),           # 64 x 64
     (1024, 1536, 8960, 2, "d15,4"),        # FFN-2 of the 1.3B block, four k parts
 ]
 
@@ -133,6 +134,62 @@ def test_gemm_matches_oracle(M, N, K, epi, tile):
 ])
 def test_gemm_every_tile_at_its_edges(M, N, K, epi, tile):
     test_gemm_matches_oracle(M, N, K, epi, "d%d" % tile)
+
+
+@pytest.mark.parametrize("tile", range(1, 19))
+@pytest.mark.parametrize("epi,biased", [(0, True), (0, False), (1, False), (2, True), (2, False), (3, False)])
+def test_gemm_several_tiles_per_workgroup(epi, biased, tile):
+    """More output tiles than workgroups for every tile size, ten k tiles (more than any ring holds): the next tile's loads
+    run under the stores.  Without a bias no load marks that they have landed, and the stores are waited for with them; bf16
+    and fp32 stores; gates of 100 rows, so that the gate changes inside a wave's tile."""
+    M, N, K, rows_per_gate = 5200, 3328, 640, 100
+    g = torch.Generator(device=DEV).manual_seed(40 + epi)
+    rand = lambda *shape: torch.randn(*shape, generator=g, device=DEV)
+    a, w = rand(M, K).to(torch.bfloat16), (rand(N, K) * 0.05).to(torch.bfloat16)
+    bias = rand(N) if biased else None
+    gate_a, gate_b, x0 = rand(N), rand(M // rows_per_gate, N), rand(M, N)
+    acc = a.double() @ w.double().t()
+    if biased:
+        acc += bias.double()
+    if epi == 1:
+        acc = torch.nn.functional.gelu(acc, approximate="tanh")
+    elif epi == 2:
+        acc = x0 + acc * (gate_a + gate_b.repeat_interleave(rows_per_gate, 0)).double()
+    elif epi == 3:
+        acc = x0 + acc
+    binding.tuning_set("gemm_tile", "d%d" % tile)
+    try:
+        for _ in range(2):
+            out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV) if epi < 2 else x0.clone()
+            binding.gemm_bf16(a, w, bias, out, epi, gate_a, gate_b, N, rows_per_gate)
+            torch.cuda.synchronize()
+            err = ((out.double() - acc).abs().max() / acc.abs().max()).item()
+            assert err < (1e-2 if epi < 2 else 1e-4), err
+    finally:
+        binding.tuning_set("gemm_tile", None)
+
+
+@pytest.mark.parametrize("heads,tokens", [(26, 77), (40, 128), (40, 77), (12, 512), (4, 16)])
+def test_text_keys_and_values_in_one_launch(heads, tokens):
+    """The two products of a prompt in one launch: the first three shapes would be split in k with scratch.  Keys (after their
+    RMSNorm) and values against 64 bits."""
+    C = 128 * heads
+    g = torch.Generator(device=DEV).manual_seed(heads)
+    rand = lambda *shape: torch.randn(*shape, generator=g, device=DEV)
+    t = {"W_ck": (rand(C, C) * 0.02).to(torch.bfloat16), "W_cv": (rand(C, C) * 0.02).to(torch.bfloat16), "b_ck": rand(C) * 0.02,
+         "b_cv": rand(C) * 0.02, "g_ck": 1.0 + 0.1 * rand(C)}
+    ctx = rand(tokens, C).to(torch.bfloat16)
+    cfg = binding.model_cfg(C, heads, 4 * C, 2, 2, tokens, 1)
+    cap = (tokens + 63) // 64 * 64
+    kt, vtt = (torch.zeros(binding.text_kv_bytes(cfg), dtype=torch.uint8, device=DEV) for _ in range(2))
+    binding.text_kv_prepare(cfg, binding.block_weights(t), ctx, kt, vtt,
+                            torch.empty(binding.text_kv_workspace_bytes(cfg), dtype=torch.uint8, device=DEV))
+    torch.cuda.synchronize()
+    K = kt.view(torch.bfloat16).view(heads, cap, 128)[:, :tokens].permute(1, 0, 2).reshape(tokens, C)
+    V = vtt.view(torch.bfloat16).view(heads, 128, cap)[:, :, binding.vt_columns(cap).to(DEV)][:, :, :tokens].permute(2, 0, 1).reshape(tokens, C)
+    k, v = (ctx.double() @ t["W_" + n].double().t() + t["b_" + n].double() for n in ("ck", "cv"))
+    k = k / (k.pow(2).mean(1, keepdim=True) + 1e-6).sqrt() * t["g_ck"].double()
+    assert max_rel_err(f64(K), f64(k)) < 1e-2 and max_rel_err(f64(V), f64(v)) < 1e-2
 
 
 @pytest.mark.parametrize("tile", [None, "1,4"] + ["d%d" % i for i in range(1, 19)])

@@ -154,8 +154,8 @@ def test_stream_batch_handle_and_planner_hooks_on_the_host(lib):
     assert lib.sdv2_stream_batch_reset(h) == binding.OK
     assert lib.sdv2_stream_batch_destroy(h) == binding.OK
     assert lib.sdv2_denoise_graph_state_bytes() >= 8 * (8 + 4 + 4 + 4)
-    # the planner's kernel names: large shapes take the 256 x 256 alternating kernel, the single-chunk attention of the 1.3B
-    # block the key-split form, a capacity that is no multiple of 128 the one-key-stream form
+    # the planner's kernel names: every shape within 32-bit offsets takes the direct-load kernel, the single-chunk attention
+    # of the 1.3B block the key-split form, a capacity that is no multiple of 128 the one-key-stream form
     assert binding.prof_kernel_name("gemm", 4, 4680, 13824, 5120, 1).startswith("gemm_alt64_kernel<")
     # an activation matrix of 4 GiB or more is beyond the 32-bit lane offsets of the direct-load kernels
     assert binding.prof_kernel_name("gemm", 8, 40000, 8192, 8192, 0).startswith("gemm_kernel<")
