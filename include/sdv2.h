@@ -512,7 +512,8 @@ int32_t sdv2_stream_batch_latents_step(sdv2_stream_batch* sb, const sdv2_model_c
  *   workspace_dev (device, 16-byte aligned; may be NULL with workspace_bytes 0): scratch that lets a shape with few
  *   output tiles and a long k split the k range over several workgroups per tile (a second small kernel adds the parts in
  *   k order, so the result does not depend on scheduling).  A workspace smaller than
- *   sdv2_gemm_workspace_bytes(M, N, K, epilogue) is accepted: the launch then does not split.
+ *   sdv2_gemm_workspace_bytes(M, N, K, epilogue) is accepted: the launch then makes the parts that fit, or does not split.
+ *   a and w may start at any bf16; 16-byte aligned ones are faster.
  *
  * sdv2_attention_bf16: o[b] = softmax(q[b] K[b]^T / sqrt(128)) V[b] over kv_len[b] slots.
  *   q: bf16 [B, L, C]; k[b]: bf16 [H][cap][128]; vt[b]: bf16 [H][128][cap] in the cache's column order (cap multiple of 64,

@@ -4,7 +4,7 @@
 // and FFN projections), plus the cross-attention projections the cost model leaves out.
 //
 // Two kernels on the matrix cores.  gemm_alt64_kernel (16x16x32 MFMAs, direct global -> LDS loads, persistent) serves
-// every shape whose operands, and 128 rows of the output, are below 4 GiB: it uses 32-bit byte offsets per lane.  gemm_kernel (32x32x16
+// every shape whose operands (16-byte aligned), and 128 rows of the output, are below 4 GiB: it uses 32-bit byte offsets per lane.  gemm_kernel (32x32x16
 // MFMAs, tiles staged through registers, 64-bit addresses) serves the larger ones.  Both operands are K-contiguous
 // (activations [M, K], weights [N, K]), so fragments are plain 16-byte pieces of rows.
 //   Split-K (few output tiles, long k: FFN-2 of one chunk) is two launches: the parts store fp32 partial sums, a second
@@ -797,7 +797,13 @@ bool fits_32bit_offsets(int M, int N, int K) {
            (unsigned long long)(M < 128 ? M : 128) * N * 4 <= kLimit;
 }
 
-// Shapes beyond that: the time of the busiest compute unit for the register-staged kernel; one k tile of a
+// Its loads go from global memory to LDS in pieces of 16 bytes, which have to start at multiples of 16; the register-staged
+// kernel's are ordinary vector loads, good for any address of a bf16.
+bool operands_aligned(const GemmArgs& g) {
+    return ((reinterpret_cast<uintptr_t>(g.a) | reinterpret_cast<uintptr_t>(g.w) | reinterpret_cast<uintptr_t>(g.w2)) & 15) == 0;
+}
+
+// What it does not serve: the time of the busiest compute unit for the register-staged kernel; one k tile of a
 // workgroup costs a fixed part (~0.25 us alone, half of it when a second workgroup fills the bubbles) plus ~21 ns per
 // MFMA a wave issues (fitted to a sweep); small tiles fit two workgroups per unit.
 TilePlan plan_register_staged(int M, int N, int K) {
@@ -930,7 +936,7 @@ const TileCost kCost[kTileConfigs + 1] = {
 };
 
 hipError_t launch_tile_config(const GemmArgs& g, int id, int splitk, hipStream_t s) {
-    if (!fits_32bit_offsets(g.M, g.N, g.K)) return hipErrorInvalidValue;     // only reachable through the tuning override
+    if (!fits_32bit_offsets(g.M, g.N, g.K) || !operands_aligned(g)) return hipErrorInvalidValue;     // only reachable through the tuning override
     switch (id) {
 #define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit, ...) \
     case id: return launch_alt64<wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit>(g, splitk, s);
@@ -1212,6 +1218,15 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(GemmArgs g, int s
 }
 }  // namespace
 
+// The plan of a call: two products of one launch (w2) make no split.
+static TilePlan plan_of(const GemmArgs& g) {
+    TilePlan p = !operands_aligned(g)  ? plan_register_staged(g.M, g.N, g.K)
+                 : g.w2 != nullptr     ? plan_tiles(g.M, g.N, g.K, g.epilogue, 0, 2)
+                                       : plan_tiles(g.M, g.N, g.K, g.epilogue, scratch_bytes(g));
+    tile_override(&p);
+    return p;
+}
+
 // Parts of k the plan can really use for this problem and scratch (1: no split).
 static int usable_splitk(const GemmArgs& g, const TilePlan& p) {
     if (p.splitk <= 1 || g.splitk_partials == nullptr) return 1;
@@ -1226,10 +1241,8 @@ static int usable_splitk(const GemmArgs& g, const TilePlan& p) {
 // when the plan does not split).  The benchmark times the two parts separately.
 static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln_done, hipStream_t s, int part = 0) {
     if (g.w2 != nullptr) {
-        // both products in one launch, without a k split
-        TilePlan p2 = plan_tiles(g.M, g.N, g.K, g.epilogue, 0, 2);
-        tile_override(&p2);
-        if (p2.dma && fits_32bit_offsets(g.M, g.N, g.K)) return launch_tile_config(g, p2.dma, 2, s);
+        const TilePlan p2 = plan_of(g);
+        if (p2.dma) return launch_tile_config(g, p2.dma, 2, s);
         GemmArgs one = g;
         one.w2 = nullptr;
         const hipError_t e1 = launch_gemm_impl(one, nullptr, nullptr, s);
@@ -1239,8 +1252,7 @@ static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln
         one.out = g.out2;
         return launch_gemm_impl(one, nullptr, nullptr, s);
     }
-    TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue, scratch_bytes(g));
-    tile_override(&p);
+    const TilePlan p = plan_of(g);
     const int splitk = usable_splitk(g, p);
     hipError_t e = hipSuccess;
     if (part != 2) {
@@ -1298,9 +1310,7 @@ hipError_t launch_gemm_then_layernorm(const GemmArgs& g, const LnArgs& ln, bool*
 hipError_t launch_gemm_part(const GemmArgs& g, hipStream_t s, int part) { return launch_gemm_impl(g, nullptr, nullptr, s, part); }
 
 bool gemm_splits_k(const GemmArgs& g) {
-    TilePlan p = plan_tiles(g.M, g.N, g.K, g.epilogue, scratch_bytes(g));
-    tile_override(&p);
-    return usable_splitk(g, p) > 1;
+    return usable_splitk(g, plan_of(g)) > 1;
 }
 
 size_t gemm_splitk_floats_bound(int M, int N, int K) {

@@ -245,6 +245,45 @@ def test_gemm_of_rows_so_wide_that_a_tile_spans_4_gib():
         assert max_rel_err(f64(out[:, c0:c0 + 8192]), f64(want)) < 1e-4, c0
 
 
+@pytest.mark.parametrize("a0,w0", [(0, 2), (1, 0), (2, 1), (4, 4)])
+@pytest.mark.parametrize("M,N,K,epi", [(257, 384, 128, 0), (1024, 1536, 1536, 3)])
+def test_gemm_of_operands_at_any_address(M, N, K, epi, a0, w0):
+    """Operands that start 2 to 8 bytes past a multiple of 16: loads straight into LDS need the multiple, so such a call goes
+    to the kernel that loads into registers; a forced tile of the other kernel is refused."""
+    g = torch.Generator(device=DEV).manual_seed(50)
+    rand = lambda n, scale: (torch.randn(n, generator=g, device=DEV) * scale).to(torch.bfloat16)
+    a, w = rand(M * K + 8, 1.0)[a0:a0 + M * K].view(M, K), rand(N * K + 8, 0.05)[w0:w0 + N * K].view(N, K)
+    assert (a.data_ptr() | w.data_ptr()) % 16 != 0
+    out = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=DEV) if epi == 0 else torch.zeros(M, N, device=DEV)
+    binding.tuning_set("gemm_tile", "d5")
+    try:
+        with pytest.raises(binding.Sdv2Error):
+            binding.gemm_bf16(a, w, None, out, epi)
+    finally:
+        binding.tuning_set("gemm_tile", None)
+    binding.gemm_bf16(a, w, None, out, epi)
+    torch.cuda.synchronize()
+    assert max_rel_err(f64(out), f64(a.double() @ w.double().t())) < (1e-2 if epi < 2 else 1e-4)
+
+
+@pytest.mark.parametrize("offset", [2, 4, 6])
+def test_append_of_rows_at_any_address(offset):
+    P, H = 6, 5
+    ccfg = binding.cache_cfg(1, 1, H, P, P, 2 * P)
+    storage = torch.full((binding.kv_cache_bytes(ccfg),), 0xFF, dtype=torch.uint8, device=DEV)
+    h = binding.kv_cache_init(ccfg, storage)
+    n = P * H * 128
+    k, v = (bf16_randn((n + 8,), s).to(DEV)[offset:offset + n].view(P, H * 128) for s in (1, 2))
+    binding.kv_cache_append_evict(h, 0, 0, k, v)
+    torch.cuda.synchronize()
+    _, _, _, cap = binding.kv_cache_device_ptrs(h, 0, 0)
+    K = storage[:H * cap * 256].view(torch.bfloat16).view(H, cap, 128)[:, :P].permute(1, 0, 2).reshape(P, H * 128)
+    V = storage[H * cap * 256:2 * H * cap * 256].view(torch.bfloat16).view(H, 128, cap)
+    V = V[:, :, binding.vt_columns(cap).to(DEV)][:, :, :P].permute(2, 0, 1).reshape(P, H * 128)
+    assert torch.equal(K, k) and torch.equal(V, v)
+    binding.kv_cache_destroy(h)
+
+
 def test_gemm_full_size_batched_480p_shape_sampled_rows():
     """FFN-1 of the 14B-shaped block on 4 streams x 4680 tokens (M 18720, N 13824, K 5120: the direct-load kernel,
     74 x 54 tiles, ragged last M tile): whole output finite, 48 sampled rows against the oracle."""
