@@ -4,9 +4,9 @@
 // and FFN projections), plus the cross-attention projections the cost model leaves out.
 //
 // Two kernels on the matrix cores.  gemm_alt64_kernel (16x16x32 MFMAs, direct global -> LDS loads, persistent) serves
-// every shape whose operands (16-byte aligned), and 128 rows of the output, are below 4 GiB: it uses 32-bit byte offsets per lane.  gemm_kernel (32x32x16
-// MFMAs, tiles staged through registers, 64-bit addresses) serves the larger ones.  Both operands are K-contiguous
-// (activations [M, K], weights [N, K]), so fragments are plain 16-byte pieces of rows.
+// every shape whose operands (16-byte aligned), and 128 rows of the output, are below 4 GiB: it uses 32-bit byte offsets
+// per lane.  gemm_kernel (32x32x16 MFMAs, tiles staged through registers, 64-bit addresses) serves the others.  Both
+// operands are K-contiguous (activations [M, K], weights [N, K]), so fragments are plain 16-byte pieces of rows.
 //   Split-K (few output tiles, long k: FFN-2 of one chunk) is two launches: the parts store fp32 partial sums, a second
 // kernel adds them in k order and applies the epilogue, and the LayerNorm that follows if there is one.  fp32 atomics
 // on the output cost ~40 us per 1.5 M elements here, and a last-arriver reduction inside one launch needs device-scope
@@ -339,8 +339,9 @@ __global__ __launch_bounds__(256, ((TM * TN <= 5 && BK == 64 && PF == 2) ? 2 : 1
 // tile: 24 fragment reads per 64 MFMAs of a k tile of 64), whole 128-byte lines per load, and tiles as large as the
 // shape allows (a 1024-row product streams its operands through the L2s at up to 19 TB/s: 128 x 160 tiles on 256
 // units, 62 us for 1024 x 5120 x 5120 where 128 x 160 register-staged tiles took 67).
-//   Main loop.  A k tile is 64 wide and holds two MFMA k steps ("halves").  While the MFMAs of one half are issued, the
-// fragments of the other half are read from LDS, and (second half) the tile loads go out, one every few MFMAs:
+//   Main loop.  A k tile is 64 wide and holds two MFMA k steps ("halves") that take turns, whence the name.  While the
+// MFMAs of one half are issued, the fragments of the other half are read from LDS, and (second half) the tile loads go out,
+// one every few MFMAs:
 //     half 0 of tile t | wait: tile t + 1 has landed, every fragment of tile t is in registers | barrier |
 //     half 1 of tile t, fragments of half 0 of tile t + 1, loads of tile t + stages into the stage tile t has left
 // One barrier per k tile, no fragment latency behind it.  The order inside a half is the program order, held by
@@ -356,6 +357,7 @@ __global__ __launch_bounds__(256, ((TM * TN <= 5 && BK == 64 && PF == 2) ? 2 : 1
 //   Epilogue from registers: the operands are swapped (W rows are the MFMA's rows), so a lane holds four consecutive
 // columns of one row; two bf16 blocks are interleaved with v_permlane16_swap into 16-byte stores, fp32 pieces are 16
 // bytes as they are.  No LDS round trip, so the ring can keep filling.
+//   The bias joins the finished sum (see store_tile); it is the wave's own 64 to 128 columns, the same for sixteen lanes.
 //   XCD-aware order: an XCD (one L2) owns a contiguous range of tiles, ordered in groups of GROUP_M tile rows that share
 // weight tiles.
 //   Tried and dropped: W fragments straight from global memory into registers, A through LDS (16 rows of 64 bytes per
@@ -960,10 +962,10 @@ float tile_cost(int id, int M, int N, float k_tiles, int parts) {
 // The planner: the configuration and number of k parts with the smallest estimate among those that the call can run.  A k
 // split pays for a second pass (4 us and its bytes at 3.9 TB/s); a residual epilogue gets back the LayerNorm that this pass
 // forms (5 us).  Parts of at least 512, as many as the call's scratch holds (a tile picked for a split that is then not made
-// is up to 1.8 times slower than the best whole one: 77 text tokens of 40 heads), and at most 48 MiB of partial sums (long sums: below).  Up to 32 MiB they fit the entry point without a workspace; more than
-// that has to be 1.5 % better by the estimate, which is careful: measured with cold weights, best within 32 MiB against
-// the plan with 32 to 48 MiB: 1024 x 5120 x 13824 146 -> 131 us, 1024 x 5120 x 20480 213 -> 188, 1024 x 3072 x 12288
-// 87 -> 77, 1560 x 3072 x 12288 124 -> 120, 512 x 5120 x 13824 81 -> 78.
+// is up to 1.8 times slower than the best whole one: 77 text tokens of 40 heads, 64 us a layer instead of 39), and at most
+// 48 MiB of partial sums (long sums: below).  Up to 32 MiB they fit the entry point without a workspace; more than that has to
+// be 1.5 % better by the estimate, which is careful: measured with cold weights, best within 32 MiB against the plan with 32
+// to 48 MiB: 1024 x 3072 x 12288 87 -> 77 us, 1560 x 3072 x 12288 124 -> 120.
 constexpr size_t kMaxPartialBytes = (size_t)48 << 20, kSmallPartialBytes = (size_t)32 << 20;
 constexpr int kMaxParts = 6;
 // Sums of more than 12 288 products take at least three parts where the scratch and 64 MiB hold them: the error of a sum
