@@ -42,6 +42,18 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v + dpp_f<0xB1>(v);   // quad_perm [1, 0, 3, 2]
 }
 
+// Maximum over the wavefront, in every lane, by the same exchanges (fmaxf: a NaN gives way to a number).
+__device__ __forceinline__ float wave_max(float v) {
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    v = fmaxf(v, dpp_f<0x128>(v));
+    v = fmaxf(v, dpp_f<0x124>(v));
+    v = fmaxf(v, dpp_f<0x4E>(v));
+    return fmaxf(v, dpp_f<0xB1>(v));
+}
+
 __device__ __forceinline__ float gelu_tanh_f(float x) {
     // 0.5 x (1 + tanh(u)) = x / (1 + exp(-2u)),  u = sqrt(2/pi) (x + 0.044715 x^3).  The exponent is formed
     // directly in base 2 and the quotient is x times the hardware reciprocal (1 ulp): the caller rounds the

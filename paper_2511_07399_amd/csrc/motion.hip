@@ -9,37 +9,47 @@
 namespace sdv2 {
 namespace {
 
-// d_t from the partial sums (added in double, fixed butterfly), then the ring of the last k + 1 values, the window
-// maximum, the clip and the moving average, for t = 0 .. T-1 in order; one wave.
-__device__ __forceinline__ void motion_recurrence(const MotionArgs& a, int n_blocks, int lane) {
+// One workgroup of four waves: d_t from the partial sums (added in double, fixed butterfly), a wave per frame, then on one
+// wave the ring of the last k + 1 values, the window maximum, the clip and the moving average, for t = 0 .. T-1 in order.
+// The partial sums of all frames and the ring are fetched at once: fetched frame by frame, sixteen frames are sixteen trips
+// to memory one after the other (31 us a call; 24 with a launch of its own for this part, 22 like this).
+__device__ __forceinline__ void motion_recurrence(const MotionArgs& a, int n_blocks, int lane, int wave) {
+    __shared__ float ds[kMotionMaxFrames];
+    __shared__ float window[kMotionMaxK + 1];
+    float* const ring = a.state + kMotionHeaderFloats;
+    const int ring_len = a.k + 1;
     float s = a.state[0];
     int count = __float_as_int(a.state[1]);
-    float* ring = a.state + kMotionHeaderFloats;
-    const int ring_len = a.k + 1;
-    for (int t = 0; t < a.T; ++t) {
+    for (int i = threadIdx.x; i < ring_len; i += 256) window[i] = i < count ? ring[i] : 0.0f;
+    for (int t = wave; t < a.T; t += 4) {
         double sum = 0.0;
         for (int b = lane; b < n_blocks; b += kWave)
             sum += (double)__hip_atomic_load(a.partial + (size_t)t * n_blocks + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
-        const float d = (float)sqrt(sum / (double)a.n);
+        if (lane == 0) ds[t] = (float)sqrt(sum / (double)a.n);
+    }
+    __syncthreads();
+    if (wave != 0) return;
+    for (int t = 0; t < a.T; ++t) {
+        const float d = ds[t];
         // the window: what the ring holds besides the entry that d replaces, and d
         const int have = count < ring_len ? count : ring_len, pos = count % ring_len;
         float mx = d;
         for (int i = lane; i < have; i += kWave)
-            if (i != pos) mx = fmaxf(mx, ring[i]);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, kWave));
+            if (i != pos) mx = fmaxf(mx, window[i]);
+        mx = wave_max(mx);
         ++count;
         const float dhat = fminf(fmaxf(mx / a.sigma, 0.0f), 1.0f);
         s = a.lambda * (a.s_max - (a.s_max - a.s_min) * dhat) + (1.0f - a.lambda) * s;
         if (lane == 0) {
+            window[pos] = d;
             ring[pos] = d;
             a.d_out[t] = d;
             a.dhat_out[t] = dhat;
             a.s_out[t] = s;
         }
-        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");       // ring[pos] before the next frame's reads
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");       // window[pos] before the next frame's reads
     }
     if (lane == 0) {
         a.state[0] = s;
@@ -89,7 +99,7 @@ __global__ __launch_bounds__(256) void motion_update_kernel(MotionArgs a) {
         if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (last && threadIdx.x < kWave) motion_recurrence(a, gridDim.x, threadIdx.x);
+    if (last) motion_recurrence(a, gridDim.x, threadIdx.x & 63, threadIdx.x >> 6);
 }
 
 __global__ void motion_init_kernel(float* state, int n_floats, float s_init) {

@@ -92,6 +92,19 @@ def test_static_stream_and_spike():
     assert list(np.round(got[:, 1], 6)) == [0, 0, 0, 0, 0, 0.5, 0.5, 0.5, 0, 0, 0, 0]
 
 
+@pytest.mark.parametrize("k,chunks", [(0, [16, 16]), (8, [16, 5, 16]), (63, [16] * 5), (64, [16] * 5), (100, [16] * 8), (1023, [7, 16])])
+def test_sixteen_frames_a_call_and_long_windows(k, chunks):
+    """The most frames a call takes, windows below, at and above a wavefront's width, rings that wrap inside a call; one jump
+    early in the stream that a long window holds on to and a short one forgets."""
+    shape = (3, 5, 7)
+    gen = torch.Generator().manual_seed(k)
+    frames = [torch.randn(shape, generator=gen)]
+    for t in range(1, sum(chunks)):
+        frames.append(frames[-1] + (1.5 if t == 4 else 0.1 + 0.3 * (t % 7 == 0)) * torch.randn(shape, generator=gen))
+    got, want = run_stream(shape, chunks, k=k, sigma=2.0, lam=0.3, s_min=0.1, s_max=0.9, s_init=0.5, frame_fn=lambda t: frames[t])
+    check(got, want)
+
+
 def test_motion_call_validation():
     binding.load_library()
     good = binding.motion_cfg(3, 1.0, 0.5, 0.1, 0.9, 0.5)
