@@ -53,12 +53,18 @@ __global__ __launch_bounds__(kSimBlock) void sink_similarity_partial_kernel(Sink
                 }
             }
         } else {
-            for (int j0 = lane; j0 < a.P; j0 += 4 * kWave) {
+            // two bytes at a time, sixteen of both frames in flight
+            for (int j0 = lane; j0 < a.P; j0 += 16 * kWave) {
+                bf16 x[16], y[16];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int j = j0 + kWave * e;
-                    if (j < a.P) add(e, (float)v[vt_column(a.src0 + j)], (float)v[vt_column(sink0 + j)]);
+                for (int u = 0; u < 16; ++u) {
+                    const int j = min(j0 + kWave * u, a.P - 1);
+                    x[u] = v[vt_column(a.src0 + j)];
+                    y[u] = v[vt_column(sink0 + j)];
                 }
+#pragma unroll
+                for (int u = 0; u < 16; ++u)
+                    if (j0 + kWave * u < a.P) add(u & 3, (float)x[u], (float)y[u]);
             }
         }
     }
