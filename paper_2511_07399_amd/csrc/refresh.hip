@@ -5,6 +5,8 @@
 #include "common.h"
 #include "refresh_ranges.h"
 
+#include <type_traits>
+
 namespace sdv2 {
 namespace {
 
@@ -53,19 +55,24 @@ __global__ __launch_bounds__(kSimBlock) void sink_similarity_partial_kernel(Sink
                 }
             }
         } else {
-            // two bytes at a time, sixteen of both frames in flight
-            for (int j0 = lane; j0 < a.P; j0 += 16 * kWave) {
-                bf16 x[16], y[16];
+            // two bytes at a time, eight or four of both frames in flight (unconditional: under a condition they go out one
+            // by one, past the end the last one again)
+            auto pieces = [&](auto count, int c0) {
+                constexpr int n = decltype(count)::value;
+                bf16 x[n], y[n];
 #pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int j = min(j0 + kWave * u, a.P - 1);
+                for (int u = 0; u < n; ++u) {
+                    const int j = min(c0 + kWave * u + lane, a.P - 1);
                     x[u] = v[vt_column(a.src0 + j)];
                     y[u] = v[vt_column(sink0 + j)];
                 }
 #pragma unroll
-                for (int u = 0; u < 16; ++u)
-                    if (j0 + kWave * u < a.P) add(u & 3, (float)x[u], (float)y[u]);
-            }
+                for (int u = 0; u < n; ++u)
+                    if (c0 + kWave * u + lane < a.P) add(u & 3, (float)x[u], (float)y[u]);
+            };
+            int c0 = 0;
+            for (; c0 + 8 * kWave <= a.P; c0 += 8 * kWave) pieces(std::integral_constant<int, 8>{}, c0);
+            for (; c0 < a.P; c0 += 4 * kWave) pieces(std::integral_constant<int, 4>{}, c0);
         }
     }
     __shared__ float red[3][kSimBlock / kWave];
@@ -144,7 +151,14 @@ __global__ __launch_bounds__(256) void refresh_sink_kernel(SinkCopyArgs a, int v
                 if (q0 + kWave * u < n) *reinterpret_cast<bf16x4*>(v + vt_column(a.dst0 + 4 * (q0 + kWave * u))) = x[u];
         }
     } else {
-        for (int j = lane; j < a.P; j += kWave) v[vt_column(a.dst0 + j)] = v[vt_column(a.src0 + j)];
+        for (int c0 = lane; c0 < a.P; c0 += 8 * kWave) {
+            bf16 x[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = v[vt_column(a.src0 + min(c0 + kWave * u, a.P - 1))];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (c0 + kWave * u < a.P) v[vt_column(a.dst0 + c0 + kWave * u)] = x[u];
+        }
     }
     if (blockIdx.x == 0)
         for (int j = threadIdx.x; j < a.P; j += 256) a.ids[a.dst0 + j] = a.ids[a.src0 + j];
