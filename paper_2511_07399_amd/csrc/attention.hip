@@ -29,6 +29,12 @@
 //   * The exponents' reference point of a query trails its running maximum loosely instead of tracking it: the
 //     steady-state loop forms no row maximum and rescales nothing; a sum of exponentials that leaves the range
 //     sends the wave to a slow path that moves the reference point (it cancels in O / l).
+//   * What a workgroup does before its first tile is a chain of latencies that a launch of a few tiles consists of: the
+//     divisions that number the workgroups are products with the launcher's reciprocals (five in software took 1.5 us), the
+//     arguments come in two batches, the queries pass through LDS (as fragments straight from memory they are 64 loads of
+//     32 pieces of 32 bytes, and the first tiles queue behind them), and the first scores wait for the first K tile alone.
+//     From the start to the first scores 5.6 -> 3.6 us; text cross-attention of the 1.3B chunk 13.0 -> 10.5 us, of the 14B
+//     chunk 25 -> 21 us.  Outputs leave in pieces of 16 bytes.
 //   * Skinny launches (few query tiles x heads) split the key range over several workgroups, which
 //     write normalised partial outputs with their (max, sum); a small kernel merges them.
 #include "common.h"
@@ -84,6 +90,71 @@ __device__ __forceinline__ void load_to_lds_b128(const void* src, void* dst) {
     __builtin_amdgcn_global_load_lds(src, (lds_void_ptr)dst, 16, 0, 0);
 }
 
+// Resident keys of stream b.  Read through the scalar cache: as a vector load it would be waited for together with the queries.
+__device__ __forceinline__ int resident_keys(const AttnArgs& a, int b) {
+    typedef const __attribute__((address_space(4))) int* scalar_int_ptr;
+    if (a.desc != nullptr) return ((scalar_int_ptr) reinterpret_cast<uintptr_t>(a.desc->kv_len))[b];
+    return a.kv_len[b];
+}
+
+// What a workgroup needs of its stream, requested in one batch.
+struct StreamKeys {
+    const bf16 *k, *vt;
+    int cap, kv_len;
+};
+__device__ __forceinline__ StreamKeys stream_keys(const AttnArgs& a, int b) {
+    StreamKeys s;
+    s.k = a.k[b];
+    s.vt = a.vt[b];
+    s.cap = a.cap[b];
+    s.kv_len = resident_keys(a, b);
+    asm volatile("" ::"s"(s.k), "s"(s.vt), "s"(s.cap), "s"(s.kv_len));
+    return s;
+}
+
+// Two groups of four channels of a query as bf16: a lane has channels 4 lh .. + 3 of two blocks of eight; the halves of the
+// wave trade words so that each lane stores eight channels in a row (lanes < 32 the first block, the others the second).
+__device__ __forceinline__ uint4 eight_channels(const bf16x4& lo, const bf16x4& hi) {
+    const uint2 a = __builtin_bit_cast(uint2, lo), b = __builtin_bit_cast(uint2, hi);
+    const auto x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+    return uint4{x[0], y[0], x[1], y[1]};
+}
+
+// Query tile, head and stream / split of a workgroup.  Workgroups are handed to the eight XCDs in turn; they are renumbered
+// so that each XCD (its own L2) works through a contiguous run of (query tile, head, stream / split) triples, query tile
+// fastest: the workgroups that share a head's K and V then sit behind the same L2.
+__device__ __forceinline__ void locate(const AttnArgs& a, int& qt, int& h, int& bz) {
+    // every argument that the first addresses need is requested at once: a scalar load that misses takes 0.2 to 0.5 us
+    const FastDiv by_q_tiles = a.by_q_tiles, by_heads = a.by_heads;
+    const unsigned n_wg = a.n_wg;
+    asm volatile("" ::"s"(a.q), "s"(a.L), "s"(a.H), "s"(a.splits), "s"(a.desc), "s"(n_wg), "s"(by_q_tiles.d), "s"(by_q_tiles.m), "s"(by_heads.d),
+                 "s"(by_heads.m));
+    const unsigned flat = blockIdx.x, xcd = flat & 7u, per = n_wg >> 3, rem = n_wg & 7u;
+    const unsigned logical = xcd * per + min(xcd, rem) + (flat >> 3);
+    const unsigned rest = divide(logical, by_q_tiles), z = divide(rest, by_heads);
+    qt = (int)(logical - rest * by_q_tiles.d);
+    h = (int)(rest - z * by_heads.d);
+    bz = (int)z;
+}
+
+// Loads of N groups of four query rows (1 KB each) to a stage whose row 0 is query q0 of the chunk, from row `first` on (past
+// the chunk's end: its last query).  Row r of the stage holds chunk c at position c ^ (r % 16), as the K rows do.
+template <int N>
+__device__ __forceinline__ void load_queries(const AttnArgs& a, int b, int h, int q0, int first, int lane, unsigned char* stage, int C) {
+    const unsigned char* src = reinterpret_cast<const unsigned char*>(a.q + (size_t)(unsigned)b * (unsigned)a.L * (unsigned)C + h * D);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const int r = first + 4 * i + (lane >> 4);
+        const size_t row = (unsigned)min(q0 + r, a.L - 1);
+        load_to_lds_b128(src + row * (unsigned)(2 * C) + (((lane & 15) ^ (r & 15)) << 4), stage + (first + 4 * i) * 256);
+    }
+}
+__device__ __forceinline__ void read_queries(bf16x8 (&qf)[D / 16], const unsigned char* stage, int l31, int lh) {
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(stage + l31 * 256 + (((2 * s + lh) ^ (l31 & 15)) << 4));
+}
+
 template <int NW>
 __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(AttnArgs a, float scale_log2e) {
     constexpr int QT = 32 * NW;                   // queries per workgroup: one 32-query block per wave
@@ -97,41 +168,36 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
     const int l31 = lane & 31;
     const int lh = lane >> 5;
 
-    // Workgroups are handed to the eight XCDs in turn; renumber them so that each XCD (its own L2) works through
-    // a contiguous run of (query tile, head, stream/split) triples, query tile fastest: the workgroups that
-    // share a head's K and V then sit behind the same L2.
-    const unsigned n_wg = gridDim.x * gridDim.y * gridDim.z;
-    const unsigned flat = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    const unsigned xcd = flat & 7u, per = n_wg >> 3, rem = n_wg & 7u;
-    const unsigned logical = xcd * per + min(xcd, rem) + (flat >> 3);
-    const int qt = (int)(logical % gridDim.x);
-    const int h = (int)((logical / gridDim.x) % gridDim.y);
-    const int bz = (int)(logical / (gridDim.x * gridDim.y));
-    const int b = bz / a.splits;
+    int qt, h, bz;
+    locate(a, qt, h, bz);
+    const int b = a.splits == 1 ? bz : bz / a.splits;
     const int split = bz - b * a.splits;
     const int C = a.H * D;
 
-    const int kv_len = __builtin_amdgcn_readfirstlane(a.desc ? a.desc->kv_len[b] : a.kv_len[b]);
-    const int cap = a.cap[b];
-    const int n_tiles = (kv_len + KT - 1) / KT;
-    const int t0 = (int)((long long)split * n_tiles / a.splits);
-    const int t1 = (int)((long long)(split + 1) * n_tiles / a.splits);
+    const StreamKeys keys = stream_keys(a, b);
+    const int cap = keys.cap, kv_len = keys.kv_len;
+    const int n_tiles = (int)((unsigned)(kv_len + KT - 1) / KT);      // one at least
+    int t0 = 0, t1 = n_tiles;
+    if (a.splits > 1) {                                               // at most 16 parts: no overflow of 32 bits below 2^33 keys
+        t0 = (int)((unsigned)(split * n_tiles) / (unsigned)a.splits);
+        t1 = (int)((unsigned)((split + 1) * n_tiles) / (unsigned)a.splits);
+    }
     const int tail_tile = (kv_len % KT) ? n_tiles - 1 : -1;           // the tile with slots past kv_len, if any
 
-    // ---- this lane's query (column of S^T) and its eight d-step fragments
+    // ---- this lane's query (column of S^T)
     const int q_in_chunk = qt * QT + wave * 32 + l31;
-    const size_t q_row = (size_t)b * a.L + min(q_in_chunk, a.L - 1);
-    bf16x8 qf[D / 16];
-    {
-        const bf16* qp = a.q + q_row * C + h * D + lh * 8;
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + s * 16);
-    }
+    const size_t q_row = (size_t)(unsigned)b * (unsigned)a.L + (unsigned)min(q_in_chunk, a.L - 1);
+
+    // ---- The wave's 32 queries, through LDS (fetched as fragments they would be 8 loads of 32 pieces of 32 bytes each).  Eight
+    // waves: behind the stages.  Four waves, two workgroups per unit: in the second stages, which are free until then.
+    unsigned char* const q_stage =
+        (NW == 8 ? smem_raw + 2 * (K_TILE_BYTES + V_TILE_BYTES) + wave * 8192 : (wave < 2 ? k_stage + K_TILE_BYTES : v_stage + V_TILE_BYTES) + (wave & 1) * 8192);
+    load_queries<8>(a, b, h, qt * QT + wave * 32, 0, lane, q_stage, C);
 
     // ---- direct loads.  A wave load fills 1 KB of LDS in lane order: 4 K rows or 8 V^T rows.  Wave w issues
     // loads w, w + NW, ... of each tile; the XOR term of a lane's chunk is the same for all of them.
-    const unsigned char* kbase = reinterpret_cast<const unsigned char*>(a.k[b] + (size_t)h * cap * D);
-    const unsigned char* vbase = reinterpret_cast<const unsigned char*>(a.vt[b] + (size_t)h * D * cap);
+    const unsigned char* kbase = reinterpret_cast<const unsigned char*>(keys.k + (size_t)h * cap * D);
+    const unsigned char* vbase = reinterpret_cast<const unsigned char*>(keys.vt + (size_t)h * D * cap);
     constexpr int LPT = 16 / NW;                  // wave loads per K tile and per V^T tile for each wave
     const int k_row = 4 * wave + (lane >> 4);                                     // + 4 NW i
     const uint32_t k_off = (uint32_t)k_row * 256u + (uint32_t)(((lane & 15) ^ (k_row & 15)) * 16);
@@ -167,6 +233,7 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
         }
     };
 
+    bf16x8 qf[D / 16];           // this lane's query: its eight d-step fragments
     f32x16 o_acc[D / 32];
 #pragma unroll
     for (int i = 0; i < D / 32; ++i)
@@ -333,9 +400,15 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
     if (t0 < t1) {
         load_k(t0, 0);
         load_v(t0, 0);
-        if (t0 + 1 < t1) load_k(t0 + 1, 1);
-        wait_loads();
+        if (NW == 8) load_k(min(t0 + 1, t1 - 1), 1);
+        __builtin_amdgcn_s_waitcnt(0x0F70 | ((NW == 8 ? 2 : 1) * LPT));      // the queries and the first K tile are there
         barrier();
+        read_queries(qf, q_stage, l31, lh);
+        if (NW == 4) {                                       // everyone has its queries: the second K stage is free
+            __builtin_amdgcn_s_waitcnt(0xC07F);
+            barrier();
+            load_k(min(t0 + 1, t1 - 1), 1);
+        }
         qk_half(s_a, k_stage, 0, nothing);
         qk_half(s_a, k_stage, 1, nothing);
     }
@@ -358,23 +431,27 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
         tile_step(with_tail, even, s_a, s_b, t_full);
     }
 
-    // ---- finish: divide by the row sum and write
+    // ---- finish: divide by the row sum and write (no direct load may still be on its way to this LDS when the wave ends)
+    wait_loads();
     const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
     const float inv_l = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
-    if (q_in_chunk >= a.L) return;
     if (a.splits == 1) {
-        bf16* op = a.o + q_row * C + h * D + 4 * lh;
+        bf16* op = a.o + q_row * C + h * D + 8 * lh;
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                bf16x4 w;
+            for (int g = 0; g < 4; g += 2) {
+                bf16x4 w[2];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = (bf16)(o_acc[db][4 * g + e] * inv_l);
-                *reinterpret_cast<bf16x4*>(op + db * 32 + 8 * g) = w;
+                for (int e = 0; e < 4; ++e) {
+                    w[0][e] = (bf16)(o_acc[db][4 * g + e] * inv_l);
+                    w[1][e] = (bf16)(o_acc[db][4 * g + 4 + e] * inv_l);
+                }
+                const uint4 v = eight_channels(w[0], w[1]);
+                if (q_in_chunk < a.L) *reinterpret_cast<uint4*>(op + db * 32 + 8 * g) = v;
             }
         }
-    } else {
+    } else if (q_in_chunk < a.L) {
         const size_t rows = (size_t)a.B * a.L;
         float* op = a.part_o + ((size_t)split * rows + q_row) * C + h * D + 4 * lh;
 #pragma unroll
@@ -426,32 +503,25 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs
     const int l31 = lane & 31;
     const int lh = lane >> 5;
 
-    const unsigned n_wg = gridDim.x * gridDim.y * gridDim.z;
-    const unsigned flat = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
-    const unsigned xcd = flat & 7u, per = n_wg >> 3, rem = n_wg & 7u;
-    const unsigned logical = xcd * per + min(xcd, rem) + (flat >> 3);
-    const int qt = (int)(logical % gridDim.x);
-    const int h = (int)((logical / gridDim.x) % gridDim.y);
-    const int b = (int)(logical / (gridDim.x * gridDim.y));
+    int qt, h, b;
+    locate(a, qt, h, b);
     const int C = a.H * D;
 
-    const int kv_len = __builtin_amdgcn_readfirstlane(a.desc ? a.desc->kv_len[b] : a.kv_len[b]);
-    const int cap = a.cap[b];
-    const int n_tiles = (kv_len + KTT - 1) / KTT;
+    const StreamKeys keys = stream_keys(a, b);
+    const int cap = keys.cap, kv_len = keys.kv_len;
+    const int n_tiles = (int)((unsigned)(kv_len + KTT - 1) / KTT);    // one at least
     const int tail_tile = (kv_len % KTT) ? n_tiles - 1 : -1;
 
     const int q_in_chunk = qt * QT + qb * 32 + l31;
-    const size_t q_row = (size_t)b * a.L + min(q_in_chunk, a.L - 1);
+    const size_t q_row = (size_t)(unsigned)b * (unsigned)a.L + (unsigned)min(q_in_chunk, a.L - 1);
+    // the workgroup's 64 queries go through the second V^T stage, which is free until the first tile is done: two loads per wave
+    unsigned char* const q_stage = v_stage + V_BYTES;
+    load_queries<2>(a, b, h, qt * QT, wave * 8, lane, q_stage, C);
     bf16x8 qf[D / 16];
-    {
-        const bf16* qp = a.q + q_row * C + h * D + lh * 8;
-#pragma unroll
-        for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + s * 16);
-    }
 
     // A wave load fills four 256-byte rows; wave w issues loads w, w + 8, w + 16, w + 24 of each tile.
-    const unsigned char* kbase = reinterpret_cast<const unsigned char*>(a.k[b] + (size_t)h * cap * D);
-    const unsigned char* vbase = reinterpret_cast<const unsigned char*>(a.vt[b] + (size_t)h * D * cap);
+    const unsigned char* kbase = reinterpret_cast<const unsigned char*>(keys.k + (size_t)h * cap * D);
+    const unsigned char* vbase = reinterpret_cast<const unsigned char*>(keys.vt + (size_t)h * D * cap);
     constexpr int LPT = KTT / 4 / NW;                     // 4 wave loads per tile and operand for each wave
     const int ld_row = 4 * wave + (lane >> 4);                                    // + 32 i
     const int ld_chunk = (lane & 15) ^ (ld_row & 15);                             // 32 i does not change row % 16
@@ -624,9 +694,10 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs
 
     load_k(0, 0);
     load_v(0, 0);
-    if (1 < n_tiles) load_k(1, 1);
-    wait_loads();
+    load_k(1, 1);
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * LPT));          // the queries and the first K tile are there
     barrier();
+    read_queries(qf, q_stage + qb * 8192, l31, lh);
     qk_half(s_a, 0, 0, nothing);
     qk_half(s_a, 0, 1, nothing);
     const int t_full = (tail_tile >= 0) ? n_tiles - 1 : n_tiles;        // tiles [0, t_full) have 128 valid slots
@@ -646,12 +717,13 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs
         tile_step(with_tail, even, s_a, s_b, t_full);
     }
 
-    // ---- merge the NKW partial results of each query block through LDS (the stages are free now)
+    // ---- merge the NKW partial results of each query block through LDS (the stages are free once every wave is past the
+    // first barrier; the sums and reference points lie behind them).  A wave writes the channels that the others add up and
+    // keeps its own 32: the writes are what this costs (13 clocks per KB).
     const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
     float* const xm = reinterpret_cast<float*>(smem_raw + 4 * K_BYTES);           // [NW][32] maxima, after the stages
     float* const xl = xm + NW * 32;                                               // [NW][32] sums
-    float* const ox = reinterpret_cast<float*>(smem_raw);                         // [NW][4][16][64] weighted outputs
-    __syncthreads();
+    f32x4* const ox = reinterpret_cast<f32x4*>(smem_raw);                         // [NW][4 db][4][64] weighted outputs
     if (lh == 0) {
         xm[wave * 32 + l31] = m_run;
         xl[wave * 32 + l31] = l_tot;
@@ -666,25 +738,34 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs
     for (int k = 0; k < NKW; ++k)
         lsum += xl[(qb + NQ * k) * 32 + l31] * __builtin_amdgcn_exp2f(xm[(qb + NQ * k) * 32 + l31] - mmax);
     const float wgt = lsum > 0.0f ? __builtin_amdgcn_exp2f(m_run - mmax) / lsum : 0.0f;
+    f32x4 own[4];
 #pragma unroll
-    for (int db = 0; db < D / 32; ++db)
+    for (int db = 0; db < D / 32; ++db) {
 #pragma unroll
-        for (int r = 0; r < 16; ++r) ox[((wave * 4 + db) * 16 + r) * 64 + lane] = o_acc[db][r] * wgt;
-    __syncthreads();
-    if (q_in_chunk >= a.L) return;
-    // wave (qb, kw) adds up and writes the 32 channels db = kw of its query block
-    bf16* op = a.o + q_row * C + h * D + kw * 32 + 4 * lh;
+        for (int g = 0; g < 4; ++g) {
+            f32x4 v;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        bf16x4 w;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            float acc = 0.0f;
-#pragma unroll
-            for (int k = 0; k < NKW; ++k) acc += ox[(((qb + NQ * k) * 4 + kw) * 16 + 4 * g + e) * 64 + lane];
-            w[e] = (bf16)acc;
+            for (int e = 0; e < 4; ++e) v[e] = o_acc[db][4 * g + e] * wgt;
+            if (db == kw) own[g] = v;
+            else ox[((wave * 4 + db) * 4 + g) * 64 + lane] = v;
         }
-        *reinterpret_cast<bf16x4*>(op + 8 * g) = w;
+    }
+    __syncthreads();
+    // wave (qb, kw) adds up, in the order of the slices, and writes the 32 channels db = kw of its query block
+    bf16* op = a.o + q_row * C + h * D + kw * 32 + 8 * lh;
+#pragma unroll
+    for (int g = 0; g < 4; g += 2) {
+        bf16x4 w[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int k = 0; k < NKW; ++k) acc += k == kw ? own[g + i] : ox[(((qb + NQ * k) * 4 + kw) * 4 + g + i) * 64 + lane];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[i][e] = (bf16)acc[e];
+        }
+        const uint4 v = eight_channels(w[0], w[1]);
+        if (q_in_chunk < a.L) *reinterpret_cast<uint4*>(op + 8 * g) = v;
     }
 }
 
@@ -802,8 +883,15 @@ void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
 
 bool attention_has_merge_pass(const AttnArgs& a) { return a.splits > 1 && !attention_plan_key_split(a); }
 
-hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part) {
-    const size_t smem = (size_t)2 * K_TILE_BYTES + 2 * V_TILE_BYTES;
+hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part) {
+    AttnArgs a = args;
+    auto one_dimension = [&](int q_tiles, int parts) {
+        a.n_wg = (unsigned)q_tiles * a.H * a.B * parts;
+        a.by_q_tiles = fast_div(q_tiles, a.n_wg);
+        a.by_heads = fast_div(a.H, a.n_wg);
+        return dim3(a.n_wg);
+    };
+    constexpr size_t smem = (size_t)2 * K_TILE_BYTES + 2 * V_TILE_BYTES, smem8 = smem + 8 * 8192;      // eight waves: their queries behind the stages
     constexpr size_t smem_ks = (size_t)4 * 32768 + 2 * 8 * 32 * sizeof(float);     // four 32 KB stages + the (m, l) exchange
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
@@ -812,7 +900,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part) {
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (attr_err == hipSuccess)
             attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<8>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem8);
         if (attr_err == hipSuccess)
             attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_ks_kernel<2, 4>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_ks);
@@ -821,7 +909,7 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part) {
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
     if (attention_plan_key_split(a)) {
         if (part == 2) return hipSuccess;
-        dim3 grid((a.L + 63) / 64, a.H, a.B);
+        const dim3 grid = one_dimension((a.L + 63) / 64, 1);
         hipLaunchKernelGGL((attention_ks_kernel<2, 4>), grid, dim3(512), smem_ks, s, a, scale_log2e);
         return hipGetLastError();
     }
@@ -831,8 +919,8 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part) {
         for (int b = 0; b < a.B; ++b) max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;
         const int nw = attention_plan_waves(a.B, a.L, a.H, max_kv);
         const int QT = 32 * nw;
-        dim3 grid((a.L + QT - 1) / QT, a.H, a.B * a.splits);
-        if (nw == 8) hipLaunchKernelGGL(attention_kernel<8>, grid, dim3(512), smem, s, a, scale_log2e);
+        const dim3 grid = one_dimension((a.L + QT - 1) / QT, a.splits);
+        if (nw == 8) hipLaunchKernelGGL(attention_kernel<8>, grid, dim3(512), smem8, s, a, scale_log2e);
         else hipLaunchKernelGGL(attention_kernel<4>, grid, dim3(256), smem, s, a, scale_log2e);
         e = hipGetLastError();
     }

@@ -114,6 +114,19 @@ struct StepDesc {
     float timestep[kMaxBatch];
 };
 
+// Division of n by d as the high half of one product, exact while n d < 2^32 (m = 0 beyond that, and for d = 1).  A division
+// in software is a chain of some forty instructions, and a kernel's first addresses wait for several of them.
+struct FastDiv {
+    unsigned d, m;
+};
+inline FastDiv fast_div(unsigned d, unsigned long long n_max) {
+    return FastDiv{d, d > 1 && n_max * d < (1ull << 32) ? (unsigned)((1ull << 32) / d) + 1u : 0u};
+}
+__device__ __forceinline__ unsigned divide(unsigned n, const FastDiv& f) {
+    if (f.m != 0) return __umulhi(n, f.m);
+    return f.d == 1 ? n : n / f.d;
+}
+
 struct AttnArgs {
     const bf16* q;                    // [B, L, C]
     const bf16* k[kMaxBatch];         // [H][cap][128]
@@ -126,6 +139,8 @@ struct AttnArgs {
     float* part_ml;                   // workspace: [splits][B*L][H][2] fp32
     int splits;                       // chosen by attention_plan
     const StepDesc* desc;             // null: kv_len above; else kv_len is read from the device descriptor
+    FastDiv by_q_tiles, by_heads;     // set by the launcher, as is the number of workgroups
+    unsigned n_wg;
 };
 int attention_plan_splits(int B, int L, int H, int max_kv_len);
 // Tuning hooks: waves per workgroup (4, 8; 0 = planner) and key-range splits (0 = planner); -1 leaves a value as is.

@@ -375,6 +375,19 @@ def test_attention_matches_oracle(B, L, H, kv_lens, splits, waves):
         assert err < 1e-2, (b, err)
 
 
+# Query tiles, heads, streams and parts that are one, odd, or no divisors of the eight XCDs over which the workgroups are
+# numbered; a chunk that ends one query into a tile, whose other rows are copies of its last.
+@pytest.mark.parametrize("waves", [4, 8, 2])
+@pytest.mark.parametrize("B,L,H,kv_lens,splits", [
+    (1, 1, 1, [1], 0),
+    (3, 257, 5, [70, 200, 65], 1),
+    (2, 129, 3, [330, 260], 2),
+    (8, 33, 1, [64, 1, 65, 127, 128, 129, 63, 200], 1),
+])
+def test_attention_workgroup_numbering(B, L, H, kv_lens, splits, waves):
+    test_attention_matches_oracle(B, L, H, kv_lens, splits, waves)
+
+
 # Score profiles along the key index, in log2 units of the exponent (what the kernel's running reference point is
 # measured in).  The kernels keep that reference only loosely behind the row maximum and form no maximum in the
 # steady state, so these walk through every way the reference has to move: maxima that keep growing across tiles,
