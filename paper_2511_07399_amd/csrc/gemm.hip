@@ -561,7 +561,6 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     // Otherwise every wave fetches a share of both, A first.
     const bool loads_a = !ROLES || wave < NL;
     const int id = loads_a ? wave : wave - NL;
-    uint32_t off[ROLES ? LMAX : LA + LW];
     const unsigned char* const base0 = reinterpret_cast<const unsigned char*>(loads_a ? g.a : g.w) + (size_t)kt0 * (BK * 2);
     const unsigned char* const base1 = reinterpret_cast<const unsigned char*>(g.w) + (size_t)kt0 * (BK * 2);
     unsigned char* const lds0 = loads_a ? smem : smem_w;
@@ -573,20 +572,34 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     auto group_of = [&](int i, int groups) { return kWhole || id + NL * i < groups ? id + NL * i : id + NL * (i - 1); };
     const int lane_row = lane >> 3;
     const uint32_t lane_col = (uint32_t)(((lane & 7) ^ ((4 * id + (lane >> 4)) & 7)) * 16), k2 = (uint32_t)g.K * 2u;
+    // kScalarRows: an address is the scalar offset of the group's first row (past the operand's end: its last group, which of A
+    // may have fewer rows than eight) and one lane offset that all loads share.  Otherwise a lane keeps an offset per load,
+    // which is fewer instructions but a register each, and another each for the next tile's: the 256 x 256 tile had to spill
+    // one, and the reload waited, once per k tile, for every tile load in flight (14B step 29.49 -> 28.82 ms without;
+    // the 192 x 256 and 256 x 192 tiles, which have the registers, are 2 % slower with scalar rows).
+    constexpr bool kScalarRows = TM * TN >= 32 && OCC == 2;
+    const uint32_t lane_off = (uint32_t)lane_row * k2 + lane_col;
+    const int last0 = (loads_a ? g.M : g.N) - 1, last1 = g.N - 1;
+    const uint32_t lane_off_last = loads_a ? (uint32_t)min(lane_row, last0 & 7) * k2 + lane_col : lane_off;
+    const uint32_t last_row_off0 = (uint32_t)(last0 & ~7) * k2;
+    uint32_t off[ROLES ? LMAX : LA + LW];
+    auto offset_of = [&](int row, int last) {
+        return kScalarRows ? (uint32_t)min(row, last & ~7) * k2 : (uint32_t)min(row + lane_row, last) * k2 + lane_col;
+    };
     auto set_off0 = [&](int m, int n) {
-        const int first = (loads_a ? m : n) + lane_row, last = (loads_a ? g.M : g.N) - 1;
+        const int first = loads_a ? m : n;
 #pragma unroll
         for (int i = 0; i < (ROLES ? LMAX : LA); ++i) {
-            off[i] = (uint32_t)min(first + 8 * group_of(i, loads_a ? GA : GW), last) * k2 + lane_col;
-            __builtin_amdgcn_sched_barrier(0);
+            off[i] = offset_of(first + 8 * group_of(i, loads_a ? GA : GW), last0);
+            if (!kScalarRows) __builtin_amdgcn_sched_barrier(0);
         }
     };
     auto set_off1 = [&](int n) {
         if constexpr (!ROLES) {
 #pragma unroll
             for (int i = 0; i < LW; ++i) {
-                off[LA + i] = (uint32_t)min(n + lane_row + 8 * group_of(i, GW), g.N - 1) * k2 + lane_col;
-                __builtin_amdgcn_sched_barrier(0);
+                off[LA + i] = offset_of(n + 8 * group_of(i, GW), last1);
+                if (!kScalarRows) __builtin_amdgcn_sched_barrier(0);
             }
         }
     };
@@ -611,15 +624,18 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
         dst1 = smem_w + st1 * SW;
         return wrap && more;
     };
+    auto load_group = [&](const unsigned char* src, uint32_t o, bool may_be_short, unsigned char* dst) {
+        if constexpr (kScalarRows) load_to_lds_b128(src + o + (may_be_short && o == last_row_off0 ? lane_off_last : lane_off), dst);
+        else load_to_lds_b128(src + o, dst);
+    };
     auto load = [&](auto lc) {
         constexpr int l = decltype(lc)::value;
         if constexpr (ROLES) {
-            if (LA == LW || l < (loads_a ? LA : LW))
-                load_to_lds_b128(src0 + off[l], dst0 + group_of(l, loads_a ? GA : GW) * 1024);
+            if (LA == LW || l < (loads_a ? LA : LW)) load_group(src0, off[l], true, dst0 + group_of(l, loads_a ? GA : GW) * 1024);
         } else if constexpr (l < LA) {
-            load_to_lds_b128(src0 + off[l], dst0 + group_of(l, GA) * 1024);
+            load_group(src0, off[l], true, dst0 + group_of(l, GA) * 1024);
         } else {
-            load_to_lds_b128(src1 + off[l], dst1 + group_of(l - LA, GW) * 1024);
+            load_group(src1, off[l], false, dst1 + group_of(l - LA, GW) * 1024);
         }
     };
     constexpr int LOADS = ROLES ? LMAX : LA + LW;

@@ -52,6 +52,9 @@ GEMM_CASES = [
     (1024, 1536, 8960, 2, None),           # 1.3B FFN-2
     (1024, 15360, 5120, 0, None),          # 14B QKV: 240 tiles of 256 x 256
     (1000, 1536, 512, 0, "d1"),            # 256 x 256, ragged M
+    (5, 384, 320, 2, "d1"),                # a single row group of fewer than eight rows, half a tile past the columns
+    (259, 512, 256, 0, "d1"),              # the second tile row holds three rows
+    (1023, 15360, 320, 0, "d1"),           # several tiles per workgroup up to a short last row group
     (300, 640, 192, 3, "d2"),              # 192 x 256, N not a multiple of the tile, 3 k tiles
     (256, 256, 64, 2, "d2"),               # a single k tile
     (520, 2048, 1024, 1, "d3"),            # 256 x 192, one wave per SIMD, GELU
