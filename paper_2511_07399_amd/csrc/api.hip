@@ -1018,11 +1018,23 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     g.bias = w->b_cq;
     g.out = ws.q;
     g.epilogue = kEpiBias;
-    RUN_GEMM(SDV2_TAG_CROSS_Q, "cross-q gemm");
-    RUN(SDV2_TAG_CROSS_Q_NORM, launch_rmsnorm_inplace(ws.q, w->g_cq, rows, C, C, cfg->eps, s), "cross-q norm");
+    // its RMSNorm: the projection applies the gain and leaves the rows' sums of squares where the q, k, v rows were, the
+    // attention kernel multiplies a query's scores by the factor of its row; in passes of its own where the plan splits k
+    g.gain = w->g_cq;
+    g.squares = reinterpret_cast<float*>(ws.qkv);        // at most C / 16 pieces of 4 bytes per row of 6 C
+    const int q_pieces = gemm_square_pieces(g);
+    if (q_pieces > 0) {
+        RUN(SDV2_TAG_CROSS_Q, launch_gemm_gain_squares(g, s), "cross-q gemm");
+    } else {
+        RUN_GEMM(SDV2_TAG_CROSS_Q, "cross-q gemm");
+        RUN(SDV2_TAG_CROSS_Q_NORM, launch_rmsnorm_inplace(ws.q, w->g_cq, rows, C, C, cfg->eps, s), "cross-q norm");
+    }
     // 7. cross-attention over the text tokens
     AttnArgs ct = at;
     ct.desc = nullptr;                                // the text keys do not change from step to step
+    ct.q_squares = q_pieces > 0 ? g.squares : nullptr;
+    ct.q_pieces = q_pieces;
+    ct.q_eps = cfg->eps;
     const int cap_t = (int)align_up((size_t)cfg->text_len, 64);
     for (int b = 0; b < B; ++b) {
         ct.k[b] = static_cast<const bf16*>(kt[b]);

@@ -68,7 +68,8 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)
 
 // ---------------------------------------------------------------- launchers (host side)
 enum GemmEpilogue { kEpiBias = 0, kEpiBiasGelu = 1, kEpiGatedResidual = 2, kEpiResidual = 3,
-                    kEpiPartial = 4 /* internal: fp32 partial sums of one k part, no bias */ };
+                    kEpiPartial = 4 /* internal: fp32 partial sums of one k part, no bias */,
+                    kEpiGainSquares = 5 /* internal: bf16 gain (A W^T + bias), and sums of (A W^T + bias)^2 over pieces of rows */ };
 
 struct GemmArgs {
     const bf16* a;        // [M, K]
@@ -91,8 +92,16 @@ struct GemmArgs {
     const bf16* w2;
     const float* bias2;
     void* out2;
+    // kEpiGainSquares: gain [N] and the sums, [pieces][M].
+    const float* gain;
+    float* squares;
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
+// The projection in front of an RMSNorm over its N columns with this gain, whose consumer multiplies by the row's factor
+// itself: out = gain (A W^T + bias), and the rows' sums of squares in gemm_square_pieces pieces (at most N / 16), [pieces][M]
+// at g.squares.  No pieces: the plan of this shape cannot (a k split, the register-staged kernel).
+int gemm_square_pieces(const GemmArgs& g);
+hipError_t launch_gemm_gain_squares(const GemmArgs& g, hipStream_t s);
 // fp32 partial sums the planned launch of an [M, K] x [N, K] product needs (0: its plan does not split k)
 size_t gemm_splitk_floats(int M, int N, int K, int epilogue);
 // the most that the planned launch of any product of at most M rows, N columns and K needs; grows with each
@@ -141,6 +150,11 @@ struct AttnArgs {
     const StepDesc* desc;             // null: kv_len above; else kv_len is read from the device descriptor
     FastDiv by_q_tiles, by_heads;     // set by the launcher, as is the number of workgroups
     unsigned n_wg;
+    // Queries whose RMSNorm over C is still to be divided out: the factor of a query's row is one number, so it joins the scale
+    // of its scores.  Sums of squares [q_pieces][B L] of the row before its gain (null: the queries are final).
+    const float* q_squares;
+    int q_pieces;
+    float q_eps;
 };
 int attention_plan_splits(int B, int L, int H, int max_kv_len);
 // Tuning hooks: waves per workgroup (4, 8; 0 = planner) and key-range splits (0 = planner); -1 leaves a value as is.

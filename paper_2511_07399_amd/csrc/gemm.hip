@@ -414,7 +414,35 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 
             }
         }
     }
-    if constexpr (EPI == kEpiBias || EPI == kEpiBiasGelu) {
+    if constexpr (EPI == kEpiBias || EPI == kEpiBiasGelu || EPI == kEpiGainSquares) {
+        f32x4 gain[EPI == kEpiGainSquares ? TN : 1];
+        if constexpr (EPI == kEpiGainSquares) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                const int c = col0 + 16 * j + 4 * lq;
+                gain[j] = *reinterpret_cast<const f32x4*>(g.gain + (FULL || c < g.N ? c : 0));
+            }
+            // a lane has 4 TN numbers of a row, the four quarters of the wave together 16 TN of them: one sum per row and wave
+            float* const sums = g.squares + (size_t)(unsigned)(col0 / (16 * TN)) * (unsigned)g.M + row0;
+#pragma unroll
+            for (int i = 0; i < TM; ++i) {
+                float q = 0.0f;
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    acc[i][j] += bias[j];
+                    if (FULL || col0 + 16 * j < g.N) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) q += acc[i][j][e] * acc[i][j][e];
+                    }
+                }
+                const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(q), __float_as_uint(q), false, false);
+                q = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+                const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(q), __float_as_uint(q), false, false);
+                q = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+                if (lq == 0 && 16 * i + l15 < rows) sums[16 * i + l15] = q;
+            }
+        }
+        auto value = [&](int i, int j) { return EPI == kEpiGainSquares ? acc[i][j] * gain[j] : acc[i][j] + bias[j]; };
         unsigned char* const base = reinterpret_cast<unsigned char*>(reinterpret_cast<bf16*>(outp) + (size_t)row0 * g.N);
         auto pack = [&](const f32x4& v, uint32_t& d0, uint32_t& d1) {
             bf16x4 w;
@@ -432,8 +460,8 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 
 #pragma unroll
             for (int j = 0; j + 1 < TN; j += 2) {
                 uint32_t a0, a1, b0, b1;
-                pack(acc[i][j] + bias[j], a0, a1);
-                pack(acc[i][j + 1] + bias[j + 1], b0, b1);
+                pack(value(i, j), a0, a1);
+                pack(value(i, j + 1), b0, b1);
                 const auto r0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
                 const auto r1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
                 uint4 u; u.x = r0[0]; u.y = r1[0]; u.z = r0[1]; u.w = r1[1];
@@ -441,7 +469,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 
             }
             if constexpr (TN % 2) {
                 uint32_t a0, a1;
-                pack(acc[i][TN - 1] + bias[TN - 1], a0, a1);
+                pack(value(i, TN - 1), a0, a1);
                 const int gcol = col0 + 16 * (TN - 1) + 4 * lq;
                 uint2 u; u.x = a0; u.y = a1;
                 if (FULL || (r < rows && gcol < g.N)) *reinterpret_cast<uint2*>(base + (ro + (uint32_t)gcol * 2u)) = u;
@@ -782,6 +810,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
             case kEpiBias: store_wave<TM, TN, kEpiBias, kScalarBias>(g, g.out, acc, bias, row0, col0, lane); break;
             case kEpiBiasGelu: store_wave<TM, TN, kEpiBiasGelu, kScalarBias>(g, g.out, acc, bias, row0, col0, lane); break;
             case kEpiGatedResidual: store_wave<TM, TN, kEpiGatedResidual, kScalarBias>(g, g.out, acc, bias, row0, col0, lane, xpre); break;
+            case kEpiGainSquares: store_wave<TM, TN, kEpiGainSquares, kScalarBias>(g, g.out, acc, bias, row0, col0, lane); break;
             case kEpiPartial:                                // the partial sums of a k part, or a plain fp32 output
                 store_wave<TM, TN, kEpiPartial, kScalarBias>(g, split ? g.splitk_partials + (size_t)ks * g.M * g.N : reinterpret_cast<float*>(g.out), acc,
                                                 bias, row0, col0, lane);
@@ -942,13 +971,13 @@ hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
 }
 
 struct TileCost {
-    int bm, bn, per_unit;
+    int bm, bn, waves_n, per_unit;
     bool one_wave;                    // a SIMD holds a single wave
     float a, b, c, p, s, q;
 };
 const TileCost kCost[kTileConfigs + 1] = {
-    {0, 0, 0, false, 0, 0, 0, 0, 0, 0},
-#define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit, a, b, c, p, s, q) {16 * tm * wm, 16 * tn * wn, per_unit, occ == 1, a, b, c, p, s, q},
+    {0, 0, 0, 0, false, 0, 0, 0, 0, 0, 0},
+#define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit, a, b, c, p, s, q) {16 * tm * wm, 16 * tn * wn, wn, per_unit, occ == 1, a, b, c, p, s, q},
     SDV2_TILE_CONFIGS(X)
 #undef X
 };
@@ -1326,6 +1355,20 @@ hipError_t launch_gemm_then_layernorm(const GemmArgs& g, const LnArgs& ln, bool*
 }
 
 hipError_t launch_gemm_part(const GemmArgs& g, hipStream_t s, int part) { return launch_gemm_impl(g, nullptr, nullptr, s, part); }
+
+// One sum per row and wave column, which is how the epilogue's lanes hold them.
+int gemm_square_pieces(const GemmArgs& g) {
+    const TilePlan p = plan_of(g);
+    if (!p.dma || usable_splitk(g, p) > 1) return 0;
+    return (g.N + kCost[p.dma].bn - 1) / kCost[p.dma].bn * kCost[p.dma].waves_n;
+}
+
+hipError_t launch_gemm_gain_squares(const GemmArgs& g, hipStream_t s) {
+    const TilePlan p = plan_of(g);
+    GemmArgs a = g;
+    a.epilogue = kEpiGainSquares;
+    return launch_tile_config(a, p.dma, 1, s);
+}
 
 bool gemm_splits_k(const GemmArgs& g) {
     return usable_splitk(g, plan_of(g)) > 1;

@@ -519,3 +519,26 @@ def test_layernorm_after_a_split_product_that_moves_the_row(bias):
     size = math.sqrt((upd ** 2).mean())
     err = math.sqrt(((xg[0].cpu().double().numpy() - xo) ** 2).mean())
     assert err <= 2.0 * (5e-3 * size + math.sqrt(3.0) * 2.8e-4), (err, size)
+
+
+def cross_attention_alone(w, layer):
+    """Self-attention and FFN add nothing; the cross-attention's update is of x's size and its softmax far from flat."""
+    for k in ("W_o", "b_o", "W_2", "b_2"):
+        w[k] *= 0.0
+    w["W_co"] *= 16.0
+    w["g_cq"] *= 4.0
+
+
+# The query projection leaves its rows' sums of squares in one piece per wave column and the attention kernel divides by the
+# root: every tile of the projection (1152 columns are no multiple of most; 24 to 72 pieces, more and fewer than a fetch of 32),
+# rows that end inside a tile and inside a wave, two streams, a text of one key tile and of several; a plan that splits k (the
+# norm is a pass of its own then).  Bar: the block's 2e-2.
+@pytest.mark.parametrize("tile", ["d%d" % i for i in range(1, 19)] + ["d17,2", "1,4", None])
+def test_cross_query_norm_of_every_tile(tile):
+    wl = wk.Workload("cross", 1152, 9, 128, 7, 19, 1, 1, 2, 77 if tile in ("d1", "d18", None) else 33, 2, 1, (1,), 1)
+    binding.tuning_set("gemm_tile", tile)
+    try:
+        res = run_stream_both(wl, 2, edit=cross_attention_alone, check_cache=False)
+    finally:
+        binding.tuning_set("gemm_tile", None)
+    assert max(res["x_err"]) <= 2e-2, res["x_err"]
