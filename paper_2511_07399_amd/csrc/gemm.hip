@@ -783,22 +783,50 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
             const unsigned char* pw = smem_w + sw * SW + w_frag;
             static_for<TM + TN>([&](auto r) { read(s0, r, pa, pw); });
         }
-        for (int t = 0; t < nk; ++t) {
-            const int na = sa + 1 == NSA ? 0 : sa + 1, nw = sw + 1 == NSW ? 0 : sw + 1;
-            __builtin_amdgcn_sched_barrier(0);
-            half(s0, smem + sa * SA + a_frag, smem_w + sw * SW + w_frag);
-            if (!landed) wait_loads(s0);
-            landed = false;
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            barrier();
-            __builtin_amdgcn_sched_barrier(0);
-            half(s1, smem + na * SA + a_frag, smem_w + nw * SW + w_frag);
-            if (next0(more, nk)) set_off0(nm0, nn0);
-            if constexpr (!ROLES) {
-                if (next1(more, nk)) set_off1(nn0);
+        // A workgroup with a single tile walks it in steps unrolled over the ring: the stage is a constant of the step and the
+        // next load's address is one product, fifteen to twenty scalar instructions a k tile where the cursors below take fifty
+        // to sixty, which with tiles of 1 to 12 MFMAs per half is most of what a wave issues.
+        constexpr bool kUnrolled = NSA == NSW && TM * TN <= 12;
+        if (kUnrolled && !more && sa == 0 && sw == 0) {
+            if constexpr (kUnrolled) {
+                int t = 0;
+                auto step = [&](auto stage) {
+                    constexpr int S = decltype(stage)::value, N = (S + 1) % NSA;
+                    if (t >= nk) return;
+                    __builtin_amdgcn_sched_barrier(0);
+                    half(s0, smem + S * SA + a_frag, smem_w + S * SW + w_frag);
+                    const uint32_t k_off = (uint32_t)min(t + NSA, nk - 1) * (BK * 2);       // past the end: the last k tile again
+                    src0 = base0 + k_off;
+                    dst0 = lds0 + S * bytes0;
+                    src1 = base1 + k_off;
+                    dst1 = smem_w + S * SW;
+                    ++t;
+                    wait_loads(s0);
+                    __builtin_amdgcn_s_waitcnt(0xC07F);
+                    barrier();
+                    __builtin_amdgcn_sched_barrier(0);
+                    half(s1, smem + N * SA + a_frag, smem_w + N * SW + w_frag);
+                };
+                while (t < nk) static_for<NSA>(step);
             }
-            sa = na;
-            sw = nw;
+        } else {
+            for (int t = 0; t < nk; ++t) {
+                const int na = sa + 1 == NSA ? 0 : sa + 1, nw = sw + 1 == NSW ? 0 : sw + 1;
+                __builtin_amdgcn_sched_barrier(0);
+                half(s0, smem + sa * SA + a_frag, smem_w + sw * SW + w_frag);
+                if (!landed) wait_loads(s0);
+                landed = false;
+                __builtin_amdgcn_s_waitcnt(0xC07F);
+                barrier();
+                __builtin_amdgcn_sched_barrier(0);
+                half(s1, smem + na * SA + a_frag, smem_w + nw * SW + w_frag);
+                if (next0(more, nk)) set_off0(nm0, nn0);
+                if constexpr (!ROLES) {
+                    if (next1(more, nk)) set_off1(nn0);
+                }
+                sa = na;
+                sw = nw;
+            }
         }
         f32x4 next_bias = {0.f, 0.f, 0.f, 0.f};
         if (more && g.bias != nullptr) {                     // waited for behind the stores, and with it every older load
