@@ -368,9 +368,15 @@ constexpr int vmcnt_only(int n) {     // s_waitcnt with only vmcnt constrained
 }
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 typedef const __attribute__((address_space(4))) float* scalar_float_ptr;      // read through the scalar cache where uniform
-// 16 bytes per lane from global memory straight into LDS at dst + 16 * lane (dst is wave-uniform).
-__device__ __forceinline__ void load_to_lds_b128(const void* src, void* dst) {
-    __builtin_amdgcn_global_load_lds(src, (lds_void_ptr)dst, 16, 0, 0);
+typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;     // 32 bits; a generic pointer is tested for null at every cast
+// 16 bytes per lane from a buffer straight into LDS at dst + 16 * lane (dst is wave-uniform): byte offsets of the lane and of
+// the wave, 32 bits each.
+__device__ __forceinline__ void load_to_lds_b128(__amdgpu_buffer_rsrc_t src, uint32_t lane_off, uint32_t wave_off, lds_byte_ptr dst) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void_ptr)dst, 16, (int)lane_off, (int)wave_off, 0, 0);
+}
+// A buffer of plain bytes (word 3: 32-bit data, no swizzle), below 4 GiB.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t byte_buffer(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
 }
 
 template <int... I, typename F>
@@ -589,9 +595,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     // Otherwise every wave fetches a share of both, A first.
     const bool loads_a = !ROLES || wave < NL;
     const int id = loads_a ? wave : wave - NL;
-    const unsigned char* const base0 = reinterpret_cast<const unsigned char*>(loads_a ? g.a : g.w) + (size_t)kt0 * (BK * 2);
-    const unsigned char* const base1 = reinterpret_cast<const unsigned char*>(g.w) + (size_t)kt0 * (BK * 2);
-    unsigned char* const lds0 = loads_a ? smem : smem_w;
+    const __amdgpu_buffer_rsrc_t buf0 = byte_buffer(loads_a ? g.a : g.w, (uint32_t)(loads_a ? g.M : g.N) * (uint32_t)g.K * 2u);
+    const __amdgpu_buffer_rsrc_t buf1 = byte_buffer(g.w, (uint32_t)g.N * (uint32_t)g.K * 2u);
+    const lds_byte_ptr lds_w = (lds_byte_ptr)smem_w, lds0 = loads_a ? (lds_byte_ptr)smem : lds_w;
+    const uint32_t k_first = (uint32_t)kt0 * (BK * 2);      // byte offset in a row of this part's first k tile
     const int bytes0 = loads_a ? SA : SW, stages0 = loads_a ? NSA : NSW;
     // Row group of this wave's i-th load (eight rows of 128 bytes); past the end the wave's previous group again.
     // Groups of a wave are NL (even) apart, so the swizzle term of a lane is the same for all of them.
@@ -633,13 +640,13 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     };
     // next k tile to fetch and the stage it goes to, per operand
     int k0 = 0, k1 = 0, st0 = 0, st1 = 0;
-    const unsigned char *src0 = base0, *src1 = base1;
-    unsigned char *dst0 = lds0, *dst1 = smem_w;
+    uint32_t src0 = k_first, src1 = k_first;
+    lds_byte_ptr dst0 = lds0, dst1 = lds_w;
     // moves a cursor on: the next k tile (0 of the next output tile past the end, if there is one), the next stage
     auto next0 = [&](bool more, int nk) {
         const bool wrap = k0 + 1 == nk;
         k0 = wrap ? (more ? 0 : k0) : k0 + 1;
-        src0 = wrap ? (more ? base0 : src0) : src0 + BK * 2;
+        src0 = k_first + (uint32_t)k0 * (BK * 2);
         st0 = st0 + 1 == stages0 ? 0 : st0 + 1;
         dst0 = lds0 + st0 * bytes0;
         return wrap && more;
@@ -647,23 +654,23 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     auto next1 = [&](bool more, int nk) {
         const bool wrap = k1 + 1 == nk;
         k1 = wrap ? (more ? 0 : k1) : k1 + 1;
-        src1 = wrap ? (more ? base1 : src1) : src1 + BK * 2;
+        src1 = k_first + (uint32_t)k1 * (BK * 2);
         st1 = st1 + 1 == NSW ? 0 : st1 + 1;
-        dst1 = smem_w + st1 * SW;
+        dst1 = lds_w + st1 * SW;
         return wrap && more;
     };
-    auto load_group = [&](const unsigned char* src, uint32_t o, bool may_be_short, unsigned char* dst) {
-        if constexpr (kScalarRows) load_to_lds_b128(src + o + (may_be_short && o == last_row_off0 ? lane_off_last : lane_off), dst);
-        else load_to_lds_b128(src + o, dst);
+    auto load_group = [&](const __amdgpu_buffer_rsrc_t& buf, uint32_t src, uint32_t o, bool may_be_short, lds_byte_ptr dst) {
+        if constexpr (kScalarRows) load_to_lds_b128(buf, may_be_short && o == last_row_off0 ? lane_off_last : lane_off, src + o, dst);
+        else load_to_lds_b128(buf, o, src, dst);
     };
     auto load = [&](auto lc) {
         constexpr int l = decltype(lc)::value;
         if constexpr (ROLES) {
-            if (LA == LW || l < (loads_a ? LA : LW)) load_group(src0, off[l], true, dst0 + group_of(l, loads_a ? GA : GW) * 1024);
+            if (LA == LW || l < (loads_a ? LA : LW)) load_group(buf0, src0, off[l], true, dst0 + group_of(l, loads_a ? GA : GW) * 1024);
         } else if constexpr (l < LA) {
-            load_group(src0, off[l], true, dst0 + group_of(l, GA) * 1024);
+            load_group(buf0, src0, off[l], true, dst0 + group_of(l, GA) * 1024);
         } else {
-            load_group(src1, off[l], false, dst1 + group_of(l - LA, GW) * 1024);
+            load_group(buf1, src1, off[l], false, dst1 + group_of(l - LA, GW) * 1024);
         }
     };
     constexpr int LOADS = ROLES ? LMAX : LA + LW;
@@ -795,11 +802,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
                     if (t >= nk) return;
                     __builtin_amdgcn_sched_barrier(0);
                     half(s0, smem + S * SA + a_frag, smem_w + S * SW + w_frag);
-                    const uint32_t k_off = (uint32_t)min(t + NSA, nk - 1) * (BK * 2);       // past the end: the last k tile again
-                    src0 = base0 + k_off;
+                    src0 = src1 = k_first + (uint32_t)min(t + NSA, nk - 1) * (BK * 2);       // past the end: the last k tile again
                     dst0 = lds0 + S * bytes0;
-                    src1 = base1 + k_off;
-                    dst1 = smem_w + S * SW;
+                    dst1 = lds_w + S * SW;
                     ++t;
                     wait_loads(s0);
                     __builtin_amdgcn_s_waitcnt(0xC07F);
