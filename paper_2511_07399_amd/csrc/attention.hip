@@ -747,6 +747,7 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs
     // ---- merge the NKW partial results of each query block through LDS (the stages are free once every wave is past the
     // first barrier; the sums and reference points lie behind them).  A wave writes the channels that the others add up and
     // keeps its own 32: the writes are what this costs (13 clocks per KB).
+    wait_loads();                                         // nor may a tile fetched past the end still be on its way to them
     const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
     float* const xm = reinterpret_cast<float*>(smem_raw + 4 * K_BYTES);           // [NW][32] maxima, after the stages
     float* const xl = xm + NW * 32;                                               // [NW][32] sums
