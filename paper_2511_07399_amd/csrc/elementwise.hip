@@ -203,35 +203,50 @@ __device__ __forceinline__ void append_vt_tile(const bf16* src, size_t ld, int n
 template <int IT>
 __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a, int norm_blocks, int tiles_per_stream) {
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int C = a.C;
     if ((int)blockIdx.x < norm_blocks) {
+        // What bounds a chunk here is a chain of latencies, so every load that does not depend on another goes out first: the row
+        // without tests of the head (past the end: the last head again), the rotation's tables, and the gains of kAhead steps,
+        // which came after the row's sums before; the row is uniform, so that its divisions and its stream's arguments are scalar.
+        // 1024 tokens of 12 heads 7.4 -> 6.8 us, of 40 heads 18.9 -> 16.2.
+        constexpr int kAhead = IT < 3 ? IT : 3;
         const int row = blockIdx.x * 4 + wave;               // over B * L
         if (row >= a.B * a.L) return;
-        const int b = row / a.L;
-        const int i = row - b * a.L;
-        const AppendStream& st = a.st[b];
         const bf16* qp = a.qkv + (size_t)row * 3 * C;
         const bf16* kp = qp + C;
         // a wave load covers four heads: lane l holds pairs 4 (l % 16) .. + 3 of head l / 16 + 4 it
         const int hl = lane >> 4;
         const int p0 = 4 * (lane & 15);                      // first of this lane's four rotation pairs
+        const int axis = a.pair_axis[lane];
+        const double inv_freq = a.inv_freq[lane];
         bf16x8 qv[IT], kv[IT];
+        f32x4 gain[IT][4];
+        auto column = [&](int it) { return min(hl + 4 * it, a.H - 1) * kHeadDim + 2 * p0; };
+        auto fetch_gain = [&](int it) {
+            const int c = column(it);
+            gain[it][0] = *reinterpret_cast<const f32x4*>(a.g_q + c);
+            gain[it][1] = *reinterpret_cast<const f32x4*>(a.g_q + c + 4);
+            gain[it][2] = *reinterpret_cast<const f32x4*>(a.g_k + c);
+            gain[it][3] = *reinterpret_cast<const f32x4*>(a.g_k + c + 4);
+        };
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
-            const int h = hl + 4 * it;
-            if (h < a.H) {
-                qv[it] = *reinterpret_cast<const bf16x8*>(qp + h * kHeadDim + 2 * p0);
-                kv[it] = *reinterpret_cast<const bf16x8*>(kp + h * kHeadDim + 2 * p0);
-            }
+            qv[it] = *reinterpret_cast<const bf16x8*>(qp + column(it));
+            kv[it] = *reinterpret_cast<const bf16x8*>(kp + column(it));
         }
+#pragma unroll
+        for (int it = 0; it < kAhead; ++it) fetch_gain(it);
+        __builtin_amdgcn_sched_barrier(0);
+        const int b = row / a.L;
+        const int i = row - b * a.L;
+        const AppendStream& st = a.st[b];
         // position of the token; lane j forms the rotation of pair j, then every lane fetches its four
         const int frame = (a.desc ? a.desc->frame_pos0[b] : st.frame_pos0) + i / a.tokens_per_frame;
         const int inside = i % a.tokens_per_frame;
-        const int axis = a.pair_axis[lane];
         const int pos = axis == 0 ? frame : (axis == 1 ? inside / a.grid_w : inside % a.grid_w);
         double sn, cs;
-        sincos((double)pos * a.inv_freq[lane], &sn, &cs);
+        sincos((double)pos * inv_freq, &sn, &cs);
         const float cf_own = (float)cs, sf_own = (float)sn;
         float cf[4], sf[4];
 #pragma unroll
@@ -259,10 +274,10 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a, int 
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
             const int h = hl + 4 * it;
+            if (it + kAhead < IT) fetch_gain(it + kAhead);
             if (h < a.H) {
                 const int c = h * kHeadDim + 2 * p0;
-                const f32x4 gq0 = *reinterpret_cast<const f32x4*>(a.g_q + c), gq1 = *reinterpret_cast<const f32x4*>(a.g_q + c + 4);
-                const f32x4 gk0 = *reinterpret_cast<const f32x4*>(a.g_k + c), gk1 = *reinterpret_cast<const f32x4*>(a.g_k + c + 4);
+                const f32x4 gq0 = gain[it][0], gq1 = gain[it][1], gk0 = gain[it][2], gk1 = gain[it][3];
                 bf16x8 qr, kr;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
