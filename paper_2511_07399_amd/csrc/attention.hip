@@ -33,6 +33,7 @@
 //     divisions that number the workgroups are products with the launcher's reciprocals (five in software took 1.5 us), the
 //     arguments come in two batches, the queries pass through LDS (as fragments straight from memory they are 64 loads of
 //     32 pieces of 32 bytes, and the first tiles queue behind them), and the first scores wait for the first K tile alone.
+//     Queries that do not start at a multiple of 16 bytes are such fragments still: a direct load needs the multiple.
 //     From the start to the first scores 5.6 -> 3.6 us; text cross-attention of the 1.3B chunk 13.0 -> 10.5 us, of the 14B
 //     chunk 25 -> 21 us.  Outputs leave in pieces of 16 bytes.
 //   * A query row's RMSNorm factor is one number, so it joins the scale of the query's scores (query_scale) instead of a pass
@@ -159,6 +160,13 @@ __device__ __forceinline__ void read_queries(bf16x8 (&qf)[D / 16], const unsigne
     for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(stage + l31 * 256 + (((2 * s + lh) ^ (l31 & 15)) << 4));
 }
 
+// The same fragments by ordinary vector loads, good for any address of a bf16.
+__device__ __forceinline__ void fetch_queries(bf16x8 (&qf)[D / 16], const AttnArgs& a, size_t q_row, int h, int lh, int C) {
+    const bf16* qp = a.q + q_row * C + h * D + lh * 8;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + s * 16);
+}
+
 // Scale of a query's scores: the softmax's, times the factor of the query's RMSNorm where that is still to be divided out.
 // The two lanes of a query fetch half of the row's sums each, sixteen at a time (coalesced: rows are next to each other).
 __device__ __forceinline__ float query_scale(const AttnArgs& a, float scale_log2e, size_t q_row, int lh) {
@@ -178,8 +186,9 @@ __device__ __forceinline__ float query_scale(const AttnArgs& a, float scale_log2
     return scale_log2e * rsqrtf(sum / (float)(a.H * D) + a.q_eps);
 }
 
-template <int NW>
-__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(AttnArgs a, float softmax_scale) {
+// STAGED: the queries go through LDS by direct loads, which need a multiple of 16 bytes.
+template <int NW, bool STAGED>
+__device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_scale) {
     constexpr int QT = 32 * NW;                   // queries per workgroup: one 32-query block per wave
     extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
     unsigned char* const k_stage = smem_raw;                          // [2][64 keys][256 B]
@@ -215,7 +224,9 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
     // waves: behind the stages.  Four waves, two workgroups per unit: in the second stages, which are free until then.
     unsigned char* const q_stage =
         (NW == 8 ? smem_raw + 2 * (K_TILE_BYTES + V_TILE_BYTES) + wave * 8192 : (wave < 2 ? k_stage + K_TILE_BYTES : v_stage + V_TILE_BYTES) + (wave & 1) * 8192);
-    load_queries<8>(a, b, h, qt * QT + wave * 32, 0, lane, q_stage, C);
+    bf16x8 qf[D / 16];           // this lane's query: its eight d-step fragments
+    if (STAGED) load_queries<8>(a, b, h, qt * QT + wave * 32, 0, lane, q_stage, C);
+    else fetch_queries(qf, a, q_row, h, lh, C);
 
     // ---- direct loads.  A wave load fills 1 KB of LDS in lane order: 4 K rows or 8 V^T rows.  Wave w issues
     // loads w, w + NW, ... of each tile; the XOR term of a lane's chunk is the same for all of them.
@@ -256,7 +267,6 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
         }
     };
 
-    bf16x8 qf[D / 16];           // this lane's query: its eight d-step fragments
     f32x16 o_acc[D / 32];
 #pragma unroll
     for (int i = 0; i < D / 32; ++i)
@@ -427,10 +437,12 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
         if (NW == 8) load_k(min(t0 + 1, t1 - 1), 1);
         __builtin_amdgcn_s_waitcnt(0x0F70 | ((NW == 8 ? 2 : 1) * LPT));      // the queries and the first K tile are there
         barrier();
-        read_queries(qf, q_stage, l31, lh);
-        if (NW == 4) {                                       // everyone has its queries: the second K stage is free
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            barrier();
+        if (STAGED) read_queries(qf, q_stage, l31, lh);
+        if (NW == 4) {
+            if (STAGED) {                                    // everyone has its queries: the second K stage is free
+                __builtin_amdgcn_s_waitcnt(0xC07F);
+                barrier();
+            }
             load_k(min(t0 + 1, t1 - 1), 1);
         }
         qk_half(s_a, k_stage, 0, nothing);
@@ -497,6 +509,15 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
     }
 }
 
+template <int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(AttnArgs a, float softmax_scale) {
+    attention_body<NW, true>(a, softmax_scale);
+}
+template <int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_any_address_kernel(AttnArgs a, float softmax_scale) {
+    attention_body<NW, false>(a, softmax_scale);
+}
+
 // ---------------------------------------------------------------------------------------------------
 // Key-split form for skinny launches (a single 1024-token chunk: heads x query tiles is well below the number of
 // SIMDs).  A workgroup is NQ query blocks x NKW key slices = 8 waves: it walks the whole key range in tiles of
@@ -507,8 +528,8 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_kernel(Att
 //   K stage:   32 NKW keys x 256 B, chunk c of row r at position c ^ (r % 16)
 //   V^T stage: 128 rows (d) x 32 NKW keys (64 NKW bytes; 256 B for NKW = 4), same swizzle
 // Needs cap % (32 NKW) == 0 (a tile never reaches past a V^T row).
-template <int NQ, int NKW>
-__global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs a, float softmax_scale) {
+template <int NQ, int NKW, bool STAGED>
+__device__ __forceinline__ void attention_ks_body(const AttnArgs& a, float softmax_scale) {
     static_assert(NKW == 4 && NQ * NKW == 8, "tiles of 128 keys, eight waves");
     constexpr int NW = NQ * NKW;
     constexpr int QT = 32 * NQ;
@@ -541,8 +562,9 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs
     const size_t q_row = (size_t)(unsigned)b * (unsigned)a.L + (unsigned)min(q_in_chunk, a.L - 1);
     // the workgroup's 64 queries go through the second V^T stage, which is free until the first tile is done: two loads per wave
     unsigned char* const q_stage = v_stage + V_BYTES;
-    load_queries<2>(a, b, h, qt * QT, wave * 8, lane, q_stage, C);
     bf16x8 qf[D / 16];
+    if (STAGED) load_queries<2>(a, b, h, qt * QT, wave * 8, lane, q_stage, C);
+    else fetch_queries(qf, a, q_row, h, lh, C);
 
     // A wave load fills four 256-byte rows; wave w issues loads w, w + 8, w + 16, w + 24 of each tile.
     const unsigned char* kbase = reinterpret_cast<const unsigned char*>(keys.k + (size_t)h * cap * D);
@@ -723,7 +745,7 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs
     load_k(1, 1);
     __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * LPT));          // the queries and the first K tile are there
     barrier();
-    read_queries(qf, q_stage + qb * 8192, l31, lh);
+    if (STAGED) read_queries(qf, q_stage + qb * 8192, l31, lh);
     qk_half(s_a, 0, 0, nothing);
     qk_half(s_a, 0, 1, nothing);
     scale_log2e = query_scale(a, softmax_scale, q_row, lh);
@@ -795,6 +817,15 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs
         const uint4 v = eight_channels(w[0], w[1]);
         if (q_in_chunk < a.L) *reinterpret_cast<uint4*>(op + 8 * g) = v;
     }
+}
+
+template <int NQ, int NKW>
+__global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_kernel(AttnArgs a, float softmax_scale) {
+    attention_ks_body<NQ, NKW, true>(a, softmax_scale);
+}
+template <int NQ, int NKW>
+__global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_any_address_kernel(AttnArgs a, float softmax_scale) {
+    attention_ks_body<NQ, NKW, false>(a, softmax_scale);
 }
 
 // out = sum_i w_i O_i / sum_i w_i,  w_i = l_i 2^(m_i - max m).  One thread per four channels.
@@ -909,6 +940,10 @@ void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
     else snprintf(out, cap, "attention_kernel<%d>", attention_plan_waves(a.B, a.L, a.H, max_kv));
 }
 
+// Direct loads of the queries go from memory to LDS in pieces of 16 bytes, which have to start at multiples of 16 (rows and
+// heads are multiples of 256 bytes, so the first address decides); queries at any other address of a bf16 are fetched into registers.
+static bool queries_aligned(const AttnArgs& a) { return (reinterpret_cast<uintptr_t>(a.q) & 15) == 0; }
+
 bool attention_has_merge_pass(const AttnArgs& a) { return a.splits > 1 && !attention_plan_key_split(a); }
 
 hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part) {
@@ -923,22 +958,26 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part) {
     constexpr size_t smem_ks = (size_t)4 * 32768 + 2 * 8 * 32 * sizeof(float);     // four 32 KB stages + the (m, l) exchange
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
+    typedef void (*Kernel)(AttnArgs, float);
     std::call_once(attr_once, [&]() {
-        attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<4>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (attr_err == hipSuccess)
-            attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_kernel<8>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem8);
-        if (attr_err == hipSuccess)
-            attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&attention_ks_kernel<2, 4>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_ks);
+        const std::pair<Kernel, size_t> kernels[] = {{attention_kernel<4>, smem},
+                                                     {attention_kernel<8>, smem8},
+                                                     {attention_ks_kernel<2, 4>, smem_ks},
+                                                     {attention_any_address_kernel<4>, smem},
+                                                     {attention_any_address_kernel<8>, smem8},
+                                                     {attention_ks_any_address_kernel<2, 4>, smem_ks}};
+        for (const auto& k : kernels)
+            if (attr_err == hipSuccess)
+                attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(k.first), hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second);
     });
     if (attr_err != hipSuccess || attributes_only()) return attr_err;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
+    const bool staged = queries_aligned(a);
     if (attention_plan_key_split(a)) {
         if (part == 2) return hipSuccess;
         const dim3 grid = one_dimension((a.L + 63) / 64, 1);
-        hipLaunchKernelGGL((attention_ks_kernel<2, 4>), grid, dim3(512), smem_ks, s, a, scale_log2e);
+        const Kernel kernel = staged ? attention_ks_kernel<2, 4> : attention_ks_any_address_kernel<2, 4>;
+        hipLaunchKernelGGL(kernel, grid, dim3(512), smem_ks, s, a, scale_log2e);
         return hipGetLastError();
     }
     hipError_t e = hipSuccess;
@@ -948,8 +987,8 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part) {
         const int nw = attention_plan_waves(a.B, a.L, a.H, max_kv);
         const int QT = 32 * nw;
         const dim3 grid = one_dimension((a.L + QT - 1) / QT, a.splits);
-        if (nw == 8) hipLaunchKernelGGL(attention_kernel<8>, grid, dim3(512), smem8, s, a, scale_log2e);
-        else hipLaunchKernelGGL(attention_kernel<4>, grid, dim3(256), smem, s, a, scale_log2e);
+        if (nw == 8) hipLaunchKernelGGL(staged ? attention_kernel<8> : attention_any_address_kernel<8>, grid, dim3(512), smem8, s, a, scale_log2e);
+        else hipLaunchKernelGGL(staged ? attention_kernel<4> : attention_any_address_kernel<4>, grid, dim3(256), smem, s, a, scale_log2e);
         e = hipGetLastError();
     }
     if (e != hipSuccess || part == 1) return e;

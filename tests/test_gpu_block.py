@@ -542,3 +542,34 @@ def test_cross_query_norm_of_every_tile(tile):
     finally:
         binding.tuning_set("gemm_tile", None)
     assert max(res["x_err"]) <= 2e-2, res["x_err"]
+
+
+@pytest.mark.parametrize("step", [False, True])
+@pytest.mark.parametrize("offset", [2, 8])
+def test_workspace_at_any_address(offset, step):
+    """A block, or a step with its conditioning, in a workspace that starts past a multiple of 16: no kernel with loads
+    straight into LDS may take its queries or activations from there.  Branches of order one, two chunks."""
+    wl = wk.WORKLOADS["tiny"]
+    edit = visible_branches(wl)
+    gpu, ora = GpuRunner(wl, n_layers=1, n_streams=1, edit=edit), OracleRunner(wl, n_layers=1, n_streams=1, edit=edit)
+    need = (binding.denoise_workspace_bytes if step else binding.block_workspace_bytes)(gpu.cfg, 1, wl.L)
+    ws = torch.empty(need + 16, dtype=torch.uint8, device=DEV)[offset:offset + need]
+    assert ws.data_ptr() % 16 != 0
+    for chunk in range(2):
+        x = wk.chunk_input(wl, chunk)
+        xg = x.to(DEV).reshape(1, wl.L, wl.C).contiguous()
+        desc = (0, chunk * wl.frames_per_chunk, wl.frames_per_chunk, 1)
+        if step:
+            tv = wk.timestep_vector(wl, chunk, 0)
+            kt, vtt = binding.ptr_array([gpu.kt[0][0]]), binding.ptr_array([gpu.vtt[0][0]])
+            binding.denoise_step(gpu.cfg, gpu.mw, gpu.cache, xg, kt, vtt, binding.chunk_descs([desc]), ws,
+                                 tvec=tv.to(DEV).reshape(1, wl.C).contiguous())
+            want = ora.denoise(x.double().numpy(), desc, tvec=tv.double().numpy())
+        else:
+            e0 = caller_e0(wl, chunk)
+            binding.dit_block_forward(gpu.cfg, gpu.bw_array[0], gpu.cache, 0, xg, e0.to(DEV).reshape(1, 6, wl.C).contiguous(),
+                                      [gpu.kt[0][0]], [gpu.vtt[0][0]], binding.chunk_descs([desc]), ws)
+            want = ora.block(0, x.double().numpy(), e0.double().numpy(), desc)
+        torch.cuda.synchronize()
+        assert max_rel_err(xg[0].cpu().numpy(), want) <= TOL_X, chunk
+    gpu.close()

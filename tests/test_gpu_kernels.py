@@ -391,6 +391,35 @@ def test_attention_workgroup_numbering(B, L, H, kv_lens, splits, waves):
     test_attention_matches_oracle(B, L, H, kv_lens, splits, waves)
 
 
+@pytest.mark.parametrize("waves,splits", [(4, 1), (4, 2), (8, 1), (8, 3), (2, 1)])
+@pytest.mark.parametrize("q0,o0", [(1, 0), (2, 1), (4, 4), (0, 2)])
+def test_attention_of_queries_at_any_address(q0, o0, waves, splits):
+    """Queries and outputs that start 2 to 8 bytes past a multiple of 16: loads straight into LDS need the multiple, so such
+    queries are fetched into registers.  Chunks that end inside a tile and inside a wave, tails of keys."""
+    B, L, H, kv_lens = 2, 157, 3, [450, 384]
+    Cw, n = H * 128, B * L * H * 128
+    q = bf16_randn((n + 8,), 10).to(DEV)[q0:q0 + n].view(B, L, Cw)
+    o = torch.full((n + 8,), float("nan"), dtype=torch.bfloat16, device=DEV)[o0:o0 + n].view(B, L, Cw)
+    assert (q.data_ptr() | o.data_ptr()) % 16 != 0
+    rows = [(bf16_randn((m, Cw), 20 + b), bf16_randn((m, Cw), 30 + b)) for b, m in enumerate(kv_lens)]
+    caps = [512, 384]
+    packed = [pack_kv(k, v, H, cap) for (k, v), cap in zip(rows, caps)]
+    ks, vts = [p[0].to(DEV) for p in packed], [p[1].to(DEV) for p in packed]
+    binding.tuning_set("attn_splits", splits)
+    binding.tuning_set("attn_waves", waves)
+    try:
+        ws = torch.empty(max(binding.attention_workspace_bytes(B, L, Cw, max(kv_lens)), 256), dtype=torch.uint8, device=DEV)
+        binding.attention_bf16(q, ks, vts, kv_lens, caps, o, H, ws)
+        torch.cuda.synchronize()
+    finally:
+        binding.tuning_set("attn_splits", None)
+        binding.tuning_set("attn_waves", None)
+    for b, m in enumerate(kv_lens):
+        want = oracle.attention_dense(f64(q[b]).reshape(L, H, 128), f64(rows[b][0]).reshape(m, H, 128),
+                                      f64(rows[b][1]).reshape(m, H, 128)).reshape(L, Cw)
+        assert max_rel_err(f64(o[b]), want) < 1e-2
+
+
 # Score profiles along the key index, in log2 units of the exponent (what the kernel's running reference point is
 # measured in).  The kernels keep that reference only loosely behind the row maximum and form no maximum in the
 # steady state, so these walk through every way the reference has to move: maxima that keep growing across tiles,
