@@ -186,6 +186,20 @@ __device__ __forceinline__ float query_scale(const AttnArgs& a, float scale_log2
     return scale_log2e * rsqrtf(sum / (float)(a.H * D) + a.q_eps);
 }
 
+// A row whose sum of squares is beyond fp32 has the factor 0: its norm is the zero row (not a number where q is infinite).  With
+// a scale of 0 its masked scores, -inf, would be 0 x inf; so the queries become that row and keep the softmax's scale.
+// True for a wave that has such a query: its scores are to be formed again.
+__device__ __forceinline__ bool zero_queries(bf16x8 (&qf)[D / 16], float& scale, float softmax_scale) {
+    const bool zero = scale == 0.0f;
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(zero) == 0, 1)) return false;
+#pragma unroll
+    for (int s = 0; s < D / 16; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) qf[s][e] = zero ? (bf16)((float)qf[s][e] * 0.0f) : qf[s][e];
+    scale = zero ? softmax_scale : scale;
+    return true;
+}
+
 // STAGED: the queries go through LDS by direct loads, which need a multiple of 16 bytes.
 template <int NW, bool STAGED>
 __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_scale) {
@@ -448,6 +462,10 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
         qk_half(s_a, k_stage, 0, nothing);
         qk_half(s_a, k_stage, 1, nothing);
         scale_log2e = query_scale(a, softmax_scale, q_row, lh);
+        if (zero_queries(qf, scale_log2e, softmax_scale)) {
+            qk_half(s_a, k_stage, 0, nothing);
+            qk_half(s_a, k_stage, 1, nothing);
+        }
     }
     // full tiles in pairs (the two S^T register sets trade places), then what is left: at most one full tile
     // and the tail tile
@@ -749,6 +767,10 @@ __device__ __forceinline__ void attention_ks_body(const AttnArgs& a, float softm
     qk_half(s_a, 0, 0, nothing);
     qk_half(s_a, 0, 1, nothing);
     scale_log2e = query_scale(a, softmax_scale, q_row, lh);
+    if (zero_queries(qf, scale_log2e, softmax_scale)) {
+        qk_half(s_a, 0, 0, nothing);
+        qk_half(s_a, 0, 1, nothing);
+    }
     const int t_full = (tail_tile >= 0) ? n_tiles - 1 : n_tiles;        // tiles [0, t_full) have 128 valid slots
     const std::false_type no_tail;
     const std::true_type with_tail;

@@ -573,3 +573,45 @@ def test_workspace_at_any_address(offset, step):
         torch.cuda.synchronize()
         assert max_rel_err(xg[0].cpu().numpy(), want) <= TOL_X, chunk
     gpu.close()
+
+
+# attn_waves, attn_splits, text tokens (tails in the first tile, in a later one, none), tile of the projection ("d17,2" splits k:
+# the norm is a pass of its own)
+@pytest.mark.parametrize("waves,splits,text,tile", [(4, 1, 33, "d15"), (4, 1, 64, "d15"), (4, 2, 300, "d1"), (8, 1, 77, "d15"),
+                                                    (2, 1, 77, "d9"), (2, 1, 77, "d17,2"), (2, 1, 300, "d18")])
+def test_cross_query_rows_beyond_single_precision(waves, splits, text, tile):
+    """Every second row's query is so large that its sum of squares is infinite in fp32.  RMSNorm then divides by infinity: a
+    query of zeros, whose softmax is flat; the rows between them are normalised as usual.  Bar: the block's."""
+    wl = wk.Workload("beyond", 1152, 9, 128, 7, 19, 1, 1, 2, text, 1, 1, (1,), 1)
+
+    def edit(large):
+        def apply(w, layer):
+            cross_attention_alone(w, layer)
+            first = w["W_cq"][:, :1].clone() / 0.02
+            w["W_cq"] *= 0.0
+            w["b_cq"] *= 0.0
+            if large:
+                w["W_cq"][:, :1] = first * 1e18           # q = 1e18 h[0] N(0, 1)
+        return apply
+
+    x = wk.chunk_input(wl, 0)
+    x[0::2, 0] = 20.0                                      # h[0] about 17: squares of 1e38 and more
+    x[1::2, 0] = 0.0                                       # h[0] below 0.2: their sum stays below 1e38
+    e0 = torch.zeros(6, wl.C)
+    desc = (0, 0, 1, 1)
+    want, flat = (OracleRunner(wl, edit=edit(large)).block(0, x.double().numpy(), e0.double().numpy(), desc) for large in (True, False))
+    assert max_rel_err(flat[0::2], want[0::2]) > 0.2
+    want[0::2] = flat[0::2]
+    binding.tuning_set("gemm_tile", tile)
+    binding.tuning_set("attn_waves", waves)
+    binding.tuning_set("attn_splits", splits)
+    try:
+        gpu = GpuRunner(wl, n_layers=1, n_streams=1, edit=edit(True))
+        xg = x.to(DEV).reshape(1, wl.L, wl.C).contiguous()
+        gpu.block(0, xg, e0.to(DEV).reshape(1, 6, wl.C).contiguous(), [desc])
+        torch.cuda.synchronize()
+        gpu.close()
+    finally:
+        for name in ("gemm_tile", "attn_waves", "attn_splits"):
+            binding.tuning_set(name, None)
+    assert max_rel_err(xg[0].cpu().numpy(), want) <= TOL_X
