@@ -428,27 +428,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 
                 const int c = col0 + 16 * j + 4 * lq;
                 gain[j] = *reinterpret_cast<const f32x4*>(g.gain + (FULL || c < g.N ? c : 0));
             }
-            // a lane has 4 TN numbers of a row, the four quarters of the wave together 16 TN of them: one sum per row and wave
-            float* const sums = g.squares + (size_t)(unsigned)(col0 / (16 * TN)) * (unsigned)g.M + row0;
-#pragma unroll
-            for (int i = 0; i < TM; ++i) {
-                float q = 0.0f;
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    acc[i][j] += bias[j];
-                    if (FULL || col0 + 16 * j < g.N) {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) q += acc[i][j][e] * acc[i][j][e];
-                    }
-                }
-                const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(q), __float_as_uint(q), false, false);
-                q = __uint_as_float(h[0]) + __uint_as_float(h[1]);
-                const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(q), __float_as_uint(q), false, false);
-                q = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-                if (lq == 0 && 16 * i + l15 < rows) sums[16 * i + l15] = q;
-            }
         }
-        auto value = [&](int i, int j) { return EPI == kEpiGainSquares ? acc[i][j] * gain[j] : acc[i][j] + bias[j]; };
         unsigned char* const base = reinterpret_cast<unsigned char*>(reinterpret_cast<bf16*>(outp) + (size_t)row0 * g.N);
         auto pack = [&](const f32x4& v, uint32_t& d0, uint32_t& d1) {
             bf16x4 w;
@@ -463,11 +443,33 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 
             __builtin_amdgcn_sched_barrier(0);
             const int r = 16 * i + l15;
             const uint32_t ro = (uint32_t)r * (uint32_t)g.N * 2u;
+            f32x4 v[TN];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) v[j] = acc[i][j] + bias[j];
+            if constexpr (EPI == kEpiGainSquares) {
+                // A lane has 4 TN numbers of a row, the four quarters of the wave together 16 TN of them: one sum per row and wave.
+                // In one pass with the stores: a pass of its own, which leaves its sums in acc, cost all epilogues of the kernel
+                // up to 40 registers and the 256 x 256 tile 75 spilled ones, whose reloads wait for every tile load in flight.
+                float q = 0.0f;
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    if (FULL || col0 + 16 * j < g.N) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) q += v[j][e] * v[j][e];
+                    }
+                    v[j] *= gain[j];
+                }
+                const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(q), __float_as_uint(q), false, false);
+                q = __uint_as_float(h[0]) + __uint_as_float(h[1]);
+                const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(q), __float_as_uint(q), false, false);
+                q = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+                if (lq == 0 && r < rows) g.squares[(size_t)(unsigned)(col0 / (16 * TN)) * (unsigned)g.M + (unsigned)(row0 + r)] = q;
+            }
 #pragma unroll
             for (int j = 0; j + 1 < TN; j += 2) {
                 uint32_t a0, a1, b0, b1;
-                pack(value(i, j), a0, a1);
-                pack(value(i, j + 1), b0, b1);
+                pack(v[j], a0, a1);
+                pack(v[j + 1], b0, b1);
                 const auto r0 = __builtin_amdgcn_permlane16_swap(a0, b0, false, false);
                 const auto r1 = __builtin_amdgcn_permlane16_swap(a1, b1, false, false);
                 uint4 u; u.x = r0[0]; u.y = r1[0]; u.z = r0[1]; u.w = r1[1];
@@ -475,7 +477,7 @@ __device__ __forceinline__ void store_tile(const GemmArgs& g, void* outp, f32x4 
             }
             if constexpr (TN % 2) {
                 uint32_t a0, a1;
-                pack(value(i, TN - 1), a0, a1);
+                pack(v[TN - 1], a0, a1);
                 const int gcol = col0 + 16 * (TN - 1) + 4 * lq;
                 uint2 u; u.x = a0; u.y = a1;
                 if (FULL || (r < rows && gcol < g.N)) *reinterpret_cast<uint2*>(base + (ro + (uint32_t)gcol * 2u)) = u;

@@ -4,6 +4,7 @@ declares, sizes its buffers as documented and rejects bad arguments before touch
 import ctypes as C
 import os
 import re
+import struct
 import subprocess
 
 import pytest
@@ -304,3 +305,40 @@ extern "C" int ranges(int H, int T, int pieces, int max_heads, int* out, int cap
             tokens = [(t0, tn) for h0, hn, t0, tn in got if (h0, hn) == h]
             assert tokens[0][0] == 0 and all(a + b == c for (a, b), (c, _) in zip(tokens, tokens[1:])) and sum(tokens[-1]) == T
         assert (n == 1) == (H * T * pieces <= 1 << 31 and H <= max_heads)
+
+
+# ------------------------------------------------------------------------------------------ what the compiler made of the kernels
+BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def kernel_metadata():
+    """The metadata (registers, scratch) that the compiler left in the library's gfx950 code objects, by kernel name."""
+    msgpack = pytest.importorskip("msgpack")
+    data = open(binding.LIB_PATH, "rb").read()
+    kernels, at = {}, data.find(BUNDLE)
+    while at >= 0:
+        n, p = struct.unpack_from("<Q", data, at + len(BUNDLE))[0], at + len(BUNDLE) + 8
+        for _ in range(n):
+            offset, size, chars = struct.unpack_from("<QQQ", data, p)
+            if b"gfx950" in data[p + 24:p + 24 + chars]:
+                elf = data[at + offset:at + offset + size]
+                sections, = struct.unpack_from("<Q", elf, 40)
+                entry, count = struct.unpack_from("<HH", elf, 58)
+                for s in range(count):
+                    kind, _, _, start = struct.unpack_from("<IQQQ", elf, sections + s * entry + 4)
+                    if kind == 7:                          # a note: the name's and the description's length, type, "AMDGPU", msgpack
+                        name, desc, _ = struct.unpack_from("<III", elf, start)
+                        first = start + 12 + (name + 3) // 4 * 4
+                        for k in msgpack.unpackb(elf[first:first + desc])["amdhsa.kernels"]:
+                            kernels[k[".name"]] = k
+            p += 24 + chars
+        at = data.find(BUNDLE, at + len(BUNDLE))
+    return kernels
+
+
+def test_matrix_kernels_spill_nothing(lib):
+    """A spilled register is reloaded from memory, and the wait for it is a wait for every tile load in flight."""
+    found = [(n, k) for n, k in kernel_metadata().items() if "gemm_alt64_kernel" in n]
+    assert len(found) == 18
+    for name, k in found:
+        assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_spill_count"])
