@@ -230,9 +230,15 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
     }
     const int tail_tile = (kv_len % KT) ? n_tiles - 1 : -1;           // the tile with slots past kv_len, if any
 
-    // ---- this lane's query (column of S^T)
-    const int q_in_chunk = qt * QT + wave * 32 + l31;
-    const size_t q_row = (size_t)(unsigned)b * (unsigned)a.L + (unsigned)min(q_in_chunk, a.L - 1);
+    // ---- this lane's query (column of S^T) and its row.  Formed anew where they are needed, in front of the loop, for the
+    // scale and at the end: kept across the loop they are spilled (256 registers), and the reloads wait for the tile loads.
+    auto own_lane = [&]() {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        return t & 63;
+    };
+    auto query_in_chunk = [&]() { return qt * QT + wave * 32 + (own_lane() & 31); };
+    auto row_of = [&](int in_chunk) { return (size_t)(unsigned)b * (unsigned)a.L + (unsigned)min(in_chunk, a.L - 1); };
 
     // ---- The wave's 32 queries, through LDS (fetched as fragments they would be 8 loads of 32 pieces of 32 bytes each).  Eight
     // waves: behind the stages.  Four waves, two workgroups per unit: in the second stages, which are free until then.
@@ -240,7 +246,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
         (NW == 8 ? smem_raw + 2 * (K_TILE_BYTES + V_TILE_BYTES) + wave * 8192 : (wave < 2 ? k_stage + K_TILE_BYTES : v_stage + V_TILE_BYTES) + (wave & 1) * 8192);
     bf16x8 qf[D / 16];           // this lane's query: its eight d-step fragments
     if (STAGED) load_queries<8>(a, b, h, qt * QT + wave * 32, 0, lane, q_stage, C);
-    else fetch_queries(qf, a, q_row, h, lh, C);
+    else fetch_queries(qf, a, row_of(query_in_chunk()), h, lh, C);
 
     // ---- direct loads.  A wave load fills 1 KB of LDS in lane order: 4 K rows or 8 V^T rows.  Wave w issues
     // loads w, w + NW, ... of each tile; the XOR term of a lane's chunk is the same for all of them.
@@ -461,7 +467,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
         }
         qk_half(s_a, k_stage, 0, nothing);
         qk_half(s_a, k_stage, 1, nothing);
-        scale_log2e = query_scale(a, softmax_scale, q_row, lh);
+        scale_log2e = query_scale(a, softmax_scale, row_of(query_in_chunk()), lh);
         if (zero_queries(qf, scale_log2e, softmax_scale)) {
             qk_half(s_a, k_stage, 0, nothing);
             qk_half(s_a, k_stage, 1, nothing);
@@ -490,6 +496,8 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
     wait_loads();
     const float l_tot = l_run + __shfl_xor(l_run, 32, kWave);
     const float inv_l = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
+    const int q_in_chunk = query_in_chunk();
+    const size_t q_row = row_of(q_in_chunk);
     if (a.splits == 1) {
         bf16* op = a.o + q_row * C + h * D + 8 * lh;
 #pragma unroll
@@ -519,7 +527,7 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
                 *reinterpret_cast<f32x4*>(op + db * 32 + 8 * g) = w;
             }
         }
-        if (lh == 0) {
+        if (own_lane() < 32) {
             float* ml = a.part_ml + (((size_t)split * rows + q_row) * a.H + h) * 2;
             ml[0] = m_run;
             ml[1] = l_tot;

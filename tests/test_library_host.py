@@ -338,7 +338,8 @@ def kernel_metadata():
 
 def test_matrix_kernels_spill_nothing(lib):
     """A spilled register is reloaded from memory, and the wait for it is a wait for every tile load in flight."""
-    found = [(n, k) for n, k in kernel_metadata().items() if "gemm_alt64_kernel" in n]
-    assert len(found) == 18
+    found = [(n, k) for n, k in kernel_metadata().items()
+             if "gemm_alt64_kernel" in n or "attention_kernel" in n or "attention_ks_kernel" in n]
+    assert len(found) == 18 + 3
     for name, k in found:
         assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_spill_count"])
