@@ -200,6 +200,8 @@ __device__ __forceinline__ bool zero_queries(bf16x8 (&qf)[D / 16], float& scale,
     return true;
 }
 
+constexpr int kNoMemory = 1;             // sched_barrier: instructions without memory access may cross
+
 // STAGED: the queries go through LDS by direct loads, which need a multiple of 16 bytes.
 template <int NW, bool STAGED>
 __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_scale) {
@@ -452,10 +454,15 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
     };
 
     if (t0 < t1) {
+        // The wait counts loads: the queries and the first K tile are there when no more are in flight than went out behind
+        // them.  So their order is held here.
+        __builtin_amdgcn_sched_barrier(kNoMemory);
         load_k(t0, 0);
+        __builtin_amdgcn_sched_barrier(kNoMemory);
         load_v(t0, 0);
         if (NW == 8) load_k(min(t0 + 1, t1 - 1), 1);
-        __builtin_amdgcn_s_waitcnt(0x0F70 | ((NW == 8 ? 2 : 1) * LPT));      // the queries and the first K tile are there
+        __builtin_amdgcn_sched_barrier(kNoMemory);
+        __builtin_amdgcn_s_waitcnt(0x0F70 | ((NW == 8 ? 2 : 1) * LPT));
         barrier();
         if (STAGED) read_queries(qf, q_stage, l31, lh);
         if (NW == 4) {
@@ -766,10 +773,14 @@ __device__ __forceinline__ void attention_ks_body(const AttnArgs& a, float softm
         __builtin_amdgcn_sched_barrier(0);
     };
 
+    // in this order (see attention_body): the wait counts what went out behind the queries and the first K tile
+    __builtin_amdgcn_sched_barrier(kNoMemory);
     load_k(0, 0);
+    __builtin_amdgcn_sched_barrier(kNoMemory);
     load_v(0, 0);
     load_k(1, 1);
-    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * LPT));          // the queries and the first K tile are there
+    __builtin_amdgcn_sched_barrier(kNoMemory);
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * LPT));
     barrier();
     if (STAGED) read_queries(qf, q_stage + qb * 8192, l31, lh);
     qk_half(s_a, 0, 0, nothing);
