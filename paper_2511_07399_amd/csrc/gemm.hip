@@ -1192,12 +1192,16 @@ namespace {
 // owns a row, adds the parts in k order, applies bias, gate and residual, stores the new fp32 row, and normalises it
 // from the registers: one launch and one read of x less than reduce + LayerNorm.  (One row per workgroup: the pass
 // reads splitk + 1 fp32 rows per output row, and with fewer, fatter workgroups it ran at 2.5 TB/s.)
-// On one chunk the pass is a chain of latencies, so all loads stand in straight-line code: behind a branch (columns past the
-// end, an absent bias) or in a loop over the parts each waits for the one before.  Columns past the end fetch the last piece,
-// an absent operand a piece that is there, and neither is used.  1024 x 1536 in four parts 10.2 -> 9.3 us (4.4 TB/s), 1024 x 5120
-// in three 27.0 -> 24.6.
+// On one chunk the pass is a chain of latencies, so the loads stand in straight-line code: behind a branch (columns past the
+// end) or in a loop over the parts each waits for the one before.  Columns past the end fetch the last piece, which is not
+// used; gate and modulation are there or not at compile time.  Rows of up to 3072 columns fetch everything at once; wider
+// ones form the new row first and fetch the LayerNorm's rows under its sums, so that two to four workgroups fit a unit.
+// Measured, behind branches -> everything at once at every width, absent operands too -> this: 512 x 5120 in three parts 14.7
+// -> 13.0 -> 12.2 us, 1024 x 5120 in three 23.2 -> 23.3 -> 21.6, 1024 x 4096 in four 18.8 -> 27.2 -> 19.1, 1024 x 6144 in three
+// 23.9 -> 33.8 -> 24.0, 1024 x 1536 in four 8.9 -> 9.1 -> 8.4; at most 5 % slower than the first at any width, rows and parts that
+// are planned.
 // SP: parts, known to the compiler where the planner picks them often (0: any number, a part of the whole row at a time).
-template <int NV, int SP>
+template <int NV, int SP, bool GATED, bool MODULATED>
 __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(GemmArgs g, int splitk, LnArgs ln) {
     __shared__ float part[4][2];
     const int lane = threadIdx.x & 63;
@@ -1211,14 +1215,10 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(GemmArgs g, int s
     const int stream = row / g.rows_per_gate;
     const int ln_stream = row / ln.rows_per_stream;
     const float pivot = xrow[0];                          // a value near the row's mean: read before the row is rewritten
-    f32x4 v[NV], sc[NV], sh[NV];
-    const bool has_bias = g.bias != nullptr, gated = g.epilogue == kEpiGatedResidual, modulated = ln.scale_b != nullptr;
+    const bool has_bias = g.bias != nullptr;
     const float* const bias = has_bias ? g.bias : ln.scale_a;
-    const float* const gate_a = gated ? g.gate_a : ln.scale_a;
-    const float* const gate_b = gated ? g.gate_b + (size_t)stream * g.gate_b_stride : ln.scale_a;
-    const float* const scale_b = modulated ? ln.scale_b + (size_t)ln_stream * ln.b_stride : ln.scale_a;
-    const float* const shift_b = modulated ? ln.shift_b + (size_t)ln_stream * ln.b_stride : ln.shift_a;
     constexpr int kEarly = SP > 0 ? SP : 1;
+    constexpr bool kLate = NV > 3;                        // the LayerNorm's rows under the sums
     f32x4 p[NV][kEarly], xv[NV];
     int col[NV];
 #pragma unroll
@@ -1229,16 +1229,31 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(GemmArgs g, int s
         xv[i] = *reinterpret_cast<const f32x4*>(xrow + c);
     }
     __builtin_amdgcn_sched_barrier(0);
-    f32x4 ba[NV], ga[NV], sca[NV], sha[NV], scb[NV], shb[NV];
+    f32x4 ba[NV], ga[NV];
+    auto load_epilogue = [&]() {
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-        const int c = col[i];
-        ba[i] = *reinterpret_cast<const f32x4*>(bias + c);
-        ga[i] = *reinterpret_cast<const f32x4*>(gate_a + c) + *reinterpret_cast<const f32x4*>(gate_b + c);
-        sca[i] = *reinterpret_cast<const f32x4*>(ln.scale_a + c);
-        sha[i] = *reinterpret_cast<const f32x4*>(ln.shift_a + c);
-        scb[i] = *reinterpret_cast<const f32x4*>(scale_b + c);
-        shb[i] = *reinterpret_cast<const f32x4*>(shift_b + c);
+        for (int i = 0; i < NV; ++i) {
+            ba[i] = *reinterpret_cast<const f32x4*>(bias + col[i]);
+            if (GATED)
+                ga[i] = *reinterpret_cast<const f32x4*>(g.gate_a + col[i]) +
+                        *reinterpret_cast<const f32x4*>(g.gate_b + (size_t)stream * g.gate_b_stride + col[i]);
+        }
+    };
+    f32x4 sca[NV], sha[NV], scb[NV], shb[NV];
+    auto load_norm = [&]() {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            sca[i] = *reinterpret_cast<const f32x4*>(ln.scale_a + col[i]);
+            sha[i] = *reinterpret_cast<const f32x4*>(ln.shift_a + col[i]);
+            if (MODULATED) {
+                scb[i] = *reinterpret_cast<const f32x4*>(ln.scale_b + (size_t)ln_stream * ln.b_stride + col[i]);
+                shb[i] = *reinterpret_cast<const f32x4*>(ln.shift_b + (size_t)ln_stream * ln.b_stride + col[i]);
+            }
+        }
+    };
+    if (!kLate) {
+        load_epilogue();
+        load_norm();
     }
     if constexpr (SP == 0) {
         for (int sp = 1; sp < splitk; ++sp) {
@@ -1249,16 +1264,23 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(GemmArgs g, int s
             for (int i = 0; i < NV; ++i) p[i][0] += next[i];
         }
     }
+    if (kLate) load_epilogue();
+    f32x4 v[NV];
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
+#pragma clang fp contract(off)                            // gate times sum is rounded before x joins, as in the other passes
         f32x4 acc = p[i][0];
 #pragma unroll
         for (int sp = 1; sp < kEarly; ++sp) acc += p[i][sp];
         acc = has_bias ? acc + ba[i] : acc;
-        acc = gated ? acc * ga[i] : acc;
+        acc = GATED ? acc * ga[i] : acc;
         v[i] = xv[i] + acc;
-        sc[i] = modulated ? (sca[i] + scb[i]) + 1.0f : sca[i];
-        sh[i] = modulated ? sha[i] + shb[i] : sha[i];
+        if (kLate) asm volatile("" : "+v"(v[i]));         // formed here, not where it is stored: its operands' registers are free
+    }
+    if (kLate) {                                          // on its way under the sums
+        __builtin_amdgcn_sched_barrier(0);
+        load_norm();
+        __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();                                      // every thread of the row has read the pivot before x changes
     float sum = 0.0f, sq = 0.0f;
@@ -1322,14 +1344,41 @@ __global__ __launch_bounds__(256) void splitk_reduce_ln_kernel(GemmArgs g, int s
     for (int i = 0; i < NV; ++i) {
         const int idx = t + 256 * i;
         if (idx < nvec) {
+            const f32x4 sc = MODULATED ? (sca[i] + scb[i]) + 1.0f : sca[i], sh = MODULATED ? sha[i] + shb[i] : sha[i];
             bf16x4 o;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16)((v[i][e] - mean) * rstd * sc[i][e] + sh[i][e]);
+            for (int e = 0; e < 4; ++e) o[e] = (bf16)((v[i][e] - mean) * rstd * sc[e] + sh[e]);
             *reinterpret_cast<bf16x4*>(op + idx * 4) = o;
         }
     }
 }
 }  // namespace
+
+// The pass above for rows of N columns (null: too many), NV = float4 values per thread.
+typedef void (*ReduceLnKernel)(GemmArgs, int, LnArgs);
+template <int NV, bool GATED, bool MODULATED>
+static ReduceLnKernel reduce_ln_kernel_of_parts(int splitk) {
+    switch (splitk) {
+        case 2: return splitk_reduce_ln_kernel<NV, 2, GATED, MODULATED>;
+        case 3: return splitk_reduce_ln_kernel<NV, 3, GATED, MODULATED>;
+        case 4: return splitk_reduce_ln_kernel<NV, 4, GATED, MODULATED>;
+    }
+    return splitk_reduce_ln_kernel<NV, 0, GATED, MODULATED>;
+}
+template <bool GATED, bool MODULATED>
+static ReduceLnKernel reduce_ln_kernel(int N, int splitk) {
+    switch ((N + 1023) / 1024) {
+        case 1: return reduce_ln_kernel_of_parts<1, GATED, MODULATED>(splitk);
+        case 2: return reduce_ln_kernel_of_parts<2, GATED, MODULATED>(splitk);
+        case 3: return reduce_ln_kernel_of_parts<3, GATED, MODULATED>(splitk);
+        case 4: return reduce_ln_kernel_of_parts<4, GATED, MODULATED>(splitk);
+        case 5: return reduce_ln_kernel_of_parts<5, GATED, MODULATED>(splitk);
+        case 6: return splitk_reduce_ln_kernel<6, 0, GATED, MODULATED>;
+        case 7: return splitk_reduce_ln_kernel<7, 0, GATED, MODULATED>;
+        case 8: return splitk_reduce_ln_kernel<8, 0, GATED, MODULATED>;
+    }
+    return nullptr;
+}
 
 // The plan of a call: two products of one launch (w2) make no split.
 static TilePlan plan_of(const GemmArgs& g) {
@@ -1374,26 +1423,15 @@ static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln
         else e = p.tm == 1 ? launch_tn<1, 2>(g, p.tn, splitk, s) : launch_tn<2, 2>(g, p.tn, splitk, s);
     }
     if (e != hipSuccess || splitk == 1 || attributes_only() || part == 1) return e;
-    const int nv = (g.N + 1023) / 1024;                 // float4 values per thread with 256 threads per row
-    if (ln != nullptr && (g.epilogue == kEpiGatedResidual || g.epilogue == kEpiResidual) && nv <= 8) {
-        const dim3 grid(g.M), block(256);
-#define SDV2_REDUCE(NV, SP) hipLaunchKernelGGL((splitk_reduce_ln_kernel<NV, SP>), grid, block, 0, s, g, splitk, *ln)
-#define SDV2_REDUCE_PARTS(NV)                  \
-    switch (splitk) {                          \
-        case 2: SDV2_REDUCE(NV, 2); break;     \
-        case 3: SDV2_REDUCE(NV, 3); break;     \
-        case 4: SDV2_REDUCE(NV, 4); break;     \
-        default: SDV2_REDUCE(NV, 0);           \
-    }
-        if (nv <= 1) { SDV2_REDUCE_PARTS(1) }
-        else if (nv <= 2) { SDV2_REDUCE_PARTS(2) }
-        else if (nv <= 3) { SDV2_REDUCE_PARTS(3) }
-        else if (nv <= 5) { SDV2_REDUCE_PARTS(5) }
-        else { SDV2_REDUCE(8, 0); }
-#undef SDV2_REDUCE_PARTS
-#undef SDV2_REDUCE
-        *ln_done = true;
-        return hipGetLastError();
+    if (ln != nullptr && (g.epilogue == kEpiGatedResidual || g.epilogue == kEpiResidual)) {
+        const bool gated = g.epilogue == kEpiGatedResidual, modulated = ln->scale_b != nullptr;
+        const ReduceLnKernel kernel = gated ? (modulated ? reduce_ln_kernel<true, true>(g.N, splitk) : reduce_ln_kernel<true, false>(g.N, splitk))
+                                            : (modulated ? reduce_ln_kernel<false, true>(g.N, splitk) : nullptr);     // no block asks for the last
+        if (kernel != nullptr) {
+            hipLaunchKernelGGL(kernel, dim3(g.M), dim3(256), 0, s, g, splitk, *ln);
+            *ln_done = true;
+            return hipGetLastError();
+        }
     }
     const size_t n = (size_t)g.M * (g.N >> 2);
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, g, splitk);

@@ -615,3 +615,29 @@ def test_cross_query_rows_beyond_single_precision(waves, splits, text, tile):
         for name in ("gemm_tile", "attn_waves", "attn_splits"):
             binding.tuning_set(name, None)
     assert max_rel_err(xg[0].cpu().numpy(), want) <= TOL_X
+
+
+@pytest.mark.parametrize("heads", [3, 8, 12, 17, 24, 26, 32, 33, 40, 41, 48, 52, 56, 60, 64])
+def test_sum_of_parts_with_layernorm_at_every_width(heads):
+    """Two blocks with every product split in 2, 3, 4 and 6 parts of k against the same blocks with whole products, whose
+    LayerNorms are passes of their own: the norm after a gated product without modulation (out-proj), after an ungated one
+    with it (cross-out) and after a gated one with it (FFN-2 of the first block).  Sums in another order round the bf16
+    activations between the kernels differently here and there, by 2^-9 each: bar 1e-2 of the largest update."""
+    wl = wk.Workload("widths", 128 * heads, heads, 768, 5, 7, 1, 1, 2, 33, 1, 2, (1,), 1)
+    out = {}
+    x = wk.chunk_input(wl, 0).to(DEV).reshape(1, wl.L, wl.C)
+    tv = wk.timestep_vector(wl, 0).to(DEV).reshape(1, wl.C).contiguous()
+    for parts in (1, 2, 3, 4, 6):
+        binding.tuning_set("gemm_tile", "d15,%d" % parts if parts > 1 else "d15")
+        try:
+            gpu = GpuRunner(wl, n_streams=1, weight_device=DEV, edit=visible_branches(wl, g1=1.0, g2=1.0, sc=1.0))
+            out[parts] = x.clone()
+            gpu.denoise(out[parts], [(0, 0, 1, 1)], tvec=tv)
+            torch.cuda.synchronize()
+            gpu.close()
+        finally:
+            binding.tuning_set("gemm_tile", None)
+    size = (out[1] - x).abs().max()
+    assert size > 0.1
+    for parts in (2, 3, 4, 6):
+        assert (out[parts] - out[1]).abs().max() <= 1e-2 * size, parts
