@@ -314,7 +314,12 @@ __global__ __launch_bounds__(256) void rope_append_kernel(RopeAppendArgs a, int 
 }
 
 // ------------------------------------------------------------------ append of rows without rotation
-template <int IT>
+// NORM: text keys, RMSNorm-ed on the way, their gains fetched with the row instead of after its sum; final keys have none.
+// Beyond 40 heads only the first gains are, the others four steps ahead, and the row stays in 16 bits across its sum: with all
+// of them, and with registers for gains in the append of final keys too, a workgroup had a unit to itself (282 registers).
+// Gains after the sum -> all ahead for either kind -> this: text of 1560 x 48 heads 14.9 -> 21.2 -> 14.1 us, of 512 x 64 heads
+// 14.0 -> 8.9 -> 8.6; final keys of 1024 x 64 heads 11.4 -> 12.7 -> 10.6 us, of 1024 x 12 heads 3.9 -> 3.7 -> 3.8.
+template <int IT, bool NORM>
 __global__ __launch_bounds__(256) void plain_append_kernel(PlainAppendArgs a, int k_blocks) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -328,13 +333,16 @@ __global__ __launch_bounds__(256) void plain_append_kernel(PlainAppendArgs a, in
 #pragma unroll
         for (int it = 0; it < IT; ++it) kv[it] = *reinterpret_cast<const bf16x8*>(a.k + (size_t)row * C + column(it));
         const int slot = slot_of(row, a.st.ring0, a.S, a.W);
-        if (a.g_k != nullptr) {
-            f32x4 gain[IT][2];                               // on their way with the row, not after its sum
+        constexpr int kAhead = !NORM ? 0 : IT <= 10 ? IT : 4;
+        f32x4 gain[IT][2];
+        auto fetch_gain = [&](int it) {
+            gain[it][0] = *reinterpret_cast<const f32x4*>(a.g_k + column(it));
+            gain[it][1] = *reinterpret_cast<const f32x4*>(a.g_k + column(it) + 4);
+        };
+        float r = 1.0f;
+        if constexpr (NORM) {
 #pragma unroll
-            for (int it = 0; it < IT; ++it) {
-                gain[it][0] = *reinterpret_cast<const f32x4*>(a.g_k + column(it));
-                gain[it][1] = *reinterpret_cast<const f32x4*>(a.g_k + column(it) + 4);
-            }
+            for (int it = 0; it < kAhead; ++it) fetch_gain(it);
             __builtin_amdgcn_sched_barrier(0);
             float sq = 0.0f;
 #pragma unroll
@@ -342,20 +350,26 @@ __global__ __launch_bounds__(256) void plain_append_kernel(PlainAppendArgs a, in
                 if (hl + 4 * it < a.H)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) sq += (float)kv[it][e] * (float)kv[it][e];
-            const float r = rsqrtf(wave_sum(sq) / (float)C + a.eps);
+            r = rsqrtf(wave_sum(sq) / (float)C + a.eps);
+            if (kAhead < IT)
 #pragma unroll
-            for (int it = 0; it < IT; ++it)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    kv[it][e] = (bf16)((float)kv[it][e] * r * gain[it][0][e]);
-                    kv[it][e + 4] = (bf16)((float)kv[it][e + 4] * r * gain[it][1][e]);
-                }
+                for (int it = 0; it < IT; ++it) asm volatile("" : "+v"(kv[it]));        // the row stays in 16 bits across its sum
         }
         if (lane == 0 && a.st.ids != nullptr) a.st.ids[slot] = a.st.g0 + row;
 #pragma unroll
         for (int it = 0; it < IT; ++it) {
             const int h = hl + 4 * it;
-            if (h < a.H) *reinterpret_cast<bf16x8*>(a.st.k_cache + ((size_t)h * a.st.cap + slot) * kHeadDim + c0) = kv[it];
+            if (NORM && it + kAhead < IT) fetch_gain(it + kAhead);
+            if (h < a.H) {
+                if constexpr (NORM) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        kv[it][e] = (bf16)((float)kv[it][e] * r * gain[it][0][e]);
+                        kv[it][e + 4] = (bf16)((float)kv[it][e + 4] * r * gain[it][1][e]);
+                    }
+                }
+                *reinterpret_cast<bf16x8*>(a.st.k_cache + ((size_t)h * a.st.cap + slot) * kHeadDim + c0) = kv[it];
+            }
         }
         // a cache may have more heads than a model's 64 (final keys only: text keys belong to a model)
         for (int h = hl + 4 * IT; h < a.H; h += 4)
@@ -517,7 +531,7 @@ hipError_t launch_rope_append(const RopeAppendArgs& a, hipStream_t s) {
 hipError_t launch_plain_append(const PlainAppendArgs& a, hipStream_t s) {
     const int k_blocks = (a.n + 3) / 4;
     const int v_blocks = ((a.n + VT_TOK - 1) / VT_TOK) * a.H;
-#define F(IT) hipLaunchKernelGGL(plain_append_kernel<IT>, dim3(k_blocks + v_blocks), dim3(256), 0, s, a, k_blocks)
+#define F(IT) hipLaunchKernelGGL((a.g_k != nullptr ? plain_append_kernel<IT, true> : plain_append_kernel<IT, false>), dim3(k_blocks + v_blocks), dim3(256), 0, s, a, k_blocks)
     SDV2_BY_STEPS(a.H, F);
 #undef F
     return hipGetLastError();

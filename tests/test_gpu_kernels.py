@@ -195,6 +195,12 @@ def test_text_keys_and_values_in_one_launch(heads, tokens):
     assert max_rel_err(f64(K), f64(k)) < 1e-2 and max_rel_err(f64(V), f64(v)) < 1e-2
 
 
+# heads in every step of the append kernel's widths, beyond 40 with gains that come a few steps ahead of their use
+@pytest.mark.parametrize("heads", [7, 16, 21, 29, 41, 44, 53, 63, 64])
+def test_text_keys_of_every_width(heads):
+    test_text_keys_and_values_in_one_launch(heads, 35)
+
+
 @pytest.mark.parametrize("tile", [None, "1,4"] + ["d%d" % i for i in range(1, 19)])
 def test_gemm_adds_the_bias_to_the_finished_sum(tile):
     """A bias 25 times the product's size must not coarsen the sum of the products: fp32 output against 64 bits.  One
