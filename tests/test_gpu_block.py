@@ -542,6 +542,33 @@ def test_cross_query_norm_of_every_tile(tile):
     finally:
         binding.tuning_set("gemm_tile", None)
     assert max(res["x_err"]) <= 2e-2, res["x_err"]
+    assert cross_update_share(wl) > 0.5
+
+
+def cross_update_share(wl):
+    """How much of the block's largest output the cross-attention adds, by the oracle: the bar is relative to that output."""
+    ora, dbg = OracleRunner(wl, n_layers=1, n_streams=1, edit=cross_attention_alone), {}
+    out = ora.block(0, wk.chunk_input(wl, 0).double().numpy(), np.zeros((6, wl.C)), (0, 0, 1, 1), debug=dbg)
+    return np.abs(dbg["upd_cross"]).max() / np.abs(out).max()
+
+
+# The forms of attention that divide by the root of those sums: 128 and 256 queries per workgroup, the key-split form, and key
+# ranges in parts, where each part scales its scores and the merge compares reference points in that scale.  Texts whose
+# capacity is and is not a multiple of 128, with and without a tail; projections of 24, 36 and 72 pieces.
+@pytest.mark.parametrize("tile", ["d1", "d15", "d18"])
+@pytest.mark.parametrize("waves,splits,text", [(4, 1, 192), (8, 1, 77), (2, 1, 300), (4, 2, 300), (8, 2, 320), (4, 5, 700), (8, 3, 450)])
+def test_cross_query_norm_in_every_form_of_attention(waves, splits, text, tile):
+    wl = wk.Workload("cross", 1152, 9, 128, 13, 21, 1, 1, 2, text, 2, 1, (1,), 1)
+    binding.tuning_set("gemm_tile", tile)
+    binding.tuning_set("attn_waves", waves)
+    binding.tuning_set("attn_splits", splits)
+    try:
+        res = run_stream_both(wl, 1, edit=cross_attention_alone, check_cache=False)
+    finally:
+        for name in ("gemm_tile", "attn_waves", "attn_splits"):
+            binding.tuning_set(name, None)
+    assert max(res["x_err"]) <= TOL_X, res["x_err"]
+    assert cross_update_share(wl) > 0.5
 
 
 @pytest.mark.parametrize("step", [False, True])
