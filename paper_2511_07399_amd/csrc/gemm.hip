@@ -374,6 +374,10 @@ typedef __attribute__((address_space(3))) unsigned char* lds_byte_ptr;     // 32
 __device__ __forceinline__ void load_to_lds_b128(__amdgpu_buffer_rsrc_t src, uint32_t lane_off, uint32_t wave_off, lds_byte_ptr dst) {
     __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (lds_void_ptr)dst, 16, (int)lane_off, (int)wave_off, 0, 0);
 }
+// The same from a 64-bit address.
+__device__ __forceinline__ void load_to_lds_b128(const unsigned char* src, lds_byte_ptr dst) {
+    __builtin_amdgcn_global_load_lds(src, (lds_void_ptr)dst, 16, 0, 0);
+}
 // A buffer of plain bytes (word 3: 32-bit data, no swizzle), below 4 GiB.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t byte_buffer(const void* p, uint32_t bytes) {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
@@ -599,6 +603,12 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     const int id = loads_a ? wave : wave - NL;
     const __amdgpu_buffer_rsrc_t buf0 = byte_buffer(loads_a ? g.a : g.w, (uint32_t)(loads_a ? g.M : g.N) * (uint32_t)g.K * 2u);
     const __amdgpu_buffer_rsrc_t buf1 = byte_buffer(g.w, (uint32_t)g.N * (uint32_t)g.K * 2u);
+    // Loads through a buffer descriptor spare the vector additions of 64-bit addresses (51 x 896 x 896 on the 32 x 32 tile 5.1 us
+    // without them, 4.6 with; 2048 x 1024 x 1024 on 128 x 64 10.2 and 9.6).  Not where a wave fetches one operand and W has more
+    // stages than A: there they are slower (1037 x 15104 x 2560 on the 192 x 192 tile 84.6 us with, 80.9 without; 707 x 4992 x
+    // 1664 on 128 x 128 18.0 and 17.5; the 192 x 256 tile 1 %).
+    constexpr bool kBuffer = !(ROLES && NSW > NSA);
+    const unsigned char* const base0 = reinterpret_cast<const unsigned char*>(loads_a ? g.a : g.w);
     const lds_byte_ptr lds_w = (lds_byte_ptr)smem_w, lds0 = loads_a ? (lds_byte_ptr)smem : lds_w;
     const uint32_t k_first = (uint32_t)kt0 * (BK * 2);      // byte offset in a row of this part's first k tile
     const int bytes0 = loads_a ? SA : SW, stages0 = loads_a ? NSA : NSW;
@@ -663,7 +673,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
     };
     auto load_group = [&](const __amdgpu_buffer_rsrc_t& buf, uint32_t src, uint32_t o, bool may_be_short, lds_byte_ptr dst) {
         if constexpr (kScalarRows) load_to_lds_b128(buf, may_be_short && o == last_row_off0 ? lane_off_last : lane_off, src + o, dst);
-        else load_to_lds_b128(buf, o, src, dst);
+        else if constexpr (kBuffer) load_to_lds_b128(buf, o, src, dst);
+        else load_to_lds_b128(base0 + src + o, dst);
     };
     auto load = [&](auto lc) {
         constexpr int l = decltype(lc)::value;
