@@ -111,6 +111,13 @@ bool cache_cfg_ok(const sdv2_cache_cfg* c, const char** why) {
     return *why == nullptr;
 }
 
+// Whether a layer's weights have left the memory-side cache (256 MB; measured: up to 240 MB in turn stay, from 320 MB on
+// nothing does) when a pass over all layers comes back to them.
+bool weights_cold(const sdv2_model_cfg* c) {
+    const size_t C = (size_t)c->C, layer = (8 * C * C + 2 * C * (size_t)c->ffn_dim) * sizeof(bf16);
+    return layer * c->n_layers > ((size_t)224 << 20);
+}
+
 void cache_geometry(const sdv2_cache_cfg* c, int* cap, size_t* k_bytes, size_t* ids_bytes, size_t* unit) {
     *cap = (int)align_up((size_t)c->sink_tokens + c->window_tokens, 64);
     *k_bytes = (size_t)c->n_heads * *cap * SDV2_HEAD_DIM * sizeof(bf16);
@@ -702,6 +709,7 @@ int32_t sdv2_text_kv_prepare(const sdv2_model_cfg* cfg, const sdv2_block_weights
     g.w2 = static_cast<const bf16*>(w->W_cv);
     g.bias2 = w->b_cv;
     g.out2 = vrows;
+    g.cold_weights = weights_cold(cfg);
     HIP_TRY(launch_gemm(g, s), "text K and V gemm");
     HIP_TRY(launch_text_relayout(krows, vrows, w->g_ck, cfg->eps, static_cast<bf16*>(kt_dev), static_cast<bf16*>(vtt_dev), Lt, C,
                                  cfg->n_heads, (int)align_up((size_t)Lt, 64), s),
@@ -958,6 +966,7 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     memset(&g, 0, sizeof(g));
     g.splitk_partials = ws.gemm_floats ? ws.gemm_partials : nullptr;
     g.splitk_floats = ws.gemm_floats;
+    g.cold_weights = weights_cold(cfg);
     g.M = rows;
     g.rows_per_gate = L;
     g.gate_b_stride = 6 * C;

@@ -66,6 +66,51 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 
+// Memory that is read soon, fetched into the memory-side cache (256 MB, in front of HBM, shared by the chip) by workgroups
+// behind a launch's own.
+constexpr int kUnits = 256;           // compute units
+constexpr int kMaxWarmRanges = 4;
+struct WarmRange {
+    const unsigned char* p;           // a multiple of 16; rows of `pitch` bytes (a multiple of 16), of which the first
+    unsigned rows, pitch, columns;    // `columns` columns of 1 KB are fetched
+};
+struct WarmArgs {
+    WarmRange range[kMaxWarmRanges];
+    unsigned ranges;                  // 0: nothing to fetch
+    unsigned blocks;                  // workgroups that share them
+};
+
+// Reads the ranges and drops what it has read: a wave takes 1 KB of a row at a time, columns before rows, so the first part of
+// every row arrives first.  Sixteen loads of a lane are in flight (128 KB of a unit; with eight, 1 % of a step slower).
+__device__ __forceinline__ void warm_memory(const WarmArgs& w, unsigned block) {
+    constexpr unsigned kInFlight = 16;
+    const unsigned lane = threadIdx.x & 63u, waves = blockDim.x >> 6;
+    const unsigned step = w.blocks * waves, wave = __builtin_amdgcn_readfirstlane(block * waves + (threadIdx.x >> 6));
+    for (unsigned n = 0; n < w.ranges; ++n) {
+        const unsigned char* const p = w.range[n].p;
+        const unsigned rows = w.range[n].rows, pitch = w.range[n].pitch, columns = w.range[n].columns;
+        const unsigned dc = step / rows, dr = step - dc * rows;
+        unsigned c = wave / rows, r = wave - c * rows;
+        while (c < columns) {
+            uint4 v[kInFlight];
+#pragma unroll
+            for (unsigned u = 0; u < kInFlight; ++u) {
+                const bool in = c < columns;                          // past the end: the first column of the first row
+                const size_t at = (size_t)(in ? r : 0u) * pitch + min((in ? c : 0u) * 1024u + lane * 16u, pitch - 16u);
+                v[u] = *reinterpret_cast<const uint4*>(p + at);
+                c += dc;
+                r += dr;
+                if (r >= rows) {
+                    r -= rows;
+                    ++c;
+                }
+            }
+#pragma unroll
+            for (unsigned u = 0; u < kInFlight; ++u) asm volatile("" ::"v"(v[u].x), "v"(v[u].y), "v"(v[u].z), "v"(v[u].w));
+        }
+    }
+}
+
 // ---------------------------------------------------------------- launchers (host side)
 enum GemmEpilogue { kEpiBias = 0, kEpiBiasGelu = 1, kEpiGatedResidual = 2, kEpiResidual = 3,
                     kEpiPartial = 4 /* internal: fp32 partial sums of one k part, no bias */,
@@ -95,6 +140,7 @@ struct GemmArgs {
     // kEpiGainSquares: gain [N] and the sums, [pieces][M].
     const float* gain;
     float* squares;
+    bool cold_weights;    // the weights are not in the memory-side cache: each layer has its own, and they exceed it
 };
 hipError_t launch_gemm(const GemmArgs& g, hipStream_t s);
 // The projection in front of an RMSNorm over its N columns with this gain, whose consumer multiplies by the row's factor

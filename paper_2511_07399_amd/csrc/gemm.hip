@@ -19,6 +19,7 @@
 
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 
 namespace sdv2 {
 
@@ -548,7 +549,7 @@ __device__ __forceinline__ void store_wave(const GemmArgs& g, void* outp, f32x4 
 }
 
 template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC>
-__global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m, int splitk) {
+__global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m, int splitk, int own, WarmArgs warm) {
     static_assert(NSW >= NSA && NSA >= 2, "stages");
     constexpr int NW = WM * WN, BK = 64;
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
@@ -566,10 +567,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs 
 
     // ---- the tiles of this workgroup: XCD x owns a contiguous range of tiles, its workgroups take them in turn
     const int tiles = tiles_m * tiles_n, total = tiles * splitk;
-    const int xcd = blockIdx.x & 7, per_xcd = gridDim.x >> 3;
+    const int xcd = blockIdx.x & 7, per_xcd = own >> 3;
     const int per = total >> 3, rem = total & 7;
     const int t_end = per * (xcd + 1) + min(xcd + 1, rem);
     int tile = per * xcd + min(xcd, rem) + (blockIdx.x >> 3);
+    if ((int)blockIdx.x >= own) return warm_memory(warm, blockIdx.x - own);      // behind the launch's own workgroups
     if (tile >= t_end) return;
     int m0, n0, ks = 0;
     auto locate = [&](int id, int& m, int& n) {
@@ -880,7 +882,6 @@ struct TilePlan {
     int dma = 0;          // otherwise: a configuration of gemm_alt64_kernel (tm, tn, pf unused)
     int splitk = 1;       // parts of the k range, each its own workgroup (needs scratch)
 };
-constexpr int kUnits = 256;                   // compute units
 
 // gemm_alt64_kernel addresses an operand, and the output from the first row of a wave's tile (at most 128 rows of fp32), with
 // 32-bit byte offsets per lane: it serves operands below 4 GiB and rows of which that many are below 4 GiB.
@@ -990,6 +991,21 @@ hipError_t launch_tn(const GemmArgs& g, int tn, int splitk, hipStream_t s) {
     X(18, 2, 2, 1, 1, 8, 8, false, 2, 2, 0.245f, 1.09f, 3.14f, 0.53f, 0.19f, 1.0f)   /* 32 x 32, two */
 constexpr int kTileConfigs = 18;
 
+// A launch that gives each compute unit one workgroup of tiles that fit it twice has its weights fetched once in large pieces
+// by workgroups in the second places, about 32 KB each, while its own begin: the k loop asks HBM for 128 bytes of every row at
+// a time, from as many DRAM pages, which costs more than the bytes.  Weights from HBM without and with this (and from the
+// memory-side cache): 1024 x 1536 x 1536 12.8 -> 10.7 us (10.5 and 10.3); 512 x 1536 x 1536 10.3 -> 8.0 (7.4 and 7.6);
+// 1024 x 2048 x 2048 19.1 -> 16.3 (15.5 and 15.8); 1.3B step 6.18 -> 6.03 ms.
+// Text keys and values of 512 x 1536, two products: 16.2 -> 14.7 us a layer.  A workgroup of a larger tile has its unit to
+// itself; fetches in front of its own loads, or in left-over units, gave nothing.  More than 16 MB would take longer than the
+// first k tiles they are to be ahead of; weights that are in the memory-side cache anyway (cold_weights) are left alone.
+constexpr size_t kMostOwnWeights = (size_t)16 << 20;
+template <int PER_UNIT>
+bool fetches_own_weights(const GemmArgs& g, int grid) {
+    return PER_UNIT == 2 && g.cold_weights && grid <= kUnits &&
+           (size_t)g.N * g.K * sizeof(bf16) * (g.w2 != nullptr ? 2 : 1) <= kMostOwnWeights;
+}
+
 template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC, int PER_UNIT>
 hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
@@ -1011,8 +1027,18 @@ hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
     // tile rows that share weight tiles: an XCD's 32 concurrent large tiles then cover 4 x 8 tiles, the shape with the
     // fewest distinct operand rows per k step
     const int group_m = BM >= 192 ? 4 : 8;
-    hipLaunchKernelGGL((gemm_alt64_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>), dim3(grid), dim3(64 * WM * WN), smem, s, g,
-                       tiles_m, tiles_n, group_m, splitk);
+    WarmArgs warm;
+    memset(&warm, 0, sizeof(warm));
+    if (fetches_own_weights<PER_UNIT>(g, grid)) {
+        const unsigned pitch = (unsigned)g.K * 2u, columns = (pitch + 1023u) / 1024u;
+        warm.ranges = g.w2 != nullptr ? 2 : 1;
+        warm.range[0] = WarmRange{reinterpret_cast<const unsigned char*>(g.w), (unsigned)g.N, pitch, columns};
+        if (g.w2 != nullptr) warm.range[1] = WarmRange{reinterpret_cast<const unsigned char*>(g.w2), (unsigned)g.N, pitch, columns};
+        const size_t blocks = (size_t)warm.ranges * g.N * pitch / (32 * 1024);
+        warm.blocks = blocks < kUnits ? (unsigned)blocks : kUnits;
+    }
+    hipLaunchKernelGGL((gemm_alt64_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>), dim3(grid + warm.blocks), dim3(64 * WM * WN), smem, s, g,
+                       tiles_m, tiles_n, group_m, splitk, grid, warm);
     return hipGetLastError();
 }
 

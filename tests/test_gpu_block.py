@@ -668,3 +668,33 @@ def test_sum_of_parts_with_layernorm_at_every_width(heads):
     assert size > 0.1
     for parts in (2, 3, 4, 6):
         assert (out[parts] - out[1]).abs().max() <= 1e-2 * size, parts
+
+
+# Whether launches fetch weights, keys and values ahead of their use depends on how much memory a pass over all layers goes
+# through (model_cfg.n_layers), and must not show in a result: rows and heads of every form of product and attention that has
+# workgroups to spare for it, whole and cut-off ranges, more ranges than there is room for.
+@pytest.mark.parametrize("heads,ffn,grid,frames,window,text,streams", [
+    (1, 128, (3, 5), 1, 2, 1, 1), (4, 640, (7, 9), 2, 3, 77, 3), (12, 8960, (32, 32), 1, 2, 512, 1), (12, 3072, (30, 41), 1, 2, 300, 2),
+    (20, 5248, (31, 33), 1, 3, 64, 1), (23, 2944, (9, 42), 2, 4, 500, 1), (40, 13824, (16, 26), 1, 2, 512, 1), (40, 5120, (32, 32), 1, 6, 400, 1)])
+def test_fetching_ahead_changes_no_result(heads, ffn, grid, frames, window, text, streams):
+    wl = wk.Workload("ahead", 128 * heads, heads, ffn, *grid, frames, 1, window, text, streams, 1, (1,), 1)
+    outs = []
+    for layers in (1, 1_000_000):
+        m = GpuRunner(wl, n_layers=1, n_streams=streams, weight_device=DEV)
+        m.cfg = binding.model_cfg(wl.C, wl.H, wl.F, wl.grid_h, wl.grid_w, wl.L_t, layers, wl.t_dim)
+        kt, vt = (torch.zeros(binding.text_kv_bytes(m.cfg), dtype=torch.uint8, device=DEV) for _ in range(2))
+        ws = torch.empty(binding.text_kv_workspace_bytes(m.cfg), dtype=torch.uint8, device=DEV)
+        binding.text_kv_prepare(m.cfg, m.bw_array[0], wk.text_context(wl, 0).to(DEV, torch.bfloat16), kt, vt, ws)
+        out = [kt, vt]
+        for chunk in range(2):
+            g = torch.Generator(device=DEV).manual_seed(chunk)
+            x = torch.randn((streams, wl.L, wl.C), generator=g, device=DEV)
+            e0 = 0.02 * torch.randn((streams, 6, wl.C), generator=g, device=DEV)
+            m.block(0, x, e0, [(s, chunk * frames, frames, 1) for s in range(streams)])
+            out.append(x)
+        out.append(m.cache_storage.clone())
+        outs.append(out)
+        m.close()
+    for one, many in zip(*outs):
+        assert torch.equal(one, many)
+    assert torch.isfinite(outs[0][-2]).all()
