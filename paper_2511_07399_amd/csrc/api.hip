@@ -111,11 +111,10 @@ bool cache_cfg_ok(const sdv2_cache_cfg* c, const char** why) {
     return *why == nullptr;
 }
 
-// Whether a layer's weights have left the memory-side cache (256 MB; measured: up to 240 MB in turn stay, from 320 MB on
-// nothing does) when a pass over all layers comes back to them.
-bool weights_cold(const sdv2_model_cfg* c) {
-    const size_t C = (size_t)c->C, layer = (8 * C * C + 2 * C * (size_t)c->ffn_dim) * sizeof(bf16);
-    return layer * c->n_layers > ((size_t)224 << 20);
+// Whether what a pass over all layers reads has left the memory-side cache when the next pass comes back to it: 256 MB;
+// measured, up to 240 MB read in turn stay, and from 320 MB on nothing does.
+bool weights_cold(const sdv2_model_cfg* c, size_t elements_per_layer) {
+    return elements_per_layer * sizeof(bf16) * c->n_layers > ((size_t)240 << 20);
 }
 
 void cache_geometry(const sdv2_cache_cfg* c, int* cap, size_t* k_bytes, size_t* ids_bytes, size_t* unit) {
@@ -709,7 +708,7 @@ int32_t sdv2_text_kv_prepare(const sdv2_model_cfg* cfg, const sdv2_block_weights
     g.w2 = static_cast<const bf16*>(w->W_cv);
     g.bias2 = w->b_cv;
     g.out2 = vrows;
-    g.cold_weights = weights_cold(cfg);
+    g.cold_weights = weights_cold(cfg, (size_t)2 * C * C);       // of a prompt for every layer; a step reads more
     HIP_TRY(launch_gemm(g, s), "text K and V gemm");
     HIP_TRY(launch_text_relayout(krows, vrows, w->g_ck, cfg->eps, static_cast<bf16*>(kt_dev), static_cast<bf16*>(vtt_dev), Lt, C,
                                  cfg->n_heads, (int)align_up((size_t)Lt, 64), s),
@@ -872,6 +871,53 @@ void fill_rope_table(const sdv2_model_cfg* cfg, RopeAppendArgs* a) {
         }
 }
 
+// What the units that a launch leaves idle fetch for the launches behind it.  With 1000 rows a product meets each byte of its
+// weights too seldom to hide HBM: a k loop asks it for 128 bytes of every row at a time, and runs slower than from the
+// memory-side cache (1024 rows: 5120 x 5120 61.5 and 51 us, 8960 x 1536 31.0 and 29.2, 4608 x 1536 20.8 and 17.1; the keys and
+// values of the attention behind it: 36 and 30 us).  So the attention kernels' idle units fetch the next products' weights, and
+// the QKV product's the keys and values.  With the products that fetch their own (fetches_own_weights): 1.3B step 6.12 -> 5.81
+// ms, 14B step 27.9 -> 27.6 (28.6 -> 28.2 on another), four rows of the 1.3B model 14.88 -> 14.61 (15.14 -> 15.10); of some 50
+// random models and batches none is slower by more than runs differ.
+// Measured and left out: more than 56 MB (what is fetched goes before what was there already: 52 MB last until they are used,
+// 105 do not), FFN-2's weights under FFN-1 (nothing where FFN-1's own are fetched, +1 % at 1976 rows), QKV's under the pass in
+// front of it (0 to +0.4 %), a launch's own in its idle units (+5 % at 14B).
+class WarmPlan {
+public:
+    explicit WarmPlan(const IdleUnits& idle) {
+        memset(&args_, 0, sizeof(args_));
+        if (idle.blocks < kLeastBlocks) return;
+        args_.blocks = idle.blocks < kMostBlocks ? idle.blocks : kMostBlocks;
+        const float rate = (float)(args_.blocks * idle.waves) * kBytesPerWave, bytes = idle.us * (rate < kBytesPerChip ? rate : kBytesPerChip);
+        room_ = bytes < (float)kMostBytes ? (size_t)bytes : kMostBytes;
+    }
+    // A [rows][cols] matrix of bf16, or its leading columns as far as there is room (part).  Nothing is taken behind one that did not fit.
+    bool add(const void* p, size_t rows, size_t cols, bool part) {
+        const size_t pitch = cols * sizeof(bf16), columns = (pitch + 1023) / 1024, column = rows * 1024;
+        if (full_ || args_.ranges == kMaxWarmRanges || reinterpret_cast<uintptr_t>(p) % 16) return false;
+        const size_t n = room_ / column < columns ? room_ / column : columns;
+        full_ = n < columns;
+        if (n == 0 || (full_ && !part)) return false;
+        args_.range[args_.ranges++] = WarmRange{static_cast<const unsigned char*>(p), (unsigned)rows, (unsigned)pitch, (unsigned)n};
+        room_ -= n * column;
+        return !full_;
+    }
+    void drop() { args_.ranges = 0; }
+    const WarmArgs* args() {
+        if (args_.ranges == 0) args_.blocks = 0;
+        return &args_;
+    }
+private:
+    static constexpr unsigned kLeastBlocks = 16, kMostBlocks = 64;
+    static constexpr size_t kMostBytes = (size_t)56 << 20;
+    static constexpr float kBytesPerWave = 5.5e3f, kBytesPerChip = 2.6e6f;       // a microsecond
+    WarmArgs args_;
+    size_t room_ = 0;
+    bool full_ = false;
+};
+
+// The QKV product of more rows takes so long that what it fetches is gone again (2000 to 4300 rows: 0 to +1.4 %).
+constexpr int kMostWarmQkvRows = 1280;
+
 // Launches one block.  State has been validated; it is advanced here and restored if a launch fails.
 // next_w: the block that runs next on the same x and workspace (null: none); when FFN-2's k-split reduce pass could
 // also write that block's adaLN-1 output into ws.h, *next_h_ready is set and the next call passes h_ready = true.
@@ -931,7 +977,7 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     // timed as two launches
 #define RUN_GEMM(tag, what)                                                         \
     do {                                                                            \
-        RUN(tag, launch_gemm_part(g, s, 1), what);                                  \
+        RUN(tag, launch_gemm_part(g, s, 1, side), what);                            \
         if (gemm_splits_k(g)) RUN(SDV2_TAG_GEMM_REDUCE, launch_gemm_part(g, s, 2), what " (sum of the k parts)"); \
     } while (0)
     // the same for a product whose result is LayerNorm-ed next: the second pass then forms that LayerNorm too (*done)
@@ -942,7 +988,7 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     } while (0)
 #define RUN_ATTN(tag, args, what)                                                   \
     do {                                                                            \
-        RUN(tag, launch_attention(args, s, 1), what);                               \
+        RUN(tag, launch_attention(args, s, 1, side), what);                         \
         if (attention_has_merge_pass(args)) RUN(SDV2_TAG_ATTN_MERGE, launch_attention(args, s, 2), what " (merge)"); \
     } while (0)
 
@@ -966,7 +1012,7 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     memset(&g, 0, sizeof(g));
     g.splitk_partials = ws.gemm_floats ? ws.gemm_partials : nullptr;
     g.splitk_floats = ws.gemm_floats;
-    g.cold_weights = weights_cold(cfg);
+    g.cold_weights = weights_cold(cfg, (size_t)C * (6 * C + 2 * F));
     g.M = rows;
     g.rows_per_gate = L;
     g.gate_b_stride = 6 * C;
@@ -977,7 +1023,17 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     g.N = 3 * C;
     g.K = C;
     g.epilogue = kEpiBias;
+    const bool cold = g.cold_weights;                 // else everything is in the memory-side cache already
+    WarmPlan under_qkv(cold && rows <= kMostWarmQkvRows ? gemm_idle_units(g) : IdleUnits{});
+    bool all = true;
+    for (int b = 0; b < B; ++b) {
+        all = all && under_qkv.add(at.k[b], H, (size_t)cache->cap * 128, false);
+        all = all && under_qkv.add(at.vt[b], H, (size_t)cache->cap * 128, false);
+    }
+    if (!all) under_qkv.drop();
+    const WarmArgs* side = under_qkv.args();
     RUN_GEMM(SDV2_TAG_QKV, "QKV gemm");
+    side = nullptr;
     // 3. q/k RMSNorm + RoPE + append into the ring
     ra.qkv = ws.qkv;
     ra.q_out = ws.q;
@@ -1003,7 +1059,19 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     at.splits = attention_plan_splits(B, L, H, max_kv);
     at.part_o = ws.attn;
     at.part_ml = ws.attn + (size_t)at.splits * rows * C;
+    WarmPlan under_self(cold ? attention_idle_units(at) : IdleUnits{});
+    g.N = C;
+    g.K = C;
+    g.epilogue = kEpiGatedResidual;
+    bool co = gemm_fetches_own_weights(g);            // and so do the two products of this size behind it
+    if (!co) {
+        under_self.add(w->W_o, C, C, true);
+        under_self.add(w->W_cq, C, C, true);
+        co = under_self.add(w->W_co, C, C, true);
+    }
+    side = under_self.args();
     RUN_ATTN(SDV2_TAG_SELF_ATTN, at, "self-attention");
+    side = nullptr;
     // 5. output projection, gated residual
     g.a = ws.o;
     g.w = static_cast<const bf16*>(w->W_o);
@@ -1053,7 +1121,12 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     }
     ct.splits = attention_plan_splits(B, L, H, cfg->text_len);
     ct.part_ml = ws.attn + (size_t)ct.splits * rows * C;
+    WarmPlan under_cross(cold ? attention_idle_units(ct) : IdleUnits{});
+    if (!co) under_cross.add(w->W_co, C, C, true);
+    under_cross.add(w->W_1, F, C, false);
+    side = under_cross.args();
     RUN_ATTN(SDV2_TAG_CROSS_ATTN, ct, "cross-attention");
+    side = nullptr;
     g.a = ws.o;
     g.w = static_cast<const bf16*>(w->W_co);
     g.bias = w->b_co;

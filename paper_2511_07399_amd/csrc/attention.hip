@@ -551,6 +551,14 @@ __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_any_addres
     attention_body<NW, false>(a, softmax_scale);
 }
 
+// With workgroups behind its own that fetch memory; kernels of their own, because in the same ones the few instructions more
+// cost every launch 0.4 us a round.
+template <int NW>
+__global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attention_fetching_kernel(AttnArgs a, float softmax_scale, WarmArgs warm) {
+    if (blockIdx.x >= a.n_wg) return warm_memory(warm, blockIdx.x - a.n_wg);
+    attention_body<NW, true>(a, softmax_scale);
+}
+
 // ---------------------------------------------------------------------------------------------------
 // Key-split form for skinny launches (a single 1024-token chunk: heads x query tiles is well below the number of
 // SIMDs).  A workgroup is NQ query blocks x NKW key slices = 8 waves: it walks the whole key range in tiles of
@@ -869,6 +877,12 @@ __global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_any_address_ker
     attention_ks_body<NQ, NKW, false>(a, softmax_scale);
 }
 
+template <int NQ, int NKW>
+__global__ __launch_bounds__(64 * NQ * NKW, 1) void attention_ks_fetching_kernel(AttnArgs a, float softmax_scale, WarmArgs warm) {
+    if (blockIdx.x >= a.n_wg) return warm_memory(warm, blockIdx.x - a.n_wg);
+    attention_ks_body<NQ, NKW, true>(a, softmax_scale);
+}
+
 // out = sum_i w_i O_i / sum_i w_i,  w_i = l_i 2^(m_i - max m).  One thread per four channels.
 __global__ __launch_bounds__(256) void attention_merge_kernel(AttnArgs a) {
     const int C = a.H * D;
@@ -985,9 +999,28 @@ void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
 // heads are multiples of 256 bytes, so the first address decides); queries at any other address of a bf16 are fetched into registers.
 static bool queries_aligned(const AttnArgs& a) { return (reinterpret_cast<uintptr_t>(a.q) & 15) == 0; }
 
+// The times are lines through 4 and 24 tiles of the key-split form and 8 and 48 of the eight-wave form.
+IdleUnits attention_idle_units(const AttnArgs& a) {
+    int max_kv = 0;
+    for (int b = 0; b < a.B; ++b) max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;
+    IdleUnits idle{0, 8, 0.0f};
+    int wgs;
+    if (attention_plan_key_split(a)) {
+        wgs = (a.L + 63) / 64 * a.H * a.B;
+        idle.us = 6.5f + (float)max_kv * (1.25f / 128);
+    } else {
+        const int nw = attention_plan_waves(a.B, a.L, a.H, max_kv), QT = 32 * nw;
+        wgs = (a.L + QT - 1) / QT * a.H * a.B * a.splits;
+        idle.waves = (unsigned)nw;
+        idle.us = (nw == 8 ? 11.0f : 7.0f) + (float)(max_kv / a.splits) * ((nw == 8 ? 1.4f : 1.0f) / 64);
+    }
+    if (wgs < kUnits) idle.blocks = (unsigned)(kUnits - wgs);
+    return idle;
+}
+
 bool attention_has_merge_pass(const AttnArgs& a) { return a.splits > 1 && !attention_plan_key_split(a); }
 
-hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part) {
+hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const WarmArgs* side) {
     AttnArgs a = args;
     auto one_dimension = [&](int q_tiles, int parts) {
         a.n_wg = (unsigned)q_tiles * a.H * a.B * parts;
@@ -1000,6 +1033,7 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part) {
     static std::once_flag attr_once;
     static hipError_t attr_err = hipSuccess;
     typedef void (*Kernel)(AttnArgs, float);
+    typedef void (*FetchingKernel)(AttnArgs, float, WarmArgs);
     std::call_once(attr_once, [&]() {
         const std::pair<Kernel, size_t> kernels[] = {{attention_kernel<4>, smem},
                                                      {attention_kernel<8>, smem8},
@@ -1010,15 +1044,21 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part) {
         for (const auto& k : kernels)
             if (attr_err == hipSuccess)
                 attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(k.first), hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second);
+        const std::pair<FetchingKernel, size_t> fetching[] = {
+            {attention_fetching_kernel<4>, smem}, {attention_fetching_kernel<8>, smem8}, {attention_ks_fetching_kernel<2, 4>, smem_ks}};
+        for (const auto& k : fetching)
+            if (attr_err == hipSuccess)
+                attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(k.first), hipFuncAttributeMaxDynamicSharedMemorySize, (int)k.second);
     });
     if (attr_err != hipSuccess || attributes_only()) return attr_err;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
-    const bool staged = queries_aligned(a);
+    const bool staged = queries_aligned(a), fetching = side != nullptr && side->blocks > 0 && staged;
     if (attention_plan_key_split(a)) {
         if (part == 2) return hipSuccess;
         const dim3 grid = one_dimension((a.L + 63) / 64, 1);
         const Kernel kernel = staged ? attention_ks_kernel<2, 4> : attention_ks_any_address_kernel<2, 4>;
-        hipLaunchKernelGGL(kernel, grid, dim3(512), smem_ks, s, a, scale_log2e);
+        if (fetching) hipLaunchKernelGGL((attention_ks_fetching_kernel<2, 4>), dim3(grid.x + side->blocks), dim3(512), smem_ks, s, a, scale_log2e, *side);
+        else hipLaunchKernelGGL(kernel, grid, dim3(512), smem_ks, s, a, scale_log2e);
         return hipGetLastError();
     }
     hipError_t e = hipSuccess;
@@ -1028,7 +1068,11 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part) {
         const int nw = attention_plan_waves(a.B, a.L, a.H, max_kv);
         const int QT = 32 * nw;
         const dim3 grid = one_dimension((a.L + QT - 1) / QT, a.splits);
-        if (nw == 8) hipLaunchKernelGGL(staged ? attention_kernel<8> : attention_any_address_kernel<8>, grid, dim3(512), smem8, s, a, scale_log2e);
+        if (fetching && nw == 8)
+            hipLaunchKernelGGL(attention_fetching_kernel<8>, dim3(grid.x + side->blocks), dim3(512), smem8, s, a, scale_log2e, *side);
+        else if (fetching)
+            hipLaunchKernelGGL(attention_fetching_kernel<4>, dim3(grid.x + side->blocks), dim3(256), smem, s, a, scale_log2e, *side);
+        else if (nw == 8) hipLaunchKernelGGL(staged ? attention_kernel<8> : attention_any_address_kernel<8>, grid, dim3(512), smem8, s, a, scale_log2e);
         else hipLaunchKernelGGL(staged ? attention_kernel<4> : attention_any_address_kernel<4>, grid, dim3(256), smem, s, a, scale_log2e);
         e = hipGetLastError();
     }

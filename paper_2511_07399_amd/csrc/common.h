@@ -66,8 +66,8 @@ __device__ __forceinline__ float gelu_tanh_f(float x) {
 
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 
-// Memory that is read soon, fetched into the memory-side cache (256 MB, in front of HBM, shared by the chip) by workgroups
-// behind a launch's own.
+// Memory that a launch soon reads, fetched into the memory-side cache (256 MB, in front of HBM, shared by the chip) by
+// workgroups behind an earlier launch's own, on compute units that those leave idle.
 constexpr int kUnits = 256;           // compute units
 constexpr int kMaxWarmRanges = 4;
 struct WarmRange {
@@ -78,6 +78,12 @@ struct WarmArgs {
     WarmRange range[kMaxWarmRanges];
     unsigned ranges;                  // 0: nothing to fetch
     unsigned blocks;                  // workgroups that share them
+};
+
+// What a launch's last round of workgroups leaves idle: waves of workgroups behind its own, and about how many microseconds.
+struct IdleUnits {
+    unsigned blocks, waves;           // workgroups, and waves of each
+    float us;
 };
 
 // Reads the ranges and drops what it has read: a wave takes 1 KB of a row at a time, columns before rows, so the first part of
@@ -202,13 +208,15 @@ struct AttnArgs {
     int q_pieces;
     float q_eps;
 };
+IdleUnits attention_idle_units(const AttnArgs& a);
 int attention_plan_splits(int B, int L, int H, int max_kv_len);
 // Tuning hooks: waves per workgroup (4, 8; 0 = planner) and key-range splits (0 = planner); -1 leaves a value as is.
 void set_attention_overrides(int waves, int splits);
 size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len);
 // the most that a call of at most B streams of at most L queries needs; grows with B, L and max_kv_len
 size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len);
-hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part = 0);   // part 1: the kernel; 2: the merge pass only
+// part 1: the kernel; 2: the merge pass only.  warm: what units that the kernel leaves idle fetch meanwhile (null: nothing).
+hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part = 0, const WarmArgs* warm = nullptr);
 bool attention_has_merge_pass(const AttnArgs& a);
 void attention_plan_name(const AttnArgs& a, char* out, size_t cap);      // only B, L, H, kv_len and cap are read
 
@@ -234,7 +242,10 @@ hipError_t launch_layernorm(const LnArgs& a, hipStream_t s);
 // launches the LayerNorm itself.
 // part 0: everything; 1: only the kernel on the matrix cores; 2: only the pass that adds the k parts.
 hipError_t launch_gemm_then_layernorm(const GemmArgs& g, const LnArgs& ln, bool* ln_done, hipStream_t s, int part = 0);
-hipError_t launch_gemm_part(const GemmArgs& g, hipStream_t s, int part);
+// warm: what part 1 fetches on the side (null: nothing).
+hipError_t launch_gemm_part(const GemmArgs& g, hipStream_t s, int part, const WarmArgs* warm = nullptr);
+IdleUnits gemm_idle_units(const GemmArgs& g);        // of the matrix part
+bool gemm_fetches_own_weights(const GemmArgs& g);    // in large pieces, before its k loop gets to them
 bool gemm_splits_k(const GemmArgs& g);               // whether the planned launch has such a second pass
 
 // In-place RMSNorm over C of bf16 rows, times gain.

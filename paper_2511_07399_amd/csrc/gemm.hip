@@ -549,332 +549,18 @@ __device__ __forceinline__ void store_wave(const GemmArgs& g, void* outp, f32x4 
 }
 
 template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC>
-__global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m, int splitk, int own, WarmArgs warm) {
-    static_assert(NSW >= NSA && NSA >= 2, "stages");
-    constexpr int NW = WM * WN, BK = 64;
-    constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
-    constexpr int GA = BM / 8, GW = BN / 8;                 // groups of eight rows
-    constexpr int NL = ROLES ? NW / 2 : NW;                 // waves that load an operand
-    constexpr int LA = (GA + NL - 1) / NL, LW = (GW + NL - 1) / NL, LMAX = LA > LW ? LA : LW;
-    static_assert(ROLES || NSW <= NSA + 1, "stages");
-    constexpr int SA = BM * BK * 2, SW = BN * BK * 2;
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    unsigned char* const smem_w = smem + NSA * SA;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
-    const int l15 = lane & 15, lq = lane >> 4;
+__global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_alt64_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m, int splitk) {
+    const unsigned workgroups = gridDim.x;
+#include "gemm_alt64_body.inc"
+}
 
-    // ---- the tiles of this workgroup: XCD x owns a contiguous range of tiles, its workgroups take them in turn
-    const int tiles = tiles_m * tiles_n, total = tiles * splitk;
-    const int xcd = blockIdx.x & 7, per_xcd = own >> 3;
-    const int per = total >> 3, rem = total & 7;
-    const int t_end = per * (xcd + 1) + min(xcd + 1, rem);
-    int tile = per * xcd + min(xcd, rem) + (blockIdx.x >> 3);
-    if ((int)blockIdx.x >= own) return warm_memory(warm, blockIdx.x - own);      // behind the launch's own workgroups
-    if (tile >= t_end) return;
-    int m0, n0, ks = 0;
-    auto locate = [&](int id, int& m, int& n) {
-        const int gsz = group_m * tiles_n, grp = id / gsz, first_m = grp * group_m;
-        const int gm = min(tiles_m - first_m, group_m), in_grp = id - grp * gsz;
-        const int q = in_grp / gm;
-        m = (first_m + in_grp - q * gm) * BM;
-        n = q * BN;
-    };
-    const int KT = g.K / BK;
-    int kt0 = 0, nk = KT;
-    const bool pair = g.w2 != nullptr;                       // two products with A in common: tile range ks is product ks
-    const bool split = splitk > 1 && !pair;
-    if (splitk > 1) {                                        // one tile per workgroup then
-        ks = tile / tiles;
-        if (split) {
-            kt0 = ks * KT / splitk;
-            nk = (ks + 1) * KT / splitk - kt0;
-            g.bias = nullptr;                                // the pass that adds the parts has it
-        } else if (ks == 1) {
-            g.w = g.w2;
-            g.bias = g.bias2;
-            g.out = g.out2;
-        }
-    }
-    locate(tile - ks * tiles, m0, n0);
-
-    // ---- tile loads.  ROLES: the first half of the waves fetches A, the second half W, each with its own wait count.
-    // Otherwise every wave fetches a share of both, A first.
-    const bool loads_a = !ROLES || wave < NL;
-    const int id = loads_a ? wave : wave - NL;
-    const __amdgpu_buffer_rsrc_t buf0 = byte_buffer(loads_a ? g.a : g.w, (uint32_t)(loads_a ? g.M : g.N) * (uint32_t)g.K * 2u);
-    const __amdgpu_buffer_rsrc_t buf1 = byte_buffer(g.w, (uint32_t)g.N * (uint32_t)g.K * 2u);
-    // Loads through a buffer descriptor spare the vector additions of 64-bit addresses (51 x 896 x 896 on the 32 x 32 tile 5.1 us
-    // without them, 4.6 with; 2048 x 1024 x 1024 on 128 x 64 10.2 and 9.6).  Not where a wave fetches one operand and W has more
-    // stages than A: there they are slower (1037 x 15104 x 2560 on the 192 x 192 tile 84.6 us with, 80.9 without; 707 x 4992 x
-    // 1664 on 128 x 128 18.0 and 17.5; the 192 x 256 tile 1 %).
-    constexpr bool kBuffer = !(ROLES && NSW > NSA);
-    const unsigned char* const base0 = reinterpret_cast<const unsigned char*>(loads_a ? g.a : g.w);
-    const lds_byte_ptr lds_w = (lds_byte_ptr)smem_w, lds0 = loads_a ? (lds_byte_ptr)smem : lds_w;
-    const uint32_t k_first = (uint32_t)kt0 * (BK * 2);      // byte offset in a row of this part's first k tile
-    const int bytes0 = loads_a ? SA : SW, stages0 = loads_a ? NSA : NSW;
-    // Row group of this wave's i-th load (eight rows of 128 bytes); past the end the wave's previous group again.
-    // Groups of a wave are NL (even) apart, so the swizzle term of a lane is the same for all of them.
-    static_assert(NL % 2 == 0, "swizzle term");
-    constexpr bool kWhole = GA % NL == 0 && GW % NL == 0;
-    auto group_of = [&](int i, int groups) { return kWhole || id + NL * i < groups ? id + NL * i : id + NL * (i - 1); };
-    const int lane_row = lane >> 3;
-    const uint32_t lane_col = (uint32_t)(((lane & 7) ^ ((4 * id + (lane >> 4)) & 7)) * 16), k2 = (uint32_t)g.K * 2u;
-    // kScalarRows: an address is the scalar offset of the group's first row (past the operand's end: its last group, which of A
-    // may have fewer rows than eight) and one lane offset that all loads share.  Otherwise a lane keeps an offset per load,
-    // which is fewer instructions but a register each, and another each for the next tile's: the 256 x 256 tile had to spill
-    // one, and the reload waited, once per k tile, for every tile load in flight (14B step 29.49 -> 28.82 ms without;
-    // the 192 x 256 and 256 x 192 tiles, which have the registers, are 2 % slower with scalar rows).
-    constexpr bool kScalarRows = TM * TN >= 32 && OCC == 2;
-    const uint32_t lane_off = (uint32_t)lane_row * k2 + lane_col;
-    const int last0 = (loads_a ? g.M : g.N) - 1, last1 = g.N - 1;
-    const uint32_t lane_off_last = loads_a ? (uint32_t)min(lane_row, last0 & 7) * k2 + lane_col : lane_off;
-    const uint32_t last_row_off0 = (uint32_t)(last0 & ~7) * k2;
-    uint32_t off[ROLES ? LMAX : LA + LW];
-    auto offset_of = [&](int row, int last) {
-        return kScalarRows ? (uint32_t)min(row, last & ~7) * k2 : (uint32_t)min(row + lane_row, last) * k2 + lane_col;
-    };
-    auto set_off0 = [&](int m, int n) {
-        const int first = loads_a ? m : n;
-#pragma unroll
-        for (int i = 0; i < (ROLES ? LMAX : LA); ++i) {
-            off[i] = offset_of(first + 8 * group_of(i, loads_a ? GA : GW), last0);
-            if (!kScalarRows) __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-    auto set_off1 = [&](int n) {
-        if constexpr (!ROLES) {
-#pragma unroll
-            for (int i = 0; i < LW; ++i) {
-                off[LA + i] = offset_of(n + 8 * group_of(i, GW), last1);
-                if (!kScalarRows) __builtin_amdgcn_sched_barrier(0);
-            }
-        }
-    };
-    // next k tile to fetch and the stage it goes to, per operand
-    int k0 = 0, k1 = 0, st0 = 0, st1 = 0;
-    uint32_t src0 = k_first, src1 = k_first;
-    lds_byte_ptr dst0 = lds0, dst1 = lds_w;
-    // moves a cursor on: the next k tile (0 of the next output tile past the end, if there is one), the next stage
-    auto next0 = [&](bool more, int nk) {
-        const bool wrap = k0 + 1 == nk;
-        k0 = wrap ? (more ? 0 : k0) : k0 + 1;
-        src0 = k_first + (uint32_t)k0 * (BK * 2);
-        st0 = st0 + 1 == stages0 ? 0 : st0 + 1;
-        dst0 = lds0 + st0 * bytes0;
-        return wrap && more;
-    };
-    auto next1 = [&](bool more, int nk) {
-        const bool wrap = k1 + 1 == nk;
-        k1 = wrap ? (more ? 0 : k1) : k1 + 1;
-        src1 = k_first + (uint32_t)k1 * (BK * 2);
-        st1 = st1 + 1 == NSW ? 0 : st1 + 1;
-        dst1 = lds_w + st1 * SW;
-        return wrap && more;
-    };
-    auto load_group = [&](const __amdgpu_buffer_rsrc_t& buf, uint32_t src, uint32_t o, bool may_be_short, lds_byte_ptr dst) {
-        if constexpr (kScalarRows) load_to_lds_b128(buf, may_be_short && o == last_row_off0 ? lane_off_last : lane_off, src + o, dst);
-        else if constexpr (kBuffer) load_to_lds_b128(buf, o, src, dst);
-        else load_to_lds_b128(base0 + src + o, dst);
-    };
-    auto load = [&](auto lc) {
-        constexpr int l = decltype(lc)::value;
-        if constexpr (ROLES) {
-            if (LA == LW || l < (loads_a ? LA : LW)) load_group(buf0, src0, off[l], true, dst0 + group_of(l, loads_a ? GA : GW) * 1024);
-        } else if constexpr (l < LA) {
-            load_group(buf0, src0, off[l], true, dst0 + group_of(l, GA) * 1024);
-        } else {
-            load_group(buf1, src1, off[l], false, dst1 + group_of(l - LA, GW) * 1024);
-        }
-    };
-    constexpr int LOADS = ROLES ? LMAX : LA + LW;
-    set_off0(m0, n0);
-    set_off1(n0);
-    f32x4 acc[TM][TN];
-    // The bias is the same for the sixteen lanes of a row: each keeps one column block's (four registers across the k loop
-    // where every lane with all of its blocks would take 4 TN).  The 256 x 256 tile has not even those: spilled, they put
-    // waits for scratch among its loads (1024 x 15360 x 5120: 154 us), so it fetches them when it stores (137 us).
-    constexpr bool kScalarBias = TM * TN >= 32 && OCC == 2;
-    f32x4 bias = {0.f, 0.f, 0.f, 0.f};
-    auto load_bias = [&](int n) {
-        const int c = n + wn * (16 * TN) + 16 * min(l15, TN - 1) + 4 * lq;
-        return *reinterpret_cast<const f32x4*>(g.bias + (c < g.N ? c : 0));
-    };
-    const int key = (l15 >> 1) & 7;
-    const int a_frag = (wm * (16 * TM) + l15) * (BK * 2), w_frag = (wn * (16 * TN) + l15) * (BK * 2);
-    const int co0 = (lq ^ key) << 4, co1 = ((4 + lq) ^ key) << 4;
-    bf16x8 fa[2][TM], fb[2][TN];
-    // fragment r of k half s: the TM rows of A, then the TN rows of W
-    auto read = [&](auto sc, auto rc, const unsigned char* pa, const unsigned char* pw) {
-        constexpr int s = decltype(sc)::value, r = decltype(rc)::value;
-        if constexpr (r < TM) fa[s][r] = *reinterpret_cast<const bf16x8*>(pa + (s ? co1 : co0) + r * (16 * BK * 2));
-        else fb[s][r - TM] = *reinterpret_cast<const bf16x8*>(pw + (s ? co1 : co0) + (r - TM) * (16 * BK * 2));
-    };
-    auto barrier = [&]() {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-    };
-    // The MFMAs of k half s in program order, with the fragment reads of the other half among the first three
-    // quarters of them and (s = 1) the tile loads spread over all of them.
-    auto half = [&](auto sc, const unsigned char* pa, const unsigned char* pw) {
-        constexpr int s = decltype(sc)::value;
-        constexpr int kM = TM * TN, kR = TM + TN, kL = s == 1 ? LOADS : 0;
-        constexpr int kSpan = kM * 3 / 4 > 0 ? kM * 3 / 4 : 1;
-        static_for<kM>([&](auto mc) {
-            constexpr int m = decltype(mc)::value;
-            constexpr int i = m / TN, j = i % 2 ? TN - 1 - m % TN : m % TN;      // back and forth: one operand stays at every turn
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[s][j], fa[s][i], acc[i][j], 0, 0, 0);
-            constexpr int r0 = m < kSpan ? m * kR / kSpan : kR, r1 = m < kSpan ? (m + 1) * kR / kSpan : kR;
-            static_for<r1 - r0>([&](auto q) { read(std::integral_constant<int, 1 - s>{}, std::integral_constant<int, r0 + decltype(q)::value>{}, pa, pw); });
-            constexpr int l0 = m * kL / kM, l1 = (m + 1) * kL / kM;
-            static_for<l1 - l0>([&](auto q) {
-                constexpr int l = l0 + decltype(q)::value;
-                load(std::integral_constant<int, l>{});
-            });
-            __builtin_amdgcn_sched_barrier(0);
-        });
-    };
-    const std::integral_constant<int, 0> s0;
-    const std::integral_constant<int, 1> s1;
-    // loads of a wave that may still be in flight when k tile t + 1 has to be there
-    constexpr int kWait0 = ROLES ? (NSA - 2) * LA : (NSA - 2) * (LA + LW) + (NSW - NSA) * LW, kWait1 = (NSW - 2) * LW;
-    auto wait_loads = [&](auto extra) {                      // extra: k tiles beyond that
-        constexpr int x = decltype(extra)::value;
-        constexpr int w0 = kWait0 + x * (ROLES || NSW > NSA ? LA : LA + LW), w1 = kWait1 + x * LW;
-        static_assert(w0 < 63 && w1 < 63, "waits");
-        if (!ROLES || w0 == w1) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_only(w0));
-        } else if (loads_a) {
-            __builtin_amdgcn_s_waitcnt(vmcnt_only(w0));
-        } else {
-            __builtin_amdgcn_s_waitcnt(vmcnt_only(w1));
-        }
-    };
-    if (g.bias != nullptr) bias = load_bias(n0);
-    constexpr bool kPre = TM * TN <= 16;
-    f32x4 xpre[kPre ? TM * TN : 1];
-    auto load_x = [&]() {
-        if constexpr (kPre) {
-            if (splitk == 1 && (g.epilogue == kEpiGatedResidual || g.epilogue == kEpiResidual)) {
-#pragma unroll
-                for (int i = 0; i < TM; ++i) {
-                    const float* xr = reinterpret_cast<const float*>(g.out) + (size_t)min(m0 + wm * (16 * TM) + 16 * i + l15, g.M - 1) * g.N;
-#pragma unroll
-                    for (int j = 0; j < TN; ++j) {
-                        const int c = n0 + wn * (16 * TN) + 16 * j + 4 * lq;
-                        xpre[i * TN + j] = *reinterpret_cast<const f32x4*>(xr + (c < g.N ? c : 0));
-                    }
-                }
-            }
-        }
-    };
-    load_x();
-    if constexpr (ROLES) {
-        for (int p = 0; p < stages0; ++p) {
-            static_for<LOADS>([&](auto l) { load(l); });
-            next0(false, nk);
-        }
-    } else {
-#pragma unroll
-        for (int p = 0; p < NSW; ++p) {
-            if (p < NSA) {
-                static_for<LA>([&](auto l) { load(l); });
-                next0(false, nk);
-            }
-            static_for<LW>([&](auto l) { load(std::integral_constant<int, LA + decltype(l)::value>{}); });
-            next1(false, nk);
-        }
-    }
-    wait_loads(s1);                                          // k tile 0 has landed
-    barrier();
-    int sa = 0, sw = 0;
-    bool landed = false;                 // k tile 1 of this output tile is known to have landed
-    for (;;) {
-        const int next = tile + per_xcd;
-        const bool more = next < t_end;
-        int nm0 = m0, nn0 = n0;
-        if (more) locate(next, nm0, nn0);
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        {
-            const unsigned char* pa = smem + sa * SA + a_frag;
-            const unsigned char* pw = smem_w + sw * SW + w_frag;
-            static_for<TM + TN>([&](auto r) { read(s0, r, pa, pw); });
-        }
-        // A workgroup with a single tile walks it in steps unrolled over the ring: the stage is a constant of the step and the
-        // next load's address is one product, fifteen to twenty scalar instructions a k tile where the cursors below take fifty
-        // to sixty, which with tiles of 1 to 12 MFMAs per half is most of what a wave issues.
-        constexpr bool kUnrolled = NSA == NSW && TM * TN <= 12;
-        if (kUnrolled && !more && sa == 0 && sw == 0) {
-            if constexpr (kUnrolled) {
-                int t = 0;
-                auto step = [&](auto stage) {
-                    constexpr int S = decltype(stage)::value, N = (S + 1) % NSA;
-                    if (t >= nk) return;
-                    __builtin_amdgcn_sched_barrier(0);
-                    half(s0, smem + S * SA + a_frag, smem_w + S * SW + w_frag);
-                    src0 = src1 = k_first + (uint32_t)min(t + NSA, nk - 1) * (BK * 2);       // past the end: the last k tile again
-                    dst0 = lds0 + S * bytes0;
-                    dst1 = lds_w + S * SW;
-                    ++t;
-                    wait_loads(s0);
-                    __builtin_amdgcn_s_waitcnt(0xC07F);
-                    barrier();
-                    __builtin_amdgcn_sched_barrier(0);
-                    half(s1, smem + N * SA + a_frag, smem_w + N * SW + w_frag);
-                };
-                while (t < nk) static_for<NSA>(step);
-            }
-        } else {
-            for (int t = 0; t < nk; ++t) {
-                const int na = sa + 1 == NSA ? 0 : sa + 1, nw = sw + 1 == NSW ? 0 : sw + 1;
-                __builtin_amdgcn_sched_barrier(0);
-                half(s0, smem + sa * SA + a_frag, smem_w + sw * SW + w_frag);
-                if (!landed) wait_loads(s0);
-                landed = false;
-                __builtin_amdgcn_s_waitcnt(0xC07F);
-                barrier();
-                __builtin_amdgcn_sched_barrier(0);
-                half(s1, smem + na * SA + a_frag, smem_w + nw * SW + w_frag);
-                if (next0(more, nk)) set_off0(nm0, nn0);
-                if constexpr (!ROLES) {
-                    if (next1(more, nk)) set_off1(nn0);
-                }
-                sa = na;
-                sw = nw;
-            }
-        }
-        f32x4 next_bias = {0.f, 0.f, 0.f, 0.f};
-        if (more && g.bias != nullptr) {                     // waited for behind the stores, and with it every older load
-            next_bias = load_bias(nn0);
-            landed = true;
-        }
-        const int row0 = m0 + wm * (16 * TM), col0 = n0 + wn * (16 * TN);
-        switch (split ? (int)kEpiPartial : g.epilogue) {
-            case kEpiBias: store_wave<TM, TN, kEpiBias, kScalarBias>(g, g.out, acc, bias, row0, col0, lane); break;
-            case kEpiBiasGelu: store_wave<TM, TN, kEpiBiasGelu, kScalarBias>(g, g.out, acc, bias, row0, col0, lane); break;
-            case kEpiGatedResidual: store_wave<TM, TN, kEpiGatedResidual, kScalarBias>(g, g.out, acc, bias, row0, col0, lane, xpre); break;
-            case kEpiGainSquares: store_wave<TM, TN, kEpiGainSquares, kScalarBias>(g, g.out, acc, bias, row0, col0, lane); break;
-            case kEpiPartial:                                // the partial sums of a k part, or a plain fp32 output
-                store_wave<TM, TN, kEpiPartial, kScalarBias>(g, split ? g.splitk_partials + (size_t)ks * g.M * g.N : reinterpret_cast<float*>(g.out), acc,
-                                                bias, row0, col0, lane);
-                break;
-            default: store_wave<TM, TN, kEpiResidual, kScalarBias>(g, g.out, acc, bias, row0, col0, lane, xpre); break;
-        }
-        if (!more) break;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) asm volatile("" : "+v"(next_bias[e]));       // the wait of `landed`
-        bias = next_bias;
-        tile = next;
-        m0 = nm0;
-        n0 = nn0;
-        load_x();
-    }
-    __builtin_amdgcn_s_waitcnt(vmcnt_only(0));               // no direct load may still be on its way to this LDS
+// With workgroups behind its own that fetch memory.  A kernel of its own: in the same one the few instructions more cost every
+// launch 1 to 4 %.
+template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC>
+__global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_fetching_kernel(GemmArgs g, int tiles_m, int tiles_n, int group_m, int splitk,
+                                                                          unsigned workgroups, WarmArgs warm) {
+    if (blockIdx.x >= workgroups) return warm_memory(warm, blockIdx.x - workgroups);
+#include "gemm_alt64_body.inc"
 }
 
 struct TilePlan {
@@ -995,10 +681,10 @@ constexpr int kTileConfigs = 18;
 // by workgroups in the second places, about 32 KB each, while its own begin: the k loop asks HBM for 128 bytes of every row at
 // a time, from as many DRAM pages, which costs more than the bytes.  Weights from HBM without and with this (and from the
 // memory-side cache): 1024 x 1536 x 1536 12.8 -> 10.7 us (10.5 and 10.3); 512 x 1536 x 1536 10.3 -> 8.0 (7.4 and 7.6);
-// 1024 x 2048 x 2048 19.1 -> 16.3 (15.5 and 15.8); 1.3B step 6.18 -> 6.03 ms.
-// Text keys and values of 512 x 1536, two products: 16.2 -> 14.7 us a layer.  A workgroup of a larger tile has its unit to
-// itself; fetches in front of its own loads, or in left-over units, gave nothing.  More than 16 MB would take longer than the
-// first k tiles they are to be ahead of; weights that are in the memory-side cache anyway (cold_weights) are left alone.
+// 1024 x 2048 x 2048 19.1 -> 16.3 (15.5 and 15.8); 1.3B step 6.18 -> 6.03 ms, prompt 487 -> 449 us.
+// A workgroup of a larger tile has its unit to itself; fetches in front of its own loads, or in left-over units, gave nothing.
+// More than 16 MB would take longer than the first k tiles they are to be ahead of; weights that are in the memory-side cache
+// anyway (cold_weights) are left alone: 65 x 1280 x 1280, two products, 9.1 us without, 9.9 with.
 constexpr size_t kMostOwnWeights = (size_t)16 << 20;
 template <int PER_UNIT>
 bool fetches_own_weights(const GemmArgs& g, int grid) {
@@ -1007,7 +693,7 @@ bool fetches_own_weights(const GemmArgs& g, int grid) {
 }
 
 template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC, int PER_UNIT>
-hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
+hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s, const WarmArgs* side) {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
     constexpr size_t smem = (size_t)(NSA * BM + NSW * BN) * 64 * sizeof(bf16);
     static_assert(smem * PER_UNIT <= 160 * 1024, "LDS stages exceed 160 KB");
@@ -1022,6 +708,9 @@ hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
     std::call_once(attr_once, [&]() {
         attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_alt64_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if (attr_err == hipSuccess)
+            attr_err = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_fetching_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     });
     if (attr_err != hipSuccess || attributes_only()) return attr_err;
     // tile rows that share weight tiles: an XCD's 32 concurrent large tiles then cover 4 x 8 tiles, the shape with the
@@ -1029,6 +718,7 @@ hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
     const int group_m = BM >= 192 ? 4 : 8;
     WarmArgs warm;
     memset(&warm, 0, sizeof(warm));
+    if (side != nullptr) warm = *side;
     if (fetches_own_weights<PER_UNIT>(g, grid)) {
         const unsigned pitch = (unsigned)g.K * 2u, columns = (pitch + 1023u) / 1024u;
         warm.ranges = g.w2 != nullptr ? 2 : 1;
@@ -1037,8 +727,12 @@ hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s) {
         const size_t blocks = (size_t)warm.ranges * g.N * pitch / (32 * 1024);
         warm.blocks = blocks < kUnits ? (unsigned)blocks : kUnits;
     }
-    hipLaunchKernelGGL((gemm_alt64_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>), dim3(grid + warm.blocks), dim3(64 * WM * WN), smem, s, g,
-                       tiles_m, tiles_n, group_m, splitk, grid, warm);
+    if (warm.blocks > 0)
+        hipLaunchKernelGGL((gemm_fetching_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>), dim3(grid + warm.blocks), dim3(64 * WM * WN), smem, s, g,
+                           tiles_m, tiles_n, group_m, splitk, (unsigned)grid, warm);
+    else
+        hipLaunchKernelGGL((gemm_alt64_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>), dim3(grid), dim3(64 * WM * WN), smem, s, g, tiles_m, tiles_n,
+                           group_m, splitk);
     return hipGetLastError();
 }
 
@@ -1054,11 +748,11 @@ const TileCost kCost[kTileConfigs + 1] = {
 #undef X
 };
 
-hipError_t launch_tile_config(const GemmArgs& g, int id, int splitk, hipStream_t s) {
+hipError_t launch_tile_config(const GemmArgs& g, int id, int splitk, hipStream_t s, const WarmArgs* warm = nullptr) {
     if (!fits_32bit_offsets(g.M, g.N, g.K) || !operands_aligned(g)) return hipErrorInvalidValue;     // only reachable through the tuning override
     switch (id) {
 #define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit, ...) \
-    case id: return launch_alt64<wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit>(g, splitk, s);
+    case id: return launch_alt64<wm, wn, tm, tn, nsa, nsw, roles, occ, per_unit>(g, splitk, s, warm);
         SDV2_TILE_CONFIGS(X)
 #undef X
     }
@@ -1438,10 +1132,10 @@ static int usable_splitk(const GemmArgs& g, const TilePlan& p) {
 
 // part 0: the whole product; 1: only the kernel on the matrix cores; 2: only the pass that adds the k parts (nothing
 // when the plan does not split).  The benchmark times the two parts separately.
-static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln_done, hipStream_t s, int part = 0) {
+static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln_done, hipStream_t s, int part = 0, const WarmArgs* side = nullptr) {
     if (g.w2 != nullptr) {
         const TilePlan p2 = plan_of(g);
-        if (p2.dma) return launch_tile_config(g, p2.dma, 2, s);
+        if (p2.dma) return launch_tile_config(g, p2.dma, 2, s, side);
         GemmArgs one = g;
         one.w2 = nullptr;
         const hipError_t e1 = launch_gemm_impl(one, nullptr, nullptr, s);
@@ -1455,7 +1149,7 @@ static hipError_t launch_gemm_impl(const GemmArgs& g, const LnArgs* ln, bool* ln
     const int splitk = usable_splitk(g, p);
     hipError_t e = hipSuccess;
     if (part != 2) {
-        if (p.dma) e = launch_tile_config(g, p.dma, splitk, s);
+        if (p.dma) e = launch_tile_config(g, p.dma, splitk, s, side);
         else if (p.pf == 3) e = p.tm == 1 ? launch_tn<1, 3>(g, p.tn, splitk, s) : launch_tn<2, 3>(g, p.tn, splitk, s);
         else e = p.tm == 1 ? launch_tn<1, 2>(g, p.tn, splitk, s) : launch_tn<2, 2>(g, p.tn, splitk, s);
     }
@@ -1505,7 +1199,29 @@ hipError_t launch_gemm_then_layernorm(const GemmArgs& g, const LnArgs& ln, bool*
     return launch_gemm_impl(g, &ln, ln_done, s, part);
 }
 
-hipError_t launch_gemm_part(const GemmArgs& g, hipStream_t s, int part) { return launch_gemm_impl(g, nullptr, nullptr, s, part); }
+hipError_t launch_gemm_part(const GemmArgs& g, hipStream_t s, int part, const WarmArgs* warm) {
+    return launch_gemm_impl(g, nullptr, nullptr, s, part, warm);
+}
+
+IdleUnits gemm_idle_units(const GemmArgs& g) {
+    const TilePlan p = plan_of(g);
+    IdleUnits idle{0, 8, 0.0f};
+    if (!p.dma || kCost[p.dma].per_unit != 1) return idle;
+    const TileCost& t = kCost[p.dma];
+    const int parts = usable_splitk(g, p), tiles = ((g.M + t.bm - 1) / t.bm) * ((g.N + t.bn - 1) / t.bn) * parts;
+    const int grid = (tiles + 7) / 8 * 8;
+    if (grid < kUnits) idle.blocks = (unsigned)(kUnits - grid);
+    idle.waves = t.one_wave ? 4 : 8;
+    idle.us = tile_cost(p.dma, g.M, g.N, (float)g.K / (64 * parts), parts);
+    return idle;
+}
+
+bool gemm_fetches_own_weights(const GemmArgs& g) {
+    const TilePlan p = plan_of(g);
+    if (!p.dma || kCost[p.dma].per_unit != 2) return false;
+    const TileCost& t = kCost[p.dma];
+    return fetches_own_weights<2>(g, ((g.M + t.bm - 1) / t.bm * ((g.N + t.bn - 1) / t.bn) * usable_splitk(g, p) + 7) / 8 * 8);
+}
 
 // One sum per row and wave column, which is how the epilogue's lanes hold them.
 int gemm_square_pieces(const GemmArgs& g) {
