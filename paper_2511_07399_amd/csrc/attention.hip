@@ -46,6 +46,7 @@
 
 #include <stdio.h>
 #include <stdlib.h>
+#include <string.h>
 
 #include <mutex>
 #include <type_traits>
@@ -928,45 +929,91 @@ void set_attention_overrides(int waves, int splits) {
     if (splits >= 0) g_force_splits = splits > 16 ? 16 : splits;
 }
 
-// Key-split form (2 query blocks x 4 key slices): when 128-query workgroups would give fewer than three quarters of
-// the compute units a workgroup each, and every stream's capacity is a whole number of its 128-key tiles.
-static bool attention_plan_key_split(const AttnArgs& a) {
-    for (int b = 0; b < a.B; ++b)
-        if (a.cap[b] % 128) return false;
-    if (g_force_waves) return g_force_waves == 2;
-    return ((a.L + 127) / 128) * a.H * a.B < 192;
+// Forms of a launch: workgroups of 4 waves (128 queries, two workgroups per compute unit) or 8 waves (256 queries, one per unit,
+// half the K/V traffic from the L2 per query), each with the key range whole or in parts of at least six tiles that a merge
+// pass joins; and the key-split form (2 query blocks x 4 key slices, one workgroup per unit), for capacities of whole 128-key
+// tiles.  Microseconds of a launch:  c + rounds (tiles a + b), rounds as for the tiles of a product (a workgroup per slot is a
+// round; of a last round that fills the share x of the slots the part p + s x, two per unit beyond a half q + (1 - q) x), and
+// m + n per MB that the merge reads and writes.  Fitted to 2616 launches (4 to 40 heads, 16 to 12 480 keys, 1 to 8 streams, keys
+// and values cold): rms error 4, 4 and 7 %.  On 1308 others the form picked is on average 0.4 % slower than the best of all;
+// the thresholds that this replaces, workgroups against units alone, 10 %: 1560 x 12 heads over 512 keys 18.2 -> 12.9 us, over
+// 4680 keys 93.8 -> 63.3, 8 x 1024 x 12 heads over 3072 keys 158.7 -> 148.9, 640 x 5 heads over 5120 keys 41.1 -> 27.9.
+struct FormCost {
+    int waves, queries, keys, slots;
+    float a, b, c, p, s, q, m, n;
+};
+const FormCost kForms[] = {{4, 128, 64, 2 * kUnits, 1.768f, 6.58f, 2.82f, 0.453f, 0.265f, 0.658f, 5.25f, 0.104f},
+                           {8, 256, 64, kUnits, 1.596f, 8.00f, 0.96f, 0.743f, 0.257f, 0.0f, 6.24f, 0.096f},
+                           {2, 64, 128, kUnits, 1.134f, 5.17f, 2.05f, 0.763f, 0.237f, 0.0f, 0.0f, 0.0f}};
+constexpr int kMostParts = 16, kLeastTiles = 6;
+constexpr float kPartsMargin = 1.03f;     // a split has to be that much better by the estimate: it needs scratch and a second launch
+
+static float attention_cost(const FormCost& f, int B, int L, int H, int max_kv, int parts) {
+    const long long wgs = (long long)((L + f.queries - 1) / f.queries) * H * B * parts;
+    const int tiles = ((max_kv + f.keys - 1) / f.keys + parts - 1) / parts;
+    const float full = (float)(wgs / f.slots), x = (float)(wgs % f.slots) / (float)f.slots;
+    float last = 0.0f;
+    if (x > 0.0f) last = f.slots == kUnits || x <= 0.5f ? f.p + f.s * x : f.q + (1.0f - f.q) * x;
+    float us = f.c + (full + last) * ((float)tiles * f.a + f.b);
+    if (parts > 1) us = (us + f.m + f.n * 1e-6f * (float)B * L * H * D * (8.0f * parts + 2.0f)) * kPartsMargin;
+    return us;
 }
 
-// Waves per workgroup: 4 (128 queries, two workgroups per compute unit) or 8 (256 queries, one workgroup per unit,
-// half the K/V traffic from the L2 per query).
-int attention_plan_waves(int B, int L, int H, int max_kv_len) {
-    if (g_force_waves == 4 || g_force_waves == 8) return g_force_waves;
-    (void)max_kv_len;
-    // 256-query workgroups only where they still give at least half of the compute units a workgroup each
-    return ((L + 255) / 256) * H * B >= 128 ? 8 : 4;
-}
-
-int attention_plan_splits(int B, int L, int H, int max_kv_len) {
-    const int forced = g_force_splits;
-    const int QT = 32 * attention_plan_waves(B, L, H, max_kv_len);
-    const int slots = QT == 128 ? 512 : 256;         // workgroups resident at once
-    const int n_tiles = (max_kv_len + KT - 1) / KT;
-    int splits = 1;
-    if (forced > 0) {
-        splits = forced;
-    } else {
-        // Two workgroups fit a compute unit: aim at no more than 512 workgroups in all, keep at least six
-        // key tiles per split (the merge pass costs about as much as two tiles), and do not split at all
-        // once every unit has a workgroup.
-        const int wgs = ((L + QT - 1) / QT) * H * B;
-        if (wgs < slots / 2) {
-            splits = slots / wgs;
-            while (splits > 1 && n_tiles / splits < 6) --splits;
+struct AttnPlan {
+    int waves, splits;      // the best of the forms that any capacity has
+    float us, us_key_split; // its estimate, and the key-split form's
+};
+// Kept for the shapes a thread has used last, as the products' plans are.
+static AttnPlan attention_plan(int B, int L, int H, int max_kv) {
+    struct Entry {
+        int key[6];
+        AttnPlan plan;
+    };
+    static thread_local Entry cache[8] = {};
+    const int key[6] = {B, L, H, max_kv, g_force_waves, g_force_splits};
+    Entry& e = cache[((unsigned)B * 31u + (unsigned)L * 17u + (unsigned)H * 7u + (unsigned)max_kv) % 8u];
+    if (memcmp(e.key, key, sizeof(key)) == 0) return e.plan;
+    AttnPlan best{4, 1, 1e30f, attention_cost(kForms[2], B, L, H, max_kv, 1)};
+    for (int f = 0; f < 2; ++f) {
+        const FormCost& form = kForms[f];
+        if ((g_force_waves == 4 || g_force_waves == 8) && form.waves != g_force_waves) continue;
+        const int tiles = (max_kv + KT - 1) / KT;
+        for (int parts = 1; parts <= kMostParts; ++parts) {
+            int n = parts;
+            if (g_force_splits > 0) {
+                n = g_force_splits;
+                while (n > 1 && tiles / n < 2) --n;
+            } else if (parts > 1 && (tiles / parts < kLeastTiles || (long long)parts * B * L * H > 65536)) {
+                break;                                       // attention_workspace_bytes_bound counts on both
+            }
+            const float us = attention_cost(form, B, L, H, max_kv, n);
+            if (us < best.us) {
+                best.waves = form.waves;
+                best.splits = n;
+                best.us = us;
+            }
+            if (g_force_splits > 0) break;
         }
     }
-    while (splits > 1 && n_tiles / splits < 2) --splits;
-    return splits > 16 ? 16 : splits;
+    memcpy(e.key, key, sizeof(key));
+    e.plan = best;
+    return best;
 }
+
+static bool attention_plan_key_split(const AttnArgs& a) {
+    int max_kv = 0;
+    for (int b = 0; b < a.B; ++b) {
+        if (a.cap[b] % 128) return false;
+        max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;
+    }
+    if (g_force_waves) return g_force_waves == 2;
+    const AttnPlan p = attention_plan(a.B, a.L, a.H, max_kv);
+    return p.us_key_split < p.us;
+}
+
+int attention_plan_waves(int B, int L, int H, int max_kv_len) { return attention_plan(B, L, H, max_kv_len).waves; }
+
+int attention_plan_splits(int B, int L, int H, int max_kv_len) { return attention_plan(B, L, H, max_kv_len).splits; }
 
 size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len) {
     const int H = C / D;
@@ -976,8 +1023,7 @@ size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len) {
     return (size_t)splits * rows * C * sizeof(float) + (size_t)splits * rows * H * 2 * sizeof(float);
 }
 
-// The plan splits only while workgroups of QT queries of a head are few: into at most slots / workgroups parts of at least
-// six key tiles.  So parts * B * L <= slots * QT / H, which is 65536 / H for both workgroup sizes.
+// The plan splits into at most 16 parts of at least six key tiles, and only while parts * B * L * H <= 65 536.
 size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len) {
     const size_t H = C / D, most_rows = 512 * 128 / H;
     const int by_tiles = (max_kv_len + KT - 1) / KT / 6;
@@ -999,21 +1045,14 @@ void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
 // heads are multiples of 256 bytes, so the first address decides); queries at any other address of a bf16 are fetched into registers.
 static bool queries_aligned(const AttnArgs& a) { return (reinterpret_cast<uintptr_t>(a.q) & 15) == 0; }
 
-// The times are lines through 4 and 24 tiles of the key-split form and 8 and 48 of the eight-wave form.
 IdleUnits attention_idle_units(const AttnArgs& a) {
     int max_kv = 0;
     for (int b = 0; b < a.B; ++b) max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;
-    IdleUnits idle{0, 8, 0.0f};
-    int wgs;
-    if (attention_plan_key_split(a)) {
-        wgs = (a.L + 63) / 64 * a.H * a.B;
-        idle.us = 6.5f + (float)max_kv * (1.25f / 128);
-    } else {
-        const int nw = attention_plan_waves(a.B, a.L, a.H, max_kv), QT = 32 * nw;
-        wgs = (a.L + QT - 1) / QT * a.H * a.B * a.splits;
-        idle.waves = (unsigned)nw;
-        idle.us = (nw == 8 ? 11.0f : 7.0f) + (float)(max_kv / a.splits) * ((nw == 8 ? 1.4f : 1.0f) / 64);
-    }
+    const AttnPlan p = attention_plan(a.B, a.L, a.H, max_kv);
+    const bool key_split = attention_plan_key_split(a);
+    const FormCost& f = kForms[key_split ? 2 : p.waves == 8 ? 1 : 0];
+    const int parts = key_split ? 1 : a.splits, wgs = (a.L + f.queries - 1) / f.queries * a.H * a.B * parts;
+    IdleUnits idle{0, f.waves == 4 ? 4u : 8u, key_split ? p.us_key_split : p.us};
     if (wgs < kUnits) idle.blocks = (unsigned)(kUnits - wgs);
     return idle;
 }
