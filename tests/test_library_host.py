@@ -3,6 +3,7 @@ declares, sizes its buffers as documented and rejects bad arguments before touch
 
 import ctypes as C
 import os
+import random
 import re
 import struct
 import subprocess
@@ -351,3 +352,21 @@ def test_row_kernels_leave_room_for_a_second_workgroup(lib):
     assert found
     for name, k in found:
         assert k[".vgpr_count"] <= 256 and k[".vgpr_spill_count"] == 0, (name, k[".vgpr_count"])
+
+
+def test_attention_plan_keeps_to_its_scratch_and_counts_rounds(lib):
+    """A planned number of parts stays within what the workspaces of a call are sized for (at most 16 parts of at least six
+    64-key tiles, parts * B * L * heads up to 65 536), and the form of a launch follows its rounds, not workgroups alone."""
+    rng = random.Random(11)
+    for _ in range(3000):
+        B, L, H, kv = rng.randint(1, 8), rng.randint(1, 3000), rng.randint(1, 40), rng.randint(1, 13000)
+        per_part = B * L * H * (128 + 2) * 4
+        n = binding.attention_workspace_bytes(B, L, 128 * H, kv)
+        assert n % per_part < 256                     # rounded up
+        parts = n // per_part
+        if parts > 0:
+            assert 2 <= parts <= 16 and (kv + 63) // 64 // parts >= 6 and parts * B * L * H <= 65536, (B, L, H, kv, parts)
+    for (B, L, H, kv, cap), form in (((1, 1560, 12, 512, 512), "attention_kernel<4>"), ((8, 1024, 12, 3072, 3072), "attention_kernel<4>"),
+                                     ((1, 1024, 12, 3072, 3072), "attention_ks_kernel<2, 4>"), ((1, 1024, 40, 3072, 3072), "attention_kernel<8>"),
+                                     ((4, 4680, 40, 10920, 10944), "attention_kernel<8>")):
+        assert binding.prof_kernel_name("attention", B, L, H, kv, cap) == form
