@@ -937,7 +937,6 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     memset(&ra, 0, sizeof(ra));
     AttnArgs at;
     memset(&at, 0, sizeof(at));
-    int max_kv = 0;
     for (int b = 0; b < B; ++b) {
         const size_t idx = (size_t)layer * cache->cfg.n_streams + chunks[b].stream_id;
         old_total[b] = cache->total[idx];
@@ -952,7 +951,6 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
         const int64_t res = (desc == nullptr && cache->total[idx] < (int64_t)S + W) ? cache->total[idx] : (int64_t)S + W;
         at.kv_len[b] = (int)res;
         at.cap[b] = cache->cap;
-        if (at.kv_len[b] > max_kv) max_kv = at.kv_len[b];
     }
     ra.desc = desc;
     at.desc = desc;
@@ -1056,7 +1054,8 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     at.B = B;
     at.L = L;
     at.H = H;
-    at.splits = attention_plan_splits(B, L, H, max_kv);
+    at.plan_kv = S + W;
+    at.splits = attention_plan_splits(B, L, H, at.plan_kv);
     at.part_o = ws.attn;
     at.part_ml = ws.attn + (size_t)at.splits * rows * C;
     WarmPlan under_self(cold ? attention_idle_units(at) : IdleUnits{});
@@ -1119,7 +1118,8 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
         ct.kv_len[b] = cfg->text_len;
         ct.cap[b] = cap_t;
     }
-    ct.splits = attention_plan_splits(B, L, H, cfg->text_len);
+    ct.plan_kv = cfg->text_len;
+    ct.splits = attention_plan_splits(B, L, H, ct.plan_kv);
     ct.part_ml = ws.attn + (size_t)ct.splits * rows * C;
     WarmPlan under_cross(cold ? attention_idle_units(ct) : IdleUnits{});
     if (!co) under_cross.add(w->W_co, C, C, true);

@@ -1000,18 +1000,20 @@ static AttnPlan attention_plan(int B, int L, int H, int max_kv) {
     return best;
 }
 
-static bool attention_plan_key_split(const AttnArgs& a) {
-    int max_kv = 0;
-    for (int b = 0; b < a.B; ++b) {
-        if (a.cap[b] % 128) return false;
-        max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;
-    }
-    if (g_force_waves) return g_force_waves == 2;
-    const AttnPlan p = attention_plan(a.B, a.L, a.H, max_kv);
-    return p.us_key_split < p.us;
+static AttnPlan attention_plan(const AttnArgs& a) {
+    int keys = a.plan_kv;
+    if (keys == 0)
+        for (int b = 0; b < a.B; ++b) keys = a.kv_len[b] > keys ? a.kv_len[b] : keys;
+    return attention_plan(a.B, a.L, a.H, keys);
 }
 
-int attention_plan_waves(int B, int L, int H, int max_kv_len) { return attention_plan(B, L, H, max_kv_len).waves; }
+static bool attention_plan_key_split(const AttnArgs& a) {
+    for (int b = 0; b < a.B; ++b)
+        if (a.cap[b] % 128) return false;
+    if (g_force_waves) return g_force_waves == 2;
+    const AttnPlan p = attention_plan(a);
+    return p.us_key_split < p.us;
+}
 
 int attention_plan_splits(int B, int L, int H, int max_kv_len) { return attention_plan(B, L, H, max_kv_len).splits; }
 
@@ -1035,10 +1037,8 @@ size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len) {
 }
 
 void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
-    int max_kv = 0;
-    for (int b = 0; b < a.B; ++b) max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;
     if (attention_plan_key_split(a)) snprintf(out, cap, "attention_ks_kernel<2, 4>");
-    else snprintf(out, cap, "attention_kernel<%d>", attention_plan_waves(a.B, a.L, a.H, max_kv));
+    else snprintf(out, cap, "attention_kernel<%d>", attention_plan(a).waves);
 }
 
 // Direct loads of the queries go from memory to LDS in pieces of 16 bytes, which have to start at multiples of 16 (rows and
@@ -1046,9 +1046,7 @@ void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
 static bool queries_aligned(const AttnArgs& a) { return (reinterpret_cast<uintptr_t>(a.q) & 15) == 0; }
 
 IdleUnits attention_idle_units(const AttnArgs& a) {
-    int max_kv = 0;
-    for (int b = 0; b < a.B; ++b) max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;
-    const AttnPlan p = attention_plan(a.B, a.L, a.H, max_kv);
+    const AttnPlan p = attention_plan(a);
     const bool key_split = attention_plan_key_split(a);
     const FormCost& f = kForms[key_split ? 2 : p.waves == 8 ? 1 : 0];
     const int parts = key_split ? 1 : a.splits, wgs = (a.L + f.queries - 1) / f.queries * a.H * a.B * parts;
@@ -1102,9 +1100,7 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const
     }
     hipError_t e = hipSuccess;
     if (part != 2) {
-        int max_kv = 0;
-        for (int b = 0; b < a.B; ++b) max_kv = a.kv_len[b] > max_kv ? a.kv_len[b] : max_kv;
-        const int nw = attention_plan_waves(a.B, a.L, a.H, max_kv);
+        const int nw = attention_plan(a).waves;
         const int QT = 32 * nw;
         const dim3 grid = one_dimension((a.L + QT - 1) / QT, a.splits);
         if (fetching && nw == 8)

@@ -199,6 +199,8 @@ struct AttnArgs {
     float* part_o;                    // workspace: [splits][B*L][C] fp32
     float* part_ml;                   // workspace: [splits][B*L][H][2] fp32
     int splits;                       // chosen by attention_plan
+    int plan_kv;                      // keys that the launch is planned for (0: the longest of kv_len): a cache's capacity, so that a
+                                      // stream keeps its form while the cache fills, and a recorded step has the eager one's
     const StepDesc* desc;             // null: kv_len above; else kv_len is read from the device descriptor
     FastDiv by_q_tiles, by_heads;     // set by the launcher, as is the number of workgroups
     unsigned n_wg;
