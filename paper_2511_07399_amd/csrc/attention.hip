@@ -42,6 +42,7 @@
 //     branch's error against 64 bits 4.4e-3 -> 4.1e-3.
 //   * Skinny launches (few query tiles x heads) split the key range over several workgroups, which
 //     write normalised partial outputs with their (max, sum); a small kernel merges them.
+#include "attention_ranges.h"
 #include "common.h"
 
 #include <stdio.h>
@@ -225,13 +226,8 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
 
     const StreamKeys keys = stream_keys(a, b);
     const int cap = keys.cap, kv_len = keys.kv_len;
-    const int n_tiles = (int)((unsigned)(kv_len + KT - 1) / KT);      // one at least
-    int t0 = 0, t1 = n_tiles;
-    if (a.splits > 1) {                                               // at most 16 parts: no overflow of 32 bits below 2^33 keys
-        t0 = (int)((unsigned)(split * n_tiles) / (unsigned)a.splits);
-        t1 = (int)((unsigned)((split + 1) * n_tiles) / (unsigned)a.splits);
-    }
-    const int tail_tile = (kv_len % KT) ? n_tiles - 1 : -1;           // the tile with slots past kv_len, if any
+    const KeyTiles part = key_tiles(kv_len, KT, split, a.splits);
+    const int t0 = part.first, t_full = part.full, t1 = part.end;     // with few keys a part may be empty
 
     // ---- this lane's query (column of S^T) and its row.  Formed anew where they are needed, in front of the loop, for the
     // scale and at the end: kept across the loop they are spilled (256 registers), and the reloads wait for the tile loads.
@@ -483,7 +479,6 @@ __device__ __forceinline__ void attention_body(const AttnArgs& a, float softmax_
     }
     // full tiles in pairs (the two S^T register sets trade places), then what is left: at most one full tile
     // and the tail tile
-    const int t_full = (t1 - 1 == tail_tile) ? t1 - 1 : t1;          // tiles [t0, t_full) have 64 valid slots
     const std::false_type no_tail;
     const std::true_type with_tail;
     const std::integral_constant<int, 0> even;

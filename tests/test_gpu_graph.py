@@ -71,6 +71,24 @@ def test_ragged_three_frame_chunks_graph():
     assert max(errs_o) <= TOL_X, errs_o
 
 
+@pytest.mark.parametrize("waves", [4, 8])
+def test_graph_of_a_cache_with_fewer_key_tiles_than_parts(waves):
+    """A recorded step keeps the parts of a full cache (here 12 of 32 key tiles) while the stream's first chunks fill four tiles
+    each, all of them full: most parts have no tile, the first of the range among them."""
+    wl = wk.Workload("filling", C=512, H=4, F=384, grid_h=16, grid_w=16, frames_per_chunk=1, sink_frames=1,
+                     window_frames=7, L_t=40, B=1, N=1, steps=(1,), chunks=4)
+    assert wl.P % 64 == 0 and (wl.S + wl.W) // 64 >= 2 * 12
+    binding.tuning_set("attn_splits", 12)
+    binding.tuning_set("attn_waves", waves)
+    try:
+        errs_o, errs_e = run_graph_vs_eager(wl, 4, 1, 1, edit=visible_branches(wl))
+    finally:
+        binding.tuning_set("attn_splits", None)
+        binding.tuning_set("attn_waves", None)
+    assert max(errs_e) <= 1e-3, errs_e
+    assert max(errs_o) <= TOL_X, errs_o
+
+
 @pytest.mark.timeout(600)
 def test_wan13b_step_graph_replays():
     """The 30-block 1.3B-shaped step: six chunks replayed (warm-up, first evictions, steady state) against the eager

@@ -397,6 +397,20 @@ def test_attention_workgroup_numbering(B, L, H, kv_lens, splits, waves):
     test_attention_matches_oracle(B, L, H, kv_lens, splits, waves)
 
 
+# Streams with fewer key tiles than the launch has parts, beside one that has more: of the parts without tiles the first is
+# first in the range.  A stream's tiles may all be full (64, 192, 256, 320 keys) or not.
+@pytest.mark.parametrize("waves", [4, 8])
+@pytest.mark.parametrize("B,L,H,kv_lens,splits", [
+    (2, 70, 2, [256, 64], 2),
+    (4, 130, 3, [64, 192, 1024, 70], 5),
+    (3, 300, 1, [320, 2048, 256], 12),
+    (8, 33, 2, [64, 2112, 128, 960, 1, 1023, 576, 65], 16),
+])
+def test_attention_of_streams_with_fewer_tiles_than_parts(B, L, H, kv_lens, splits, waves):
+    assert min(kv_lens) <= 64 * (splits - 1) and max(kv_lens) >= 128 * splits         # so many parts are made
+    test_attention_matches_oracle(B, L, H, kv_lens, splits, waves)
+
+
 @pytest.mark.parametrize("waves,splits", [(4, 1), (4, 2), (8, 1), (8, 3), (2, 1)])
 @pytest.mark.parametrize("q0,o0", [(1, 0), (2, 1), (4, 4), (0, 2)])
 def test_attention_of_queries_at_any_address(q0, o0, waves, splits):

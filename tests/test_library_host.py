@@ -308,6 +308,34 @@ extern "C" int ranges(int H, int T, int pieces, int max_heads, int* out, int cap
         assert (n == 1) == (H * T * pieces <= 1 << 31 and H <= max_heads)
 
 
+def test_parts_of_a_key_range_cover_its_tiles_once(tmp_path):
+    """The tiles that the parts of an attention's key range walk: every tile of the range once, the one with slots past the
+    range as such, and none in a part without tiles (a range of fewer tiles than parts, its length a multiple of the tile or not)."""
+    source = tmp_path / "tiles.cpp"
+    source.write_text('''
+#include "attention_ranges.h"
+extern "C" void tiles(int kv_len, int tile, int part, int parts, int* out) {
+    const sdv2::KeyTiles t = sdv2::key_tiles(kv_len, tile, part, parts);
+    out[0] = t.first; out[1] = t.full; out[2] = t.end;
+}''')
+    so = tmp_path / "tiles.so"
+    csrc = os.path.join(os.path.dirname(binding.LIB_PATH), "csrc")
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", csrc, str(source), "-o", str(so)], check=True)
+    f = C.CDLL(str(so)).tiles
+    buf = (C.c_int * 3)()
+    for kv_len in [*range(1, 1200), 3072, 4680, 10920, 1 << 30, (1 << 30) + 1]:
+        n, whole = (kv_len + 63) // 64, kv_len // 64
+        for parts in range(1, 17):
+            at = 0
+            for part in range(parts):
+                f(kv_len, 64, part, parts, buf)
+                first, full, end = buf
+                assert first == at and first <= full <= end <= n, (kv_len, part, parts)
+                assert full == max(first, min(end, whole)), (kv_len, part, parts)
+                at = end
+            assert at == n
+
+
 # ------------------------------------------------------------------------------------------ what the compiler made of the kernels
 BUNDLE = b"__CLANG_OFFLOAD_BUNDLE__"
 
