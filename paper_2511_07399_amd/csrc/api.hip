@@ -646,7 +646,6 @@ int32_t sdv2_attention_bf16(const void* q_dev, const void* const* k_dev, const v
         if (kv_len_host[b] > max_kv) max_kv = kv_len_host[b];
     }
     const int C = n_heads * SDV2_HEAD_DIM;
-    a.splits = attention_plan_splits(B, L, n_heads, max_kv);
     const size_t need = align_up(attention_workspace_bytes(B, L, C, max_kv), 256);
     if (need > 0 && (!workspace_dev || workspace_bytes < need))
         return fail(SDV2_WORKSPACE_TOO_SMALL, "attention workspace %zu < %zu", workspace_bytes, need);
@@ -655,6 +654,7 @@ int32_t sdv2_attention_bf16(const void* q_dev, const void* const* k_dev, const v
     a.B = B;
     a.L = L;
     a.H = n_heads;
+    plan_attention(&a);
     a.part_o = static_cast<float*>(workspace_dev);
     a.part_ml = a.part_o ? a.part_o + (size_t)a.splits * B * L * C : nullptr;
     HIP_TRY(launch_attention(a, static_cast<hipStream_t>(hip_stream)), "attention kernel");
@@ -1054,8 +1054,8 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     at.B = B;
     at.L = L;
     at.H = H;
-    at.plan_kv = S + W;
-    at.splits = attention_plan_splits(B, L, H, at.plan_kv);
+    at.full_kv = S + W;
+    plan_attention(&at);
     at.part_o = ws.attn;
     at.part_ml = ws.attn + (size_t)at.splits * rows * C;
     WarmPlan under_self(cold ? attention_idle_units(at) : IdleUnits{});
@@ -1118,8 +1118,8 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
         ct.kv_len[b] = cfg->text_len;
         ct.cap[b] = cap_t;
     }
-    ct.plan_kv = cfg->text_len;
-    ct.splits = attention_plan_splits(B, L, H, ct.plan_kv);
+    ct.full_kv = 0;
+    plan_attention(&ct);
     ct.part_ml = ws.attn + (size_t)ct.splits * rows * C;
     WarmPlan under_cross(cold ? attention_idle_units(ct) : IdleUnits{});
     if (!co) under_cross.add(w->W_co, C, C, true);
@@ -1960,6 +1960,7 @@ int32_t sdv2_prof_kernel_name(int32_t kind, int32_t B, int32_t L, int32_t a0, in
             a.kv_len[b] = a1;
             a.cap[b] = a2;
         }
+        plan_attention(&a);
         attention_plan_name(a, out, capacity);
         return SDV2_OK;
     }

@@ -940,6 +940,7 @@ struct FormCost {
 const FormCost kForms[] = {{4, 128, 64, 2 * kUnits, 1.768f, 6.58f, 2.82f, 0.453f, 0.265f, 0.658f, 5.25f, 0.104f},
                            {8, 256, 64, kUnits, 1.596f, 8.00f, 0.96f, 0.743f, 0.257f, 0.0f, 6.24f, 0.096f},
                            {2, 64, 128, kUnits, 1.134f, 5.17f, 2.05f, 0.763f, 0.237f, 0.0f, 0.0f, 0.0f}};
+static const FormCost& form_of(int waves) { return kForms[waves == 2 ? 2 : waves == 8 ? 1 : 0]; }
 constexpr int kMostParts = 16, kLeastTiles = 6;
 constexpr float kPartsMargin = 1.03f;     // a split has to be that much better by the estimate: it needs scratch and a second launch
 
@@ -955,22 +956,23 @@ static float attention_cost(const FormCost& f, int B, int L, int H, int max_kv, 
 }
 
 struct AttnPlan {
-    int waves, splits;      // the best of the forms that any capacity has
-    float us, us_key_split; // its estimate, and the key-split form's
+    int waves, splits;      // of kForms
+    float us;               // its estimate
 };
 // Kept for the shapes a thread has used last, as the products' plans are.
-static AttnPlan attention_plan(int B, int L, int H, int max_kv) {
+static AttnPlan attention_plan(int B, int L, int H, int max_kv, bool key_split) {
     struct Entry {
-        int key[6];
+        int key[7];
         AttnPlan plan;
     };
     static thread_local Entry cache[8] = {};
-    const int key[6] = {B, L, H, max_kv, g_force_waves, g_force_splits};
+    const int key[7] = {B, L, H, max_kv, key_split, g_force_waves, g_force_splits};
     Entry& e = cache[((unsigned)B * 31u + (unsigned)L * 17u + (unsigned)H * 7u + (unsigned)max_kv) % 8u];
     if (memcmp(e.key, key, sizeof(key)) == 0) return e.plan;
-    AttnPlan best{4, 1, 1e30f, attention_cost(kForms[2], B, L, H, max_kv, 1)};
+    AttnPlan best{4, 1, 1e30f};
     for (int f = 0; f < 2; ++f) {
         const FormCost& form = kForms[f];
+        if (key_split && g_force_waves == 2) break;
         if ((g_force_waves == 4 || g_force_waves == 8) && form.waves != g_force_waves) continue;
         const int tiles = (max_kv + KT - 1) / KT;
         for (int parts = 1; parts <= kMostParts; ++parts) {
@@ -990,27 +992,40 @@ static AttnPlan attention_plan(int B, int L, int H, int max_kv) {
             if (g_force_splits > 0) break;
         }
     }
+    if (key_split && (g_force_waves == 0 || g_force_waves == 2)) {
+        const float us = attention_cost(form_of(2), B, L, H, max_kv, 1);
+        if (us < best.us) best = AttnPlan{2, 1, us};
+    }
     memcpy(e.key, key, sizeof(key));
     e.plan = best;
     return best;
 }
 
-static AttnPlan attention_plan(const AttnArgs& a) {
-    int keys = a.plan_kv;
-    if (keys == 0)
-        for (int b = 0; b < a.B; ++b) keys = a.kv_len[b] > keys ? a.kv_len[b] : keys;
-    return attention_plan(a.B, a.L, a.H, keys);
+// While a cache fills, a launch goes by the keys that are there: with the form and parts of a full cache the first chunks took
+// longer (a step of 1024 x 8 heads with room for 7168 keys, us a layer: first chunk 134.1 -> 120.9, second 137.1 -> 130.6; 20 heads,
+// first chunk 294.3 -> 251.9).  But a recorded step has the full cache's, and other parts add in another order, so an eager one
+// differs only where a tenth of the launch is to be had, more than the estimates are off by.
+constexpr float kWorthAnotherForm = 1.1f;
+
+void plan_attention(AttnArgs* a) {
+    int max_kv = 0;
+    bool key_split = true;
+    for (int b = 0; b < a->B; ++b) {
+        if (a->cap[b] % 128) key_split = false;
+        max_kv = a->kv_len[b] > max_kv ? a->kv_len[b] : max_kv;
+    }
+    AttnPlan p = attention_plan(a->B, a->L, a->H, max_kv, key_split);
+    if (a->full_kv > max_kv) {
+        const AttnPlan full = attention_plan(a->B, a->L, a->H, a->full_kv, key_split);
+        const float us = attention_cost(form_of(full.waves), a->B, a->L, a->H, max_kv, full.splits);
+        if (us <= kWorthAnotherForm * p.us) p = AttnPlan{full.waves, full.splits, us};
+    }
+    a->waves = p.waves;
+    a->splits = p.splits;
+    a->us = p.us;
 }
 
-static bool attention_plan_key_split(const AttnArgs& a) {
-    for (int b = 0; b < a.B; ++b)
-        if (a.cap[b] % 128) return false;
-    if (g_force_waves) return g_force_waves == 2;
-    const AttnPlan p = attention_plan(a);
-    return p.us_key_split < p.us;
-}
-
-int attention_plan_splits(int B, int L, int H, int max_kv_len) { return attention_plan(B, L, H, max_kv_len).splits; }
+static int attention_plan_splits(int B, int L, int H, int max_kv_len) { return attention_plan(B, L, H, max_kv_len, false).splits; }
 
 size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len) {
     const int H = C / D;
@@ -1032,8 +1047,8 @@ size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len) {
 }
 
 void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
-    if (attention_plan_key_split(a)) snprintf(out, cap, "attention_ks_kernel<2, 4>");
-    else snprintf(out, cap, "attention_kernel<%d>", attention_plan(a).waves);
+    if (a.waves == 2) snprintf(out, cap, "attention_ks_kernel<2, 4>");
+    else snprintf(out, cap, "attention_kernel<%d>", a.waves);
 }
 
 // Direct loads of the queries go from memory to LDS in pieces of 16 bytes, which have to start at multiples of 16 (rows and
@@ -1041,16 +1056,12 @@ void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
 static bool queries_aligned(const AttnArgs& a) { return (reinterpret_cast<uintptr_t>(a.q) & 15) == 0; }
 
 IdleUnits attention_idle_units(const AttnArgs& a) {
-    const AttnPlan p = attention_plan(a);
-    const bool key_split = attention_plan_key_split(a);
-    const FormCost& f = kForms[key_split ? 2 : p.waves == 8 ? 1 : 0];
-    const int parts = key_split ? 1 : a.splits, wgs = (a.L + f.queries - 1) / f.queries * a.H * a.B * parts;
-    IdleUnits idle{0, f.waves == 4 ? 4u : 8u, key_split ? p.us_key_split : p.us};
+    const FormCost& f = form_of(a.waves);
+    const int wgs = (a.L + f.queries - 1) / f.queries * a.H * a.B * a.splits;
+    IdleUnits idle{0, f.waves == 4 ? 4u : 8u, a.us};
     if (wgs < kUnits) idle.blocks = (unsigned)(kUnits - wgs);
     return idle;
 }
-
-bool attention_has_merge_pass(const AttnArgs& a) { return a.splits > 1 && !attention_plan_key_split(a); }
 
 hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const WarmArgs* side) {
     AttnArgs a = args;
@@ -1085,7 +1096,7 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const
     if (attr_err != hipSuccess || attributes_only()) return attr_err;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
     const bool staged = queries_aligned(a), fetching = side != nullptr && side->blocks > 0 && staged;
-    if (attention_plan_key_split(a)) {
+    if (a.waves == 2) {
         if (part == 2) return hipSuccess;
         const dim3 grid = one_dimension((a.L + 63) / 64, 1);
         const Kernel kernel = staged ? attention_ks_kernel<2, 4> : attention_ks_any_address_kernel<2, 4>;
@@ -1095,8 +1106,7 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const
     }
     hipError_t e = hipSuccess;
     if (part != 2) {
-        const int nw = attention_plan(a).waves;
-        const int QT = 32 * nw;
+        const int nw = a.waves, QT = 32 * nw;
         const dim3 grid = one_dimension((a.L + QT - 1) / QT, a.splits);
         if (fetching && nw == 8)
             hipLaunchKernelGGL(attention_fetching_kernel<8>, dim3(grid.x + side->blocks), dim3(512), smem8, s, a, scale_log2e, *side);

@@ -198,9 +198,7 @@ struct AttnArgs {
     int B, L, H;
     float* part_o;                    // workspace: [splits][B*L][C] fp32
     float* part_ml;                   // workspace: [splits][B*L][H][2] fp32
-    int splits;                       // chosen by attention_plan
-    int plan_kv;                      // keys that the launch is planned for (0: the longest of kv_len): a cache's capacity, so that a
-                                      // stream keeps its form while the cache fills, and a recorded step has the eager one's
+    int splits;                       // set by plan_attention
     const StepDesc* desc;             // null: kv_len above; else kv_len is read from the device descriptor
     FastDiv by_q_tiles, by_heads;     // set by the launcher, as is the number of workgroups
     unsigned n_wg;
@@ -209,9 +207,13 @@ struct AttnArgs {
     const float* q_squares;
     int q_pieces;
     float q_eps;
+    // Host only.  full_kv: the keys of a full cache, of which kv_len are there (0: there will be no more).
+    int full_kv;
+    int waves;                        // set by plan_attention: 4 or 8 per workgroup; 2: the key-split form (splits = 1)
+    float us;                         // its estimate of the launch
 };
+void plan_attention(AttnArgs* a);     // from B, L, H, kv_len, cap and full_kv; what follows here takes planned arguments
 IdleUnits attention_idle_units(const AttnArgs& a);
-int attention_plan_splits(int B, int L, int H, int max_kv_len);
 // Tuning hooks: waves per workgroup (4, 8; 0 = planner) and key-range splits (0 = planner); -1 leaves a value as is.
 void set_attention_overrides(int waves, int splits);
 size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len);
@@ -219,8 +221,8 @@ size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len);
 size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len);
 // part 1: the kernel; 2: the merge pass only.  warm: what units that the kernel leaves idle fetch meanwhile (null: nothing).
 hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part = 0, const WarmArgs* warm = nullptr);
-bool attention_has_merge_pass(const AttnArgs& a);
-void attention_plan_name(const AttnArgs& a, char* out, size_t cap);      // only B, L, H, kv_len and cap are read
+inline bool attention_has_merge_pass(const AttnArgs& a) { return a.splits > 1; }
+void attention_plan_name(const AttnArgs& a, char* out, size_t cap);
 
 // LayerNorm over C with an affine that is either adaLN modulation or a plain (gamma, beta).
 struct LnArgs {

@@ -670,6 +670,24 @@ def test_sum_of_parts_with_layernorm_at_every_width(heads):
         assert (out[parts] - out[1]).abs().max() <= 1e-2 * size, parts
 
 
+def test_attention_is_planned_for_the_keys_that_are_there():
+    """While a cache fills, an eager call's self-attention has the form of its resident keys, not of the full cache: here one
+    launch over the first chunk's keys, and parts with a pass that merges them over the full cache's."""
+    wl = wk.Workload("filling", 1024, 8, 1280, 32, 32, 1, 1, 6, 64, 1, 1, (1,), 7)
+    form = [binding.prof_kernel_name("attention", 1, wl.L, wl.H, (c + 1) * wl.L, wl.S + wl.W) for c in range(7)]
+    assert form[0] == "attention_ks_kernel<2, 4>" and form[6] == "attention_kernel<8>"
+    m = GpuRunner(wl, n_layers=1, n_streams=1, weight_device=DEV)
+    merge = binding.LAUNCH_TAGS.index("split-KV merge")
+    merges = []
+    for chunk in range(7):
+        x = torch.zeros((1, wl.L, wl.C), device=DEV)
+        binding.prof_begin(64)
+        m.denoise(x, [(0, chunk, 1, 1)], timesteps=[500.0])
+        merges.append([tag for tag, _ in binding.prof_end(64)].count(merge))
+    m.close()
+    assert merges[0] == 0 and merges[6] == 1, (form, merges)
+
+
 # Whether launches fetch weights, keys and values ahead of their use depends on how much memory a pass over all layers goes
 # through (model_cfg.n_layers), and must not show in a result: rows and heads of every form of product and attention that has
 # workgroups to spare for it, whole and cut-off ranges, more ranges than there is room for.
