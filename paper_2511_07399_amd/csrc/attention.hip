@@ -925,8 +925,7 @@ void set_attention_overrides(int waves, int splits) {
 }
 
 // Forms of a launch: workgroups of 4 waves (128 queries, two workgroups per compute unit) or 8 waves (256 queries, one per unit,
-// half the K/V traffic from the L2 per query), each with the key range whole or in parts of at least six tiles that a merge
-// pass joins; and the key-split form (2 query blocks x 4 key slices, one workgroup per unit), for capacities of whole 128-key
+// half the K/V traffic from the L2 per query), each with the key range whole or in parts (most_parts) that a merge pass joins; and the key-split form (2 query blocks x 4 key slices, one workgroup per unit), for capacities of whole 128-key
 // tiles.  Microseconds of a launch:  c + rounds (tiles a + b), rounds as for the tiles of a product (a workgroup per slot is a
 // round; of a last round that fills the share x of the slots the part p + s x, two per unit beyond a half q + (1 - q) x), and
 // m + n per MB that the merge reads and writes.  Fitted to 2616 launches (4 to 40 heads, 16 to 12 480 keys, 1 to 8 streams, keys
@@ -955,6 +954,27 @@ static float attention_cost(const FormCost& f, int B, int L, int H, int max_kv, 
     return us;
 }
 
+// The most parts that a launch makes, for which its workspace has room: no more workgroups than have a place at once, at least
+// six tiles each.  It never falls with more keys, as the best number of parts may (748 x 9 heads: nine over 7003 keys, eight over
+// 8648), so a workspace for the longest key range serves every shorter one.  The places are those of the 256-query form where its
+// workgroups give at least half of the units one, of the 128-query form elsewhere; either way parts x queries x heads stay within
+// 65 536.  Of 3924 measured launches two would take more parts, and gain nothing by them.
+static int most_parts(int B, int L, int H, int max_kv) {
+    const int tiles = (max_kv + KT - 1) / KT;
+    if (g_force_splits > 0) {
+        int n = g_force_splits;
+        while (n > 1 && tiles / n < 2) --n;
+        return n;
+    }
+    const bool wide = g_force_waves == 8 || (g_force_waves != 4 && (long long)((L + 255) / 256) * H * B >= kUnits / 2);
+    const FormCost& form = form_of(wide ? 8 : 4);
+    const long long wgs = (long long)((L + form.queries - 1) / form.queries) * H * B;
+    if (wgs >= form.slots / 2) return 1;
+    const int by_slots = (int)(form.slots / wgs), by_tiles = tiles / kLeastTiles;
+    const int n = by_slots < by_tiles ? by_slots : by_tiles;
+    return n < 1 ? 1 : n > kMostParts ? kMostParts : n;
+}
+
 struct AttnPlan {
     int waves, splits;      // of kForms
     float us;               // its estimate
@@ -970,26 +990,14 @@ static AttnPlan attention_plan(int B, int L, int H, int max_kv, bool key_split) 
     Entry& e = cache[((unsigned)B * 31u + (unsigned)L * 17u + (unsigned)H * 7u + (unsigned)max_kv) % 8u];
     if (memcmp(e.key, key, sizeof(key)) == 0) return e.plan;
     AttnPlan best{4, 1, 1e30f};
+    const int most = most_parts(B, L, H, max_kv);
     for (int f = 0; f < 2; ++f) {
         const FormCost& form = kForms[f];
         if (key_split && g_force_waves == 2) break;
         if ((g_force_waves == 4 || g_force_waves == 8) && form.waves != g_force_waves) continue;
-        const int tiles = (max_kv + KT - 1) / KT;
-        for (int parts = 1; parts <= kMostParts; ++parts) {
-            int n = parts;
-            if (g_force_splits > 0) {
-                n = g_force_splits;
-                while (n > 1 && tiles / n < 2) --n;
-            } else if (parts > 1 && (tiles / parts < kLeastTiles || (long long)parts * B * L * H > 65536)) {
-                break;                                       // attention_workspace_bytes_bound counts on both
-            }
-            const float us = attention_cost(form, B, L, H, max_kv, n);
-            if (us < best.us) {
-                best.waves = form.waves;
-                best.splits = n;
-                best.us = us;
-            }
-            if (g_force_splits > 0) break;
+        for (int parts = g_force_splits > 0 ? most : 1; parts <= most; ++parts) {
+            const float us = attention_cost(form, B, L, H, max_kv, parts);
+            if (us < best.us) best = AttnPlan{form.waves, parts, us};
         }
     }
     if (key_split && (g_force_waves == 0 || g_force_waves == 2)) {
@@ -1025,17 +1033,15 @@ void plan_attention(AttnArgs* a) {
     a->us = p.us;
 }
 
-static int attention_plan_splits(int B, int L, int H, int max_kv_len) { return attention_plan(B, L, H, max_kv_len, false).splits; }
-
 size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len) {
     const int H = C / D;
-    const int splits = attention_plan_splits(B, L, H, max_kv_len);
+    const int splits = most_parts(B, L, H, max_kv_len);
     if (splits == 1) return 0;
     const size_t rows = (size_t)B * L;
     return (size_t)splits * rows * C * sizeof(float) + (size_t)splits * rows * H * 2 * sizeof(float);
 }
 
-// The plan splits into at most 16 parts of at least six key tiles, and only while parts * B * L * H <= 65 536.
+// most_parts at its most: 16 parts, at least six key tiles each, parts * B * L * H up to 65 536.
 size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len) {
     const size_t H = C / D, most_rows = 512 * 128 / H;
     const int by_tiles = (max_kv_len + KT - 1) / KT / 6;

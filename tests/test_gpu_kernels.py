@@ -384,6 +384,21 @@ def test_attention_matches_oracle(B, L, H, kv_lens, splits, waves):
         assert err < 1e-2, (b, err)
 
 
+def test_attention_workspace_of_the_longest_range_serves_the_shorter_ones():
+    L, H, D, longest = 748, 9, 128, 8648
+    q, k_rows, v_rows = (bf16_randn((n, H * D), 40 + i) for i, n in enumerate((L, longest, longest)))
+    ws = torch.empty(binding.attention_workspace_bytes(1, L, H * D, longest), dtype=torch.uint8, device=DEV)
+    for n in (longest, 7003, 700, 64):
+        cap = (n + 63) // 64 * 64
+        K, VT = pack_kv(k_rows[:n], v_rows[:n], H, cap)
+        o = torch.full((1, L, H * D), float("nan"), dtype=torch.bfloat16, device=DEV)
+        binding.attention_bf16(q[None].to(DEV), [K.to(DEV)], [VT.to(DEV)], [n], [cap], o, H, ws)
+        heads = lambda x: x.to(DEV).float().reshape(-1, H, D).transpose(0, 1)
+        p = torch.softmax(heads(q) @ heads(k_rows[:n]).transpose(1, 2) / math.sqrt(D), dim=-1)
+        want = (p @ heads(v_rows[:n])).transpose(0, 1).reshape(1, L, H * D)
+        assert max_rel_err(f64(o), f64(want)) < 1e-2, n
+
+
 # Query tiles, heads, streams and parts that are one, odd, or no divisors of the eight XCDs over which the workgroups are
 # numbered; a chunk that ends one query into a tile, whose other rows are copies of its last.
 @pytest.mark.parametrize("waves", [4, 8, 2])

@@ -394,6 +394,11 @@ def test_attention_plan_keeps_to_its_scratch_and_counts_rounds(lib):
         parts = n // per_part
         if parts > 0:
             assert 2 <= parts <= 16 and (kv + 63) // 64 // parts >= 6 and parts * B * L * H <= 65536, (B, L, H, kv, parts)
+    # a workspace for the longest key range of a program serves its shorter ones
+    for B, L, H, lengths in [(1, 748, 9, (7003, 8648))] + [
+            (rng.randint(1, 8), rng.randint(1, 2500), rng.randint(1, 40), sorted(rng.randint(1, 13000) for _ in range(8))) for _ in range(1500)]:
+        sizes = [binding.attention_workspace_bytes(B, L, 128 * H, kv) for kv in lengths]
+        assert sizes == sorted(sizes), (B, L, H, lengths, sizes)
     for (B, L, H, kv, cap), form in (((1, 1560, 12, 512, 512), "attention_kernel<4>"), ((8, 1024, 12, 3072, 3072), "attention_kernel<4>"),
                                      ((1, 1024, 12, 3072, 3072), "attention_ks_kernel<2, 4>"), ((1, 1024, 40, 3072, 3072), "attention_kernel<8>"),
                                      ((4, 4680, 40, 10920, 10944), "attention_kernel<8>")):
