@@ -277,16 +277,14 @@ def measure(workload, steps, warmup, copy_calibration, n_dist=0):
     gemm_tflops = sum(flops[t] for t in gemm_tags) / (sum_us(gemm_tags) * 1e-6) / 1e12
     attn_tflops = sum(flops[t] for t in attn_tags) / (sum_us(attn_tags) * 1e-6) / 1e12
     # Dominant kernel = the kernel instantiation (as a profiler names it) whose launch sites together take the largest
-    # share of the step: the library tells which instantiation its planner picks for each site's shape.
-    cap = (wl.S + wl.W + 63) // 64 * 64
-    cap_t = (wl.L_t + 63) // 64 * 64
-    site_kernel = {
-        1: binding.prof_kernel_name("gemm", B, L, 3 * Cw, Cw, 0), 4: binding.prof_kernel_name("gemm", B, L, Cw, Cw, 2),
-        6: binding.prof_kernel_name("gemm", B, L, Cw, Cw, 0), 9: binding.prof_kernel_name("gemm", B, L, Cw, Cw, 3),
-        11: binding.prof_kernel_name("gemm", B, L, wl.F, Cw, 1), 12: binding.prof_kernel_name("gemm", B, L, Cw, wl.F, 2),
-        3: binding.prof_kernel_name("attention", B, L, wl.H, l_kv, cap),
-        8: binding.prof_kernel_name("attention", B, L, wl.H, wl.L_t, cap_t),
-    }
+    # share of the step: the library tells which instantiation each launch ran.
+    ran = {}
+    for i, (tag, _) in enumerate(samples):
+        if tag in flops:
+            name = binding.prof_sample_kernel(i)
+            ran.setdefault(tag, {}).setdefault(name, 0)
+            ran[tag][name] += 1
+    site_kernel = {tag: max(names, key=names.get) for tag, names in ran.items()}
     groups = {}
     for tag, name in site_kernel.items():
         if tag in per_tag:

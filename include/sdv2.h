@@ -567,6 +567,9 @@ enum sdv2_launch_tag {
 };
 int32_t sdv2_prof_begin(int32_t max_samples);
 int32_t sdv2_prof_end(int32_t* tags_out, float* ms_out, int32_t capacity, int32_t* n_out);
+/* sdv2_prof_sample_kernel: the matrix kernel (product or attention) that launch number `sample` of the samples that the
+ * last sdv2_prof_end returned ran, spelled as a profiler prints it; an empty string for the other launches.  Host only. */
+int32_t sdv2_prof_sample_kernel(int32_t sample, char* out, size_t capacity);
 
 /* ------------------------------------------------------------------------------------------------
  * What the chip sustains, measured by the benchmark beside the published peaks (not part of the streaming path).
@@ -582,10 +585,13 @@ int32_t sdv2_prof_end(int32_t* tags_out, float* ms_out, int32_t capacity, int32_
  *   uint64 at the start of scratch_dev (dev, 256-byte aligned, >= 40960 bytes, contents overwritten; the direct loads
  *   read its bytes 8192 .. 40959).  Clocks per wave instruction = ticks / (iters * 8 * 8).  Enqueue only.
  * ------------------------------------------------------------------------------------------------ */
-/* sdv2_prof_kernel_name: the kernel instantiation the library's planner picks, spelled as a profiler prints it, so
- * that the benchmark can group launch sites by kernel the way a rocprofv3 summary does.
+/* sdv2_prof_kernel_name: the kernel instantiation the library's planner picks for a shape, spelled as a profiler prints it.
+ * Which variant of it a launch then takes depends on the call (gemm_fetching_kernel, attention_fetching_kernel and
+ * attention_ks_fetching_kernel read memory for the launches behind them, attention_any_address_kernel and
+ * attention_ks_any_address_kernel take unaligned queries): sdv2_prof_sample_kernel tells.
  *   kind 0: the GEMM of B * L rows with N = a0, K = a1, epilogue a2;  kind 1: attention of B streams x L queries,
- *   a0 heads, a1 keys, cache capacity a2 slots.  Host only; `out` receives a NUL-terminated string. */
+ *   a0 heads, a1 keys of a stream that will not have more, cache capacity a2 slots.  Host only; `out` receives a
+ *   NUL-terminated string. */
 int32_t sdv2_prof_kernel_name(int32_t kind, int32_t B, int32_t L, int32_t a0, int32_t a1, int32_t a2, char* out,
                               size_t capacity);
 /* sdv2_prof_gemm_plan: what the planner picks for a product of M rows, N columns and K (epilogue 0 .. 3, or 4 for a plain

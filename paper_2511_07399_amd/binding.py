@@ -80,7 +80,7 @@ EXPORTS = (
     "sdv2_motion_update", "sdv2_slo_pick_batch", "sdv2_text_kv_bytes", "sdv2_text_kv_workspace_bytes", "sdv2_text_kv_prepare",
     "sdv2_conditioning_workspace_bytes", "sdv2_conditioning", "sdv2_block_workspace_bytes",
     "sdv2_dit_block_forward", "sdv2_denoise_workspace_bytes", "sdv2_denoise_step", "sdv2_gemm_workspace_bytes", "sdv2_gemm_bf16",
-    "sdv2_attention_workspace_bytes", "sdv2_attention_bf16", "sdv2_prof_begin", "sdv2_prof_end",
+    "sdv2_attention_workspace_bytes", "sdv2_attention_bf16", "sdv2_prof_begin", "sdv2_prof_end", "sdv2_prof_sample_kernel",
     "sdv2_prof_peak_mfma", "sdv2_prof_peak_copy", "sdv2_prof_lds_rates", "sdv2_prof_kernel_name", "sdv2_prof_gemm_plan", "sdv2_tuning_set", "sdv2_gemm_noalloc_max_scratch_bytes",
     "sdv2_gemm_bf16_noalloc", "sdv2_stream_batch_rows_bytes", "sdv2_stream_batch_create", "sdv2_stream_batch_destroy",
     "sdv2_stream_batch_reset", "sdv2_stream_batch_step", "sdv2_denoise_graph_state_bytes", "sdv2_denoise_graph_create",
@@ -161,6 +161,7 @@ def load_library():
     lib.sdv2_prof_peak_copy.argtypes = [vp, vp, sz, vp]
     lib.sdv2_prof_lds_rates.argtypes = [i32, vp, sz, vp]
     lib.sdv2_tuning_set.argtypes = [C.c_char_p, C.c_char_p]
+    lib.sdv2_prof_sample_kernel.argtypes = [i32, C.c_char_p, sz]
     lib.sdv2_prof_kernel_name.argtypes = [i32, i32, i32, i32, i32, i32, C.c_char_p, sz]
     lib.sdv2_prof_gemm_plan.argtypes = [i32, i32, i32, i32, i32, sz, C.POINTER(i32), C.POINTER(i32), C.POINTER(C.c_float)]
     lib.sdv2_gemm_noalloc_max_scratch_bytes.restype = sz
@@ -518,6 +519,14 @@ def prof_end(capacity):
     n = C.c_int32()
     _check(_lib.sdv2_prof_end(tags, ms, capacity, C.byref(n)))
     return [(tags[i], ms[i]) for i in range(n.value)]
+
+
+def prof_sample_kernel(sample):
+    """The matrix kernel that launch number `sample` of prof_end's list ran ("" for other launches)."""
+    load_library()
+    buf = C.create_string_buffer(128)
+    _check(_lib.sdv2_prof_sample_kernel(sample, buf, 128))
+    return buf.value.decode()
 
 
 def prof_peak_mfma(iters, workgroups, sink):

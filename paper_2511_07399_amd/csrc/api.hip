@@ -50,6 +50,7 @@ struct Profiler {
     int n = 0;
     std::vector<hipEvent_t> start, stop;
     std::vector<int> tag;
+    std::vector<std::string> kernel;      // of the matrix launches; kept until the next sdv2_prof_begin
 };
 Profiler g_prof;
 
@@ -60,8 +61,10 @@ hipError_t timed(int tag, hipStream_t s, F&& launch) {
     g_prof.tag[i] = tag;
     hipError_t e = hipEventRecord(g_prof.start[i], s);
     if (e != hipSuccess) return e;
+    g_launch_note.kernel[0] = 0;
     e = launch();
     if (e != hipSuccess) return e;
+    g_prof.kernel[i] = g_launch_note.kernel;
     return hipEventRecord(g_prof.stop[i], s);
 }
 
@@ -1982,19 +1985,20 @@ int32_t sdv2_prof_begin(int32_t max_samples) {
     g_prof.start.resize(max_samples);
     g_prof.stop.resize(max_samples);
     g_prof.tag.assign(max_samples, -1);
+    g_prof.kernel.assign(max_samples, std::string());
     for (int i = 0; i < max_samples; ++i) {
         HIP_TRY(hipEventCreate(&g_prof.start[i]), "event create");
         HIP_TRY(hipEventCreate(&g_prof.stop[i]), "event create");
     }
     g_prof.n = 0;
-    g_prof.on = true;
+    g_prof.on = g_launch_note.on = true;
     return SDV2_OK;
 }
 
 int32_t sdv2_prof_end(int32_t* tags_out, float* ms_out, int32_t capacity, int32_t* n_out) {
     if (!g_prof.on) return fail(SDV2_BAD_STATE, "profiling is not on");
     if (!tags_out || !ms_out || !n_out) return fail(SDV2_INVALID_ARG, "null pointer");
-    g_prof.on = false;
+    g_prof.on = g_launch_note.on = false;
     int32_t rc = SDV2_OK;
     const int n = g_prof.n < capacity ? g_prof.n : capacity;
     for (int i = 0; i < n && rc == SDV2_OK; ++i) {
@@ -2004,6 +2008,7 @@ int32_t sdv2_prof_end(int32_t* tags_out, float* ms_out, int32_t capacity, int32_
         tags_out[i] = g_prof.tag[i];
     }
     *n_out = n;
+    g_prof.kernel.resize(g_prof.n);
     for (size_t i = 0; i < g_prof.start.size(); ++i) {
         hipEventDestroy(g_prof.start[i]);
         hipEventDestroy(g_prof.stop[i]);
@@ -2012,6 +2017,14 @@ int32_t sdv2_prof_end(int32_t* tags_out, float* ms_out, int32_t capacity, int32_
     g_prof.stop.clear();
     g_prof.n = 0;
     return rc;
+}
+
+int32_t sdv2_prof_sample_kernel(int32_t sample, char* out, size_t capacity) {
+    if (!out || capacity < 8) return fail(SDV2_INVALID_ARG, "out is null or too small");
+    if (g_prof.on) return fail(SDV2_BAD_STATE, "profiling is still on");
+    if (sample < 0 || (size_t)sample >= g_prof.kernel.size()) return fail(SDV2_INVALID_ARG, "no sample %d", sample);
+    snprintf(out, capacity, "%s", g_prof.kernel[sample].c_str());
+    return SDV2_OK;
 }
 
 }  // extern "C"

@@ -1041,10 +1041,12 @@ size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len) {
     return planned > bound ? planned : bound;
 }
 
-void attention_plan_name(const AttnArgs& a, char* out, size_t cap) {
-    if (a.waves == 2) snprintf(out, cap, "attention_ks_kernel<2, 4>");
-    else snprintf(out, cap, "attention_kernel<%d>", a.waves);
+static void kernel_name(char* out, size_t cap, int waves, const char* variant) {
+    if (waves == 2) snprintf(out, cap, "attention_ks_%skernel<2, 4>", variant);
+    else snprintf(out, cap, "attention_%skernel<%d>", variant, waves);
 }
+
+void attention_plan_name(const AttnArgs& a, char* out, size_t cap) { kernel_name(out, cap, a.waves, ""); }
 
 // Direct loads of the queries go from memory to LDS in pieces of 16 bytes, which have to start at multiples of 16 (rows and
 // heads are multiples of 256 bytes, so the first address decides); queries at any other address of a bf16 are fetched into registers.
@@ -1091,6 +1093,8 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const
     if (attr_err != hipSuccess || attributes_only()) return attr_err;
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
     const bool staged = queries_aligned(a), fetching = side != nullptr && side->blocks > 0 && staged;
+    if (g_launch_note.on && part != 2)
+        kernel_name(g_launch_note.kernel, sizeof(g_launch_note.kernel), a.waves, fetching ? "fetching_" : staged ? "" : "any_address_");
     if (a.waves == 2) {
         if (part == 2) return hipSuccess;
         const dim3 grid = one_dimension((a.L + 63) / 64, 1);

@@ -118,6 +118,13 @@ __device__ __forceinline__ void warm_memory(const WarmArgs& w, unsigned block) {
 }
 
 // ---------------------------------------------------------------- launchers (host side)
+// While launches are profiled (sdv2_prof_begin), the launchers of the matrix kernels leave here which one they took, spelled as a
+// profiler prints it.
+struct LaunchNote {
+    bool on;
+    char kernel[96];
+};
+inline LaunchNote g_launch_note{};
 enum GemmEpilogue { kEpiBias = 0, kEpiBiasGelu = 1, kEpiGatedResidual = 2, kEpiResidual = 3,
                     kEpiPartial = 4 /* internal: fp32 partial sums of one k part, no bias */,
                     kEpiGainSquares = 5 /* internal: bf16 gain (A W^T + bias), and sums of (A W^T + bias)^2 over pieces of rows */ };

@@ -625,6 +625,7 @@ hipError_t launch_one(const GemmArgs& g, int splitk, hipStream_t s) {
     });
     if (attr_err != hipSuccess || attributes_only()) return attr_err;
     const int group_m = 8;
+    if (g_launch_note.on) snprintf(g_launch_note.kernel, sizeof(g_launch_note.kernel), "gemm_kernel<%d, %d, %d, %d>", TM, TN, BK, PF);
     hipLaunchKernelGGL((gemm_kernel<TM, TN, BK, PF>), dim3(grid), dim3(256), smem, s, g, tiles_m, tiles_n, group_m, splitk);
     return hipGetLastError();
 }
@@ -694,6 +695,11 @@ bool fetches_own_weights(const GemmArgs& g, int grid) {
            (size_t)g.N * g.K * sizeof(bf16) * (g.w2 != nullptr ? 2 : 1) <= kMostOwnWeights;
 }
 
+void alt64_name(char* out, size_t cap, bool fetching, int wm, int wn, int tm, int tn, int nsa, int nsw, bool roles, int occ) {
+    snprintf(out, cap, "gemm_%s_kernel<%d, %d, %d, %d, %d, %d, %s, %d>", fetching ? "fetching" : "alt64", wm, wn, tm, tn, nsa, nsw,
+             roles ? "true" : "false", occ);
+}
+
 template <int WM, int WN, int TM, int TN, int NSA, int NSW, bool ROLES, int OCC, int PER_UNIT>
 hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s, const WarmArgs* side) {
     constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
@@ -729,6 +735,7 @@ hipError_t launch_alt64(const GemmArgs& g, int splitk, hipStream_t s, const Warm
         const size_t blocks = (size_t)warm.ranges * g.N * pitch / (32 * 1024);
         warm.blocks = blocks < kUnits ? (unsigned)blocks : kUnits;
     }
+    if (g_launch_note.on) alt64_name(g_launch_note.kernel, sizeof(g_launch_note.kernel), warm.blocks > 0, WM, WN, TM, TN, NSA, NSW, ROLES, OCC);
     if (warm.blocks > 0)
         hipLaunchKernelGGL((gemm_fetching_kernel<WM, WN, TM, TN, NSA, NSW, ROLES, OCC>), dim3(grid + warm.blocks), dim3(64 * WM * WN), smem, s, g,
                            tiles_m, tiles_n, group_m, splitk, (unsigned)grid, warm);
@@ -1186,7 +1193,7 @@ void gemm_plan_name(int M, int N, int K, int epilogue, char* out, size_t cap) {
     switch (p.dma) {
 #define X(id, wm, wn, tm, tn, nsa, nsw, roles, occ, ...)                                                                 \
     case id:                                                                                                             \
-        snprintf(out, cap, "gemm_alt64_kernel<%d, %d, %d, %d, %d, %d, %s, %d>", wm, wn, tm, tn, nsa, nsw, roles ? "true" : "false", occ); \
+        alt64_name(out, cap, false, wm, wn, tm, tn, nsa, nsw, roles, occ);                                               \
         return;
         SDV2_TILE_CONFIGS(X)
 #undef X

@@ -670,6 +670,33 @@ def test_sum_of_parts_with_layernorm_at_every_width(heads):
         assert (out[parts] - out[1]).abs().max() <= 1e-2 * size, parts
 
 
+def test_profiled_launches_name_the_kernel_that_ran():
+    """A launch that reads memory for those behind it runs a kernel of its own, and is reported as that one; the planner's name
+    for the shape is the ordinary one."""
+    wl = wk.Workload("names", 1536, 12, 8960, 32, 32, 1, 1, 2, 512, 1, 1, (1,), 1)
+    for layers, fetching in ((1, False), (30, True)):
+        m = GpuRunner(wl, n_layers=1, n_streams=1, weight_device=DEV)
+        m.cfg = binding.model_cfg(wl.C, wl.H, wl.F, wl.grid_h, wl.grid_w, wl.L_t, layers, wl.t_dim)
+        x, e0 = torch.zeros((1, wl.L, wl.C), device=DEV), torch.zeros((1, 6, wl.C), device=DEV)
+        binding.prof_begin(64)
+        m.block(0, x, e0, [(0, 0, 1, 1)])
+        tags = [binding.LAUNCH_TAGS[tag] for tag, _ in binding.prof_end(64)]
+        ran = {tag: binding.prof_sample_kernel(i) for i, tag in enumerate(tags)}
+        with pytest.raises(binding.Sdv2Error):
+            binding.prof_sample_kernel(len(tags))
+        m.close()
+        plan = {"QKV gemm": binding.prof_kernel_name("gemm", 1, wl.L, 3 * wl.C, wl.C, 0),
+                "out-proj gemm": binding.prof_kernel_name("gemm", 1, wl.L, wl.C, wl.C, 2),
+                "FFN-1 gemm": binding.prof_kernel_name("gemm", 1, wl.L, wl.F, wl.C, 1),
+                "self-attn": binding.prof_kernel_name("attention", 1, wl.L, wl.H, wl.L, wl.S + wl.W),
+                "cross-attn": binding.prof_kernel_name("attention", 1, wl.L, wl.H, wl.L_t, wl.L_t)}
+        own = {"out-proj gemm": ("alt64", "fetching"), "cross-attn": ("attention_ks_", "attention_ks_fetching_"),
+               "QKV gemm": ("alt64", "fetching")} if fetching else {}
+        for tag, name in plan.items():
+            assert ran[tag] == name.replace(*own.get(tag, ("", ""))), (layers, tag, ran[tag])
+        assert ran["rope+append"] == ran["adaLN-1"] == ""
+
+
 def test_attention_is_planned_for_the_keys_that_are_there():
     """While a cache fills, an eager call's self-attention has the form of its resident keys, not of the full cache: here one
     launch over the first chunk's keys, and parts with a pass that merges them over the full cache's."""

@@ -168,6 +168,9 @@ def test_stream_batch_handle_and_planner_hooks_on_the_host(lib):
     assert binding.prof_kernel_name("attention", 1, 1024, 12, 3072, 3072) == "attention_ks_kernel<2, 4>"
     assert binding.prof_kernel_name("attention", 1, 1024, 12, 3072, 3136).startswith("attention_kernel<")
     assert binding.prof_kernel_name("attention", 4, 4680, 40, 10920, 10944) == "attention_kernel<8>"
+    # the kernel of a sample that no profiled run has
+    assert lib.sdv2_prof_sample_kernel(1 << 29, C.create_string_buffer(64), 64) == binding.INVALID_ARG
+    assert lib.sdv2_prof_sample_kernel(0, None, 64) == binding.INVALID_ARG
     binding.tuning_set("gemm_tile", "1,3")
     try:
         assert binding.prof_kernel_name("gemm", 4, 4680, 13824, 5120, 1) == "gemm_kernel<1, 3, 64, 2>"
