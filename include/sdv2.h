@@ -614,6 +614,7 @@ int32_t sdv2_prof_lds_rates(int32_t iters, void* scratch_dev, size_t scratch_byt
  *   "attn_waves":  "4" or "8": query blocks (waves) per attention workgroup, one key stream; "2": the key-split form
  *                  (2 query blocks x 4 key slices per workgroup; used only when every capacity is a multiple of 128)
  *   "attn_splits": parts of the key range over workgroups (1 .. 16)
+ *   "fetch_ahead": "0": no launch reads weights, keys or values ahead of their use
  * Errors: unknown name or a value that does not parse: SDV2_INVALID_ARG (the previous setting stays).
  * ------------------------------------------------------------------------------------------------ */
 int32_t sdv2_tuning_set(const char* name, const char* value);

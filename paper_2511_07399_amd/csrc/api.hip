@@ -116,8 +116,9 @@ bool cache_cfg_ok(const sdv2_cache_cfg* c, const char** why) {
 
 // Whether what a pass over all layers reads has left the memory-side cache when the next pass comes back to it: 256 MB;
 // measured, up to 240 MB read in turn stay, and from 320 MB on nothing does.
+bool g_fetch_nothing = false;       // sdv2_tuning_set("fetch_ahead", "0")
 bool weights_cold(const sdv2_model_cfg* c, size_t elements_per_layer) {
-    return elements_per_layer * sizeof(bf16) * c->n_layers > ((size_t)240 << 20);
+    return !g_fetch_nothing && elements_per_layer * sizeof(bf16) * c->n_layers > ((size_t)240 << 20);
 }
 
 void cache_geometry(const sdv2_cache_cfg* c, int* cap, size_t* k_bytes, size_t* ids_bytes, size_t* unit) {
@@ -172,6 +173,11 @@ int32_t sdv2_tuning_set(const char* name, const char* value) {
         } else {
             set_attention_overrides(-1, v);
         }
+        return SDV2_OK;
+    }
+    if (!strcmp(name, "fetch_ahead")) {
+        if (!clear && strcmp(value, "0")) return fail(SDV2_INVALID_ARG, "fetch_ahead must be \"0\" or cleared");
+        g_fetch_nothing = !clear;
         return SDV2_OK;
     }
     return fail(SDV2_INVALID_ARG, "unknown tuning name \"%s\"", name);

@@ -716,30 +716,74 @@ def test_attention_is_planned_for_the_keys_that_are_there():
 
 
 # Whether launches fetch weights, keys and values ahead of their use depends on how much memory a pass over all layers goes
-# through (model_cfg.n_layers), and must not show in a result: rows and heads of every form of product and attention that has
-# workgroups to spare for it, whole and cut-off ranges, more ranges than there is room for.
+# through (model_cfg.n_layers; the layers of 40 heads are enough each by itself), and must not show in a result: rows and heads of
+# every form of product and attention that has workgroups to spare for it, whole and cut-off ranges, more ranges than there is
+# room for.
 @pytest.mark.parametrize("heads,ffn,grid,frames,window,text,streams", [
     (1, 128, (3, 5), 1, 2, 1, 1), (4, 640, (7, 9), 2, 3, 77, 3), (12, 8960, (32, 32), 1, 2, 512, 1), (12, 3072, (30, 41), 1, 2, 300, 2),
     (20, 5248, (31, 33), 1, 3, 64, 1), (23, 2944, (9, 42), 2, 4, 500, 1), (40, 13824, (16, 26), 1, 2, 512, 1), (40, 5120, (32, 32), 1, 6, 400, 1)])
 def test_fetching_ahead_changes_no_result(heads, ffn, grid, frames, window, text, streams):
     wl = wk.Workload("ahead", 128 * heads, heads, ffn, *grid, frames, 1, window, text, streams, 1, (1,), 1)
-    outs = []
-    for layers in (1, 1_000_000):
-        m = GpuRunner(wl, n_layers=1, n_streams=streams, weight_device=DEV)
-        m.cfg = binding.model_cfg(wl.C, wl.H, wl.F, wl.grid_h, wl.grid_w, wl.L_t, layers, wl.t_dim)
-        kt, vt = (torch.zeros(binding.text_kv_bytes(m.cfg), dtype=torch.uint8, device=DEV) for _ in range(2))
-        ws = torch.empty(binding.text_kv_workspace_bytes(m.cfg), dtype=torch.uint8, device=DEV)
-        binding.text_kv_prepare(m.cfg, m.bw_array[0], wk.text_context(wl, 0).to(DEV, torch.bfloat16), kt, vt, ws)
-        out = [kt, vt]
-        for chunk in range(2):
-            g = torch.Generator(device=DEV).manual_seed(chunk)
-            x = torch.randn((streams, wl.L, wl.C), generator=g, device=DEV)
-            e0 = 0.02 * torch.randn((streams, 6, wl.C), generator=g, device=DEV)
-            m.block(0, x, e0, [(s, chunk * frames, frames, 1) for s in range(streams)])
-            out.append(x)
-        out.append(m.cache_storage.clone())
+    outs, kernels = [], []
+    for layers, fetch_ahead in ((1, None), (1_000_000, None), (1_000_000, "0")):
+        binding.tuning_set("fetch_ahead", fetch_ahead)
+        try:
+            m = GpuRunner(wl, n_layers=1, n_streams=streams, weight_device=DEV)
+            m.cfg = binding.model_cfg(wl.C, wl.H, wl.F, wl.grid_h, wl.grid_w, wl.L_t, layers, wl.t_dim)
+            kt, vt = (torch.zeros(binding.text_kv_bytes(m.cfg), dtype=torch.uint8, device=DEV) for _ in range(2))
+            ws = torch.empty(binding.text_kv_workspace_bytes(m.cfg), dtype=torch.uint8, device=DEV)
+            binding.text_kv_prepare(m.cfg, m.bw_array[0], wk.text_context(wl, 0).to(DEV, torch.bfloat16), kt, vt, ws)
+            out, ran = [kt, vt], []
+            for chunk in range(2):
+                g = torch.Generator(device=DEV).manual_seed(chunk)
+                x = torch.randn((streams, wl.L, wl.C), generator=g, device=DEV)
+                e0 = 0.02 * torch.randn((streams, 6, wl.C), generator=g, device=DEV)
+                binding.prof_begin(64)
+                m.block(0, x, e0, [(s, chunk * frames, frames, 1) for s in range(streams)])
+                ran += [binding.prof_sample_kernel(i) for i in range(len(binding.prof_end(64)))]
+                out.append(x)
+            out.append(m.cache_storage.clone())
+        finally:
+            binding.tuning_set("fetch_ahead", None)
         outs.append(out)
+        kernels.append(ran)
         m.close()
-    for one, many in zip(*outs):
-        assert torch.equal(one, many)
+    # the same launches, of which some fetch, and none with the setting; a layer of 40 heads is beyond the cache by itself
+    fetching = [[("fetching" in name) for name in ran] for ran in kernels]
+    ordinary = [[name.replace("gemm_fetching", "gemm_alt64").replace("_fetching", "") for name in ran] for ran in kernels]
+    assert ordinary[0] == ordinary[1] == ordinary[2]
+    assert any(fetching[1]) and not any(fetching[2]) and any(fetching[0]) == (heads == 40), kernels
+    for per_run in zip(*outs):
+        assert all(torch.equal(per_run[0], other) for other in per_run[1:])
     assert torch.isfinite(outs[0][-2]).all()
+
+
+@pytest.mark.parametrize("tile", range(1, 19))
+def test_fetching_kernel_of_every_tile(tile):
+    """The variant of each tile that also fetches memory, with rows, columns and keys that end inside the tiles, against the ordinary
+    one: a tile that fits a unit twice fetches its own weights, a larger one the layer's keys and values."""
+    wl = wk.Workload("tiles", 384, 3, 640, 5, 33, 1, 1, 2, 70, 2, 1, (1,), 1)
+    outs = []
+    binding.tuning_set("gemm_tile", "d%d" % tile)
+    try:
+        for fetch_ahead in (None, "0"):
+            binding.tuning_set("fetch_ahead", fetch_ahead)
+            m = GpuRunner(wl, n_layers=1, n_streams=2, weight_device=DEV)
+            m.cfg = binding.model_cfg(wl.C, wl.H, wl.F, wl.grid_h, wl.grid_w, wl.L_t, 1_000_000, wl.t_dim)
+            m.cache_storage.zero_()
+            g = torch.Generator(device=DEV).manual_seed(tile)
+            x = torch.randn((2, wl.L, wl.C), generator=g, device=DEV)
+            e0 = 0.02 * torch.randn((2, 6, wl.C), generator=g, device=DEV)
+            binding.prof_begin(64)
+            for chunk in range(2):
+                m.block(0, x, e0, [(s, chunk, 1, 1) for s in range(2)])
+            ran = {binding.prof_sample_kernel(i) for i in range(len(binding.prof_end(64)))}
+            assert any(n.startswith("gemm_fetching_kernel") for n in ran) == (fetch_ahead is None), ran
+            assert not any(n.startswith("gemm_kernel") for n in ran)
+            outs.append((x, m.cache_storage.clone()))
+            m.close()
+    finally:
+        binding.tuning_set("gemm_tile", None)
+        binding.tuning_set("fetch_ahead", None)
+    assert torch.isfinite(outs[0][0]).all()
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])

@@ -176,7 +176,7 @@ def test_stream_batch_handle_and_planner_hooks_on_the_host(lib):
         assert binding.prof_kernel_name("gemm", 4, 4680, 13824, 5120, 1) == "gemm_kernel<1, 3, 64, 2>"
     finally:
         binding.tuning_set("gemm_tile", None)
-    for name, value in (("gemm_tile", "9,9"), ("attn_waves", "3"), ("no_such_knob", "1")):
+    for name, value in (("gemm_tile", "9,9"), ("attn_waves", "3"), ("fetch_ahead", "2"), ("no_such_knob", "1")):
         with pytest.raises(binding.Sdv2Error) as e:
             binding.tuning_set(name, value)
         assert e.value.code == binding.INVALID_ARG
@@ -369,10 +369,13 @@ def kernel_metadata():
 
 
 def test_matrix_kernels_spill_nothing(lib):
-    """A spilled register is reloaded from memory, and the wait for it is a wait for every tile load in flight."""
-    found = [(n, k) for n, k in kernel_metadata().items()
-             if "gemm_alt64_kernel" in n or "attention_kernel" in n or "attention_ks_kernel" in n]
-    assert len(found) == 18 + 3
+    """A spilled register is reloaded from memory, and the wait for it is a wait for every tile load in flight.  Of the ordinary
+    kernels and of those that also read memory for other launches."""
+    kernels = kernel_metadata()
+    found = [(n, k) for n, k in kernels.items() if "gemm_alt64_kernel" in n or "attention_kernel" in n or "attention_ks_kernel" in n]
+    fetching = [(n, k) for n, k in kernels.items() if "fetching_kernel" in n]
+    assert len(found) == len(fetching) == 18 + 3
+    found += fetching
     for name, k in found:
         assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, (name, k[".vgpr_spill_count"])
 
