@@ -884,9 +884,10 @@ void fill_rope_table(const sdv2_model_cfg* cfg, RopeAppendArgs* a) {
 // weights too seldom to hide HBM: a k loop asks it for 128 bytes of every row at a time, and runs slower than from the
 // memory-side cache (1024 rows: 5120 x 5120 61.5 and 51 us, 8960 x 1536 31.0 and 29.2, 4608 x 1536 20.8 and 17.1; the keys and
 // values of the attention behind it: 36 and 30 us).  So the attention kernels' idle units fetch the next products' weights, and
-// the QKV product's the keys and values.  With the products that fetch their own (fetches_own_weights): 1.3B step 6.12 -> 5.81
-// ms, 14B step 27.9 -> 27.6 (28.6 -> 28.2 on another), four rows of the 1.3B model 14.88 -> 14.61 (15.14 -> 15.10); of some 50
-// random models and batches none is slower by more than runs differ.
+// the QKV product's the keys and values.  With the products that fetch their own (fetches_own_weights), without and with, in turn
+// in one process: 1.3B step 5.96 -> 5.62 ms, 14B step 28.0 -> 27.6, four rows of the 1.3B model 14.75 -> 14.50 (from build to build 0 to
+// 1 % on other cards), one row of 1560 tokens and eight rows the same; of 14 random models and batches none is slower by more than
+// runs differ.
 // Measured and left out: more than 56 MB (what is fetched goes before what was there already: 52 MB last until they are used,
 // 105 do not), FFN-2's weights under FFN-1 (nothing where FFN-1's own are fetched, +1 % at 1976 rows), QKV's under the pass in
 // front of it (0 to +0.4 %), a launch's own in its idle units (+5 % at 14B).
@@ -924,7 +925,9 @@ private:
     bool full_ = false;
 };
 
-// The QKV product of more rows takes so long that what it fetches is gone again (2000 to 4300 rows: 0 to +1.4 %).
+// The QKV product of more rows takes so long that what it fetches may be gone again.  Steps of 8, 12 and 20 heads with and without
+// this fetch: 1024 rows -2.4 to 0.0 %, 1196 to 1280 -0.1 to +0.2, 1300 to 2080 -3.2 to +2.9 in no order of rows (mean +0.2); 2000 to
+// 4300 rows 0 to +1.4.
 constexpr int kMostWarmQkvRows = 1280;
 
 // Launches one block.  State has been validated; it is advanced here and restored if a launch fails.
@@ -1030,7 +1033,7 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     g.N = 3 * C;
     g.K = C;
     g.epilogue = kEpiBias;
-    const bool cold = g.cold_weights;                 // else everything is in the memory-side cache already
+    const bool cold = g.cold_weights;                 // of weights alone; where they stay in the memory-side cache nothing is fetched
     WarmPlan under_qkv(cold && rows <= kMostWarmQkvRows ? gemm_idle_units(g) : IdleUnits{});
     bool all = true;
     for (int b = 0; b < B; ++b) {

@@ -657,8 +657,8 @@ hipError_t launch_tn(const GemmArgs& g, int tn, int splitk, hipStream_t s) {
 // launches in a steady state (weights cold, the chip at its power limit) of 156 random shapes of 128 to 18 720 rows,
 // K = 512 to 18 000: root mean square error 4 to 10 %, and the configuration picked is on average 0.5 % slower than the
 // best of all of them.  256 x 256 fitted again since its loads go by scalar rows (a was 1.60): of 3000 random products of such
-// models 128 take it now that did not, 44 of those 3.3 % faster on average (6656 x 4096 x 12800 649 -> 590 us, 9504 x 3072 x
-// 3072 160 -> 149; 14896 x 16000 x 5120 1911 -> 1933).
+// models 132 take it now that did not; 44 of those measured are 2.8 % faster on average (6656 x 4096 x 12800 636 -> 588 us, 9504 x
+// 3072 x 3072 152 -> 141; the worst 0.9 % slower, 14896 x 16000 x 5120 1882 -> 1896).
 #define SDV2_TILE_CONFIGS(X)                                                                                  \
     X(1, 2, 4, 8, 4, 2, 3, false, 2, 1, 1.505f, 7.1f, 2.8f, 0.77f, 0.23f, 1.0f)   /* 256 x 256 */             \
     X(2, 2, 4, 6, 4, 2, 3, true, 2, 1, 1.156f, 4.3f, 3.4f, 0.68f, 0.32f, 1.0f)    /* 192 x 256 */             \
@@ -681,7 +681,7 @@ hipError_t launch_tn(const GemmArgs& g, int tn, int splitk, hipStream_t s) {
 constexpr int kTileConfigs = 18;
 
 // A launch that gives each compute unit one workgroup of tiles that fit it twice has its weights fetched once in large pieces
-// by workgroups in the second places, about 32 KB each, while its own begin: the k loop asks HBM for 128 bytes of every row at
+// by workgroups in the second places, 32 KB each (64 KB of the largest: 256 workgroups at most), while its own begin: the k loop asks HBM for 128 bytes of every row at
 // a time, from as many DRAM pages, which costs more than the bytes.  Weights from HBM without and with this (and from the
 // memory-side cache): 1024 x 1536 x 1536 12.8 -> 10.7 us (10.5 and 10.3); 512 x 1536 x 1536 10.3 -> 8.0 (7.4 and 7.6);
 // 1024 x 2048 x 2048 19.1 -> 16.3 (15.5 and 15.8); 1.3B step 6.18 -> 6.03 ms, prompt 487 -> 449 us.
