@@ -641,7 +641,7 @@ int32_t sdv2_attention_bf16(const void* q_dev, const void* const* k_dev, const v
                             int32_t n_heads, void* workspace_dev, size_t workspace_bytes, void* hip_stream) {
     if (!q_dev || !k_dev || !vt_dev || !kv_len_host || !cap_host || !o_dev) return fail(SDV2_INVALID_ARG, "null pointer");
     if (B <= 0 || B > SDV2_MAX_BATCH || L <= 0 || n_heads <= 0) return fail(SDV2_INVALID_ARG, "bad B, L or n_heads");
-    AttnArgs a;
+    AttnLaunch a;
     memset(&a, 0, sizeof(a));
     int max_kv = 0;
     for (int b = 0; b < B; ++b) {
@@ -947,7 +947,7 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
     int32_t old_last[SDV2_MAX_BATCH];
     RopeAppendArgs ra;
     memset(&ra, 0, sizeof(ra));
-    AttnArgs at;
+    AttnLaunch at;
     memset(&at, 0, sizeof(at));
     for (int b = 0; b < B; ++b) {
         const size_t idx = (size_t)layer * cache->cfg.n_streams + chunks[b].stream_id;
@@ -1118,7 +1118,7 @@ int32_t run_block(const sdv2_model_cfg* cfg, const sdv2_block_weights* w, sdv2_k
         RUN(SDV2_TAG_CROSS_Q_NORM, launch_rmsnorm_inplace(ws.q, w->g_cq, rows, C, C, cfg->eps, s), "cross-q norm");
     }
     // 7. cross-attention over the text tokens
-    AttnArgs ct = at;
+    AttnLaunch ct = at;
     ct.desc = nullptr;                                // the text keys do not change from step to step
     ct.q_squares = q_pieces > 0 ? g.squares : nullptr;
     ct.q_pieces = q_pieces;
@@ -1357,7 +1357,7 @@ int32_t sdv2_denoise_graph_create(const sdv2_model_cfg* cfg, const sdv2_model_we
             g.splitk_floats = ws.gemm_floats;
             if (e == hipSuccess) e = launch_gemm(g, nullptr);
         }
-        AttnArgs at;
+        AttnLaunch at;
         memset(&at, 0, sizeof(at));
         at.B = B;
         at.L = L0;
@@ -1963,7 +1963,7 @@ int32_t sdv2_prof_kernel_name(int32_t kind, int32_t B, int32_t L, int32_t a0, in
     }
     if (kind == 1) {                                   // attention: a0 = heads, a1 = keys, a2 = capacity in slots
         if (B <= 0 || B > SDV2_MAX_BATCH || L <= 0 || a0 <= 0 || a1 <= 0 || a2 < a1) return fail(SDV2_INVALID_ARG, "bad attention shape");
-        AttnArgs a;
+        AttnLaunch a;
         memset(&a, 0, sizeof(a));
         a.B = B;
         a.L = L;

@@ -1004,7 +1004,7 @@ static AttnPlan attention_plan(int B, int L, int H, int max_kv, bool key_split) 
 // differs only where a tenth of the launch is to be had, more than the estimates are off by.
 constexpr float kWorthAnotherForm = 1.1f;
 
-void plan_attention(AttnArgs* a) {
+void plan_attention(AttnLaunch* a) {
     int max_kv = 0;
     bool key_split = true;
     for (int b = 0; b < a->B; ++b) {
@@ -1046,13 +1046,13 @@ static void kernel_name(char* out, size_t cap, int waves, const char* variant) {
     else snprintf(out, cap, "attention_%skernel<%d>", variant, waves);
 }
 
-void attention_plan_name(const AttnArgs& a, char* out, size_t cap) { kernel_name(out, cap, a.waves, ""); }
+void attention_plan_name(const AttnLaunch& a, char* out, size_t cap) { kernel_name(out, cap, a.waves, ""); }
 
 // Direct loads of the queries go from memory to LDS in pieces of 16 bytes, which have to start at multiples of 16 (rows and
 // heads are multiples of 256 bytes, so the first address decides); queries at any other address of a bf16 are fetched into registers.
 static bool queries_aligned(const AttnArgs& a) { return (reinterpret_cast<uintptr_t>(a.q) & 15) == 0; }
 
-IdleUnits attention_idle_units(const AttnArgs& a) {
+IdleUnits attention_idle_units(const AttnLaunch& a) {
     const FormCost& f = form_of(a.waves);
     const int wgs = (a.L + f.queries - 1) / f.queries * a.H * a.B * a.splits;
     IdleUnits idle{0, f.waves == 4 ? 4u : 8u, a.us};
@@ -1060,8 +1060,9 @@ IdleUnits attention_idle_units(const AttnArgs& a) {
     return idle;
 }
 
-hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const WarmArgs* side) {
-    AttnArgs a = args;
+hipError_t launch_attention(const AttnLaunch& launch, hipStream_t s, int part, const WarmArgs* side) {
+    AttnArgs a = launch;
+    const int waves = launch.waves;
     auto one_dimension = [&](int q_tiles, int parts) {
         a.n_wg = (unsigned)q_tiles * a.H * a.B * parts;
         a.by_q_tiles = fast_div(q_tiles, a.n_wg);
@@ -1094,8 +1095,8 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const
     const float scale_log2e = 1.4426950408889634f / sqrtf((float)D);
     const bool staged = queries_aligned(a), fetching = side != nullptr && side->blocks > 0 && staged;
     if (g_launch_note.on && part != 2)
-        kernel_name(g_launch_note.kernel, sizeof(g_launch_note.kernel), a.waves, fetching ? "fetching_" : staged ? "" : "any_address_");
-    if (a.waves == 2) {
+        kernel_name(g_launch_note.kernel, sizeof(g_launch_note.kernel), waves, fetching ? "fetching_" : staged ? "" : "any_address_");
+    if (waves == 2) {
         if (part == 2) return hipSuccess;
         const dim3 grid = one_dimension((a.L + 63) / 64, 1);
         const Kernel kernel = staged ? attention_ks_kernel<2, 4> : attention_ks_any_address_kernel<2, 4>;
@@ -1105,13 +1106,13 @@ hipError_t launch_attention(const AttnArgs& args, hipStream_t s, int part, const
     }
     hipError_t e = hipSuccess;
     if (part != 2) {
-        const int nw = a.waves, QT = 32 * nw;
-        const dim3 grid = one_dimension((a.L + QT - 1) / QT, a.splits);
-        if (fetching && nw == 8)
+        const int queries = 32 * waves;
+        const dim3 grid = one_dimension((a.L + queries - 1) / queries, a.splits);
+        if (fetching && waves == 8)
             hipLaunchKernelGGL(attention_fetching_kernel<8>, dim3(grid.x + side->blocks), dim3(512), smem8, s, a, scale_log2e, *side);
         else if (fetching)
             hipLaunchKernelGGL(attention_fetching_kernel<4>, dim3(grid.x + side->blocks), dim3(256), smem, s, a, scale_log2e, *side);
-        else if (nw == 8) hipLaunchKernelGGL(staged ? attention_kernel<8> : attention_any_address_kernel<8>, grid, dim3(512), smem8, s, a, scale_log2e);
+        else if (waves == 8) hipLaunchKernelGGL(staged ? attention_kernel<8> : attention_any_address_kernel<8>, grid, dim3(512), smem8, s, a, scale_log2e);
         else hipLaunchKernelGGL(staged ? attention_kernel<4> : attention_any_address_kernel<4>, grid, dim3(256), smem, s, a, scale_log2e);
         e = hipGetLastError();
     }

@@ -16,7 +16,8 @@ constexpr KeyTiles key_tiles(int kv_len, int tile, int part, int parts) {
         t.first = (int)((unsigned)(part * n) / (unsigned)parts);
         t.end = (int)((unsigned)((part + 1) * n) / (unsigned)parts);
     }
-    t.full = t.end - (t.end == n && (unsigned)kv_len % (unsigned)tile != 0 ? 1 : 0);      // the part that ends with the last tile has a tile
+    const int short_end = (unsigned)kv_len % (unsigned)tile != 0 ? n : -1;      // where a part ends whose last tile is short
+    t.full = t.end == short_end ? t.end - 1 : t.end;                            // such a part has a tile
     return t;
 }
 

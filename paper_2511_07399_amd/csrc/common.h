@@ -214,22 +214,24 @@ struct AttnArgs {
     const float* q_squares;
     int q_pieces;
     float q_eps;
-    // Host only.  full_kv: the keys of a full cache, of which kv_len are there (0: there will be no more).
-    int full_kv;
+};
+// What the host keeps of a launch beside the kernel's arguments.
+struct AttnLaunch : AttnArgs {
+    int full_kv;                      // the keys of a full cache, of which kv_len are there (0: there will be no more)
     int waves;                        // set by plan_attention: 4 or 8 per workgroup; 2: the key-split form (splits = 1)
     float us;                         // its estimate of the launch
 };
-void plan_attention(AttnArgs* a);     // from B, L, H, kv_len, cap and full_kv; what follows here takes planned arguments
-IdleUnits attention_idle_units(const AttnArgs& a);
+void plan_attention(AttnLaunch* a);   // from B, L, H, kv_len, cap and full_kv; what follows here takes a planned launch
+IdleUnits attention_idle_units(const AttnLaunch& a);
 // Tuning hooks: waves per workgroup (4, 8; 0 = planner) and key-range splits (0 = planner); -1 leaves a value as is.
 void set_attention_overrides(int waves, int splits);
 size_t attention_workspace_bytes(int B, int L, int C, int max_kv_len);
 // the most that a call of at most B streams of at most L queries needs; grows with B, L and max_kv_len
 size_t attention_workspace_bytes_bound(int B, int L, int C, int max_kv_len);
 // part 1: the kernel; 2: the merge pass only.  warm: what units that the kernel leaves idle fetch meanwhile (null: nothing).
-hipError_t launch_attention(const AttnArgs& a, hipStream_t s, int part = 0, const WarmArgs* warm = nullptr);
-inline bool attention_has_merge_pass(const AttnArgs& a) { return a.splits > 1; }
-void attention_plan_name(const AttnArgs& a, char* out, size_t cap);
+hipError_t launch_attention(const AttnLaunch& a, hipStream_t s, int part = 0, const WarmArgs* warm = nullptr);
+inline bool attention_has_merge_pass(const AttnLaunch& a) { return a.splits > 1; }
+void attention_plan_name(const AttnLaunch& a, char* out, size_t cap);
 
 // LayerNorm over C with an affine that is either adaLN modulation or a plain (gamma, beta).
 struct LnArgs {
