@@ -517,7 +517,8 @@ int32_t sdv2_stream_batch_latents_step(sdv2_stream_batch* sb, const sdv2_model_c
  *
  * sdv2_attention_bf16: o[b] = softmax(q[b] K[b]^T / sqrt(128)) V[b] over kv_len[b] slots.
  *   q: bf16 [B, L, C]; k[b]: bf16 [H][cap][128]; vt[b]: bf16 [H][128][cap] in the cache's column order (cap multiple of 64,
- *   >= kv_len[b] > 0); o: bf16 [B, L, C].  workspace: sdv2_attention_workspace_bytes(B, L, C, max kv_len).
+ *   >= kv_len[b] > 0); o: bf16 [B, L, C].  workspace: sdv2_attention_workspace_bytes(B, L, C, max kv_len),
+ *   which does not fall with more keys: one for the longest key range serves the shorter ones.
  *   q and o may start at any bf16 (16-byte aligned queries are faster); k[b] and vt[b] are 16-byte aligned.
  * ------------------------------------------------------------------------------------------------ */
 size_t sdv2_gemm_workspace_bytes(int32_t M, int32_t N, int32_t K, int32_t epilogue);

@@ -928,8 +928,8 @@ void set_attention_overrides(int waves, int splits) {
 // tiles.  Microseconds of a launch:  c + rounds (tiles a + b), rounds as for the tiles of a product (a workgroup per slot is a
 // round; of a last round that fills the share x of the slots the part p + s x, two per unit beyond a half q + (1 - q) x), and
 // m + n per MB that the merge reads and writes.  Fitted to 2616 launches (4 to 40 heads, 16 to 12 480 keys, 1 to 8 streams, keys
-// and values cold): rms error 4, 4 and 7 %.  On 1308 others the form picked is on average 0.4 % slower than the best of all;
-// the thresholds that this replaces, workgroups against units alone, 10 %: 1560 x 12 heads over 512 keys 18.2 -> 12.9 us, over
+// and values cold): rms error 4, 4 and 7 %.  On 1308 others the form picked is on average 0.3 % slower than the best of all;
+// the thresholds that this replaces, workgroups against units alone, 9 %: 1560 x 12 heads over 512 keys 18.2 -> 12.9 us, over
 // 4680 keys 93.8 -> 63.3, 8 x 1024 x 12 heads over 3072 keys 158.7 -> 148.9, 640 x 5 heads over 5120 keys 41.1 -> 27.9.
 struct FormCost {
     int waves, queries, keys, slots;

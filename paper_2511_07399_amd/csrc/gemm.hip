@@ -816,8 +816,8 @@ float plan_cost(int id, int M, int N, int K, int epilogue, int parts, int produc
     // An fp32 x beyond half of that cache is read and written again in HBM by the epilogue, which a single wave per SIMD hides
     // least of all (more loads of x in flight change nothing).  What the residual adds to the same product with a bf16 store, 256
     // x 256, 192 x 256, 256 x 192 and 256 x 160 tiles: 18720 x 5120 x 5120 110, 120, 159 and 131 us; 12480 x 5120 x 5120 85, 99,
-    // 136 and 101; 8192 x 5120 x 5120 52, 51, 73 and 39; 8192 x 2560 x 2560 (x of 84 MB) 23, 16, 18 and 13.  With this the first
-    // takes 192 x 256: 932 -> 865 us.
+    // 136 and 101; 8192 x 5120 x 5120 52, 51, 73 and 39; 8192 x 2560 x 2560 (x of 84 MB) 23, 16, 18 and 13.  The lines
+    // alone put 256 x 192 (922 us) level with 256 x 256 and 192 x 256 (840 and 843) for the first.
     if (parts == 1 && residual && kCost[id].one_wave && (size_t)M * N * sizeof(float) > ((size_t)120 << 20)) cost += (float)M * N * 8.0f / 15e6f;
     return cost;
 }
